@@ -166,13 +166,18 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                total_q_tokens until the next ooco_plan -- for callers that repeat one batch (benchmarks,
  *                the layers of one iteration, graph replay), who then answer for the device arrays still
  *                matching it
- *   "overlap"    0/1/2 (default 1): in a batch that holds both prefill chunks and decode sequences,
- *                run the prefill kernel on the context's own side stream (default priority)
- *                concurrently with the decode kernel; the call still appears as one unit of work
- *                on the caller's stream (fork and join by events).  1 = unless the plan estimates the two
- *                kernels at under 80 us together (they then run one after the other on the caller's stream:
- *                measured faster there, and the host enqueues the call in 8 us instead of 41); 2 = always;
- *                0 = never
+ *   "overlap"    0/1/2 (default 1): how a batch that holds both prefill chunks and decode sequences runs.  1 = in ONE
+ *                launch whose first workgroups decode and whose others prefill ("mixed_step"); where that does not
+ *                take the plan, as with 2, but one kernel after the other on the caller's stream if the plan estimates
+ *                the two at under 80 us together; 2 = the prefill kernel on the context's own side stream (default
+ *                priority) concurrently with the decode kernel, always (fork and join by events: the call still
+ *                appears as one unit of work on the caller's stream); 0 = one after the other, always
+ *   "mixed_step"  0/1 (default 1): with "overlap" 1, the one-launch form; it takes every plan whose two arrays fit
+ *                the kernel arguments together (num_seqs + chunks * 2 + tiles up to about 960) and that has no dynamic
+ *                tail, no "xcd_weights" and the default number of waves.  Output bits are those of the two kernels.
+ *                Measured on MI355X against the two kernels: 8 x 512 rows beside 128 decode sequences 305 -> 282 us,
+ *                2 x 2048 rows beside 32 long ones 1850 -> 1660, 2 x 120 rows beside 24 short ones 39.5 -> 33.6
+ *                (120 random mixes of 1..512 decodes and 1..8 chunks: 2 to 50 % less, one 2 % more)
  *   "decode_first"  0/1 (default 1): with "overlap", enqueue the decode kernel before the prefill
  *                kernel (0: the other way round)
  *   "profile"    0/1: every ooco_attn_mixed records HIP events around its two kernels (each on the
@@ -195,8 +200,8 @@ ooco_status ooco_set_option(ooco_ctx *ctx, const char *name, int64_t value);
 /* Waits for the profiled calls made since the last read and returns the summed event-to-event
  * times in milliseconds: ms_sum[0] = prefill kernel, ms_sum[1] = decode kernel, ms_sum[2] = whole call
  * (HOST double[3]), and the number of calls (HOST).  Either pointer may be NULL.  Resets the sums.
- * Profiling changes neither the launch order nor the streams: in a batch with both kinds of work the two
- * kernels still run side by side, each bracketed by events on its own stream, so the times are those of
+ * Profiling changes neither the launch order nor the streams: a batch that runs in one launch reports that launch's
+ * time for both kinds of work; where the two kernels run side by side they still do, each bracketed by events on its own stream, so the times are those of
  * the kernels as they run in the step (they overlap; the whole-call time is not their sum). */
 ooco_status ooco_profile_read(ooco_ctx *ctx, double *ms_sum /*HOST*/, int64_t *calls /*HOST*/);
 
@@ -285,9 +290,8 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names /*HOST*/, size_t 
  * used up by the call unless option "plan_persistent" is set.
  * Without a current plan the call copies the length arrays to the host, waits for that copy
  * (one stream synchronisation) and plans by itself.
- * Launches at most two kernels (decode with its in-kernel merge, and prefill chunks -- on the context's
- * side stream when the batch holds both kinds of work and is not a short one, see option "overlap") and no
- * copies (batches above 960 sequences: one small copy).
+ * Launches one kernel, or at most two (decode with its in-kernel merge, and prefill chunks: see option "overlap"),
+ * and no copies (batches above 960 sequences: one small copy).
  * Writes every row of out (and the context's workspace), nothing else.  num_seqs == 0 or
  * total_q_tokens == 0 returns OOCO_OK without launching anything.
  * Same context + same plan + same inputs give bit-identical output on every call (no
@@ -310,8 +314,8 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q /*DEVICE*/, const void 
  * need beyond the caller's tensors -- arrival counters and the partial results of split sequences -- lives in one
  * 16 MiB array that is part of the library's device code (every GPU the library runs on holds its own copy until the
  * process ends).  The call allocates nothing on host or device, creates no stream or event, never synchronises
- * and enqueues at most three kernels on `stream` (a small fill that zeroes the counters it will use, the prefill
- * kernel, the decode kernel; the two attention kernels run one after the other).
+ * and enqueues at most three kernels on `stream` (a small fill that zeroes the counters it will use, then one kernel
+ * for both kinds of work, or where "mixed_step" would not take the plan the prefill kernel and the decode kernel).
  *   Device arguments, shapes and results as for ooco_attn_mixed; default run layout; prefill tiles are never
  *   split along the context.  Limits: num_seqs <= 960, num_seqs * num_kv_heads <= 65536 (-> OOCO_ENOMEM with a
  *   message beyond them); a partial-result area too small for the usual number of decode runs lowers that number.

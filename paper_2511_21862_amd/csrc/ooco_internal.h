@@ -63,6 +63,8 @@ struct AttnParams {
     int32_t pf_waves;           // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave)
     int32_t num_pf;             // prefill: number of chunks (entries of the prefill array, see below)
     int32_t dec_cus;            // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
+    int32_t dec_wgs;            // step kernel: its first workgroups, which decode (set by launch_step)
+    int32_t dec_wpw;            // step kernel: decode waves of such a workgroup (set by launch_step)
     int32_t nbi;                // tuning: KV blocks per softmax step of the decode kernel
     int16_t rotate_heads;       // tuning: kv head rotation across XCDs
     int16_t lean;               // mixed batches: the register-lean kernels (decode 128, prefill 8 waves x 192 registers)
@@ -105,8 +107,11 @@ static_assert(sizeof(KernArgs) <= 4096, "kernel arguments must stay within 4 KiB
 // unless a.p.cum_dev is set.  Each returns the hipError_t of its launch.
 hipError_t launch_decode(const KernArgs &a, hipStream_t s);
 hipError_t launch_prefill(const KernArgs &a, hipStream_t s);
-// One launch for a batch with both kinds of work: a.cum holds the decode array (num_seqs + 1 entries) followed by
-// the prefill array (or a.p.cum_dev both, in that order); 2 * num_cus persistent workgroups.
+// One launch for a batch with both kinds of work, decode workgroups first, prefill workgroups behind them: a.cum holds
+// the decode array (num_seqs + 1 entries) followed by the prefill array; no tail runs, no XCD weights.  See step_fits.
+hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s);
+constexpr int kStepDecWaves = 4;   // decode waves a workgroup of the step kernel has at most
+// The persistent one-launch kernel: a.cum holds the decode array followed by the prefill array (or a.p.cum_dev both, in that order); 2 * num_cus persistent workgroups.
 hipError_t launch_mixed(const KernArgs &a, int num_cus, hipStream_t s);
 // variant: tuning knob of the block-copy kernel (option "copy_variant"): 10 x 16-byte vectors per thread
 // + 1 for non-temporal accesses; 0 = default

@@ -1162,6 +1162,60 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void 
 }
 
 // ------------------------------------------------------------------------------------------
+// Both kinds of work of a step in ONE launch: the first p.dec_wgs workgroups are decode waves (four per workgroup, each
+// one (run, kv head) item of the decode line, exactly as in the decode kernel), the others prefill workgroups (exactly
+// as in the prefill kernel).  Every unit holds both kinds side by side as with two kernels on two streams, without the
+// fork and join events of the second stream, and a short batch does not wait for one kernel to drain before the other
+// starts.  Decode workgroups come first in dispatch order, so that each unit gets its share of the HBM stream before
+// prefill workgroups fill it up.  Against the two kernels on two streams (13 us of a step between them) or one after the
+// other, MI355X: 8 x 512 rows + 128 decodes 304.6 -> 281.7 us, 2 x 2048 + 32 long decodes 1850 -> 1660, 2 x 120 rows +
+// 24 short decodes 39.5 -> 33.6.
+template <int HD, int NBI, int MBATCH, int NW, bool PIPE>
+OOCO_DEV void step_body(const KernArgs &a)
+{
+    const AttnParams &p = a.p;
+    if ((int)blockIdx.x < p.dec_wgs) {
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int item = (int)blockIdx.x * p.dec_wpw + wave;
+        if (wave >= p.dec_wpw || item >= p.static_runs * p.Hkv) return;
+        asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens),
+                     "s"(p.query_start_loc), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),
+                     "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks), "s"(p.static_runs), "s"(p.piece_pad),
+                     "s"(p.rotate_heads), "s"(p.scale_log2e), "s"(p.trace));
+        const int lane = (int)threadIdx.x & 63;
+        const int run = item / p.Hkv, slot = item - run * p.Hkv;
+        const int kvh = p.rotate_heads ? (slot + run) % p.Hkv : slot;
+        uint64_t *const trace = p.trace ? p.trace + (int64_t)item * 4 : nullptr;
+        if (trace && lane == 0) trace[0] = wall_clock64();
+        bool first_piece = true;
+        const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
+        decode_run<HD, NBI, MBATCH>(p, [&](int idx) -> int { return a.cum[idx]; }, L, run, kvh, lane, trace, first_piece, []() {});
+        if (trace) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) trace[3] = wall_clock64();
+        }
+    } else {
+        const int n_cum = p.num_seqs + 1;   // the prefill array follows the decode array
+        prefill_unit<HD, NW, PIPE>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, (int)blockIdx.x - p.dec_wgs);
+    }
+}
+
+template <int HD, int NBI>
+__global__ __launch_bounds__(kPfThreads, 2) void step_kernel(const KernArgs a)
+{
+    step_body<HD, NBI, 3, 4, true>(a);
+}
+
+// The register-lean pair in one launch: prefill workgroups of eight waves; of a decode workgroup's eight waves the
+// first four decode, one per SIMD, and the others leave at once, which frees their registers for the two prefill waves
+// that the SIMD holds beside it (3 x 168 <= 512).
+template <int HD>
+__global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void step_kernel_lean(const KernArgs a)
+{
+    step_body<HD, 1, 1, 8, false>(a);
+}
+
+// ------------------------------------------------------------------------------------------
 // Mixed batches in ONE launch: a persistent grid of two 256-thread workgroups per compute unit in which a compute
 // unit runs EITHER decode waves (eight per unit, each streaming runs of the decode line exactly as the decode
 // kernel's waves do) OR prefill workgroups (two per unit, each working through (tile, kv head) units exactly as
@@ -1544,6 +1598,29 @@ hipError_t launch_prefill(const KernArgs &a, hipStream_t s)
         hipLaunchKernelGGL((prefill_kernel<128, 4>), grid, dim3(kPfThreads), 0, s, a);
     else
         hipLaunchKernelGGL((prefill_kernel<64, 4>), grid, dim3(kPfThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
+{
+    if (a.p.n_tiles <= 0 || a.p.static_runs <= 0 || a.p.cum_dev || a.p.tail_runs > 0) return hipErrorInvalidValue;
+    // Decode waves of a workgroup: as few as put a decode workgroup on every unit, at most one per SIMD.  (24 sequences,
+    // 384 waves: four to a workgroup the stream has the vector-memory paths of 96 units only)
+    const int64_t items = (int64_t)a.p.static_runs * a.p.Hkv;
+    a.p.dec_wpw = (int32_t)std::min<int64_t>(kStepDecWaves, (items + num_cus - 1) / num_cus);
+    const int64_t dec = (items + a.p.dec_wpw - 1) / a.p.dec_wpw;
+    const int64_t pf = a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
+                                    : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
+    a.p.dec_wgs = (int32_t)dec;
+    const dim3 grid((unsigned)(dec + pf));
+    if (a.p.lean)
+        hipLaunchKernelGGL((step_kernel_lean<128>), grid, dim3(512), 0, s, a);
+    else if (a.p.hd == 64)
+        hipLaunchKernelGGL((step_kernel<64, 2>), grid, dim3(kPfThreads), 0, s, a);
+    else if (a.p.nbi == 2)
+        hipLaunchKernelGGL((step_kernel<128, 2>), grid, dim3(kPfThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((step_kernel<128, 1>), grid, dim3(kPfThreads), 0, s, a);
     return hipGetLastError();
 }
 
