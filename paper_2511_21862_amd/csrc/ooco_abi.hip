@@ -81,6 +81,7 @@ struct PlanGeometry {
     int64_t pf_split_opt = 0;   // parts per prefill tile; 0 = automatic
     int64_t piece_pad = 0;      // line units charged for starting a piece (see build_plan)
     int64_t pf_waves_opt = 0;   // waves per prefill workgroup: 4, 8, or 0 = automatic
+    int64_t coop_opt = 1;       // cooperative decode workgroups: 0 never, 1 by rule, 2 always
     int64_t lean_opt = 0;       // mixed batches: register-lean kernels (see HostPlan::lean)
     int64_t fused = 0;          // batches with both kinds of work run in the one-launch mixed kernel
     int64_t dec_cus_opt = 0;    // mixed kernel: compute units per XCD that decode; 0 = automatic
@@ -115,6 +116,7 @@ struct HostPlan {
     // a batch with both kinds of work whose two kernels, one after the other, are estimated to take under 80 us: they
     // then run in sequence on the caller's stream (the fork and join of the second stream cost more than they gain)
     bool brief = false;
+    int32_t coop = 0;            // decode runs are worked on by workgroups of four waves (decode_coop_kernel); kCoopBySequence: run i is sequence i
     int32_t nbi = 0;             // KV blocks per softmax step of the decode kernel that the plan asks for (0 = the kernel's default)
 };
 
@@ -149,9 +151,10 @@ constexpr size_t storage_ints(size_t seqs_cap) { return (seqs_cap + 1) + (2 * se
 // Run layout of the decode block line (see ooco_internal.h): how many static runs, their XCD weights, the dynamic tail,
 // the partial-result slots; fills out.static_runs / static_blocks / tail_runs / slots / cw / nbi.
 // dec_blocks: units of the line (blocks + piece pads), kv_blocks: KV blocks of all decode sequences, dec_seqs: decode
-// sequences that hold a block, lean: the batch runs the register-lean pair of kernels.
-void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks, int64_t kv_blocks, int64_t dec_seqs, bool lean,
-                      HostPlan &out)
+// sequences that hold a block, max_blocks: blocks of the longest, pf_wgs: (tile, kv head) pairs of the batch's prefill
+// part, lean: the batch runs the register-lean pair of kernels.
+void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks, int64_t kv_blocks, int64_t dec_seqs, int64_t max_blocks,
+                      int64_t pf_wgs, bool lean, HostPlan &out)
 {
     // static runs: by default three waves per CU (measured best on MI355X: enough loads in
     // flight to saturate HBM, few enough waves that start-up and partial results stay small)
@@ -162,29 +165,75 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     int64_t wave_slots = lean ? std::max<int64_t>(1, (int64_t)geo.num_cus * 4 / geo.Hkv) : out.dec_cus == 99 ? std::max<int64_t>(1, (int64_t)geo.num_cus * 4 / geo.Hkv)
                                : out.dec_cus > 0 ? std::max<int64_t>(1, (int64_t)out.dec_cus * kXcds * 8 / geo.Hkv)
                                                : std::max<int64_t>(1, (int64_t)geo.num_cus * 3 / geo.Hkv);
-    // A small batch (at most 36,864 (block, kv head) tiles of head_dim 128) cannot keep HBM busy anyway: what
-    // counts is the length of every wave's chain of dependent steps.  Two blocks per step and at most half the
-    // usual number of runs: one 8K-token sequence 21.0 -> 18.3 us, eight sequences (1121 blocks) 25.9 -> 21.4 us,
-    // sixteen (2277 blocks) 35.2 -> 31.9 us; from 32 sequences (5296 blocks) on the usual layout is faster.
-    // (between 24,576 and 36,864 tiles two thirds of the usual runs: 3814 blocks 49.2 -> 46.6 us; at 4739 blocks the
-    // two layouts are level)
     // A batch of SHORT sequences (24 blocks = 384 tokens on average, or fewer) is a line of many short pieces, each
     // with its own start (query vectors, first tiles): four waves per compute unit hide those better than three, and
     // one block per step wastes no padded step.  512 sequences of 128 tokens 58.5 -> 50.9 us, 900 of 64 71.9 -> 62.0,
     // 2048 of 256 403 -> 382, 1024 of 384 285 -> 275; 4096 of 512 tokens are faster with three waves (1430 / 1449 us).
-    const bool short_seqs = geo.hd == 128 && !lean && out.dec_cus == 0 && dec_seqs > 0 && kv_blocks <= 24 * dec_seqs;
-    const bool small = geo.hd == 128 && !lean && out.dec_cus == 0 && !short_seqs && kv_blocks * geo.Hkv <= 36864;
     // (up to 16,384 tiles of them two blocks per step, and as many runs as sequences even if those hold fewer than 16
     // blocks: 32 sequences of 128 tokens 13.0 -> 10.2 us, 64 of 256 15.2 -> 13.2, 128 of 128 17.7 -> 14.8; 128 of 384
     // tokens, 24,576 tiles: 34.5 / 33.7 us)
-    if (small) out.nbi = 2;
-    if (short_seqs) out.nbi = kv_blocks * geo.Hkv <= 16384 ? 2 : 1;
-    if (short_seqs && geo.segments_opt == 0) wave_slots = std::max<int64_t>(1, (int64_t)geo.num_cus * 4 / geo.Hkv);
-    const int64_t min_blocks = 16 * 128 / geo.hd;
-    if (small && geo.segments_opt == 0)
-        wave_slots = std::max<int64_t>(1, kv_blocks * geo.Hkv <= 24576 ? wave_slots / 2 : wave_slots * 2 / 3);
+    // A SMALL batch (at most 36,864 (block, kv head) tiles of head_dim 128) cannot keep HBM busy anyway: what counts
+    // is the chain start -> steps of a wave -> partial result -> merge.
+    //   * While a run holds two or fewer beginnings of sequences on average (beside a prefill part, whose workgroups
+    //     stretch the steps: one) its work is shared by the four waves of a workgroup (decode_coop_kernel), one
+    //     workgroup per unit: one sequence of 1000 tokens 11.1 -> 7.8 us, of 4000 14.1 -> 10.0, of 16,000 24.1 -> 18.8,
+    //     four of 2000..4000 20.1 -> 16.2, sixteen of them 37.7 -> 36.2 (4 kv heads: 25.3 -> 22.8); with more pieces
+    //     than that every piece's start costs four waves: 32 of 1000..2000 tokens 38.3 against 36.1 in single waves.
+    //     Runs of 16 blocks at least -- 8 where the sequences are of 64 blocks or fewer on average and so have few parts
+    //     to merge (four of 500..1000 tokens 11.3 -> 8.5 us, but one of 4000 10.0 -> 12.3).
+    //   * Else single waves, two blocks per step, two waves per unit: 32 sequences of 1000..2000 tokens 37.6 -> 36.1,
+    //     64 of 300..900 35.0 -> 31.8.
+    // (head_dim 64: a tile is half as large, the limits in blocks are the same)
+    const int64_t tiles = kv_blocks * geo.Hkv * geo.hd / 128;
+    const bool plain = !lean && out.dec_cus == 0 && dec_seqs > 0;
+    const bool short_seqs = plain && kv_blocks <= 24 * dec_seqs;
+    const bool small = plain && tiles <= 36864;
+    const int64_t per_unit = std::max<int64_t>(1, (int64_t)geo.num_cus / geo.Hkv);   // runs that put one workgroup (of one kv head) on every unit
+    const bool coop_can = plain && geo.tail_pct == 0 && geo.xcd_cw[kXcds - 1] == 0;
+    const bool coop_rule = small && (short_seqs ? dec_seqs == 1 : dec_seqs * (pf_wgs > 0 ? 1 : 2) <= per_unit);
+    // A batch of a few short sequences takes one workgroup per (sequence, kv head) and cuts nothing: no partial results,
+    // no arrival counters, no merge through memory.  Up to 768 tokens (48 blocks of head_dim 128: six steps of the four
+    // waves; sixteen sequences of 300..600 tokens 13.5 -> 10.3 us, 32 of 200..500 16.7 -> 11.0, four of 60..200
+    // 9.8 -> 5.1; one of 1000 tokens is faster cut, 13.0 against 7.8) and four workgroups per unit (256 sequences of
+    // 100..300 tokens and 4 kv heads 30.9 -> 28.2, with 8 kv heads 46.0 -> 51.4) -- two beside a prefill part, whose
+    // workgroups wait behind them (128 of 60..200 tokens, 4 kv heads, beside 100 rows 20.3 against 23.0).
+    if (coop_can && geo.coop_opt && geo.segments_opt == 0 && max_blocks * geo.hd <= 48 * 128 &&
+        (int64_t)num_seqs * geo.Hkv <= (pf_wgs > 0 ? 2 : 4) * (int64_t)geo.num_cus) {
+        out.coop = kCoopBySequence;
+        out.nbi = geo.hd == 128 ? 2 : 0;
+        out.static_runs = num_seqs;
+        out.static_blocks = (int32_t)dec_blocks;
+        return;
+    }
+    out.coop = coop_can && (geo.coop_opt >= 2 || (geo.coop_opt == 1 && coop_rule));
+    if (geo.hd == 128 && short_seqs)
+        out.nbi = tiles <= 16384 ? 2 : 1;
+    else if (geo.hd == 128 && small)
+        out.nbi = 2;
+    int64_t min_blocks = 16 * 128 / geo.hd, at_least = 0;   // blocks of a run; runs whatever they hold
+    if (out.coop) {
+        // (beside a prefill part longer runs, which leave it units: one sequence of 16,000 tokens, 4 kv heads, beside
+        // 100 rows 23.4 -> 16.9 us)
+        wave_slots = per_unit;
+        min_blocks = kv_blocks > 512 * dec_seqs || (pf_wgs > 0 && kv_blocks > 256) ? 32 : pf_wgs > 0 || kv_blocks <= 16 || kv_blocks > 64 * dec_seqs ? 16 : 8;
+        if (short_seqs) at_least = dec_seqs;
+    } else if (short_seqs && (geo.hd == 128 || small)) {
+        wave_slots = std::max<int64_t>(1, (int64_t)geo.num_cus * 4 / geo.Hkv);
+        min_blocks = 16;
+        at_least = dec_seqs;
+        // sequences of unequal lengths, of six blocks or more on average: runs that do not follow them anyway may as well
+        // be short, up to two waves per unit (sixteen of 60..200 tokens 10.5 -> 8.6 us; head_dim 64: 64 of them
+        // 18.7 -> 7.8; three waves per unit: 64 of 16..292 tokens, four layers, 48.9 -> 52.1).  Beside a prefill part
+        // runs of 12 blocks (100 rows and 32 of 100..400 tokens, 4 kv heads, 14.7 us, with runs of 4 blocks 18.5).
+        if (tiles <= 16384 && max_blocks * dec_seqs > kv_blocks + kv_blocks / 4 && kv_blocks >= 6 * dec_seqs)
+            at_least = std::max(at_least, std::min<int64_t>((int64_t)geo.num_cus * 2 / geo.Hkv, kv_blocks / (pf_wgs > 0 ? 12 : 4)));
+    } else if (small) {
+        // (head_dim 64 keeps three: 363 sequences of 770 tokens on average 58.3 against 69.9 us with two)
+        wave_slots = std::max<int64_t>(1, (int64_t)geo.num_cus * (geo.hd == 128 ? 2 : 3) / geo.Hkv);
+        min_blocks = pf_wgs > 0 ? 24 : 16;
+    }
     int64_t runs = geo.segments_opt > 0 ? geo.segments_opt
-                                        : std::min<int64_t>(wave_slots, std::max<int64_t>((kv_blocks + min_blocks - 1) / min_blocks, short_seqs ? dec_seqs : 0));
+                                        : std::min<int64_t>(wave_slots, std::max<int64_t>((kv_blocks + min_blocks - 1) / min_blocks, at_least));
     runs = std::max<int64_t>(1, std::min<int64_t>(runs, dec_blocks));
     for (;;) {
         // weighted runs come in groups of one run per XCD
@@ -427,7 +476,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     // runs cut the line into equal lengths, so a run that starts several pieces streams correspondingly fewer
     // blocks (starting a piece costs a wave about as long as streaming three 8 KiB tiles).
     int64_t dec_blocks = 0, kv_blocks = 0, tiles = 0, tile_steps = 0, max_tile_steps = 1;
-    int64_t dec_seqs = 0;    // decode sequences that hold at least one block
+    int64_t dec_seqs = 0, max_dec_blocks = 0;    // decode sequences that hold at least one block, blocks of the longest
     double pf_pairs = 0.0;   // visible (query row, key) pairs of all prefill chunks
     const int64_t pad = geo.piece_pad;
     // Waves per prefill workgroup.  Eight waves share every K/V tile staged in LDS among 256 query columns instead
@@ -484,6 +533,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
             dec_blocks += nb + pad;
             kv_blocks += nb;
             dec_seqs += nb > 0;
+            max_dec_blocks = std::max(max_dec_blocks, nb);
         }
         if (ql > 1) {
             pf_pairs += (double)ql * (double)h_ctx_lens[i] + (double)ql * (double)(ql + 1) / 2.0;
@@ -575,7 +625,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         out.dec_cus = dec;
     }
     // ---- run layout of the decode block line (see plan_decode_runs)
-    if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, lean, out);
+    if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, max_dec_blocks, tiles * geo.Hkv, lean, out);
     // ---- prefill tiles cut along the context (see plan_prefill_parts)
     if (tiles > 0) {
         const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, pf_waves, dec_blocks, kv_blocks, pf_pairs};
@@ -586,11 +636,11 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
 
 // Whether the step kernel can run the plan: both kinds of work, both arrays together in the kernel arguments, no
 // dynamic tail and no XCD weights, and decode waves that it is instantiated for (nbi: KV blocks per softmax step).
-bool step_fits(const HostPlan &pl, int hd, int nbi)
+bool step_fits(const HostPlan &pl, int hd, bool coop, int nbi)
 {
     return pl.n_tiles > 0 && pl.static_runs > 0 && pl.tail_runs == 0 && pl.cw[kXcds - 1] == 0 && pl.dec_cus == 0 &&
            (size_t)pl.num_seqs + 1 + pl.pf_size <= (size_t)kInlineSeqs + 1 &&
-           (pl.lean ? hd == 128 && pl.pf_waves == 8 : pl.pf_waves == 4 && (nbi == 2 || (nbi == 1 && hd == 128)));
+           (pl.lean ? hd == 128 && pl.pf_waves == 8 : pl.pf_waves == 4 && (coop || nbi == 2 || (nbi == 1 && hd == 128)));
 }
 
 // Pieces of the decode line as the kernel walks them (host mirror of the device logic).
@@ -603,7 +653,11 @@ std::vector<Piece> enumerate_pieces(const HostPlan &pl)
     const RunLayout L = {pl.dec_blocks, pl.static_blocks, pl.static_runs, pl.tail_runs, pl.cw};
     for (int32_t k = 0; k < pl.static_runs + pl.tail_runs; ++k) {
         int32_t lo, hi;
-        run_bounds(L, k, lo, hi);
+        if (pl.coop == kCoopBySequence)
+            lo = pl.dcum[(size_t)k], hi = pl.dcum[(size_t)k + 1];
+        else
+            run_bounds(L, k, lo, hi);
+        if (lo >= hi) continue;
         int seq = 0;
         while (pl.dcum[(size_t)seq + 1] <= lo) ++seq;
         int64_t pos = lo;
@@ -705,6 +759,7 @@ struct ooco_ctx {
     int64_t opt_lean = 1;           // mixed batches: the register-lean kernels (0 never, 1 automatic, 2 always)
     int64_t opt_pf_waves = 0;       // waves per prefill workgroup: 0 = automatic, 4, 8
     int64_t opt_fused = 0;          // mixed batches in one launch (mixed kernel) instead of two kernels on two streams
+    int64_t opt_coop = 1;           // cooperative decode workgroups (0 never, 1 by rule, 2 always)
     int64_t opt_step = 1;           // mixed batches in one launch of the step kernel (0 never, 1 by rule, 2 whenever it takes the plan)
     int64_t opt_dec_cus = 0;        // mixed kernel: decoding compute units per XCD, 0 = automatic
     hipStream_t side_stream = nullptr;   // default priority; carries the prefill kernel of mixed batches
@@ -730,10 +785,13 @@ int decode_nbi(const ooco_ctx *ctx)
 {
     return ctx->opt_nbi ? (int)ctx->opt_nbi : ctx->plan.nbi ? ctx->plan.nbi : (ctx->hd == 64 ? 2 : 1);
 }
+// Whether its runs are worked on by cooperative workgroups (a number of blocks per step forced after the plan takes
+// single waves on the same runs where it can).
+int decode_coop(const ooco_ctx *ctx) { return ctx->plan.coop == kCoopBySequence || ctx->opt_nbi == 0 ? ctx->plan.coop : 0; }
 // Whether the current plan runs in one launch of the step kernel ("overlap" 0 and 2 ask for two kernels).
 bool runs_as_step(const ooco_ctx *ctx)
 {
-    return ctx->opt_step && ctx->opt_overlap == 1 && step_fits(ctx->plan, ctx->hd, decode_nbi(ctx));
+    return ctx->opt_step && ctx->opt_overlap == 1 && step_fits(ctx->plan, ctx->hd, decode_coop(ctx) != 0, decode_nbi(ctx));
 }
 
 ooco_status fail(const ooco_ctx *ctx, ooco_status code, const char *fmt, ...)
@@ -926,6 +984,8 @@ ooco_status ooco_set_option(ooco_ctx *ctx, const char *name, int64_t value)
     }
     else if (!strcmp(name, "mixed_lean"))
         ctx->opt_lean = value;
+    else if (!strcmp(name, "decode_coop"))
+        ctx->opt_coop = value;
     else if (!strcmp(name, "mixed_fused"))
         ctx->opt_fused = value;
     else if (!strcmp(name, "mixed_dec_cus"))
@@ -1009,6 +1069,7 @@ ooco_status ooco_plan(ooco_ctx *ctx, int num_seqs, const int32_t *h_seq_lens, co
     geo.piece_pad = ctx->opt_piece_pad;
     geo.pf_waves_opt = ctx->opt_pf_waves;
     geo.lean_opt = ctx->opt_lean;
+    geo.coop_opt = ctx->opt_nbi ? 0 : ctx->opt_coop;   // (a forced number of blocks per step asks for single waves)
     geo.fused = ctx->opt_fused && ctx->opt_overlap;
     geo.dec_cus_opt = ctx->opt_dec_cus;
     geo.pf_table_opt = ctx->opt_pf_table;
@@ -1143,15 +1204,19 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
     if (!names || cap == 0) return fail(ctx, OOCO_EINVAL, "ooco_plan_kernels: no buffer");
     const HostPlan &pl = ctx->plan;
     const bool dec = pl.static_runs > 0, pf = pl.n_tiles > 0;
-    const int nbi = decode_nbi(ctx);
+    const bool coop = decode_coop(ctx) != 0;
+    const int nbi = coop ? 256 / ctx->hd : decode_nbi(ctx);
     char d[64] = "", f[64] = "";
     if (runs_as_step(ctx))
-        snprintf(d, sizeof d, pl.lean ? "step_kernel_lean<%d>" : "step_kernel<%d, %d>", ctx->hd, nbi);
+        snprintf(d, sizeof d, pl.lean ? "step_kernel_lean<%d>" : coop ? "step_kernel<%d, %d, true>" : "step_kernel<%d, %d, false>", ctx->hd,
+                 nbi);
     else if (dec && pf && pl.dec_cus > 0)
         snprintf(d, sizeof d, "mixed_kernel<%d>", ctx->hd);
     else {
         if (dec && pl.lean)
             snprintf(d, sizeof d, "decode_kernel_lean<%d>", ctx->hd);
+        else if (dec && coop)
+            snprintf(d, sizeof d, "decode_coop_kernel<%d, %d>", ctx->hd, nbi);
         else if (dec)
             snprintf(d, sizeof d, "decode_kernel<%d, %d>", ctx->hd, nbi);
         if (pf && pl.lean && pl.pf_waves == 8)
@@ -1276,10 +1341,11 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     p.queue_base = ctx->queue_base;
     p.n_tiles = pl.n_tiles;
     p.num_pf = pl.num_pf;
-    p.dec_cus = pl.dec_cus;
-    p.pf_waves = pl.pf_waves;
+    p.dec_cus = (int16_t)pl.dec_cus;
+    p.pf_waves = (int16_t)pl.pf_waves;
     p.nbi = ctx->opt_nbi ? (int32_t)ctx->opt_nbi : pl.nbi;
     p.rotate_heads = (int16_t)(ctx->opt_rotate != 0);
+    p.coop = (int16_t)decode_coop(ctx);
     p.lean = (int16_t)pl.lean;
     for (int k = 0; k < kXcds; ++k) p.xcd_cw[k] = pl.cw[k];
 
@@ -1488,8 +1554,9 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.queue_base = 0;
     p.n_tiles = pl.n_tiles;
     p.num_pf = pl.num_pf;
-    p.pf_waves = pl.pf_waves;
+    p.pf_waves = (int16_t)pl.pf_waves;
     p.nbi = pl.nbi;
+    p.coop = (int16_t)pl.coop;
     p.rotate_heads = 1;
     p.pf_acc = nullptr;
     p.pf_ml = nullptr;
@@ -1500,8 +1567,8 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // The array keeps whatever the last call on this GPU left: the arrival counters this call will count in
     // start at zero (a small fill kernel, not a memset node, so that the call can be captured into a graph).
-    if (pl.static_runs > 1) e = launch_fill_zero(counters, (int64_t)num_seqs * num_kv_heads, s);
-    if (e == hipSuccess && step_fits(pl, head_dim, pl.nbi ? pl.nbi : (head_dim == 64 ? 2 : 1))) {
+    if (pl.slots > 0) e = launch_fill_zero(counters, (int64_t)num_seqs * num_kv_heads, s);
+    if (e == hipSuccess && step_fits(pl, head_dim, pl.coop, pl.nbi ? pl.nbi : (head_dim == 64 ? 2 : 1))) {
         // both kinds of work side by side in one launch: a step of four decodes and one prompt 16.6 -> 11.4 us
         memcpy(ka.cum, pl.dcum, ((size_t)num_seqs + 1) * sizeof(int32_t));
         memcpy(ka.cum + num_seqs + 1, pl.pf, pl.pf_size * sizeof(int32_t));

@@ -60,13 +60,14 @@ struct AttnParams {
     int32_t dec_blocks, static_blocks, static_runs, tail_runs;   // decode run layout
     int32_t piece_pad;   // line units in front of every decode sequence's blocks (the cost of starting a piece)
     int32_t n_tiles;            // prefill: tiles per kv head
-    int32_t pf_waves;           // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave)
     int32_t num_pf;             // prefill: number of chunks (entries of the prefill array, see below)
-    int32_t dec_cus;            // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
     int32_t dec_wgs;            // step kernel: its first workgroups, which decode (set by launch_step)
-    int32_t dec_wpw;            // step kernel: decode waves of such a workgroup (set by launch_step)
+    int16_t dec_cus;            // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
+    int16_t pf_waves;           // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave)
+    int16_t dec_wpw;            // step kernel: decode waves of such a workgroup (set by launch_step)
     int32_t nbi;                // tuning: KV blocks per softmax step of the decode kernel
     int16_t rotate_heads;       // tuning: kv head rotation across XCDs
+    int16_t coop;               // decode: workgroups of four waves that share every piece of a run (decode_coop_kernel): 1, kCoopBySequence, or 0
     int16_t lean;               // mixed batches: the register-lean kernels (decode 128, prefill 8 waves x 192 registers)
     uint16_t xcd_cw[8];         // cumulative XCD weights of the static runs (RunLayout::cw); zeros = equal runs
     uint32_t queue_base;        // ticket value at which this launch's tail runs start
@@ -96,6 +97,8 @@ __host__ __device__ inline int entry_tile(int32_t e) { return (int)(((uint32_t)e
 __host__ __device__ inline int entry_part(int32_t e) { return (int)(((uint32_t)e >> 20) & 63u); }
 __host__ __device__ inline int entry_parts(int32_t e) { return (int)(((uint32_t)e >> 26) & 63u) + 1; }
 static_assert(kSortedTiles <= 1024, "tile and chunk indices of a list entry have 10 bits");
+
+constexpr int kCoopBySequence = 2;   // AttnParams::coop: run i of the line is sequence i, whole, whatever its length
 
 struct KernArgs {
     AttnParams p;

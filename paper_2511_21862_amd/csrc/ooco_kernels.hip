@@ -17,6 +17,7 @@
 #include "ooco_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ooco {
 
@@ -30,6 +31,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 #define OOCO_DEV __device__ __forceinline__
+
+constexpr int kNoVmem = 0x78F;   // sched_barrier mask: everything but vector-memory operations may cross
 
 OOCO_DEV uint32_t pack2_bf16(float a, float b)
 {
@@ -229,11 +232,12 @@ OOCO_DEV int count_le(CumAt cum_at, int n, int x, int lane)
 // stores (acc, m, l) in fp32 into partial slot k + seq, then bumps the arrival counter of
 // (seq, kv head); the piece that arrives last merges all slots of the sequence in slot order
 // (so the result does not depend on which piece is last) and resets the counter.
-// One run of the decode line for one kv head, all its pieces, executed by one wave (see above).
-// `at_stream_end()` is called once the last piece of the run has been streamed, before its epilogue.
-template <int HD, int NBI, int MBATCH, class CumAt, class AtStreamEnd>
-OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, int run, int kvh, int lane, uint64_t *trace,
-                         bool &first_piece, AtStreamEnd at_stream_end)
+// The blocks [blk_begin, blk_begin + nblk) of sequence seq (not none) against its query row, streamed by wave `wave` of NW
+// waves that take steps of NBI blocks in turn: un-normalised output O, running maximum m (the same in the four rows of a
+// lane column) and this lane's share lsum of the sum, as laid out above.  A wave without a step has (0, -inf, 0).
+template <int HD, int NBI, int NW>
+OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin, int nblk, int seq_len, int q_row, int wave,
+                            int lane, uint64_t *trace, bool &first_piece, f32x4 (&O)[HD / 16], float &m, float &lsum)
 {
     constexpr int KC = HD / 32;
     constexpr int NB = HD / 16;
@@ -241,6 +245,163 @@ OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, 
     const int kq = lane >> 4;
     const int g = p.g;
     const int64_t tile_elems = (int64_t)HD * kBlockSize;   // one (block, kv head) tile
+    const int head = kvh * g + col;
+    const int nstep = ((nblk + NBI - 1) / NBI - wave + NW - 1) / NW;   // of this wave
+    if (NW > 1 && nstep <= 0) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m = -INFINITY;
+        lsum = 0.f;
+        return;
+    }
+    // block (of the piece) that is this wave's i-th
+    auto blk_of = [&](int i) -> int { return NW == 1 ? i : (i / NBI * NW + wave) * NBI + i % NBI; };
+
+    // Q as B operand: head col, dims 32c + 8kq .. +8
+    u32x4 qb[KC];
+    {
+        const u32x4 *qp = reinterpret_cast<const u32x4 *>(p.q + ((int64_t)q_row * p.Hq + (col < g ? head : 0)) * HD);
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+            u32x4 t = qp[c * 4 + kq];
+            qb[c] = (col < g) ? t : u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    // rolling window of the physical ids of this wave's next 64 blocks, one per lane
+    const int32_t *table = p.block_tables + (int64_t)seq * p.max_blocks_per_seq + blk_begin;
+    int wbase = 0;
+    int idv = table[min(blk_of(lane), nblk - 1)];
+    int idn = table[min(blk_of(64 + lane), nblk - 1)];
+
+    u32x4 kreg[NBI][KC];
+    u32x2 vreg[NBI][NB];
+    int64_t offs[NBI];
+    auto tile_off = [&](int j) -> int64_t {   // j (of this wave's blocks) is wave-uniform and non-decreasing
+        if (j - wbase >= 64) {
+            wbase += 64;
+            idv = idn;
+            asm volatile("" : "+v"(idv));   // (waited for here, in the rare path, and not where the ids are used)
+            idn = table[min(blk_of(wbase + 64 + lane), nblk - 1)];
+        }
+        const int pb = __builtin_amdgcn_readlane(idv, j - wbase);
+        return ((int64_t)pb * p.Hkv + kvh) * tile_elems;
+    };
+    // K and V tiles are read once per kv head and never again in this launch: they are loaded with the
+    // non-temporal policy (`nt`), so that the stream does not push other data out of the caches on its way
+    // through them.  Measured on MI355X: 64 sequences 115.7 -> 103.3 us, 512 sequences 1.149 -> 1.030 ms
+    // (6.1 -> 6.8 TB/s).
+    // Loads are issued unconditionally (steps past the end re-read the last block, an L2 hit)
+    // so that every step has the same number of loads in flight and the waits before the
+    // MFMAs can leave the younger loads outstanding.
+    auto issue_k = [&](int step) {
+#pragma unroll
+        for (int u = 0; u < NBI; ++u) {
+            offs[u] = tile_off(min(step * NBI + u, NW == 1 ? nblk - 1 : nstep * NBI - 1));
+            const u32x4 *kp = reinterpret_cast<const u32x4 *>(p.k_cache + offs[u]);
+#pragma unroll
+            for (int c = 0; c < KC; ++c) kreg[u][c] = __builtin_nontemporal_load(&kp[c * 64 + lane]);
+        }
+    };
+    auto issue_v = [&]() {
+#pragma unroll
+        for (int u = 0; u < NBI; ++u) {
+            const u32x2 *vp = reinterpret_cast<const u32x2 *>(p.v_cache + offs[u]);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) vreg[u][nb] = __builtin_nontemporal_load(&vp[(nb * 16 + col) * 4 + kq]);
+        }
+    };
+
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m = -INFINITY;
+    lsum = 0.f;
+
+    issue_k(0);
+    // The K loads stay ahead of the V loads also here: the waits of the loop are the longest that either way into it
+    // needs, and K loads that the scheduler moves behind V loads make every step wait for the V tiles before its scores.
+    __builtin_amdgcn_sched_barrier(kNoVmem);
+    issue_v();
+    if (trace && first_piece) {   // time at which the first K/V tiles of the wave have arrived
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) trace[1] = wall_clock64();
+        first_piece = false;
+    }
+    for (int t = 0; t < nstep; ++t) {
+        f32x4 S[NBI];
+#pragma unroll
+        for (int u = 0; u < NBI; ++u) {
+            S[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+                S[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kreg[u][c]),
+                                                               __builtin_bit_cast(bf16x8, qb[c]), S[u], 0, 0, 0);
+        }
+        issue_k(min(t + 1, nstep - 1));
+        float mloc = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < NBI; ++u) {
+            const int j = blk_of(t * NBI + u);
+            int nvalid = seq_len - (blk_begin + j) * kBlockSize;
+            if (NBI > 1 && j >= nblk) nvalid = 0;
+            if (nvalid < kBlockSize) {   // wave-uniform: tail block of the sequence, or past the piece
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[u][r] = (4 * kq + r < nvalid) ? S[u][r] * p.scale_log2e : -INFINITY;
+                const uint32_t m0 = (4 * kq + 0 < nvalid ? 0x0000FFFFu : 0u) | (4 * kq + 1 < nvalid ? 0xFFFF0000u : 0u);
+                const uint32_t m1 = (4 * kq + 2 < nvalid ? 0x0000FFFFu : 0u) | (4 * kq + 3 < nvalid ? 0xFFFF0000u : 0u);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    vreg[u][nb][0] &= m0;
+                    vreg[u][nb][1] &= m1;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[u][r] *= p.scale_log2e;
+            }
+            mloc = fmaxf(mloc, fmaxf(fmaxf(S[u][0], S[u][1]), fmaxf(S[u][2], S[u][3])));
+        }
+        mloc = rows_max(mloc);
+        const float m_new = fmaxf(m, mloc);
+        const float alpha = fast_exp2(m - m_new);
+        const bool grow = m_new > m;
+        m = m_new;
+        float psum = 0.f;
+        s16x4 P[NBI];
+#pragma unroll
+        for (int u = 0; u < NBI; ++u) {
+            float e[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) e[r] = fast_exp2(S[u][r] - m_new);
+            psum += (e[0] + e[1]) + (e[2] + e[3]);
+            const u32x2 pk = {pack2_bf16(e[0], e[1]), pack2_bf16(e[2], e[3])};
+            P[u] = __builtin_bit_cast(s16x4, pk);
+        }
+        lsum = lsum * alpha + psum;
+        if (__any(grow)) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) O[nb][r] *= alpha;
+        }
+#pragma unroll
+        for (int u = 0; u < NBI; ++u)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                O[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, vreg[u][nb]), P[u],
+                                                                  O[nb], 0, 0, 0);
+        issue_v();
+    }
+}
+
+// One run of the decode line for one kv head, all its pieces, executed by one wave (see above).
+// `at_stream_end()` is called once the last piece of the run has been streamed, before its epilogue.
+template <int HD, int NBI, int MBATCH, class CumAt, class AtStreamEnd>
+OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, int run, int kvh, int lane, uint64_t *trace,
+                         bool &first_piece, AtStreamEnd at_stream_end)
+{
+    constexpr int NB = HD / 16;
+    const int col = lane & 15;
+    const int kq = lane >> 4;
+    const int g = p.g;
     const int head = kvh * g + col;
     int lo, hi;
     run_bounds(L, run, lo, hi);
@@ -269,136 +430,9 @@ OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, 
         const int seq_len = p.seq_lens[seq];
         const int q_row = min(max(p.query_start_loc[seq], 0), p.total_q - 1);
 
-        // Q as B operand: head col, dims 32c + 8kq .. +8
-        u32x4 qb[KC];
-        {
-            const u32x4 *qp = reinterpret_cast<const u32x4 *>(p.q + ((int64_t)q_row * p.Hq + (col < g ? head : 0)) * HD);
-#pragma unroll
-            for (int c = 0; c < KC; ++c) {
-                u32x4 t = qp[c * 4 + kq];
-                qb[c] = (col < g) ? t : u32x4{0u, 0u, 0u, 0u};
-            }
-        }
-        // rolling window of 64 physical block ids, one per lane
-        const int32_t *table = p.block_tables + (int64_t)seq * p.max_blocks_per_seq + blk_begin;
-        int wbase = 0;
-        int idv = table[min(lane, nblk - 1)];
-        int idn = table[min(64 + lane, nblk - 1)];
-
-        u32x4 kreg[NBI][KC];
-        u32x2 vreg[NBI][NB];
-        int64_t offs[NBI];
-        auto tile_off = [&](int j) -> int64_t {   // j is wave-uniform and non-decreasing
-            if (j - wbase >= 64) {
-                wbase += 64;
-                idv = idn;
-                idn = table[min(wbase + 64 + lane, nblk - 1)];
-            }
-            const int pb = __builtin_amdgcn_readlane(idv, j - wbase);
-            return ((int64_t)pb * p.Hkv + kvh) * tile_elems;
-        };
-        // K and V tiles are read once per kv head and never again in this launch: they are loaded with the
-        // non-temporal policy (`nt`), so that the stream does not push other data out of the caches on its way
-        // through them.  Measured on MI355X: 64 sequences 115.7 -> 103.3 us, 512 sequences 1.149 -> 1.030 ms
-        // (6.1 -> 6.8 TB/s).
-        // Loads are issued unconditionally (steps past the end re-read the last block, an L2 hit)
-        // so that every step has the same number of loads in flight and the waits before the
-        // MFMAs can leave the younger loads outstanding.
-        auto issue_k = [&](int step) {
-#pragma unroll
-            for (int u = 0; u < NBI; ++u) {
-                offs[u] = tile_off(min(step * NBI + u, nblk - 1));
-                const u32x4 *kp = reinterpret_cast<const u32x4 *>(p.k_cache + offs[u]);
-#pragma unroll
-                for (int c = 0; c < KC; ++c) kreg[u][c] = __builtin_nontemporal_load(&kp[c * 64 + lane]);
-            }
-        };
-        auto issue_v = [&]() {
-#pragma unroll
-            for (int u = 0; u < NBI; ++u) {
-                const u32x2 *vp = reinterpret_cast<const u32x2 *>(p.v_cache + offs[u]);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) vreg[u][nb] = __builtin_nontemporal_load(&vp[(nb * 16 + col) * 4 + kq]);
-            }
-        };
-
         f32x4 O[NB];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float m = -INFINITY, lsum = 0.f;
-
-        const int nstep = (nblk + NBI - 1) / NBI;
-        issue_k(0);
-        issue_v();
-        if (trace && first_piece) {   // time at which the first K/V tiles of the wave have arrived
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (lane == 0) trace[1] = wall_clock64();
-            first_piece = false;
-        }
-        for (int t = 0; t < nstep; ++t) {
-            f32x4 S[NBI];
-#pragma unroll
-            for (int u = 0; u < NBI; ++u) {
-                S[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = 0; c < KC; ++c)
-                    S[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kreg[u][c]),
-                                                                   __builtin_bit_cast(bf16x8, qb[c]), S[u], 0, 0, 0);
-            }
-            issue_k(min(t + 1, nstep - 1));
-            float mloc = -INFINITY;
-#pragma unroll
-            for (int u = 0; u < NBI; ++u) {
-                const int j = t * NBI + u;
-                int nvalid = seq_len - (blk_begin + j) * kBlockSize;
-                if (NBI > 1 && j >= nblk) nvalid = 0;
-                if (nvalid < kBlockSize) {   // wave-uniform: tail block of the sequence, or past the piece
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) S[u][r] = (4 * kq + r < nvalid) ? S[u][r] * p.scale_log2e : -INFINITY;
-                    const uint32_t m0 = (4 * kq + 0 < nvalid ? 0x0000FFFFu : 0u) | (4 * kq + 1 < nvalid ? 0xFFFF0000u : 0u);
-                    const uint32_t m1 = (4 * kq + 2 < nvalid ? 0x0000FFFFu : 0u) | (4 * kq + 3 < nvalid ? 0xFFFF0000u : 0u);
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        vreg[u][nb][0] &= m0;
-                        vreg[u][nb][1] &= m1;
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) S[u][r] *= p.scale_log2e;
-                }
-                mloc = fmaxf(mloc, fmaxf(fmaxf(S[u][0], S[u][1]), fmaxf(S[u][2], S[u][3])));
-            }
-            mloc = rows_max(mloc);
-            const float m_new = fmaxf(m, mloc);
-            const float alpha = fast_exp2(m - m_new);
-            const bool grow = m_new > m;
-            m = m_new;
-            float psum = 0.f;
-            s16x4 P[NBI];
-#pragma unroll
-            for (int u = 0; u < NBI; ++u) {
-                float e[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) e[r] = fast_exp2(S[u][r] - m_new);
-                psum += (e[0] + e[1]) + (e[2] + e[3]);
-                const u32x2 pk = {pack2_bf16(e[0], e[1]), pack2_bf16(e[2], e[3])};
-                P[u] = __builtin_bit_cast(s16x4, pk);
-            }
-            lsum = lsum * alpha + psum;
-            if (__any(grow)) {
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) O[nb][r] *= alpha;
-            }
-#pragma unroll
-            for (int u = 0; u < NBI; ++u)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    O[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, vreg[u][nb]), P[u],
-                                                                      O[nb], 0, 0, 0);
-            issue_v();
-        }
+        float m, lsum;
+        decode_stream<HD, NBI, 1>(p, kvh, seq, blk_begin, nblk, seq_len, q_row, 0, lane, trace, first_piece, O, m, lsum);
 
         if (trace && stop == hi && lane == 0) trace[2] = wall_clock64();   // end of streaming
         if (stop == hi) at_stream_end();
@@ -586,6 +620,188 @@ __global__ __launch_bounds__(64, 3) void decode_kernel_lean(const KernArgs a)
 }
 
 // ------------------------------------------------------------------------------------------
+// Cooperative decode: one workgroup of four waves per (run, kv head).  The waves share every piece of the run, step by
+// step in turn, and merge their four results in LDS; only a piece that does not cover its whole sequence goes through
+// the partial slots and the arrival counter, one part per workgroup, and the merge of those parts is done by all 256
+// threads.  For small batches, whose time is the length of the chain
+//   start -> steps of a wave, one after the other -> partial result -> arrival -> merge,
+// this makes the chain short at both ends: a quarter of the steps per wave and of the parts per sequence.  Measured on
+// MI355X against single waves: one sequence of 4000 tokens 14.1 -> 10.0 us, four of 60..200 (whole, nothing to merge
+// through memory) 9.8 -> 5.1, sixteen of 2000..4000 (155 MB, then bound by HBM) 37.7 -> 36.2.
+template <int HD>
+constexpr int kCoopStride = HD + 16;   // floats from one head's partial output to the next in LDS (16-byte writes of four
+                                       // heads' lanes then fall on 64 different banks)
+template <int HD>
+constexpr int kCoopFloats = 4 * 16 * kCoopStride<HD> + 4 * 16 * 2 + 4;   // LDS the four waves need
+
+template <int HD, int NBI, class CumAt>
+OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, int run, int kvh, float *lds,
+                              uint64_t *trace)
+{
+    constexpr int NB = HD / 16;
+    constexpr int STRIDE = kCoopStride<HD>;
+    constexpr int MAXU = (16 * HD / 4 + 255) / 256;   // 16-byte units of the output a thread may own
+    float *const l_ml = lds + 4 * 16 * STRIDE;
+    int *const l_last = reinterpret_cast<int *>(l_ml + 4 * 16 * 2);
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, kq = lane >> 4;
+    const int g = p.g, units = g * (HD / 4);
+    bool first_piece = wave == 0;
+    if (wave != 0) trace = nullptr;
+    int lo, hi, seq;
+    if (p.coop == kCoopBySequence) {   // run i is sequence i, whole
+        seq = run;
+        lo = cum_at(run);
+        hi = cum_at(run + 1);
+        if (trace && lo >= hi && lane == 0) trace[1] = trace[2] = wall_clock64();
+    } else {
+        run_bounds(L, run, lo, hi);
+        seq = count_le(cum_at, p.num_seqs, lo, lane);
+    }
+    int pos = lo;
+    while (pos < hi) {   // (everything here is the same in all four waves)
+        seq = __builtin_amdgcn_readfirstlane(seq);
+        int cs = cum_at(seq), ce = cum_at(seq + 1);
+        while (ce <= pos) {   // sequences without decode blocks
+            ++seq;
+            cs = ce;
+            ce = cum_at(seq + 1);
+        }
+        const int stop = min(hi, ce);
+        const int first = cs + p.piece_pad;
+        const int begin = max(pos, first);
+        if (begin >= stop) {   // the run ends before the first block of this sequence
+            if (trace && lane == 0) trace[2] = wall_clock64();
+            pos = stop;
+            continue;
+        }
+        const bool whole = (begin == first) && (stop == ce);
+        const int seq_len = p.seq_lens[seq];
+        const int q_row = min(max(p.query_start_loc[seq], 0), p.total_q - 1);
+        f32x4 O[NB];
+        float m, lsum;
+        decode_stream<HD, NBI, 4>(p, kvh, seq, begin - first, stop - begin, seq_len, q_row, wave, lane, trace, first_piece, O, m,
+                                  lsum);
+        if (trace && stop == hi && lane == 0) trace[2] = wall_clock64();
+        const float lw = rows_sum(lsum);
+        if (pos != lo) __syncthreads();   // the last piece's results have been read
+        if (col < g) {
+            float *o = lds + (wave * 16 + col) * STRIDE + 4 * kq;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<f32x4 *>(o + 16 * nb) = O[nb];
+            if (kq == 0) *reinterpret_cast<f32x2 *>(l_ml + (wave * 16 + col) * 2) = f32x2{m, lw};
+        }
+        __syncthreads();
+        auto put = [&](int hh, int d4, const f32x4 &acc, float l) {
+            const float inv = 1.0f / l;
+            uint16_t *op = p.out + ((int64_t)q_row * p.Hq + kvh * g + hh) * HD + 4 * d4;
+            *reinterpret_cast<u32x2 *>(op) = u32x2{pack2_bf16(acc[0] * inv, acc[1] * inv), pack2_bf16(acc[2] * inv, acc[3] * inv)};
+        };
+#pragma unroll
+        for (int i = 0; i < MAXU; ++i) {
+            const int u = tid + 256 * i;
+            if (u < units) {
+                const int hh = u / (HD / 4), d4 = u % (HD / 4);
+                f32x2 ml[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) ml[w] = *reinterpret_cast<const f32x2 *>(l_ml + (w * 16 + hh) * 2);
+                const float M = fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0]));
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                float l = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {   // in wave order
+                    const float wt = fast_exp2(ml[w][0] - M);
+                    const f32x4 o = *reinterpret_cast<const f32x4 *>(lds + (w * 16 + hh) * STRIDE + 4 * d4);
+                    l += ml[w][1] * wt;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[r] += o[r] * wt;
+                }
+                if (whole) {
+                    put(hh, d4, acc, l);
+                } else {
+                    const int64_t row = (int64_t)(run + seq) * p.Hq + kvh * g + hh;
+                    store_dev4(p.part_acc + row * HD + 4 * d4, acc);
+                    if (d4 == 0) store_dev2(p.part_ml + row * 2, M, l);
+                }
+            }
+        }
+        if (!whole) {
+            const int first_run = run_of(L, first);
+            const int nparts = run_of(L, (int64_t)ce - 1) - first_run + 1;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial has reached memory ...
+            __syncthreads();                                    // ... and so have the other waves'
+            int32_t *const counter = p.counters + (int64_t)seq * p.Hkv + kvh;
+            if (tid == 0) *l_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nparts - 1;
+            __syncthreads();
+            if (*l_last) {   // last part of this (sequence, kv head): merge, in slot order
+#pragma unroll
+                for (int i = 0; i < MAXU; ++i) {
+                    const int u = tid + 256 * i;
+                    if (u < units) {
+                        const int hh = u / (HD / 4), d4 = u % (HD / 4);
+                        float M = -INFINITY, l = 0.f;
+                        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                        auto merge = [&](auto batch, int j0) {   // parts j0 .. whose loads are on their way together
+                            constexpr int BATCH = decltype(batch)::value;
+                            f32x2 ml[BATCH], t[BATCH][2];
+#pragma unroll
+                            for (int b = 0; b < BATCH; ++b) {
+                                const int64_t row = (int64_t)(first_run + min(j0 + b, nparts - 1) + seq) * p.Hq + kvh * g + hh;
+                                ml[b] = load_dev2(p.part_ml + row * 2);
+                                t[b][0] = load_dev2(p.part_acc + row * HD + 4 * d4);
+                                t[b][1] = load_dev2(p.part_acc + row * HD + 4 * d4 + 2);
+                            }
+#pragma unroll
+                            for (int b = 0; b < BATCH; ++b) {
+                                if (j0 + b < nparts) {
+                                    const float M_new = fmaxf(M, ml[b][0]);
+                                    const float w_old = fast_exp2(M - M_new), w_new = fast_exp2(ml[b][0] - M_new);
+                                    M = M_new;
+                                    l = l * w_old + ml[b][1] * w_new;
+#pragma unroll
+                                    for (int r = 0; r < 4; ++r) acc[r] = acc[r] * w_old + t[b][r >> 1][r & 1] * w_new;
+                                }
+                            }
+                        };
+                        int j0 = 0;
+                        for (; j0 + 4 < nparts; j0 += 16) merge(std::integral_constant<int, 16>(), j0);
+                        if (j0 < nparts) merge(std::integral_constant<int, 4>(), j0);
+                        put(hh, d4, acc, l);
+                    }
+                }
+                if (tid == 0)   // ready for the next call
+                    __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        pos = stop;
+        ++seq;
+    }
+}
+
+template <int HD, int NBI>
+__global__ __launch_bounds__(256, 2) void decode_coop_kernel(const KernArgs a)
+{
+    const AttnParams &p = a.p;
+    __shared__ __align__(16) float lds[kCoopFloats<HD>];
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens), "s"(p.query_start_loc),
+                 "s"(p.cum_dev), "s"(p.trace), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),
+                 "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks), "s"(p.static_runs), "s"(p.piece_pad),
+                 "s"(p.rotate_heads), "s"(p.scale_log2e));
+    const int run = blockIdx.x / p.Hkv, slot = blockIdx.x - run * p.Hkv;
+    const int kvh = p.rotate_heads ? (slot + run) % p.Hkv : slot;
+    uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
+    if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
+    const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
+    decode_coop_run<HD, NBI>(p, [&](int idx) -> int { return p.cum_dev ? p.cum_dev[idx] : a.cum[idx]; }, L, run, kvh, lds, trace);
+    if (trace) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (threadIdx.x == 0) trace[3] = wall_clock64();
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Prefill chunk: one workgroup of four waves per (tile of query rows, kv head).  The 128 query
 // columns of a workgroup are the (row, head) pairs of tile_rows = 128/g consecutive query rows
 // and the g query heads that share the kv head (column c = row*g + head), 32 columns per wave,
@@ -626,6 +842,14 @@ OOCO_DEV int plan_entry(const KernArgs &a, int idx)
     return v;
 }
 
+// The K and V tiles of two steps, as one array (the cooperative decode workgroups of the step kernel use the same memory).
+template <int HD>
+OOCO_DEV u32x4 *stage_lds()
+{
+    __shared__ u32x4 lds[4 * kPfBlocks * HD * 2];
+    return lds;
+}
+
 // One workgroup's work on virtual block index `vb` (what blockIdx.x is in the stand-alone kernel): with the plan's
 // tile list, entry vb / Hkv of the list -- a (tile, part of its keys) pair -- for kv head vb % Hkv; without it, unit
 // vb / split = (tile, kv head), part vb % split of its keys.  `cum_at(i)` reads the prefill array of the plan.  All
@@ -648,8 +872,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     constexpr int CH = HD * 2;         // 16-byte chunks per (block, kv head) tile
     constexpr int STAGE = kPfBlocks * CH;               // chunks of one step's K (or V) tiles
     constexpr int NCP = STAGE / THREADS;                // chunks each thread moves per stage
-    __shared__ u32x4 ldsK[2][STAGE];
-    __shared__ u32x4 ldsV[2][STAGE];
+    u32x4 (*const ldsK)[STAGE] = reinterpret_cast<u32x4 (*)[STAGE]>(stage_lds<HD>()), (*const ldsV)[STAGE] = ldsK + 2;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1170,11 +1393,23 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void 
 // prefill workgroups fill it up.  Against the two kernels on two streams (13 us of a step between them) or one after the
 // other, MI355X: 8 x 512 rows + 128 decodes 304.6 -> 281.7 us, 2 x 2048 + 32 long decodes 1850 -> 1660, 2 x 120 rows +
 // 24 short decodes 39.5 -> 33.6.
-template <int HD, int NBI, int MBATCH, int NW, bool PIPE>
+template <int HD, int NBI, int MBATCH, int NW, bool PIPE, bool COOP>
 OOCO_DEV void step_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
-    if ((int)blockIdx.x < p.dec_wgs) {
+    if (COOP && (int)blockIdx.x < p.dec_wgs) {   // cooperative decode workgroups
+        static_assert(kCoopFloats<HD> * sizeof(float) <= 4 * kPfBlocks * HD * 2 * sizeof(u32x4), "fits the stage memory");
+        const int run = (int)blockIdx.x / p.Hkv, slot = (int)blockIdx.x - run * p.Hkv;
+        uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
+        if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
+        const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
+        decode_coop_run<HD, NBI>(p, [&](int idx) -> int { return a.cum[idx]; }, L, run, p.rotate_heads ? (slot + run) % p.Hkv : slot,
+                                 reinterpret_cast<float *>(stage_lds<HD>()), trace);
+        if (trace) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (threadIdx.x == 0) trace[3] = wall_clock64();
+        }
+    } else if (!COOP && (int)blockIdx.x < p.dec_wgs) {
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
         const int item = (int)blockIdx.x * p.dec_wpw + wave;
         if (wave >= p.dec_wpw || item >= p.static_runs * p.Hkv) return;
@@ -1200,10 +1435,10 @@ OOCO_DEV void step_body(const KernArgs &a)
     }
 }
 
-template <int HD, int NBI>
+template <int HD, int NBI, bool COOP>
 __global__ __launch_bounds__(kPfThreads, 2) void step_kernel(const KernArgs a)
 {
-    step_body<HD, NBI, 3, 4, true>(a);
+    step_body<HD, NBI, 3, 4, true, COOP>(a);
 }
 
 // The register-lean pair in one launch: prefill workgroups of eight waves; of a decode workgroup's eight waves the
@@ -1212,7 +1447,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void step_kernel(const KernArgs a)
 template <int HD>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void step_kernel_lean(const KernArgs a)
 {
-    step_body<HD, 1, 1, 8, false>(a);
+    step_body<HD, 1, 1, 8, false, false>(a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1559,6 +1794,13 @@ hipError_t launch_decode(const KernArgs &a, hipStream_t s)
 {
     if (a.p.static_runs <= 0 || a.p.dec_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)((int64_t)a.p.static_runs * a.p.Hkv)), block(64);
+    if (a.p.coop) {
+        if (a.p.hd == 128)
+            hipLaunchKernelGGL((decode_coop_kernel<128, 2>), grid, dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL((decode_coop_kernel<64, 4>), grid, dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
     if (a.p.lean && a.p.hd == 128) {
         hipLaunchKernelGGL((decode_kernel_lean<128>), grid, block, 0, s, a);
         return hipGetLastError();
@@ -1607,7 +1849,7 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
     // Decode waves of a workgroup: as few as put a decode workgroup on every unit, at most one per SIMD.  (24 sequences,
     // 384 waves: four to a workgroup the stream has the vector-memory paths of 96 units only)
     const int64_t items = (int64_t)a.p.static_runs * a.p.Hkv;
-    a.p.dec_wpw = (int32_t)std::min<int64_t>(kStepDecWaves, (items + num_cus - 1) / num_cus);
+    a.p.dec_wpw = a.p.coop ? 1 : (int16_t)std::min<int64_t>(kStepDecWaves, (items + num_cus - 1) / num_cus);
     const int64_t dec = (items + a.p.dec_wpw - 1) / a.p.dec_wpw;
     const int64_t pf = a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
                                     : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
@@ -1615,12 +1857,16 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
     const dim3 grid((unsigned)(dec + pf));
     if (a.p.lean)
         hipLaunchKernelGGL((step_kernel_lean<128>), grid, dim3(512), 0, s, a);
+    else if (a.p.hd == 64 && a.p.coop)
+        hipLaunchKernelGGL((step_kernel<64, 4, true>), grid, dim3(kPfThreads), 0, s, a);
     else if (a.p.hd == 64)
-        hipLaunchKernelGGL((step_kernel<64, 2>), grid, dim3(kPfThreads), 0, s, a);
+        hipLaunchKernelGGL((step_kernel<64, 2, false>), grid, dim3(kPfThreads), 0, s, a);
+    else if (a.p.coop)
+        hipLaunchKernelGGL((step_kernel<128, 2, true>), grid, dim3(kPfThreads), 0, s, a);
     else if (a.p.nbi == 2)
-        hipLaunchKernelGGL((step_kernel<128, 2>), grid, dim3(kPfThreads), 0, s, a);
+        hipLaunchKernelGGL((step_kernel<128, 2, false>), grid, dim3(kPfThreads), 0, s, a);
     else
-        hipLaunchKernelGGL((step_kernel<128, 1>), grid, dim3(kPfThreads), 0, s, a);
+        hipLaunchKernelGGL((step_kernel<128, 1, false>), grid, dim3(kPfThreads), 0, s, a);
     return hipGetLastError();
 }
 
