@@ -751,7 +751,7 @@ struct ooco_ctx {
     int32_t *pf_counters = nullptr;   // [kPrefillSplitUnits] arrival counters of split prefill tiles, zero between calls
     uint16_t xcd_cw[kXcds] = {};   // option "xcd_weights"
     int64_t opt_overlap = 1;
-    int64_t opt_copy_sort = 1;      // block copy: order the pairs by destination id on the device (0 never, 1 from kCopySortMin pairs, 2 always)
+    int64_t opt_copy_sort = 1;      // block copy: order the pairs by destination id on the device (0 never, 1 where the copy is large enough, 2 always)
     void *sort_buf = nullptr;       // [2 * sort_cap int64 (sorted dst, sorted src)] + temporary storage of the sort
     int64_t sort_cap = 0;           // pairs the buffer holds
     size_t sort_temp_bytes = 0;
@@ -1604,8 +1604,13 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
     hipError_t e = hipSuccess;
     // Large copies take their pairs in order of destination id (sorted on the device into a buffer of the context,
     // which grows on demand -- never while the stream is being captured, a captured copy keeps the caller's order).
-    constexpr int64_t kCopySortMin = 2048;
-    if (ctx->opt_copy_sort >= 2 || (ctx->opt_copy_sort == 1 && num_pairs >= kCopySortMin)) {
+    // The order is worth about an eighth of the copy's time and costs 6 us and 0.25 us per 1000 pairs in one workgroup, up
+    // to kOrderPairsMax pairs, and 28 us and more in the radix sort beyond.  Measured on MI355X, unordered / ordered:
+    // 8 kv heads of 128, 2048 pairs 53.0 / 51.6 us, 8192 209 / 187; 4 heads of 128, 4096 pairs 52.5 / 53.6, 8192 107 / 101;
+    // 4 heads of 64, 8192 pairs 53.2 / 55.1, 16,384 106.1 / 105.5, 32,768 211 / 216 (radix), 65,536 427 / 405 (radix).
+    const int64_t bytes_one_way = 2 * num_pairs * block_bytes;
+    const bool order_pays = bytes_one_way >= (num_pairs <= kOrderPairsMax ? (int64_t)192 << 20 : (int64_t)640 << 20);
+    if (ctx->opt_copy_sort >= 2 || (ctx->opt_copy_sort == 1 && order_pays)) {
         bool ready = num_pairs <= ctx->sort_cap;
         if (!ready) {
             hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -1637,7 +1642,8 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
             // a smaller one)
             int bits = 1;
             while (bits < 32 && ((int64_t)1 << bits) < ctx->num_blocks) ++bits;
-            e = launch_sort_pairs(temp, ctx->sort_temp_bytes, dst_block_ids, dst_sorted, src_block_ids, src_sorted, num_pairs,
+            e = num_pairs <= kOrderPairsMax ? launch_order_pairs(dst_block_ids, dst_sorted, src_block_ids, src_sorted, num_pairs, bits, s)
+                                            : launch_sort_pairs(temp, ctx->sort_temp_bytes, dst_block_ids, dst_sorted, src_block_ids, src_sorted, num_pairs,
                                   bits, s);
             if (e == hipSuccess) {
                 src_block_ids = src_sorted;

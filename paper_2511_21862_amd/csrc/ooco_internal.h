@@ -128,6 +128,11 @@ hipError_t sort_pairs_temp_bytes(int64_t num_pairs, size_t *bytes);
 hipError_t launch_sort_pairs(void *temp, size_t temp_bytes, const int64_t *dst_ids, int64_t *dst_sorted,
                              const int64_t *src_ids, int64_t *src_sorted, int64_t num_pairs, int bits, hipStream_t s);
 
+// The same order up to the leading bits of the destination ids, in one launch; up to kOrderPairsMax pairs.
+constexpr int64_t kOrderPairsMax = 16384;   // (they are held in LDS)
+hipError_t launch_order_pairs(const int64_t *dst_ids, int64_t *dst_out, const int64_t *src_ids, int64_t *src_out,
+                              int64_t num_pairs, int bits, hipStream_t s);
+
 hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache, void *v_cache, const int32_t *block_tables,
                             const int32_t *query_start_loc, const int32_t *ctx_lens, int num_seqs, int total_q, int Hkv,
                             int hd, int max_blocks_per_seq, int64_t num_blocks, int parts_opt, hipStream_t s);

@@ -1881,6 +1881,89 @@ hipError_t launch_mixed(const KernArgs &a, int num_cus, hipStream_t s)
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------------------------------
+// The pairs of a block copy in order of the region of the destination pool they go to (see ooco_sort.hip for why the
+// order matters): a counting sort by the leading bits of the destination id, one workgroup, one launch.  What the copy
+// needs is that the few hundred blocks written at a time are neighbours, so pairs of one bucket stay in any order, and a
+// full sort by all bits (the library's radix sort, five launches, 28 us for 11,000 pairs) buys nothing more.  Bound by
+// latency -- load the ids, count, scan, write --, so the ids stay in registers between the passes, the pairs are put in
+// order in LDS (8-byte stores scattered over memory by one unit would cost more than all the rest) and written out in
+// whole lines.  Whatever the ids, the result is a permutation of the pairs (ids of blocks fit 31 bits).
+constexpr int kOrderThreads = 1024, kOrderBuckets = 4096;
+__global__ __launch_bounds__(kOrderThreads) void order_pairs_kernel(const int64_t *dst_ids, const int64_t *src_ids,
+                                                                    int64_t *dst_out, int64_t *src_out, int num_pairs,
+                                                                    int shift)
+{
+    constexpr int U = (int)(kOrderPairsMax / kOrderThreads), PER = kOrderBuckets / kOrderThreads;
+    static_assert(U * kOrderThreads == kOrderPairsMax, "whole passes");
+    __shared__ u32x2 pairs[kOrderPairsMax];
+    __shared__ int start[kOrderBuckets];
+    __shared__ int wave_sum[kOrderThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t d[U], s[U];
+    int rank[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min(u * kOrderThreads + tid, num_pairs - 1);
+        if (u * kOrderThreads < num_pairs) {
+            d[u] = (uint32_t)dst_ids[i];
+            s[u] = (uint32_t)src_ids[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) start[i * kOrderThreads + tid] = 0;
+    __syncthreads();
+    auto bucket = [&](uint32_t id) -> int { return (int)((id >> shift) & (uint32_t)(kOrderBuckets - 1)); };
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u * kOrderThreads + tid < num_pairs) rank[u] = atomicAdd(&start[bucket(d[u])], 1);
+    __syncthreads();
+    // exclusive scan: PER buckets a thread, then the waves, then the workgroup
+    int c[PER], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        c[i] = sum;
+        sum += start[tid * PER + i];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int before = incl - sum;
+#pragma unroll
+    for (int w = 0; w < kOrderThreads / 64; ++w) before += w < wave ? wave_sum[w] : 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) start[tid * PER + i] = before + c[i];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u * kOrderThreads + tid < num_pairs) pairs[start[bucket(d[u])] + rank[u]] = u32x2{d[u], s[u]};
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = u * kOrderThreads + tid;
+        if (i < num_pairs) {
+            const u32x2 x = pairs[i];
+            dst_out[i] = (int64_t)x[0];
+            src_out[i] = (int64_t)x[1];
+        }
+    }
+}
+
+hipError_t launch_order_pairs(const int64_t *dst_ids, int64_t *dst_out, const int64_t *src_ids, int64_t *src_out,
+                              int64_t num_pairs, int bits, hipStream_t s)
+{
+    int shift = 0;
+    while (((int64_t)kOrderBuckets << shift) < ((int64_t)1 << bits)) ++shift;
+    hipLaunchKernelGGL(order_pairs_kernel, dim3(1), dim3(kOrderThreads), 0, s, dst_ids, src_ids, dst_out, src_out, (int)num_pairs,
+                       shift);
+    return hipGetLastError();
+}
+
 hipError_t launch_block_copy(const void *k_src, const void *v_src, void *k_dst, void *v_dst, const int64_t *src_ids,
                              const int64_t *dst_ids, int64_t num_pairs, int64_t block_bytes, int variant, hipStream_t s)
 {

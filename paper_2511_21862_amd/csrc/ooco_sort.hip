@@ -1,8 +1,8 @@
 // Device-side ordering of the (source, destination) block pairs of ooco_kv_block_copy by destination id.
 // The copy kernel takes its pairs in array order and the hardware dispatches its workgroups in index order, so
 // with sorted pairs the blocks written at any one time are neighbours in the destination pool; on MI355X that is
-// worth more than the sort costs once a copy moves a few thousand blocks.  The sort itself is the library radix
-// sort (hipCUB); nothing of the copy's semantics depends on it (pairs are independent, destination ids distinct).
+// worth more than the sort costs once a copy moves a few hundred MB.  Up to kOrderPairsMax pairs are ordered by
+// order_pairs_kernel; the sort here, for more, is the library radix sort (hipCUB); nothing of the copy's semantics depends on it (pairs are independent, destination ids distinct).
 #include "ooco_internal.h"
 
 #include <hipcub/hipcub.hpp>

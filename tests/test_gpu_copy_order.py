@@ -1,0 +1,36 @@
+"""Block copies ordered by destination region: every pair arrives, at the sizes where the ordering kernel changes its passes
+or gives way to the radix sort."""
+import pytest
+import torch
+
+from paper_2511_21862_amd import binding as B
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("pool", [1 << 15, 40000, 16500])
+@pytest.mark.parametrize("n", [1, 63, 1023, 1024, 1025, 16383, 16384, 16385])
+def test_ordered_copies_move_every_block(n, pool):
+    say(f"case: {n} pairs, pool of {pool} blocks")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    elems = 2 * 64 * 16
+    src = [torch.randint(-32768, 32767, (pool, elems), dtype=torch.int16, device="cuda", generator=g).view(torch.bfloat16) for _ in range(2)]
+    # destinations all over the pool, in its upper end only (one bucket or few), and descending
+    spread = torch.randperm(pool, generator=g, device="cuda")[:n]
+    for dst_ids in (spread, torch.arange(pool - n, pool, device="cuda"), torch.arange(n - 1, -1, -1, device="cuda")):
+        src_ids = torch.randperm(pool, generator=g, device="cuda")[:n].contiguous()
+        dst_ids = dst_ids.contiguous()
+        dst = [torch.zeros((pool, elems), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        want = [torch.zeros_like(d) for d in dst]
+        for w, s in zip(want, src):
+            w[dst_ids] = s[src_ids]
+        with B.Context(8, 2, 64, 16, pool, 8) as ctx:
+            ctx.set_option("copy_sort", 2)
+            ids = src_ids.clone(), dst_ids.clone()
+            ctx.kv_block_copy(src[0], src[1], dst[0], dst[1], src_ids, dst_ids)
+            torch.cuda.synchronize()
+            assert torch.equal(ids[0], src_ids) and torch.equal(ids[1], dst_ids)
+        for w, d in zip(want, dst):
+            assert torch.equal(w.view(torch.int16), d.view(torch.int16))
