@@ -108,13 +108,17 @@ def _host_i32(a):
     if a is None:
         return None, 0
     arr = np.ascontiguousarray(a, dtype=np.int32)
-    return arr, arr.ctypes.data
+    try:
+        return arr, ctypes.addressof(ctypes.c_char.from_buffer(arr))   # a third of the time of arr.ctypes.data (0.4 / 1.1 us)
+    except (TypeError, ValueError):                                     # read-only or empty
+        return arr, arr.ctypes.data
 
 
 def _stream_handle(stream) -> int:
     if stream is None:
-        import torch
-
+        # (the handle alone: making the Stream object of torch.cuda.current_stream() takes longer than the launch's checks)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
