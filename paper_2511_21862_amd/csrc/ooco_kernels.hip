@@ -1632,8 +1632,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
 {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    // `parts` workgroups share a (sequence, block) pair: each takes every parts-th slice of the K chunks and of the
-    // V elements, so that a pair whose rows cover its block only partly (many narrow stores) does not end last
+    // `parts` workgroups share a (sequence, block) pair: each takes every parts-th slice of the rows' elements, so that a pair whose rows cover its block only partly (many narrow stores) does not end last
     const int w = blockIdx.x / parts;
     const int part = blockIdx.x - w * parts;
     auto g_at = [&](int idx) -> int { return query_start_loc[idx] / kBlockSize + 2 * idx; };
@@ -1689,77 +1688,104 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
     const int t_lo = max(0, bidx * kBlockSize - ctx);
     const int slot0 = ctx + t_lo - bidx * kBlockSize;
     const int nrow = min(kBlockSize - slot0, q_len - t_lo);
-    const int row_elems = Hkv * hd;
+    const int row_elems = Hkv * hd, chunks = row_elems / 8;
     const int64_t row0 = (int64_t)(q0 + t_lo);
-    // K: thread -> (row r = tid % 16, 16-byte chunk c = tid / 16 + 16 i): the 16 rows of a chunk are adjacent in
-    // the cache, so a wave's stores cover 4 chunks x 256 contiguous bytes
-    {
-        const int chunks = row_elems / 8;
-        const int r = tid & 15;
-        if (r < nrow) {
-            const u32x4 *src = reinterpret_cast<const u32x4 *>(k_new + (row0 + r) * row_elems);
-            u32x4 *dst = reinterpret_cast<u32x4 *>(k_cache) + (int64_t)blk * chunks * kBlockSize + slot0 + r;
-            constexpr int kSlice = kAppendThreads / 16;   // chunks a workgroup moves per pass
-            for (int c0 = (tid >> 4) + kSlice * part; c0 < chunks; c0 += 2 * kSlice * parts) {
-                u32x4 v[2];
+    const uint16_t *const k_src = k_new + row0 * row_elems, *const v_src = v_new + row0 * row_elems;
+    u32x4 *const k_dst = reinterpret_cast<u32x4 *>(k_cache) + (int64_t)blk * chunks * kBlockSize + slot0;
+    uint16_t *const v_dst = v_cache + (int64_t)blk * row_elems * kBlockSize;   // slot 0 of the first cache row
+    if (nrow == kBlockSize) {   // a whole block
+        // K: thread -> (row r = tid % 16, 16-byte chunk c = tid / 16 + 16 i): the 16 rows of a chunk are adjacent in
+        // the cache, so a wave's stores cover 4 chunks x 256 contiguous bytes
+        const u32x4 *src = reinterpret_cast<const u32x4 *>(k_src + (int64_t)(tid & 15) * row_elems);
+        u32x4 *dst = k_dst + (tid & 15);
+        constexpr int kSlice = kAppendThreads / 16;   // chunks a workgroup moves per pass
+        for (int c0 = (tid >> 4) + kSlice * part; c0 < chunks; c0 += 2 * kSlice * parts) {
+            u32x4 v[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int c = c0 + i * kSlice * parts;
-                    if (c < chunks) v[i] = src[c];
-                }
+            for (int i = 0; i < 2; ++i) {
+                const int c = c0 + i * kSlice * parts;
+                if (c < chunks) v[i] = src[c];
+            }
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int c = c0 + i * kSlice * parts;
-                    if (c < chunks && blk_ok) dst[(int64_t)c * kBlockSize] = v[i];
-                }
+            for (int i = 0; i < 2; ++i) {
+                const int c = c0 + i * kSlice * parts;
+                if (c < chunks && blk_ok) dst[(int64_t)c * kBlockSize] = v[i];
             }
         }
-    }
-    // V: thread -> element e = (kv head, dim); cache row (blk * Hkv * hd + e) * 16, slots slot0 .. slot0 + nrow - 1
-    {
-        const uint16_t *src0 = v_new + row0 * row_elems;
-        uint16_t *dst0 = v_cache + (int64_t)blk * row_elems * kBlockSize + slot0;
+        // V: thread -> element e = (kv head, dim) of all rows, 32 contiguous bytes of the cache.  (Two adjacent elements
+        // per thread, or all loads of a workgroup before its first store, are slower here: 8 x 512 rows and 128 decodes
+        // 11.1 -> 12.3 and 12.5 us.)
         for (int e = tid + kAppendThreads * part; e < row_elems; e += kAppendThreads * parts) {
-            const uint16_t *src = src0 + e;
-            uint16_t *dst = dst0 + (int64_t)e * kBlockSize;
-            if (nrow == kBlockSize) {
-                uint32_t x[8];
+            const uint16_t *s = v_src + e;
+            uint32_t x[8];
 #pragma unroll
-                for (int r = 0; r < 8; ++r)
-                    x[r] = (uint32_t)src[(int64_t)(2 * r) * row_elems] | ((uint32_t)src[(int64_t)(2 * r + 1) * row_elems] << 16);
-                u32x4 *d4 = reinterpret_cast<u32x4 *>(dst);
-                if (blk_ok) {
-                    d4[0] = u32x4{x[0], x[1], x[2], x[3]};
-                    d4[1] = u32x4{x[4], x[5], x[6], x[7]};
-                }
-            } else {
-                // all loads before the first store (one memory round trip instead of one per row); x[s] = value of
-                // slot s of the block.  Quarters of the cache row (4 slots = 8 bytes) that the step covers whole are
-                // written with one store each, the ragged ends slot by slot.
-                uint16_t x[kBlockSize];
+            for (int r = 0; r < 8; ++r)
+                x[r] = (uint32_t)s[(int64_t)(2 * r) * row_elems] | ((uint32_t)s[(int64_t)(2 * r + 1) * row_elems] << 16);
+            u32x4 *d4 = reinterpret_cast<u32x4 *>(v_dst + (int64_t)e * kBlockSize);
+            if (blk_ok) {
+                d4[0] = u32x4{x[0], x[1], x[2], x[3]};
+                d4[1] = u32x4{x[4], x[5], x[6], x[7]};
+            }
+        }
+        return;
+    }
+    // A block that the step covers partly -- a decode row, the ends of a chunk --: few bytes, so what counts is the
+    // number of memory round trips, and a pass over the elements of every row sends off all its loads, of K and of V,
+    // before its first store (128 decodes 6.5 -> 5.6 us, 512 15.7 -> 12.9).  K as above; V: E adjacent elements per
+    // thread, x[s] = their values in slot s of the block.  Two elements, or one for rows that two would leave half the
+    // threads without (4 heads of 64, six chunks of 3..14 rows: 4.6 us, with two 5.1).
+    const bool v_aligned = ((uintptr_t)v_new & 3) == 0;   // (rows have an even number of elements)
+    auto partly = [&](auto per_thread) {
+        constexpr int E = decltype(per_thread)::value, PASS = E * kAppendThreads;
+        for (int e0 = PASS * part; e0 < row_elems; e0 += PASS * parts) {
+            constexpr int KI = PASS / 8 / (kAppendThreads / 16);
+            const int r = tid & 15, c0 = e0 / 8 + (tid >> 4), e = e0 + E * tid;
+            u32x4 kv[KI];
+#pragma unroll
+            for (int i = 0; i < KI; ++i)
+                if (r < nrow && c0 + 16 * i < chunks)
+                    kv[i] = reinterpret_cast<const u32x4 *>(k_src + (int64_t)r * row_elems)[c0 + 16 * i];
+            uint32_t x[kBlockSize];
+            if (e < row_elems) {
 #pragma unroll
                 for (int sl = 0; sl < kBlockSize; ++sl) {
-                    const int r = sl - slot0;
-                    x[sl] = (r >= 0 && r < nrow) ? src[(int64_t)r * row_elems] : (uint16_t)0;
+                    const uint16_t *const src = v_src + (int64_t)(sl - slot0) * row_elems + e;
+                    x[sl] = 0;
+                    if (sl >= slot0 && sl < slot0 + nrow)
+                        x[sl] = E == 1 ? (uint32_t)src[0]
+                                : v_aligned ? *reinterpret_cast<const uint32_t *>(src) : (uint32_t)src[0] | ((uint32_t)src[1] << 16);
                 }
-                uint16_t *row = dst - slot0;   // slot 0 of the cache row (32-byte aligned)
+            }
+            if (!blk_ok) continue;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (!blk_ok) {
-                    } else if (4 * q >= slot0 && 4 * q + 4 <= slot0 + nrow) {
-                        *reinterpret_cast<u32x2 *>(row + 4 * q) =
-                            u32x2{(uint32_t)x[4 * q] | ((uint32_t)x[4 * q + 1] << 16), (uint32_t)x[4 * q + 2] | ((uint32_t)x[4 * q + 3] << 16)};
-                    } else {
+            for (int i = 0; i < KI; ++i)
+                if (r < nrow && c0 + 16 * i < chunks) k_dst[(int64_t)(c0 + 16 * i) * kBlockSize + r] = kv[i];
+            if (e < row_elems) {
+                // quarters of a cache row (4 slots = 8 bytes) that the step covers whole are written with one store
+                // each, the ragged ends slot by slot
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int sl = 4 * q + k;
-                            if (sl >= slot0 && sl < slot0 + nrow) row[sl] = x[sl];
+                for (int h = 0; h < E; ++h) {
+                    uint16_t *const row = v_dst + (int64_t)(e + h) * kBlockSize;   // (32-byte aligned)
+                    auto at = [&](int sl) -> uint32_t { return h ? x[sl] >> 16 : x[sl] & 0xFFFFu; };
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (4 * q >= slot0 && 4 * q + 4 <= slot0 + nrow) {
+                            *reinterpret_cast<u32x2 *>(row + 4 * q) =
+                                u32x2{at(4 * q) | (at(4 * q + 1) << 16), at(4 * q + 2) | (at(4 * q + 3) << 16)};
+                        } else {
+#pragma unroll
+                            for (int sl = 4 * q; sl < 4 * q + 4; ++sl)
+                                if (sl >= slot0 && sl < slot0 + nrow) row[sl] = (uint16_t)at(sl);
                         }
                     }
                 }
             }
         }
-    }
+    };
+    if (row_elems >= 2 * kAppendThreads)
+        partly(std::integral_constant<int, 2>());
+    else
+        partly(std::integral_constant<int, 1>());
 }
 
 hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache, void *v_cache, const int32_t *block_tables,
@@ -1767,7 +1793,9 @@ hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache,
                             int hd, int max_blocks_per_seq, int64_t num_blocks, int parts_opt, hipStream_t s)
 {
     if (total_q <= 0 || num_seqs <= 0) return hipSuccess;
-    const int parts = parts_opt > 0 ? std::min(parts_opt, 8) : std::max(1, std::min(2, Hkv * hd / (2 * kAppendThreads)));   // two for 8 kv heads x 128: measured best (1: 13.6 us, 2: 11.2, 4: 14.6 on 4,224 tokens)
+    // One workgroup per 512 elements of a row.  8 kv heads x 128, 4,224 tokens, 1 / 2 / 4 / 8 parts: 12.7 / 10.4 / 13.1 /
+    // 16.5 us; 32 x 128, 16 decodes: 18.2 / 10.2 / 6.6 / 4.7, 4096 chunk rows: 61 / 41 / 36 / 32.
+    const int parts = parts_opt > 0 ? std::min(parts_opt, 8) : std::max(1, std::min(8, Hkv * hd / (2 * kAppendThreads)));
     const unsigned grid = (unsigned)((total_q / kBlockSize + 2 * (int64_t)num_seqs + 1) * parts);
     hipLaunchKernelGGL(kv_append_kernel, dim3(grid), dim3(kAppendThreads), 0, s, (const uint16_t *)k_new,
                        (const uint16_t *)v_new, (uint16_t *)k_cache, (uint16_t *)v_cache, block_tables, query_start_loc,

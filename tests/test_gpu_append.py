@@ -101,3 +101,28 @@ def test_append_skips_rows_it_cannot_place():
         mask[blk0, :, :, 3, :] = False
         assert (k1[mask] == k0[mask]).all()                                # nothing else changed
         B.ooco_kv_append(ctx.h, new, new, d.k_cache, d.v_cache, t(bt_bad), t(b.query_start_loc), t(b.ctx_lens), 0, 0)
+
+
+@pytest.mark.parametrize("Hkv,hd", [(1, 64), (4, 64), (7, 64), (4, 128), (5, 128), (8, 128), (32, 128), (33, 128)])
+def test_append_of_partly_covered_blocks(Hkv, hd):
+    # row sizes around one pass of a workgroup (256 and 512 elements) and several workgroups per block; every start slot and
+    # number of rows of a block; new vectors at an odd element of their allocation
+    ql = [1, 2, 3, 4, 5, 7, 8, 11, 12, 13, 15, 16, 17, 30, 1, 9]
+    cx = [0, 15, 13, 4, 3, 9, 8, 2, 4, 3, 1, 16, 7, 20, 31, 28]
+    need = int(sum((q + c + 15) // 16 for q, c in zip(ql, cx)))
+    b = W.build_batch(Hq=Hkv, Hkv=Hkv, hd=hd, q_lens=ql, ctx_lens=cx, num_blocks=need + 3, seed=70 + Hkv)
+    say(f"case: append partly covered blocks Hkv={Hkv} hd={hd}")
+    rng = np.random.default_rng(Hkv)
+    new = rng.integers(0, 65536, size=(2, b.total_q, Hkv, hd)).astype(np.uint16)
+    k_ref, v_ref = b.k_cache.copy(), b.v_cache.copy()
+    ref_numpy.kv_append(new[0], new[1], k_ref, v_ref, b.block_tables, b.query_start_loc, b.ctx_lens)
+    bt, _, qsl, cl = device_meta(b)
+    for odd in (0, 1):
+        d = W.to_device(b)
+        k_dev = torch.from_numpy(new[0].view(np.int16)).cuda().view(torch.bfloat16)
+        v_flat = torch.zeros(new[1].size + odd, dtype=torch.bfloat16, device="cuda")
+        v_flat[odd:].view(torch.int16).copy_(torch.from_numpy(new[1].view(np.int16).reshape(-1)))
+        with B.Context(Hkv, Hkv, hd, b.BS, b.num_blocks, b.max_blocks_per_seq) as ctx:
+            ctx.kv_append(k_dev, v_flat[odd:].view(b.total_q, Hkv, hd), d.k_cache, d.v_cache, bt, qsl, cl)
+            torch.cuda.synchronize()
+        assert (bits(d.k_cache) == k_ref).all() and (bits(d.v_cache) == v_ref).all(), odd
