@@ -152,9 +152,9 @@ constexpr size_t storage_ints(size_t seqs_cap) { return (seqs_cap + 1) + (2 * se
 // the partial-result slots; fills out.static_runs / static_blocks / tail_runs / slots / cw / nbi.
 // dec_blocks: units of the line (blocks + piece pads), kv_blocks: KV blocks of all decode sequences, dec_seqs: decode
 // sequences that hold a block, max_blocks: blocks of the longest, pf_wgs: (tile, kv head) pairs of the batch's prefill
-// part, lean: the batch runs the register-lean pair of kernels.
+// part, lean: the batch runs the register-lean pair of kernels, dcum: the line, whose pads may grow here.
 void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks, int64_t kv_blocks, int64_t dec_seqs, int64_t max_blocks,
-                      int64_t pf_wgs, bool lean, HostPlan &out)
+                      int64_t pf_wgs, bool lean, int32_t *dcum, HostPlan &out)
 {
     // static runs: by default three waves per CU (measured best on MI355X: enough loads in
     // flight to saturate HBM, few enough waves that start-up and partial results stay small)
@@ -217,6 +217,20 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         wave_slots = per_unit;
         min_blocks = kv_blocks > 512 * dec_seqs || (pf_wgs > 0 && kv_blocks > 256) ? 32 : pf_wgs > 0 || kv_blocks <= 16 || kv_blocks > 64 * dec_seqs ? 16 : 8;
         if (short_seqs) at_least = dec_seqs;
+        // Starting a piece costs the whole workgroup, so it weighs more in the line: as much as 12 tiles of head_dim 128.
+        // Pads of 3 / 6 / 12 / 24: sixteen sequences of 512..4096 tokens 31.5 / 31.1 / 30.6 / 30.5 us, sixteen of
+        // 1000..2000 22.8 / 22.0 / 21.0 / 21.8; head_dim 64, pads of 6 / 12 / 24 / 36: 12.3 / 11.3 / 10.2 / 10.2.
+        if (geo.piece_pad == default_piece_pad(geo.hd)) {
+            const int32_t more = 3 * default_piece_pad(geo.hd);
+            int32_t added = 0;
+            for (int i = 0; i < num_seqs; ++i) {
+                if (dcum[i + 1] + added > dcum[i]) added += more;   // (dcum[i] has its share already)
+                dcum[i + 1] += added;
+            }
+            dec_blocks += added;
+            out.dec_blocks = (int32_t)dec_blocks;
+            out.piece_pad += more;
+        }
     } else if (short_seqs && (geo.hd == 128 || small)) {
         wave_slots = std::max<int64_t>(1, (int64_t)geo.num_cus * 4 / geo.Hkv);
         min_blocks = 16;
@@ -625,7 +639,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         out.dec_cus = dec;
     }
     // ---- run layout of the decode block line (see plan_decode_runs)
-    if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, max_dec_blocks, tiles * geo.Hkv, lean, out);
+    if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, max_dec_blocks, tiles * geo.Hkv, lean, dcum, out);
     // ---- prefill tiles cut along the context (see plan_prefill_parts)
     if (tiles > 0) {
         const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, pf_waves, dec_blocks, kv_blocks, pf_pairs};
