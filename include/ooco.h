@@ -177,7 +177,9 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                the two at under 80 us together; 2 = the prefill kernel on the context's own side stream (default
  *                priority) concurrently with the decode kernel, always (fork and join by events: the call still
  *                appears as one unit of work on the caller's stream); 0 = one after the other, always
- *   "mixed_step"  0/1 (default 1): with "overlap" 1, the one-launch form; it takes every plan whose two arrays fit
+ *   "mixed_step"  0/1/2 (default 1): with "overlap" 1, the one-launch form (1 = but for batches outside "mixed_lean"
+ *                with more than 180 us of decode K/V at 6.8 TB/s beside more than 128 prefill workgroups, which run 1 to
+ *                3 % faster as two kernels; 2 = those too); it takes every plan whose two arrays fit
  *                the kernel arguments together (num_seqs + chunks * 2 + tiles up to about 960) and that has no dynamic
  *                tail, no "xcd_weights" and the default number of waves.  Output bits are those of the two kernels.
  *                Measured on MI355X against the two kernels: 8 x 512 rows beside 128 decode sequences 305 -> 282 us,

@@ -116,6 +116,7 @@ struct HostPlan {
     // a batch with both kinds of work whose two kernels, one after the other, are estimated to take under 80 us: they
     // then run in sequence on the caller's stream (the fork and join of the second stream cost more than they gain)
     bool brief = false;
+    bool two_streams = false;    // a batch with both kinds of work that runs faster as two kernels on two streams than in one launch
     int32_t coop = 0;            // decode runs are worked on by workgroups of four waves (decode_coop_kernel); kCoopBySequence: run i is sequence i
     int32_t nbi = 0;             // KV blocks per softmax step of the decode kernel that the plan asks for (0 = the kernel's default)
 };
@@ -620,6 +621,11 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         const double t_dec = (double)kv_blocks * BS * 2.0 * geo.Hkv * geo.hd * 2.0 / 6.8e12 + 15e-6;
         const double t_pf = 4.0 * geo.Hq * geo.hd * pf_pairs / 1.05e15 + 12e-6;
         out.brief = t_dec + t_pf < 80e-6;
+        // One launch for both kinds saves the second stream's fork and join (about 13 us), and its decode workgroups are
+        // spread over the units a little less evenly than the decode kernel's single waves, which a long stream pays for:
+        // 32/8 heads, 131 / 276 / 412 us of K/V at 6.8 TB/s beside 4 x 528 rows 172 -> 171, 321 -> 328, 461 -> 470 us; beside
+        // 128 workgroups (1 x 512 rows) 164 -> 159, 316 -> 307, 460 -> 457.  (The register-lean pair gains at any length.)
+        out.two_streams = !lean && t_dec - 15e-6 > 180e-6 && tiles * geo.Hkv > geo.num_cus / 2;
     }
     // ---- one launch for both kinds of work: how many compute units of every XCD decode.  The decode part is
     // bound by HBM and reaches its bandwidth from a part of the units; the prefill part is bound by the matrix
@@ -805,7 +811,7 @@ int decode_coop(const ooco_ctx *ctx) { return ctx->plan.coop == kCoopBySequence 
 // Whether the current plan runs in one launch of the step kernel ("overlap" 0 and 2 ask for two kernels).
 bool runs_as_step(const ooco_ctx *ctx)
 {
-    return ctx->opt_step && ctx->opt_overlap == 1 && step_fits(ctx->plan, ctx->hd, decode_coop(ctx) != 0, decode_nbi(ctx));
+    return ctx->opt_step && ctx->opt_overlap == 1 && (ctx->opt_step >= 2 || !ctx->plan.two_streams) && step_fits(ctx->plan, ctx->hd, decode_coop(ctx) != 0, decode_nbi(ctx));
 }
 
 ooco_status fail(const ooco_ctx *ctx, ooco_status code, const char *fmt, ...)

@@ -93,3 +93,28 @@ def test_static_entry_runs_both_kinds_in_one_launch(name):
                                  d.k_cache, d.v_cache, bt, sl, qsl, cl, out, len(b.seq_lens), b.total_q)
         torch.cuda.synchronize()
         assert_parity(out.view(torch.int16).cpu().numpy().view(np.uint16), want, name)
+
+
+def test_long_decode_parts_run_on_two_streams_with_the_same_bits():
+    # more than 180 us of decode K/V beside more than half a prefill workgroup per unit: two kernels, as "mixed_step" 2 is not
+    seqs = 96
+    q_lens, ctx_lens = [1] * seqs + [300, 300], [3600 + 7 * i for i in range(seqs)] + [40, 0]
+    b = W.build_batch(Hq=32, Hkv=8, hd=128, q_lens=q_lens, ctx_lens=ctx_lens,
+                      num_blocks=int(sum((q + c + 15) // 16 for q, c in zip(q_lens, ctx_lens))) + 5, seed=45, device="cuda")
+    say("case: long decode part")
+    assert len(planned_kernels(b, {})) == 2 and len(planned_kernels(b, {"mixed_step": 2})) == 1
+    short = W.build_batch(Hq=32, Hkv=8, hd=128, q_lens=q_lens[60:], ctx_lens=ctx_lens[60:],
+                          num_blocks=b.num_blocks, seed=45, device="cuda")
+    assert len(planned_kernels(short, {})) == 1
+    bt, sl, qsl, cl = device_meta(b)
+    outs = []
+    for opts in ({}, {"mixed_step": 2}):
+        out = torch.zeros((b.total_q, 32, 128), dtype=torch.bfloat16, device="cuda")
+        with B.Context(32, 8, 128, 16, b.num_blocks, b.max_blocks_per_seq) as ctx:
+            for k, v in opts.items():
+                ctx.set_option(k, v)
+            ctx.plan(b.seq_lens, b.query_start_loc, b.ctx_lens)
+            ctx.attn_mixed(b.q, b.k_cache, b.v_cache, bt, sl, qsl, cl, out)
+            torch.cuda.synchronize()
+        outs.append(out.view(torch.int16))
+    assert torch.equal(outs[0], outs[1]) and bool((outs[0] != 0).any())
