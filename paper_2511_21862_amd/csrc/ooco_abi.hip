@@ -389,7 +389,14 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
             double best = est((double)units, (double)(big * geo.Hkv), 0.0, (double)max_tile_steps) * 0.97;   // a split must win 3 %
             // (a launch of two or more workgroups per unit whose longest tile is no longer than the units' average
             // load cannot gain from more workgroups)
-            const bool full = wg_weight * (double)units >= 2.0 * cus && wg_weight * all_steps / cus * 0.975 >= (double)max_tile_steps * 1.95;
+            // Beside a decode part that lasts longer anyway, parts beyond what hides the prefill part behind it only add
+            // partial results to the memory traffic the decode part waits for: the fewest that do.  (48 sequences of
+            // 500..4000 tokens, 8 kv heads, beside 2 x 120 rows on 600 tokens 83.5 -> 78.6 us, 4 x 60 on 1500 89.4 -> 82.3;
+            // beside decode parts under 50 us, which start-up and merges stretch, the estimate's minimum stays best.)
+            const double dec_us = (double)kv_blocks * BS * 2.0 * geo.Hkv * geo.hd * 2.0 / 6.8e6;
+            const double hidden = pf_waves == 4 && !geo.fused && dec_us > 50.0 ? 0.8 * dec_us : 0.0;
+            const bool full = best <= 0.97 * hidden ||
+                              (wg_weight * (double)units >= 2.0 * cus && wg_weight * all_steps / cus * 0.975 >= (double)max_tile_steps * 1.95);
             for (int64_t k = 2; !full && k <= kMaxPrefillSplit && k <= max_tile_steps; ++k) {
                 const int64_t e = entries_of(k, true, &big, &split_ones);
                 if (!list_fits(e, split_ones)) break;
@@ -398,6 +405,7 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
                 if (t < best) {
                     best = t;
                     split = k;
+                    if (t <= hidden) break;
                 } else if (k >= split + 4) {
                     break;   // (four values in a row without a gain: the estimate only grows from here)
                 }
@@ -1390,18 +1398,19 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
         }
         ev = ctx->prof_ev.data() + kProfEvents * ctx->prof_calls++;
     }
-    // A mixed batch runs its two kernels side by side: the prefill kernel (matrix-core bound) goes to
+    // A mixed batch runs in one launch (the step kernel) where runs_as_step allows.  Else its two kernels run side by
+    // side: the prefill kernel (matrix-core bound) goes to
     // the context's side stream, forked from and joined back into the caller's stream with events,
     // the decode kernel (HBM bound) stays on the caller's stream.  The decode kernel is enqueued first
     // (its three waves per compute unit take their places before the prefill workgroups fill the
     // register files; measured 1.5 % faster on a long-context mixed batch, no difference on a short one).
-    // With per-kernel profiling on, the launch order and the streams stay exactly as they are without it:
-    // every kernel is bracketed by two events on the stream it runs on (ev[0..1] decode, ev[2..3] prefill)
+    // With per-kernel profiling on, the launch order and the streams stay exactly as they are without it (one launch
+    // for both kinds of work counts as both): every kernel is bracketed by two events on the stream it runs on (ev[0..1] decode, ev[2..3] prefill)
     // and the whole call by two on the caller's stream (ev[4..5]), so the times are those of the kernels
     // as they run in the step.
     const bool mixed = pl.n_tiles > 0 && pl.static_runs > 0;
-    // ... or, by default, in ONE launch: the mixed kernel, whose compute units either decode or prefill (the plan
-    // says how many do which).  Both arrays of the plan travel together (in the kernel arguments if they fit).
+    // (option "mixed_fused": the persistent mixed kernel, whose compute units either decode or prefill -- the plan says how
+    // many do which.  Both arrays of the plan travel together there, in the kernel arguments if they fit.)
     const bool fused = mixed && pl.dec_cus > 0;
     const bool step = runs_as_step(ctx);
     const bool overlap = mixed && !fused && !step && ctx->side_stream && (ctx->opt_overlap >= 2 || (ctx->opt_overlap == 1 && !pl.brief));

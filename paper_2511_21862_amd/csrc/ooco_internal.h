@@ -13,7 +13,8 @@
 //             cum[i] = number of line units before sequence i (cum[num_seqs] = dec_blocks).
 //             A piece that does not cover its whole sequence writes a partial result into slot
 //             (run index) + i; the last piece of a sequence to finish merges the slots (arrival
-//             counter per sequence and kv head).
+//             counter per sequence and kv head).  In small batches a run belongs to a workgroup of
+//             four waves that share its pieces (decode_coop_kernel), or run i is sequence i, whole.
 //   prefill - the P chunks (q_len > 1) are listed longest sequence first; cum[k] = number of query
 //             tiles (tile_rows = 128 / (Hq/Hkv) rows each, all heads of a GQA group) before
 //             chunk k of that list, cum[P+1+k] = its sequence index; one workgroup per

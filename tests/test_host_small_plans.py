@@ -1,0 +1,61 @@
+"""Plans of small decode batches and of prefill parts hidden behind a decode part (CPU: the planner's dry run)."""
+import numpy as np
+import pytest
+
+from paper_2511_21862_amd import binding as B
+
+
+def dry(heads, q_lens, ctx_lens, **kw):
+    ql, cx = np.asarray(q_lens, np.int32), np.asarray(ctx_lens, np.int32)
+    qsl = np.zeros(len(ql) + 1, np.int32)
+    qsl[1:] = np.cumsum(ql)
+    return B.ooco_plan_dry_run(*heads, 16, 8192, 256, kw.pop("workspace", 128 << 20), cx + ql, qsl, cx, **kw)
+
+
+def check_cover(r, q_lens, ctx_lens):
+    pieces = r["decode_pieces"]
+    for i, (q, c) in enumerate(zip(q_lens, ctx_lens)):
+        mine = sorted((int(p[1]), int(p[2])) for p in pieces if p[0] == i)
+        if q != 1:
+            assert not mine
+            continue
+        assert mine[0][0] == 0 and mine[-1][1] == (c + 1 + 15) // 16 and all(a[1] == b[0] for a, b in zip(mine, mine[1:]))
+
+
+@pytest.mark.parametrize("heads,limit", [((32, 8, 128), 768), ((28, 4, 128), 768), ((32, 4, 64), 1536)])
+def test_short_sequences_are_taken_whole_up_to_the_limit(heads, limit):
+    for longest, whole in ((limit, True), (limit + 1, False)):
+        q, c = [1, 1, 20, 1], [longest - 1, 33, 100, 0]
+        r = dry(heads, q, c)
+        assert (r["decode_runs"] == len(q) and all(int(p[3]) < 0 for p in r["decode_pieces"])) == whole
+        check_cover(r, q, c)
+    # four workgroups per unit, two beside a prefill part
+    per_unit = 256 // heads[1]
+    for n, chunk, whole in ((4 * per_unit, 0, True), (4 * per_unit + 1, 0, False), (2 * per_unit - 1, 1, True), (2 * per_unit, 1, False)):
+        q, c = [1] * n + [20] * chunk, [63 + i % 9 for i in range(n)] + [0] * chunk
+        r = dry(heads, q, c)
+        assert all(int(p[3]) < 0 for p in r["decode_pieces"]) == whole and (r["decode_runs"] == n + chunk) == whole
+        check_cover(r, q, c)
+
+
+@pytest.mark.parametrize("heads", [(32, 8, 128), (28, 4, 128), (32, 4, 64), (16, 1, 128)])
+@pytest.mark.parametrize("workspace", [128 << 20, 1 << 20, 40000])
+def test_lines_with_larger_pads_cover_every_block_once(heads, workspace):
+    rng = np.random.default_rng(7)
+    for n in (1, 2, 5, 16):
+        q = [1] * n
+        c = [int(x) for x in rng.integers(800, 6000, size=n)]
+        if n > 2:
+            q.insert(2, 50)
+            c.insert(2, 17)
+        check_cover(dry(heads, q, c, workspace=workspace), q, c)
+
+
+def test_prefill_parts_hidden_behind_a_long_decode_part_stay_few():
+    dec = [2250] * 48
+    alone = dry((32, 8, 128), [60] * 4, [1500] * 4)["prefill_parts"]
+    beside = dry((32, 8, 128), [60] * 4 + [1] * 48, [1500] * 4 + dec)["prefill_parts"]
+    few = dry((32, 8, 128), [60] * 4 + [1] * 8, [1500] * 4 + dec[:8])["prefill_parts"]
+    assert beside < min(alone, few)
+    # ... but a chunk that would outlast the decode part is still cut
+    assert dry((32, 8, 128), [100] + [1] * 48, [10000] + dec)["prefill_parts"] >= 5
