@@ -351,9 +351,10 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
  * no dst id may equal any src id; neither is checked (ids live on the device) and violating
  * it gives unspecified block contents.  Ids must lie inside their pools (unchecked).
  * num_pairs == 0 returns OOCO_OK without a launch.  ctx supplies the block geometry.
- * Large copies (option "copy_sort") are carried out in order of destination id: the result is the same, the
- * caller's id lists are not modified; the first such call on a context allocates the buffer for the ordered lists
- * (never on a capturing stream: a captured copy keeps the caller's order). */
+ * Large copies (option "copy_sort") are carried out in order of destination region: the result is the same, the
+ * caller's id lists are not modified.  The ordered lists live in a buffer of the context that such a call allocates
+ * or enlarges.  On a capturing stream a copy always keeps the caller's order and uses nothing of the context's, so
+ * that a graph stays valid whatever later calls do with that buffer. */
 ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src /*DEVICE*/, const void *v_src /*DEVICE*/,
                                void *k_dst /*DEVICE*/, void *v_dst /*DEVICE*/,
                                const int64_t *src_block_ids /*DEVICE*/,

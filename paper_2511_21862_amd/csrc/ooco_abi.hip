@@ -1625,7 +1625,8 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
     if (num_pairs == 0) return OOCO_OK;
     if (!k_src || !v_src || !k_dst || !v_dst || !src_block_ids || !dst_block_ids)
         return fail(ctx, OOCO_EINVAL, "ooco_kv_block_copy: NULL pointer argument");
-    if (num_pairs > (int64_t)1 << 26)
+    constexpr int64_t kMaxCopyPairs = (int64_t)1 << 26;
+    if (num_pairs > kMaxCopyPairs)
         return fail(ctx, OOCO_EINVAL, "ooco_kv_block_copy: num_pairs=%lld too large", (long long)num_pairs);
     const int64_t block_bytes = (int64_t)ctx->Hkv * ctx->BS * ctx->hd * 2;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -1639,13 +1640,22 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
     // 4 heads of 64, 8192 pairs 53.2 / 55.1, 16,384 106.1 / 105.5, 32,768 211 / 216 (radix), 65,536 427 / 405 (radix).
     const int64_t bytes_one_way = 2 * num_pairs * block_bytes;
     const bool order_pays = bytes_one_way >= (num_pairs <= kOrderPairsMax ? (int64_t)192 << 20 : (int64_t)640 << 20);
-    if (ctx->opt_copy_sort >= 2 || (ctx->opt_copy_sort == 1 && order_pays)) {
+    // (nor may a captured copy name the buffer a context has already: a later call frees it when it needs a larger one,
+    // and replays would go on using the freed memory)
+    bool ordered = ctx->opt_copy_sort >= 2 || (ctx->opt_copy_sort == 1 && order_pays);
+    if (ordered) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        const hipError_t q = hipStreamIsCapturing(s, &cs);
+        if (q != hipSuccess) (void)hipGetLastError();
+        ordered = q == hipSuccess && cs == hipStreamCaptureStatusNone;
+    }
+    if (ordered) {
         bool ready = num_pairs <= ctx->sort_cap;
         if (!ready) {
-            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            const bool capturing = hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+            // (at least twice the last size, so that slowly growing copies do not reallocate every time)
+            const int64_t cap = std::max({num_pairs, std::min(2 * ctx->sort_cap, kMaxCopyPairs), kOrderPairsMax});
             size_t temp = 0;
-            if (!capturing && sort_pairs_temp_bytes(num_pairs, &temp) == hipSuccess) {
+            if (sort_pairs_temp_bytes(cap, &temp) == hipSuccess) {
                 // (work of earlier calls may still read the old buffer: wait for it before freeing)
                 if (ctx->sort_buf) {
                     (void)hipStreamSynchronize(s);
@@ -1653,9 +1663,9 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
                     ctx->sort_buf = nullptr;
                     ctx->sort_cap = 0;
                 }
-                const size_t ids = ((size_t)num_pairs * 2 * sizeof(int64_t) + 255) / 256 * 256;
+                const size_t ids = ((size_t)cap * 2 * sizeof(int64_t) + 255) / 256 * 256;
                 if (hipMalloc(&ctx->sort_buf, ids + temp) == hipSuccess) {
-                    ctx->sort_cap = num_pairs;
+                    ctx->sort_cap = cap;
                     ctx->sort_temp_bytes = temp;
                     ready = true;
                 } else {
