@@ -17,6 +17,7 @@
 #include "ooco_internal.h"
 
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 namespace ooco {
@@ -234,7 +235,8 @@ OOCO_DEV int count_le(CumAt cum_at, int n, int x, int lane)
 // (so the result does not depend on which piece is last) and resets the counter.
 // The blocks [blk_begin, blk_begin + nblk) of sequence seq (not none) against its query row, streamed by wave `wave` of NW
 // waves that take steps of NBI blocks in turn: un-normalised output O, running maximum m (the same in the four rows of a
-// lane column) and this lane's share lsum of the sum, as laid out above.  A wave without a step has (0, -inf, 0).
+// lane column) and this lane's share lsum of the sum, as laid out above.  A wave without a step has (0, -inf, 0), one whose
+// scores are all -inf (0, -FLT_MAX, 0); neither weighs anything beside one with a score.
 template <int HD, int NBI, int NW>
 OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin, int nblk, int seq_len, int q_row, int wave,
                             int lane, uint64_t *trace, bool &first_piece, f32x4 (&O)[HD / 16], float &m, float &lsum)
@@ -313,7 +315,7 @@ OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin
 
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m = -INFINITY;
+    m = -FLT_MAX;   // (finite: a first step whose scores all overflow to -inf weighs nothing, where -inf - -inf would make it NaN)
     lsum = 0.f;
 
     issue_k(0);

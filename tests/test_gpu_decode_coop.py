@@ -97,3 +97,28 @@ def test_replays_and_later_calls_find_clean_counters(chunk):
             torch.cuda.synchronize()
             assert torch.equal(out.view(torch.int16), want.view(torch.int16))
     assert_parity(want.view(torch.int16).cpu().numpy().view(np.uint16), oracle(b), "replayed")
+
+
+# K blocks whose scores overflow to -inf in fp32 (their weight is zero): the first steps of a piece, of one wave, of all but
+# one wave of four, all of a piece but its last block
+MASKED = {"start": [(0, 4)], "one-wave": [(2, 4), (10, 12)], "middle": [(8, 16)], "second-half": [(0.5, 1.0)], "all-but-last": [(0, -1)],
+          "all-but-first": [(1, 1.0)]}
+
+
+@pytest.mark.parametrize("opts", [{}, {"decode_coop": 0}, {"decode_coop": 2, "decode_segments": 9}, {"decode_nbi": 1}],
+                         ids=["default", "single", "9runs", "nbi1"])
+@pytest.mark.parametrize("masked", list(MASKED))
+def test_keys_whose_scores_are_minus_infinity_weigh_nothing(masked, opts):
+    for heads, chunk in (((32, 8, 128), None), ((4, 1, 64), None), ((28, 4, 128), (37, 100))):
+        b = decode_batch(heads, [600, 40, 3000], seed=54, chunk=chunk)
+        say(f"case: {heads} {masked} {opts} chunk {chunk}")
+        b.q = np.where(b.q == b.q, np.uint16(0x3F80), np.uint16(0))                  # ones
+        for i, (n, ql) in enumerate(zip(b.seq_lens, b.q_lens)):
+            nb = (int(n) + 15) // 16
+            if ql > 1 or nb < 16:
+                continue
+            for lo, hi in MASKED[masked]:
+                lo = int(lo * nb) if isinstance(lo, float) else lo
+                hi = int(hi * nb) if isinstance(hi, float) else hi % nb
+                b.k_cache[b.block_tables[i, lo:hi]] = 0xFF61                        # -2.98e38: scores below -FLT_MAX
+        assert_parity(run_gpu(b, options=opts), oracle(b), masked)
