@@ -152,9 +152,10 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                         decode kernel's 3 %, a longer one not the lean prefill kernel's 5 %); 0 = never (the
  *                         stand-alone kernels side by side); 2 = whenever the batch holds both kinds of work.
  *   "decode_coop"         0/1/2 (default 1; batches without XCD weights or a dynamic tail): 1 = small batches run in
- *                         workgroups of four waves that share every piece of a run and merge in LDS, and batches of a
- *                         few sequences of at most 768 tokens (1536 with head_dim 64) take one such workgroup per
- *                         sequence and kv head; 0 = single waves; 2 = such workgroups always.  (Forcing "decode_nbi"
+ *                         workgroups of four waves that share every piece of a run and merge in LDS, and batches of
+ *                         sequences of at most 768 tokens (1536 with head_dim 64) take one such workgroup per
+ *                         sequence and kv head while that is one per compute unit -- or up to four, where that is
+ *                         measured faster than single waves; 0 = single waves; 2 = such workgroups always.  (Forcing "decode_nbi"
  *                         asks for single waves.)
  *   "prefill_waves"       waves per prefill workgroup: 4 (128 query columns per staged K/V tile), 8 (256), or
  *                         0 (default) = 4, and 8 where "mixed_lean" applies.  Other values -> OOCO_EINVAL.

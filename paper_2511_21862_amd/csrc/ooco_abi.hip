@@ -192,14 +192,32 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     const int64_t per_unit = std::max<int64_t>(1, (int64_t)geo.num_cus / geo.Hkv);   // runs that put one workgroup (of one kv head) on every unit
     const bool coop_can = plain && geo.tail_pct == 0 && geo.xcd_cw[kXcds - 1] == 0;
     const bool coop_rule = small && (short_seqs ? dec_seqs == 1 : dec_seqs * (pf_wgs > 0 ? 1 : 2) <= per_unit);
-    // A batch of a few short sequences takes one workgroup per (sequence, kv head) and cuts nothing: no partial results,
-    // no arrival counters, no merge through memory.  Up to 768 tokens (48 blocks of head_dim 128: six steps of the four
-    // waves; sixteen sequences of 300..600 tokens 13.5 -> 10.3 us, 32 of 200..500 16.7 -> 11.0, four of 60..200
-    // 9.8 -> 5.1; one of 1000 tokens is faster cut, 13.0 against 7.8) and four workgroups per unit (256 sequences of
-    // 100..300 tokens and 4 kv heads 30.9 -> 28.2, with 8 kv heads 46.0 -> 51.4) -- two beside a prefill part, whose
-    // workgroups wait behind them (128 of 60..200 tokens, 4 kv heads, beside 100 rows 20.3 against 23.0).
-    if (coop_can && geo.coop_opt && geo.segments_opt == 0 && max_blocks * geo.hd <= 48 * 128 &&
-        (int64_t)num_seqs * geo.Hkv <= (pf_wgs > 0 ? 2 : 4) * (int64_t)geo.num_cus) {
+    // A batch of short sequences takes one workgroup per (sequence, kv head) and cuts nothing: no partial results, no arrival
+    // counters, no merge through memory.  Sequences of up to 768 tokens (48 blocks of head_dim 128: six steps of the four
+    // waves; one of 1000 tokens is faster cut, 13.0 against 7.8 us), and by the number of workgroups per unit, against
+    // single waves:
+    //   * up to one: always (equal lengths 0.9 of the time, unequal ones 0.4..0.9).
+    //   * up to two: but for equal lengths with head_dim 128 -- single waves, one run per sequence, cut nothing there either
+    //     and start with one wave (64 sequences of 250 tokens, 8 kv heads, 14.9 against 12.2 us; unequal lengths 11.1
+    //     against 13.9) --, and, without a prefill part, from 1.5 on but for sequences of more than 512 tokens that are much
+    //     longer than the others (64 of median 150, longest 600: 1.09 of the time).
+    //   * up to four, without a prefill part (whose workgroups would wait behind them: 128 of 60..200 tokens, 4 kv heads,
+    //     beside 100 rows 23.0 against 20.3): unequal lengths in groups of so many heads that their partial results cost
+    //     single waves most (256 of 62..250 tokens, 28/4 heads, 21.9 against 25.7; 640 of 150..600, 16/1 heads, 30.1
+    //     against 38.3; 64/8 heads 0.75..1.0 of the time; 32/8 up to 2.5 workgroups 0.7..1.05, four 0.8..1.1; 32/32 0.9..1.3:
+    //     smaller groups beyond that only up to 128 tokens, 0.75..1.0); up to 2.5 also equal ones of more than 384 tokens
+    //     (0.8..0.98).
+    const int64_t wgs = (int64_t)num_seqs * geo.Hkv, cus = geo.num_cus, g = geo.Hq / geo.Hkv;
+    const int64_t longest = max_blocks * geo.hd;   // (in blocks of head_dim 1)
+    const bool equal = max_blocks * dec_seqs == kv_blocks, skewed = 5 * kv_blocks < 2 * max_blocks * dec_seqs;
+    bool whole = longest <= 48 * 128;
+    if (whole && wgs > 2 * cus) {
+        const int64_t up_to = geo.hd == 64 ? (g >= 4 ? 32 : 8) : g >= 6 || (g >= 4 && 2 * wgs <= 5 * cus) ? 48 : 8;
+        whole = pf_wgs == 0 && longest <= up_to * 128 && (equal ? 2 * wgs <= 5 * cus && longest > 24 * 128 : wgs <= 4 * cus);
+    } else if (whole && wgs > cus) {
+        whole = (geo.hd == 64 || !equal) && (pf_wgs > 0 || 2 * wgs <= 3 * cus || longest <= 32 * 128 || !skewed);
+    }
+    if (coop_can && geo.coop_opt && geo.segments_opt == 0 && whole) {
         out.coop = kCoopBySequence;
         out.nbi = geo.hd == 128 ? 2 : 0;
         out.static_runs = num_seqs;

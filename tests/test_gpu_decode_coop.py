@@ -58,6 +58,18 @@ def test_small_batches(heads, lens):
     assert np.array_equal(got, run_gpu(b))
 
 
+@pytest.mark.parametrize("heads", [(32, 8, 128), (32, 4, 64)], ids=lambda h: "-".join(map(str, h)))
+@pytest.mark.parametrize("lens", ["equal", "unequal"])
+def test_two_workgroups_per_unit(heads, lens):
+    # equal lengths: single waves, one run per sequence (head_dim 128), unequal ones: whole sequences in four waves
+    n = 2 * 256 // heads[1]
+    b = decode_batch(heads, [100] * n if lens == "equal" else [40 + 16 * (i % 5) for i in range(n)], seed=55)
+    names, runs = kernels(b, {})
+    say(f"case: {n} {lens} sequences, {heads}: {names}, {runs} runs")
+    assert names[0].startswith("decode_kernel" if lens == "equal" and heads[2] == 128 else "decode_coop_kernel") and runs == n
+    assert_parity(run_gpu(b), oracle(b), lens)
+
+
 @pytest.mark.parametrize("opts", [{"decode_coop": 2, "decode_segments": 1}, {"decode_coop": 2, "decode_segments": 7},
                                   {"decode_coop": 2, "decode_segments": 10 ** 6}, {"decode_coop": 2, "rotate_heads": 0}, {"decode_nbi": 1}],
                          ids=["1run", "7runs", "block-runs", "no-rotate", "nbi1"])

@@ -38,6 +38,39 @@ def test_short_sequences_are_taken_whole_up_to_the_limit(heads, limit):
         check_cover(r, q, c)
 
 
+def whole(heads, lens, chunk=None):
+    q, c = [1] * len(lens), [n - 1 for n in lens]
+    if chunk:
+        q.append(chunk[0])
+        c.append(chunk[1])
+    r = dry(heads, q, c)
+    check_cover(r, q, c)
+    return r["decode_runs"] == len(q) and all(int(p[3]) < 0 for p in r["decode_pieces"]) and \
+        [int(p[4]) for p in sorted(r["decode_pieces"], key=lambda p: p[4])] == [i for i, x in enumerate(q) if x == 1]
+
+
+def mixed_lengths(n, longest, shortest=None):
+    return [longest] + [(shortest or longest // 2) + 16 * (i % 3) for i in range(n - 1)]
+
+
+@pytest.mark.parametrize("heads", [(32, 8, 128), (64, 8, 128), (32, 32, 128), (32, 4, 64)], ids=lambda h: "-".join(map(str, h)))
+def test_batches_of_several_workgroups_per_unit(heads):
+    # measured against single waves: equal lengths only up to one workgroup per unit with head_dim 128 (single waves, one run
+    # per sequence, cut nothing there either), long outliers up to 1.5, more than two per unit by the group's size
+    per_unit, hd, g = 256 // heads[1], heads[2], heads[0] // heads[1]
+    n = lambda r: int(per_unit * r)
+    assert whole(heads, [240] * n(1)) and whole(heads, mixed_lengths(n(1), 700, 64))
+    # (a line of equal sequences in as many runs as sequences cuts nothing, but its workgroups would be cooperative)
+    for r in (1.5, 2):
+        assert whole(heads, mixed_lengths(n(r), 500))
+        assert whole(heads, mixed_lengths(n(r), 600 * 128 // hd, 64)) == (r <= 1.5)
+        assert whole(heads, mixed_lengths(n(r) - 1, 600 * 128 // hd, 64), (40, 100))
+    assert whole(heads, mixed_lengths(n(4), 100)) and not whole(heads, mixed_lengths(n(4) + per_unit // 8, 100))
+    assert whole(heads, mixed_lengths(n(4), 600)) == (g >= 6)
+    assert whole(heads, mixed_lengths(n(2.5), 600)) == (g >= 4)
+    assert not whole(heads, mixed_lengths(n(3) - 1, 100), (40, 100))
+
+
 @pytest.mark.parametrize("heads", [(32, 8, 128), (28, 4, 128), (32, 4, 64), (16, 1, 128)])
 @pytest.mark.parametrize("workspace", [128 << 20, 1 << 20, 40000])
 def test_lines_with_larger_pads_cover_every_block_once(heads, workspace):
