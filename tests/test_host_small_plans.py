@@ -71,6 +71,19 @@ def test_batches_of_several_workgroups_per_unit(heads):
     assert not whole(heads, mixed_lengths(n(3) - 1, 100), (40, 100))
 
 
+@pytest.mark.parametrize("heads,n,longest,runs", [((64, 8, 128), 24, 1000, 48), ((32, 8, 128), 40, 768, 40), ((32, 8, 128), 35, 1536, 64),
+                                                  ((32, 32, 128), 12, 1000, 12), ((32, 8, 128), 48, 1536, 48)])
+def test_equal_sequences_get_as_many_runs_each(heads, n, longest, runs):
+    # ... unless that leaves too few waves for long sequences
+    r = dry(heads, [1] * n, [longest - 1] * n)
+    assert r["decode_runs"] == runs
+    check_cover(r, [1] * n, [longest - 1] * n)
+    if runs % n == 0:
+        assert len(r["decode_pieces"]) == runs
+    uneven = [longest - 1 - 16 * (i % 2) for i in range(n)]
+    assert dry(heads, [1] * n, uneven)["decode_runs"] >= runs
+
+
 @pytest.mark.parametrize("heads", [(32, 8, 128), (28, 4, 128), (32, 4, 64), (16, 1, 128)])
 @pytest.mark.parametrize("workspace", [128 << 20, 1 << 20, 40000])
 def test_lines_with_larger_pads_cover_every_block_once(heads, workspace):
