@@ -121,9 +121,10 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *   "decode_piece_pad"    what starting a piece is charged when the line is cut into runs, in KV
  *                         blocks: a run that holds the beginnings of n sequences streams n times
  *                         this many blocks less than a run that holds none, so that all waves
- *                         finish together.  Default 3 * 128 / head_dim (a wave needs about 3 us
- *                         from one piece to the first tile of the next); 0 = runs of equal
- *                         block counts; at most 64.
+ *                         finish together.  Unset: 3 * 128 / head_dim (a wave needs about 3 us
+ *                         from one piece to the first tile of the next), four times that in runs that
+ *                         workgroups of four waves share ("decode_coop"); 0 = runs of equal
+ *                         block counts; at most 64.  A value that is set holds for both.
  * Prefill tiles (takes effect at the next ooco_plan):
  *   "prefill_split"       parts a prefill tile's key range is cut into, 1..16 (more is taken as 16); every part is
  *                         a workgroup of its own and the last one to finish merges their partial

@@ -79,7 +79,7 @@ struct PlanGeometry {
     int64_t tail_pct;       // share of the decode line handed out dynamically, in percent
     int64_t tail_blocks;    // KV blocks per dynamically fetched run
     int64_t pf_split_opt = 0;   // parts per prefill tile; 0 = automatic
-    int64_t piece_pad = 0;      // line units charged for starting a piece (see build_plan)
+    int64_t piece_pad = -1;     // line units charged for starting a piece (see build_plan); < 0 = automatic
     int64_t pf_waves_opt = 0;   // waves per prefill workgroup: 4, 8, or 0 = automatic
     int64_t coop_opt = 1;       // cooperative decode workgroups: 0 never, 1 by rule, 2 always
     int64_t lean_opt = 0;       // mixed batches: register-lean kernels (see HostPlan::lean)
@@ -239,7 +239,7 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         // Starting a piece costs the whole workgroup, so it weighs more in the line: as much as 12 tiles of head_dim 128.
         // Pads of 3 / 6 / 12 / 24: sixteen sequences of 512..4096 tokens 31.5 / 31.1 / 30.6 / 30.5 us, sixteen of
         // 1000..2000 22.8 / 22.0 / 21.0 / 21.8; head_dim 64, pads of 6 / 12 / 24 / 36: 12.3 / 11.3 / 10.2 / 10.2.
-        if (geo.piece_pad == default_piece_pad(geo.hd)) {
+        if (geo.piece_pad < 0) {
             const int32_t more = 3 * default_piece_pad(geo.hd);
             int32_t added = 0;
             for (int i = 0; i < num_seqs; ++i) {
@@ -524,7 +524,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     int64_t dec_blocks = 0, kv_blocks = 0, tiles = 0, tile_steps = 0, max_tile_steps = 1;
     int64_t dec_seqs = 0, max_dec_blocks = 0;    // decode sequences that hold at least one block, blocks of the longest
     double pf_pairs = 0.0;   // visible (query row, key) pairs of all prefill chunks
-    const int64_t pad = geo.piece_pad;
+    const int64_t pad = geo.piece_pad < 0 ? default_piece_pad(geo.hd) : geo.piece_pad;
     // Waves per prefill workgroup.  Eight waves share every K/V tile staged in LDS among 256 query columns instead
     // of 128, which halves the traffic from L2 into the compute units.  Measured on MI355X it is no faster (that
     // traffic is not what bounds the kernel) and its 220-register waves leave no room for decode waves beside
@@ -798,7 +798,7 @@ struct ooco_ctx {
     int64_t opt_pf_table = 1;       // few prefill tiles: dispatched by decreasing number of steps across chunks
     int opt_copy_variant = 0;       // block copy: 10 x vectors per thread + non-temporal flag, 0 = default
     int64_t opt_decode_first = 1;   // mixed batches: enqueue the decode kernel before the prefill kernel
-    int64_t opt_piece_pad = 0;   // set at creation: 3 tiles of head_dim 128
+    int64_t opt_piece_pad = -1;   // < 0: automatic (3 tiles of head_dim 128, 12 in cooperative plans)
     int32_t *pf_counters = nullptr;   // [kPrefillSplitUnits] arrival counters of split prefill tiles, zero between calls
     uint16_t xcd_cw[kXcds] = {};   // option "xcd_weights"
     int64_t opt_overlap = 1;
@@ -900,7 +900,6 @@ ooco_status ooco_ctx_create(ooco_ctx **out, int num_q_heads, int num_kv_heads, i
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess && cus > 0)
             c->num_cus = cus;
     }
-    c->opt_piece_pad = default_piece_pad(head_dim);
     if (e == hipSuccess) {
         if (workspace) {
             c->ws = workspace;
@@ -1170,7 +1169,7 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
         geo.tail_blocks = decode_tail_blocks;
         geo.pf_split_opt = prefill_split;
         geo.lean_opt = 1;   // (the default of a context)
-        geo.piece_pad = decode_piece_pad < 0 ? default_piece_pad(head_dim) : decode_piece_pad;
+        geo.piece_pad = decode_piece_pad;
         if (xcd_weights && !xcd_weights_to_cw(xcd_weights, geo.xcd_cw)) {
             snprintf(err, sizeof err, "ooco_plan_dry_run: xcd_weights needs eight values in 1..255 that differ by at most 4x");
             st = OOCO_EINVAL;
@@ -1555,7 +1554,6 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     geo.tail_pct = 0;
     geo.tail_blocks = 0;
     geo.pf_split_opt = 1;
-    geo.piece_pad = default_piece_pad(head_dim);
     int32_t store[storage_ints(kInlineSeqs)];
     HostPlan pl;
     ooco_status st = build_plan(geo, num_seqs, h_seq_lens, h_query_start_loc, h_ctx_lens, carve_storage(store, kInlineSeqs), pl, err);

@@ -105,3 +105,14 @@ def test_prefill_parts_hidden_behind_a_long_decode_part_stay_few():
     assert beside < min(alone, few)
     # ... but a chunk that would outlast the decode part is still cut
     assert dry((32, 8, 128), [100] + [1] * 48, [10000] + dec)["prefill_parts"] >= 5
+
+
+@pytest.mark.parametrize("heads,default,grown", [((32, 8, 128), 3, 12), ((32, 4, 64), 6, 24)])
+def test_a_piece_pad_that_is_set_to_the_default_is_taken_as_it_is(heads, default, grown):
+    # (cooperative plans charge a piece's start four times as much unless the option says otherwise)
+    rng = np.random.default_rng(8)
+    q, c = [1] * 16, [int(x) for x in rng.integers(2000, 4000, size=16)]
+    pieces = lambda pad: dry(heads, q, c, decode_piece_pad=pad)["decode_pieces"].tolist()
+    assert pieces(-1) == pieces(grown)
+    assert pieces(default) != pieces(grown)
+    check_cover(dry(heads, q, c, decode_piece_pad=default), q, c)
