@@ -195,8 +195,8 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *   "trace"      0/1: see ooco_trace_read
  * Tuning knobs kept for experiments (defaults are the measured best): "decode_nbi" (KV blocks per
  * softmax step of the decode kernel: 1, 2 or 4; 0 = the plan's choice: 1 for head_dim 128 -- 2 for small batches, whose
- * waves are chains of dependent steps --, 2 for head_dim 64), "copy_sort" (block copy: 0 = pairs in the caller's order, 1 = default: copies of 192 MiB of K and V or more -- 640 MiB
- * above 16,384 pairs -- are first ordered by destination region on the device, into a buffer of the context that grows on
+ * waves are chains of dependent steps --, 2 for head_dim 64), "copy_sort" (block copy: 0 = pairs in the caller's order, 1 = default: copies of 2048 pairs or more
+ * that are 192 MiB of K and V or more -- 640 MiB above 16,384 pairs -- are first ordered by destination region on the device, into a buffer of the context that grows on
  * demand -- measured on MI355X, 8192 blocks of 64 KiB into random slots of a staging pool: 209 -> 187 us including the
  * ordering, which costs about 8 us and does not pay when the slots are handed out in ascending order anyway -- 2 = always),
  * "append_parts" (KV append: workgroups that share one (sequence, KV block) pair,

@@ -1659,8 +1659,10 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
     // to kOrderPairsMax pairs, and 28 us and more in the radix sort beyond.  Measured on MI355X, unordered / ordered:
     // 8 kv heads of 128, 2048 pairs 53.0 / 51.6 us, 8192 209 / 187; 4 heads of 128, 4096 pairs 52.5 / 53.6, 8192 107 / 101;
     // 4 heads of 64, 8192 pairs 53.2 / 55.1, 16,384 106.1 / 105.5, 32,768 211 / 216 (radix), 65,536 427 / 405 (radix).
+    // Below 2048 pairs, whose blocks are then of 96 KiB and more, slots handed out in ascending order lose what others gain:
+    // 32 heads of 128, 1000 pairs 98.6 / 93.1 us, ascending 89.4 / 92.9; 2047 pairs 203.9 / 188.2, ascending 182.5 / 186.9.
     const int64_t bytes_one_way = 2 * num_pairs * block_bytes;
-    const bool order_pays = bytes_one_way >= (num_pairs <= kOrderPairsMax ? (int64_t)192 << 20 : (int64_t)640 << 20);
+    const bool order_pays = num_pairs >= 2048 && bytes_one_way >= (num_pairs <= kOrderPairsMax ? (int64_t)192 << 20 : (int64_t)640 << 20);
     // (nor may a captured copy name the buffer a context has already: a later call frees it when it needs a larger one,
     // and replays would go on using the freed memory)
     bool ordered = ctx->opt_copy_sort >= 2 || (ctx->opt_copy_sort == 1 && order_pays);

@@ -78,3 +78,23 @@ def test_a_captured_copy_does_not_use_the_buffer_of_ordered_copies():
             torch.cuda.synchronize()
             for w, d in zip(want, dst):
                 assert torch.equal(w.view(torch.int16), d.view(torch.int16)), f"replay {rep}"
+
+
+@pytest.mark.parametrize("n,ordered", [(2047, False), (2048, True)])
+def test_copies_of_few_large_blocks_keep_the_callers_order(n, ordered):
+    # (an ordered copy allocates the context's buffer: seen here over many contexts)
+    say(f"case: {n} pairs of 128 KiB")
+    pool = 2048
+    src = [torch.zeros((pool, 32 * 128 * 16), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    dst = [torch.empty_like(s) for s in src]
+    ids = torch.arange(n, dtype=torch.int64, device="cuda")
+    ctxs = [B.Context(32, 32, 128, 16, pool, 8, workspace_bytes=1 << 20) for _ in range(40)]
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    for c in ctxs:
+        c.kv_block_copy(src[0], src[1], dst[0], dst[1], ids, ids)
+    torch.cuda.synchronize()
+    used = before - torch.cuda.mem_get_info()[0]
+    for c in ctxs:
+        c.close()
+    assert (used >= 40 * 16384 * 16) == ordered, used
