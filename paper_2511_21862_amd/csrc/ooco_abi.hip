@@ -258,8 +258,16 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         // be short, up to two waves per unit (sixteen of 60..200 tokens 10.5 -> 8.6 us; head_dim 64: 64 of them
         // 18.7 -> 7.8; three waves per unit: 64 of 16..292 tokens, four layers, 48.9 -> 52.1).  Beside a prefill part
         // runs of 12 blocks (100 rows and 32 of 100..400 tokens, 4 kv heads, 14.7 us, with runs of 4 blocks 18.5).
-        if (tiles <= 16384 && max_blocks * dec_seqs > kv_blocks + kv_blocks / 4 && kv_blocks >= 6 * dec_seqs)
-            at_least = std::max(at_least, std::min<int64_t>((int64_t)geo.num_cus * 2 / geo.Hkv, kv_blocks / (pf_wgs > 0 ? 12 : 4)));
+        // No shorter than about the root of the longest sequence, though: one wave merges that one's parts, a quarter,
+        // half or all of them in a row for groups of up to 4, 8 and 16 heads (16/1 heads, 128 sequences of median 250,
+        // longest 1000 tokens, runs of 4 / 6 / 8 / 12 / 16 blocks 22.5 / 17.3 / 14.8 / 13.8 / 14.8; 127 of 30..300 and one
+        // of 8000 in runs of 4 blocks 66.7, of 14 26.0).
+        if (tiles <= 16384 && max_blocks * dec_seqs > kv_blocks + kv_blocks / 4 && kv_blocks >= 6 * dec_seqs) {
+            const int64_t in_a_row = max_blocks * (g <= 4 ? 1 : g <= 8 ? 2 : 4) * geo.hd / 128;
+            int64_t len = pf_wgs > 0 ? 12 : 4;
+            while (8 * len * len < 5 * in_a_row) ++len;
+            at_least = std::max(at_least, std::min<int64_t>((int64_t)geo.num_cus * 2 / geo.Hkv, kv_blocks / len));
+        }
     } else if (small) {
         // (head_dim 64 keeps three: 363 sequences of 770 tokens on average 58.3 against 69.9 us with two)
         wave_slots = std::max<int64_t>(1, (int64_t)geo.num_cus * (geo.hd == 128 ? 2 : 3) / geo.Hkv);

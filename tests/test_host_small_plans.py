@@ -116,3 +116,16 @@ def test_a_piece_pad_that_is_set_to_the_default_is_taken_as_it_is(heads, default
     assert pieces(-1) == pieces(grown)
     assert pieces(default) != pieces(grown)
     check_cover(dry(heads, q, c, decode_piece_pad=default), q, c)
+
+
+@pytest.mark.parametrize("heads", [(16, 1, 128), (28, 4, 128), (64, 8, 128), (32, 8, 128), (32, 4, 64)], ids=lambda h: "-".join(map(str, h)))
+def test_one_long_sequence_among_short_ones_is_not_cut_into_crumbs(heads):
+    # its parts are merged by one wave, one after the other
+    rng = np.random.default_rng(9)
+    n = 256 // heads[1]
+    for longest in (2500, 8000):
+        q, c = [1] * n, [int(x) for x in rng.integers(30, 250, size=n - 1)] + [longest - 1]
+        r = dry(heads, q, c)
+        check_cover(r, q, c)
+        parts = sum(int(p[0]) == n - 1 for p in r["decode_pieces"])
+        assert 4 <= parts <= (40 if longest == 8000 else 20), (longest, parts)
