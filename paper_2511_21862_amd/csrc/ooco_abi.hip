@@ -275,7 +275,7 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         // (sequences of equal lengths: as many runs to each, so that no run holds the end of one and the start of the next --
         // 24 of 1000 tokens, 64/8 heads, in 48 runs 21.2 us, in 64 23.7; 40 of 768, 8 kv heads, in 40 23.2, cut 28.1 --
         // unless too few waves are left for long ones: 35 of 1536 in 35 runs 41.9, in 64 39.8)
-        const int64_t odd = equal && wave_slots > dec_seqs ? wave_slots % dec_seqs : 0;
+        const int64_t odd = geo.hd == 128 && equal && wave_slots > dec_seqs ? wave_slots % dec_seqs : 0;
         if (8 * odd <= 3 * wave_slots || longest <= 48 * 128) wave_slots -= odd;
     }
     int64_t runs = geo.segments_opt > 0 ? geo.segments_opt
