@@ -117,6 +117,7 @@ struct HostPlan {
     // then run in sequence on the caller's stream (the fork and join of the second stream cost more than they gain)
     bool brief = false;
     bool two_streams = false;    // a batch with both kinds of work that runs faster as two kernels on two streams than in one launch
+    bool near = false;           // step kernel: AttnParams::dec_near
     int32_t coop = 0;            // decode runs are worked on by workgroups of four waves (decode_coop_kernel); kCoopBySequence: run i is sequence i
     int32_t nbi = 0;             // KV blocks per softmax step of the decode kernel that the plan asks for (0 = the kernel's default)
 };
@@ -685,6 +686,10 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     }
     // ---- run layout of the decode block line (see plan_decode_runs)
     if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, max_dec_blocks, tiles * geo.Hkv, lean, dcum, out);
+    // The lean pair's decode waves of a workgroup side by side (half a percent of a long stream), but not where the longest
+    // sequence is cut into more than 32 parts, whose merges then meet on one unit (see step_body): near / far by parts, 64/8
+    // heads, 100,000 tokens: 16 0.99, 32 0.98, 43 1.04, 64 1.10, 128 1.17; 28/4 heads, 400,000: 32 1.02, 85 1.12, 128 1.24.
+    out.near = lean && dec_blocks > 0 && max_dec_blocks * out.static_runs <= 32 * (int64_t)out.dec_blocks;
     // ---- prefill tiles cut along the context (see plan_prefill_parts)
     if (tiles > 0) {
         const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, pf_waves, dec_blocks, kv_blocks, pf_pairs};
@@ -1404,6 +1409,7 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     p.nbi = ctx->opt_nbi ? (int32_t)ctx->opt_nbi : pl.nbi;
     p.rotate_heads = (int16_t)(ctx->opt_rotate != 0);
     p.coop = (int16_t)decode_coop(ctx);
+    p.dec_near = (int16_t)pl.near;
     p.lean = (int16_t)pl.lean;
     for (int k = 0; k < kXcds; ++k) p.xcd_cw[k] = pl.cw[k];
 
@@ -1615,6 +1621,7 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.pf_waves = (int16_t)pl.pf_waves;
     p.nbi = pl.nbi;
     p.coop = (int16_t)pl.coop;
+    p.dec_near = (int16_t)pl.near;
     p.rotate_heads = 1;
     p.pf_acc = nullptr;
     p.pf_ml = nullptr;

@@ -66,6 +66,7 @@ struct AttnParams {
     int16_t dec_cus;            // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
     int16_t pf_waves;           // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave)
     int16_t dec_wpw;            // step kernel: decode waves of such a workgroup (set by launch_step)
+    int16_t dec_near;           // step kernel: they take items side by side (the kv heads of one run), else far apart
     int32_t nbi;                // tuning: KV blocks per softmax step of the decode kernel
     int16_t rotate_heads;       // tuning: kv head rotation across XCDs
     int16_t coop;               // decode: workgroups of four waves that share every piece of a run (decode_coop_kernel): 1, kCoopBySequence, or 0

@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void 
 }
 
 // ------------------------------------------------------------------------------------------
-// Both kinds of work of a step in ONE launch: the first p.dec_wgs workgroups are decode waves (four per workgroup, each
+// Both kinds of work of a step in ONE launch: the first p.dec_wgs workgroups are decode waves (up to four per workgroup, each
 // one (run, kv head) item of the decode line, exactly as in the decode kernel), the others prefill workgroups (exactly
 // as in the prefill kernel).  Every unit holds both kinds side by side as with two kernels on two streams, without the
 // fork and join events of the second stream, and a short batch does not wait for one kernel to drain before the other
@@ -1413,7 +1413,10 @@ OOCO_DEV void step_body(const KernArgs &a)
         }
     } else if (!COOP && (int)blockIdx.x < p.dec_wgs) {
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        const int item = (int)blockIdx.x * p.dec_wpw + wave;
+        // (the waves of a workgroup take items far apart: side by side they hold the kv heads of one run, finish together and
+        // merge one long sequence's parts on one unit, which reads no faster for three waves than for one -- a sequence of
+        // 73,000 tokens in 80 parts, 64/8 heads: 52 us from the last step to the end, and 26 apart)
+        const int item = p.dec_near ? (int)blockIdx.x * p.dec_wpw + wave : wave * p.dec_wgs + (int)blockIdx.x;
         if (wave >= p.dec_wpw || item >= p.static_runs * p.Hkv) return;
         asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens),
                      "s"(p.query_start_loc), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),

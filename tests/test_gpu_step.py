@@ -38,6 +38,8 @@ CASES = {
     "g16": ((16, 1, 128), [9, 1, 1, 17], [40, 3000, 15, 260]),
     # more than one decode wave per workgroup, cut sequences, a split chunk
     "waves": ((32, 8, 128), [1] * 20 + [150], [1400 + 97 * i for i in range(20)] + [3000]),
+    # a sequence in so many parts that the lean pair's decode waves are spread too
+    "one-long": ((64, 8, 128), [40, 1, 1], [100, 30000, 500]),
     "qwen": ((28, 4, 128), [105, 1, 1, 132, 1, 1], [858, 4095, 130, 268, 17, 2222]),
 }
 
