@@ -29,9 +29,9 @@ if not os.path.exists(LIB_PATH):
 # with libooco.so (linked against the system's runtime) loaded before torch, the process holds two runtimes and the
 # second to touch the GPU finds no device
 try:
-    import torch  # noqa: F401
+    import torch
 except ImportError:      # host-only use (planner, model, scheduling functions)
-    pass
+    torch = None
 
 _lib = ctypes.CDLL(LIB_PATH)
 _P = ctypes.c_void_p
@@ -114,11 +114,18 @@ def _host_i32(a):
         return arr, arr.ctypes.data
 
 
+# The handle of the current stream alone, without the Stream object that torch.cuda.current_stream() builds (which takes
+# longer than the launch's checks).  Names that torch keeps to itself: where it has them no more, the public way serves.
+_raw_stream = getattr(getattr(torch, "_C", None), "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(getattr(torch, "_C", None), "_cuda_getDevice", None)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
-        # (the handle alone: making the Stream object of torch.cuda.current_stream() takes longer than the launch's checks)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if torch is None:
+            raise ImportError("without torch there is no current stream: pass a stream handle")
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

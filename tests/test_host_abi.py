@@ -1,8 +1,10 @@
 """Host-side checks that need no GPU: the library loads, exports every declared symbol, and the
 planner validates lengths and covers every KV block / query row exactly once."""
 import ctypes
+import importlib.util
 import os
 import re
+import types
 
 import numpy as np
 import pytest
@@ -31,6 +33,24 @@ def test_library_exports_every_declared_symbol():
     assert set(names) == set(B.EXPORTS)
     for n in names:
         assert getattr(lib, n) is not None
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_without_torchs_private_names(monkeypatch, private):
+    # the short way to the current stream's handle uses names that torch keeps to itself; without them the public way serves
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    for name, value in (("_cuda_getCurrentRawStream", 55), ("_cuda_getDevice", 0)):
+        if private:
+            monkeypatch.setattr(torch._C, name, lambda *a, v=value: v, raising=False)
+        else:
+            monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_again", B.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream_handle(None) == (55 if private else 77)
+    assert again._stream_handle(types.SimpleNamespace(cuda_stream=9)) == 9 and again._stream_handle(8) == 8
 
 
 def test_ctx_create_rejects_bad_geometry_before_touching_a_device():
