@@ -82,6 +82,21 @@ def test_forced_layouts(chunk, opts):
 
 
 @pytest.mark.parametrize("chunk", [None, (20, 100)], ids=["decode", "mixed"])
+@pytest.mark.parametrize("opts", [{}, {"decode_coop": 2, "decode_segments": 300}, {"decode_coop": 2}], ids=["whole", "300runs", "runs"])
+def test_batches_whose_plan_is_read_from_device_memory(opts, chunk):
+    # more than 960 sequences: the plan's arrays do not fit the kernel arguments.  "runs" has lengths past the limit up to
+    # which sequences are taken whole
+    top = 1600 if opts == {"decode_coop": 2} else 90
+    b = decode_batch((4, 1, 64), [1 + (37 * i) % 90 for i in range(979)] + [top], seed=56, chunk=chunk)
+    names, runs = kernels(b, opts)
+    say(f"case: {len(b.seq_lens)} sequences, {opts}: {names}, {runs} runs")
+    if opts or not chunk:
+        assert names[0].startswith("decode_coop_kernel") and len(names) == (2 if chunk else 1)
+    assert_parity(run_gpu(b, options=opts), oracle(b), str(opts))
+    assert_parity(run_gpu(b, plan=False, options=opts), oracle(b), f"{opts}, planned in the call")
+
+
+@pytest.mark.parametrize("chunk", [None, (20, 100)], ids=["decode", "mixed"])
 def test_replays_and_later_calls_find_clean_counters(chunk):
     # sequences cut into parts: the arrival counters are zero again after every launch, also inside a captured graph
     b = decode_batch((32, 8, 128), [5000, 1500, 64], seed=53, chunk=chunk)

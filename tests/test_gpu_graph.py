@@ -13,12 +13,13 @@ from gpu_util import device_meta, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("mixed", [False, True, "split", "lean", "in sequence"])
+@pytest.mark.parametrize("mixed", [False, True, "split", "lean", "in sequence", "step", "step-split", "step-lean"])
 def test_captured_calls_replay_to_the_eager_result(mixed):
     # "split": the chunk sits on a long prefix, so its tiles are cut along the context and merged through the
     # workspace and the arrival counters, which every replay must find reset
     ql = [1, 1, 96, 1, 1] if mixed else [1, 1, 1, 1, 1]
-    ctx_lens = [3000, 129, 4000 if mixed == "split" else 400, 64, 900]
+    split = mixed in ("split", "step-split")
+    ctx_lens = [3000, 129, 4000 if split else 400, 64, 900]
     b = W.build_batch(Hq=32, Hkv=8, hd=128, q_lens=ql, ctx_lens=ctx_lens, num_blocks=560, seed=91)
     d = W.to_device(b)
     bt, sl, qsl, cl = device_meta(b)
@@ -27,17 +28,21 @@ def test_captured_calls_replay_to_the_eager_result(mixed):
     out = torch.zeros_like(eager)
     with B.Context(b.Hq, b.Hkv, b.hd, b.BS, b.num_blocks, b.max_blocks_per_seq) as ctx:
         ctx.set_option("plan_persistent", 1)     # one plan serves the eager calls, the capture and nothing changes in between
-        # a batch this short runs its two kernels one after the other by default ("in sequence"); the other mixed
-        # variants force the fork onto the context's second stream and the join, which is what a capture must record
-        if mixed and mixed != "in sequence":
+        # "step...": both kinds of work in one launch, which is the default; "in sequence": two kernels one after the other;
+        # the other mixed variants force the fork onto the context's second stream and the join
+        if mixed == "in sequence":
+            ctx.set_option("overlap", 0)
+        elif mixed and not str(mixed).startswith("step"):
             ctx.set_option("overlap", 2)
-        if mixed == "lean":                      # the register-lean pair of kernels of large mixed batches, forced here
+        if mixed in ("lean", "step-lean"):       # the register-lean kernels of large mixed batches, forced here
             ctx.set_option("mixed_lean", 2)
-        if mixed and mixed != "split":           # (the planner would cut even this short chunk's tiles in three)
+        if mixed and not split:                  # (the planner would cut even this short chunk's tiles in three)
             ctx.set_option("prefill_split", 1)
         ctx.plan(b.seq_lens, b.query_start_loc, b.ctx_lens)
-        if mixed not in ("lean", "in sequence"):
-            assert (ctx.plan_info()["prefill_parts"] > 1) == (mixed == "split")
+        names = ctx.plan_kernels()
+        assert len(names) == (1 if not mixed or str(mixed).startswith("step") else 2), names
+        assert ("lean" in names[0]) == (mixed in ("lean", "step-lean")) and names[0].startswith("step") == str(mixed).startswith("step")
+        assert (ctx.plan_info()["prefill_parts"] > 1) == split
         ctx.attn_mixed(d.q, d.k_cache, d.v_cache, bt, sl, qsl, cl, eager)
         torch.cuda.synchronize()
         side = torch.cuda.Stream()
