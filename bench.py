@@ -7,7 +7,7 @@ The default workload is the largest mixed configuration (cfg5: 2 online prefill 
 decode sequences of 32K-131K tokens, 64/8 heads).
 
 A step = one pass of the whole path over one synthetic batch already resident in HBM: host
-planning (ooco_plan) + ooco_attn_mixed (prefill kernel, decode kernel with its in-kernel merge).  Steps
+planning (ooco_plan) + ooco_attn_mixed (both kinds of work in one launch, or a prefill and a decode kernel).  Steps
 rotate over copies of the batch placed in disjoint physical blocks so that no step finds its KV
 in the 256 MB last-level cache.  Prints ONE JSON line.
 """
@@ -575,12 +575,16 @@ def main():
     elif work["decode_seqs"] == 0:
         kern["prefill_ms"] = min(kern["prefill_ms"], region_ms_per_step)
     kern["region_ms_per_step"] = region_ms_per_step
-    kern["overlapped"] = bool(mixed)
+    # (a batch with both kinds of work in ONE launch has that launch's time under both names, and nothing beside it)
+    one_launch = mixed and len(kernels) == 1
+    kern["one_launch"] = one_launch
+    kern["overlapped"] = mixed and not one_launch
 
     whole_step_frac = work["bytes_total"] / (region_ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS
     if dominant == "decode":
-        # the dominant kernel as it runs in the step (beside the prefill kernel when the batch holds both kinds)
-        alg = work["bytes_decode"]
+        # the dominant kernel as it runs in the step (beside the prefill kernel when the batch holds both kinds; in one
+        # launch with it, its bytes are those of both)
+        alg = work["bytes_total"] if one_launch else work["bytes_decode"]
         dur = kern["decode_ms"] * 1e-3
         achieved = alg / dur / 1e9 if dur > 0 else 0.0
         roofline = {"bound": "hbm", "kernel": kernels[0], "achieved": achieved, "peak": HBM_PEAK_GBS,
@@ -588,6 +592,9 @@ def main():
                     "algorithmic_bytes_per_launch": alg, "kernel_ms": kern["decode_ms"],
                     "whole_step_frac": whole_step_frac, "whole_step_bytes": work["bytes_total"],
                     "whole_step_ms": region_ms_per_step}
+        if one_launch:
+            roofline["decode_bytes_per_launch"] = work["bytes_decode"]
+            roofline["tflops_causal"] = work["flops_causal"] / dur / 1e12 if dur > 0 else 0.0
     else:
         alg = work["flops_causal_prefill"]
         dur = kern["prefill_ms"] * 1e-3
