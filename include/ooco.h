@@ -184,9 +184,11 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                3 % faster as two kernels; 2 = those too); it takes every plan whose two arrays fit
  *                the kernel arguments together (num_seqs + chunks * 2 + tiles up to about 960) and that has no dynamic
  *                tail, no "xcd_weights" and the default number of waves.  Output bits are those of the two kernels.
- *                Measured on MI355X against the two kernels: 8 x 512 rows beside 128 decode sequences 305 -> 282 us,
- *                2 x 2048 rows beside 32 long ones 1850 -> 1660, 2 x 120 rows beside 24 short ones 39.5 -> 33.6
- *                (120 random mixes of 1..512 decodes and 1..8 chunks: 2 to 50 % less, one 2 % more)
+ *                Measured on MI355X, one launch / two kernels on two streams: a call on an idle GPU 283 / 297 us
+ *                (8 x 512 rows beside 128 decode sequences) and 1635 / 1653 (2 x 2048 rows beside 32 long ones); in a
+ *                loop of calls level (268 / 266, 1630 / 1625), but 340 and 2170 in a context whose side stream shares
+ *                a hardware queue with the caller's stream, so that its kernels run in sequence (one or two of eight
+ *                contexts made in a row); 2 x 120 rows beside 24 short ones 29 / 45 (37.5 in sequence)
  *   "decode_first"  0/1 (default 1): with "overlap", enqueue the decode kernel before the prefill
  *                kernel (0: the other way round)
  *   "profile"    0/1: every ooco_attn_mixed records HIP events around its two kernels (each on the
@@ -306,7 +308,9 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names /*HOST*/, size_t 
  * Same context + same plan + same inputs give bit-identical output on every call (no
  * floating-point atomics).  One context serves one stream at a time.
  * A planned call enqueues only kernels and event records / waits, so it can be recorded into a HIP
- * graph (stream capture) and replayed; keep "profile" and "trace" off for captured calls.  A plan
+ * graph (stream capture) and replayed; keep "profile" and "trace" off for captured calls.  (Above 960
+ * sequences the kernels read the plan from a buffer of the context: no other plan of such a batch may
+ * be made on it while the graph is in use.)  A plan
  * with a dynamic tail ("decode_tail_pct") is refused on a capturing stream with OOCO_EINVAL (the
  * tail's ticket base is fixed at enqueue time).
  * Errors: OOCO_EINVAL for null pointers / negative sizes, OOCO_ESHAPE when sizes contradict

@@ -171,21 +171,24 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     // with its own start (query vectors, first tiles): four waves per compute unit hide those better than three, and
     // one block per step wastes no padded step.  512 sequences of 128 tokens 58.5 -> 50.9 us, 900 of 64 71.9 -> 62.0,
     // 2048 of 256 403 -> 382, 1024 of 384 285 -> 275; 4096 of 512 tokens are faster with three waves (1430 / 1449 us).
-    // (up to 16,384 tiles of them two blocks per step, and as many runs as sequences even if those hold fewer than 16
+    // Up to 16,384 tiles of them two blocks per step, and as many runs as sequences even if those hold fewer than 16
     // blocks: 32 sequences of 128 tokens 13.0 -> 10.2 us, 64 of 256 15.2 -> 13.2, 128 of 128 17.7 -> 14.8; 128 of 384
-    // tokens, 24,576 tiles: 34.5 / 33.7 us)
-    // A SMALL batch (at most 36,864 (block, kv head) tiles of head_dim 128) cannot keep HBM busy anyway: what counts
-    // is the chain start -> steps of a wave -> partial result -> merge.
-    //   * While a run holds two or fewer beginnings of sequences on average (beside a prefill part, whose workgroups
-    //     stretch the steps: one) its work is shared by the four waves of a workgroup (decode_coop_kernel), one
-    //     workgroup per unit: one sequence of 1000 tokens 11.1 -> 7.8 us, of 4000 14.1 -> 10.0, of 16,000 24.1 -> 18.8,
-    //     four of 2000..4000 20.1 -> 16.2, sixteen of them 37.7 -> 36.2 (4 kv heads: 25.3 -> 22.8); with more pieces
-    //     than that every piece's start costs four waves: 32 of 1000..2000 tokens 38.3 against 36.1 in single waves.
-    //     Runs of 16 blocks at least -- 8 where the sequences are of 64 blocks or fewer on average and so have few parts
-    //     to merge (four of 500..1000 tokens 11.3 -> 8.5 us, but one of 4000 10.0 -> 12.3).
+    // tokens, 24,576 tiles: 34.5 / 33.7 us.
+    // A SMALL batch (at most 36,864 tiles, a tile being a (block, kv head) pair's 8 KiB of head_dim 128: with head_dim 64
+    // twice as many blocks) cannot keep HBM busy anyway: what counts is the chain start -> steps of a wave -> partial
+    // result -> merge.
+    //   * One sequence, or sequences of more than 384 tokens on average with at most one beginning per two runs -- per run
+    //     beside a prefill part, whose workgroups hold units that single waves would want too --: its work is shared by the four waves of a workgroup
+    //     (decode_coop_kernel), one workgroup per unit: one sequence of 1000 tokens 11.1 -> 7.8 us, of 4000 14.1 -> 10.0,
+    //     of 16,000 24.1 -> 18.8, four of 2000..4000 20.1 -> 16.2, sixteen of 1250..5000 39.8 -> 36.1
+    //     (28/4 heads, 28 of them: 41.0 -> 39.2); the more pieces, the more of their starts cost four waves each: level at
+    //     32 to 40 sequences of 8 kv heads.
+    //     Runs hold at least 16 blocks -- 8 where the sequences are of 64 blocks or fewer on average and so have few parts
+    //     to merge (four of 500..1000 tokens 11.3 -> 8.5 us, but one of 4000 10.0 -> 12.3); 32 for sequences of more than
+    //     512 blocks on average, whose many parts cost more than the shorter chain gains (one of 16,000 tokens, 64/8 heads,
+    //     runs of 16 / 32 / 64 blocks 25.0 / 18.9 / 19.3), and beside a prefill part from 256 blocks on.
     //   * Else single waves, two blocks per step, two waves per unit: 32 sequences of 1000..2000 tokens 37.6 -> 36.1,
     //     64 of 300..900 35.0 -> 31.8.
-    // (head_dim 64: a tile is half as large, the limits in blocks are the same)
     const int64_t tiles = kv_blocks * geo.Hkv * geo.hd / 128;
     const bool plain = !lean && out.dec_cus == 0 && dec_seqs > 0;
     const bool short_seqs = plain && kv_blocks <= 24 * dec_seqs;
@@ -273,7 +276,7 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         // (head_dim 64 keeps three: 363 sequences of 770 tokens on average 58.3 against 69.9 us with two)
         wave_slots = std::max<int64_t>(1, (int64_t)geo.num_cus * (geo.hd == 128 ? 2 : 3) / geo.Hkv);
         min_blocks = pf_wgs > 0 ? 24 : 16;
-        // (sequences of equal lengths: as many runs to each, so that no run holds the end of one and the start of the next --
+        // (head_dim 128, sequences of equal lengths: as many runs to each, so that no run holds the end of one and the start of the next --
         // 24 of 1000 tokens, 64/8 heads, in 48 runs 21.2 us, in 64 23.7; 40 of 768, 8 kv heads, in 40 23.2, cut 28.1 --
         // unless too few waves are left for long ones: 35 of 1536 in 35 runs 41.9, in 64 39.8)
         const int64_t odd = geo.hd == 128 && equal && wave_slots > dec_seqs ? wave_slots % dec_seqs : 0;
@@ -661,7 +664,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         const double t_dec = (double)kv_blocks * BS * 2.0 * geo.Hkv * geo.hd * 2.0 / 6.8e12 + 15e-6;
         const double t_pf = 4.0 * geo.Hq * geo.hd * pf_pairs / 1.05e15 + 12e-6;
         out.brief = t_dec + t_pf < 80e-6;
-        // One launch for both kinds saves the second stream's fork and join (about 13 us), and its decode workgroups are
+        // One launch for both kinds saves the second stream's fork and join (13 to 18 us of a call on an idle GPU), and its decode workgroups are
         // spread over the units a little less evenly than the decode kernel's single waves, which a long stream pays for:
         // 32/8 heads, 131 / 276 / 412 us of K/V at 6.8 TB/s beside 4 x 528 rows 172 -> 171, 321 -> 328, 461 -> 470 us; beside
         // 128 workgroups (1 x 512 rows) 164 -> 159, 316 -> 307, 460 -> 457.  (The register-lean pair gains at any length.)
@@ -815,7 +818,7 @@ struct ooco_ctx {
     int32_t *pf_counters = nullptr;   // [kPrefillSplitUnits] arrival counters of split prefill tiles, zero between calls
     uint16_t xcd_cw[kXcds] = {};   // option "xcd_weights"
     int64_t opt_overlap = 1;
-    int64_t opt_copy_sort = 1;      // block copy: order the pairs by destination id on the device (0 never, 1 where the copy is large enough, 2 always)
+    int64_t opt_copy_sort = 1;      // block copy: order the pairs by destination region on the device (0 never, 1 where the copy is large enough, 2 always)
     void *sort_buf = nullptr;       // [2 * sort_cap int64 (sorted dst, sorted src)] + temporary storage of the sort
     int64_t sort_cap = 0;           // pairs the buffer holds
     size_t sort_temp_bytes = 0;
@@ -1634,7 +1637,8 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     // start at zero (a small fill kernel, not a memset node, so that the call can be captured into a graph).
     if (pl.slots > 0) e = launch_fill_zero(counters, (int64_t)num_seqs * num_kv_heads, s);
     if (e == hipSuccess && step_fits(pl, head_dim, pl.coop, pl.nbi ? pl.nbi : (head_dim == 64 ? 2 : 1))) {
-        // both kinds of work side by side in one launch: a step of four decodes and one prompt 16.6 -> 11.4 us
+        // both kinds of work side by side in one launch: a step of four decodes and one prompt 16.6 -> 11.4 us (7.5 with
+        // whole sequences)
         memcpy(ka.cum, pl.dcum, ((size_t)num_seqs + 1) * sizeof(int32_t));
         memcpy(ka.cum + num_seqs + 1, pl.pf, pl.pf_size * sizeof(int32_t));
         e = launch_step(ka, dev.num_cus, s);
@@ -1668,7 +1672,7 @@ ooco_status ooco_kv_block_copy(ooco_ctx *ctx, const void *k_src, const void *v_s
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     ctx->note_stream(s);
     hipError_t e = hipSuccess;
-    // Large copies take their pairs in order of destination id (sorted on the device into a buffer of the context,
+    // Large copies take their pairs in order of destination region (ordered on the device into a buffer of the context,
     // which grows on demand -- never while the stream is being captured, a captured copy keeps the caller's order).
     // The order is worth about an eighth of the copy's time and costs 6 us and 0.25 us per 1000 pairs in one workgroup, up
     // to kOrderPairsMax pairs, and 28 us and more in the radix sort beyond.  Measured on MI355X, unordered / ordered:

@@ -233,6 +233,7 @@ OOCO_DEV int count_le(CumAt cum_at, int n, int x, int lane)
 // stores (acc, m, l) in fp32 into partial slot k + seq, then bumps the arrival counter of
 // (seq, kv head); the piece that arrives last merges all slots of the sequence in slot order
 // (so the result does not depend on which piece is last) and resets the counter.
+
 // The blocks [blk_begin, blk_begin + nblk) of sequence seq (not none) against its query row, streamed by wave `wave` of NW
 // waves that take steps of NBI blocks in turn: un-normalised output O, running maximum m (the same in the four rows of a
 // lane column) and this lane's share lsum of the sum, as laid out above.  A wave without a step has (0, -inf, 0), one whose
@@ -1392,9 +1393,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void 
 // as in the prefill kernel).  Every unit holds both kinds side by side as with two kernels on two streams, without the
 // fork and join events of the second stream, and a short batch does not wait for one kernel to drain before the other
 // starts.  Decode workgroups come first in dispatch order, so that each unit gets its share of the HBM stream before
-// prefill workgroups fill it up.  Against the two kernels on two streams (13 us of a step between them) or one after the
-// other, MI355X: 8 x 512 rows + 128 decodes 304.6 -> 281.7 us, 2 x 2048 + 32 long decodes 1850 -> 1660, 2 x 120 rows +
-// 24 short decodes 39.5 -> 33.6.
+// prefill workgroups fill it up.  Against the two kernels on two streams, MI355X: a call on an idle GPU 297 -> 283 us (8 x 512
+// rows + 128 decodes) and 1653 -> 1635 (2 x 2048 + 32 long decodes); in a loop of calls level, 266 / 268 and 1625 / 1630, but
+// 340 and 2170 on a context whose side stream shares a hardware queue with the caller's stream (one or two of eight contexts
+// made in a row), where the kernels run in sequence.  2 x 120 rows + 24 short decodes, in sequence before: 37.5 -> 29.
 template <int HD, int NBI, int MBATCH, int NW, bool PIPE, bool COOP>
 OOCO_DEV void step_body(const KernArgs &a)
 {
