@@ -103,7 +103,8 @@ const char *ooco_last_error(const ooco_ctx *ctx);
 /* Options (name, value >= 0).  Unknown name -> OOCO_EINVAL.
  *
  * Decode run layout; these take effect at the next ooco_plan.  The KV blocks of all decode
- * sequences, laid end to end, are streamed in runs, one launched wave per run and kv head.  A run
+ * sequences, laid end to end, are streamed in runs, one launched wave per run and kv head -- or one
+ * workgroup of four waves, see "decode_coop".  A run
  * that crosses a sequence boundary, or a sequence that spans several runs, is handled by partial
  * results merged inside the decode kernel.
  *   "decode_segments"     number of static runs (0 = automatic: three waves per compute unit,
@@ -227,7 +228,8 @@ ooco_status ooco_profile_read_calls(ooco_ctx *ctx, double *per_call_ms /*HOST*/,
  * wave start, first K/V tiles arrived, end of KV streaming, wave end (after partial results and
  * merge).  ooco_trace_read waits for the streams the context's calls were given and copies the stamps of the last
  * traced call:
- *   stamps: HOST uint64 [cap_waves][4], wave index = run * num_kv_heads + kv head;
+ *   stamps: HOST uint64 [cap_waves][4], wave index = run * num_kv_heads + kv head (a workgroup of four waves that
+ *   share a run stamps once, its first wave);
  *   waves: HOST, receives the number of decode waves of that call.
  * A traced batch WITHOUT decode sequences stores per prefill workgroup instead (workgroup index = (tile in
  * dispatch order * num_kv_heads + kv head) * parts + part): start, XCD * 256 + compute-unit id, phases, end; `waves`
@@ -281,7 +283,7 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
                               const int32_t *xcd_weights /*HOST, 8 values in 1..255, or NULL*/,
                               int64_t prefill_split, int64_t decode_piece_pad);
 
-/* Numbers describing the last plan made, current or used up (any pointer may be NULL): decode runs (waves per kv head),
+/* Numbers describing the last plan made, current or used up (any pointer may be NULL): decode runs (waves, or workgroups of four, per kv head),
  * prefill tiles, KV blocks of all decode sequences, bytes of workspace the partial results use,
  * the most parts a prefill tile's key range is cut into (1 = no tile is split). */
 ooco_status ooco_plan_info(const ooco_ctx *ctx, int64_t *decode_waves, int64_t *prefill_tiles,
