@@ -136,6 +136,12 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                         steps (the tile with the most steps k parts, the others as many as keep their parts no
  *                         longer than that tile's), so that a chunk on a short context stays whole beside one on a
  *                         long context.  A tile never gets more parts than it has 64-key steps.
+ *   "prefill_groups"      key groups of a prefill workgroup: 4 = workgroups of eight waves on 64 query columns whose
+ *                         four groups walk a quarter of the keys each, 128 keys per step, and merge in LDS; 1 =
+ *                         workgroups of four waves on 128 columns; 0 (default) = by the number and the length of the
+ *                         tiles: a batch of few tiles takes half as many steps one after the other.  Batches without
+ *                         decode sequences (4: any batch outside the register-lean pair); automatic "prefill_split"
+ *                         then cuts a tile into up to 64 parts.
  *   "prefill_sorted"      0/1/2 (default 1): a batch of at most 896 prefill tiles dispatches the tiles of ALL its
  *                         chunks -- the parts of its tiles, if they are split -- by decreasing number of 64-key
  *                         steps (one list entry per tile or part, in the kernel arguments; at most 896 entries);
@@ -270,7 +276,8 @@ ooco_status ooco_plan(ooco_ctx *ctx, int num_seqs, const int32_t *h_seq_lens /*H
  *   msg: HOST buffer of msg_cap bytes receiving the error text.  Any output pointer may be NULL.
  *   xcd_weights: NULL for equal static runs, else the relative run lengths per XCD that option
  *     "xcd_weights" would set (static run v then belongs to XCD v % 8).
- *   prefill_split: what option "prefill_split" would set (0 = automatic).
+ *   prefill_split: what option "prefill_split" would set (0 = automatic), in the low 16 bits; what option
+ *     "prefill_groups" would set above them, 0 standing for 1 here (workgroups of four waves) and 15 for automatic.
  *   decode_piece_pad: what option "decode_piece_pad" would set; negative = the default. */
 ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, int block_size,
                               int max_blocks_per_seq, int num_cus, size_t workspace_bytes,

@@ -81,6 +81,7 @@ struct PlanGeometry {
     int64_t pf_split_opt = 0;   // parts per prefill tile; 0 = automatic
     int64_t piece_pad = -1;     // line units charged for starting a piece (see build_plan); < 0 = automatic
     int64_t pf_waves_opt = 0;   // waves per prefill workgroup: 4, 8, or 0 = automatic
+    int64_t pf_groups_opt = 0;  // key groups per prefill workgroup: 1, 4, or 0 = automatic
     int64_t coop_opt = 1;       // cooperative decode workgroups: 0 never, 1 by rule, 2 always
     int64_t lean_opt = 0;       // mixed batches: register-lean kernels (see HostPlan::lean)
     int64_t fused = 0;          // batches with both kinds of work run in the one-launch mixed kernel
@@ -106,7 +107,10 @@ struct HostPlan {
     int32_t n_tiles = 0, total_q = 0, num_seqs = 0;
     int32_t pf_split = 1;        // parts a prefill tile's keys are cut into (with the tile list: the most any tile has)
     int64_t pf_slots = 0;        // partial-result slots of the split tiles per kv head (with the list: its leading entries that are parts)
-    int32_t pf_waves = 4;        // waves per prefill workgroup (32 query columns each)
+    int32_t pf_waves = 4;        // waves per prefill workgroup (32 query columns each, of a key group)
+    int32_t pf_groups = 1;       // key groups of a workgroup (1, or kKeyGroups in workgroups of eight waves)
+    int32_t pf_col_waves() const { return pf_waves / pf_groups; }   // waves per tile of query columns
+    int32_t pf_step_keys() const { return pf_groups > 1 ? 128 : 64; }   // keys of a workgroup's step
     // mixed batches (head_dim 128): the register-lean pair of kernels -- prefill workgroups of eight waves (176
     // registers, no software pipeline) and decode waves of 144 registers, four per compute unit -- so that a SIMD
     // holds two prefill waves and a decode wave at once
@@ -321,6 +325,7 @@ struct PrefillFacts {
     size_t n_order;                              // prefill chunks
     const int32_t *st;                           // with the tile list: steps of the listed tiles, in list order
     int pf_waves;
+    int64_t max_cols;                            // query columns of the widest tile
     int64_t dec_blocks, kv_blocks;               // decode part: units of its line, KV blocks
     double pf_pairs;                             // visible (query row, key) pairs of all chunks
 };
@@ -339,7 +344,7 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
     const int BS = geo.BS;
     const int64_t units = tiles * geo.Hkv;
     int64_t split = 1;
-    const size_t part_bytes = (size_t)(32 * pf_waves) * (geo.hd + 2) * sizeof(float);
+    const size_t part_bytes = (size_t)(32 * out.pf_col_waves()) * (geo.hd + 2) * sizeof(float);
     const size_t left = geo.ws_bytes - std::min(geo.ws_bytes, ((size_t)out.slots * slot_bytes(geo) + 255) / 256 * 256);
     const double cus = (double)geo.num_cus;
     // Estimated time in microseconds of a launch of w workgroups in all, the longest of them `longest` 64-key steps,
@@ -417,6 +422,35 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
     if (units <= kPrefillSplitUnits) {
         if (geo.pf_split_opt > 0) {
             split = std::min<int64_t>(std::min<int64_t>(geo.pf_split_opt, kMaxPrefillSplit), max_tile_steps);
+        } else if (out.pf_table && out.pf_groups > 1) {
+            by_steps = true;
+            // Workgroups of several key groups: one per compute unit, so no more than those.  Time of a launch of r workgroups
+            // per unit, the longest of L 128-key steps, in k parts, fitted to 934 batches of 1..8 equal chunks of 2..256 rows
+            // on 0..30,000 cached tokens x 13 forced splits (the choice is 0.7 % above the best of them on average):
+            // start-up and end 8.0 us (head_dim 64: 5.6), a step 1.06 .. 1.36 us by r (0.78 .. 0.98), the merge 2.0 us and
+            // 0.21 per part, 0.36 with two waves' columns in it (1.5, 0.14, 0.24).
+            const bool wide = geo.hd == 128;
+            const double merge = (wide ? 0.21 : 0.14) + (f.max_cols > 32 ? (wide ? 0.15 : 0.10) : 0.0);
+            auto est_groups = [&](int64_t wgs, int64_t longest, int64_t k) {
+                const double r = std::min(1.0, (double)wgs / cus);
+                const double step = !wide ? 0.78 + 0.2 * r : k > 1 ? 1.05 + 0.4 * r : 1.06 + 0.6 * std::max(0.0, r - 0.5);
+                return (wide ? 8.0 : 5.6) + (double)longest * step + (k > 1 ? (wide ? 2.0 : 1.5) + merge * (double)k : 0.0);
+            };
+            double best = est_groups(units, max_tile_steps, 1);
+            int64_t worse = 0;
+            for (int64_t k = 2; k <= kMaxGroupSplit && k <= max_tile_steps && worse < 8; ++k) {
+                int64_t split_ones = 0;
+                const int64_t e = entries_of(k, true, nullptr, &split_ones);
+                if (e * geo.Hkv > geo.num_cus || !list_fits(e, split_ones)) break;
+                const double t = est_groups(e * geo.Hkv, (max_tile_steps + k - 1) / k, k);
+                if (t < best) {
+                    best = t;
+                    split = k;
+                    worse = 0;
+                } else {
+                    ++worse;
+                }
+            }
         } else if (out.pf_table) {
             by_steps = true;
             int64_t big = 0, split_ones = 0;
@@ -504,6 +538,42 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
     }
 }
 
+// Whether the prefill part of a batch without decode work runs in workgroups of key groups: eight waves, 64 query columns,
+// each of the four groups walking a quarter of the keys, their results merged in LDS.  Such a workgroup has a compute unit to
+// itself and takes 1.06 .. 1.36 us for 128 keys (one of four waves and 128 columns 1.08 .. 1.3 for 64), so it halves the chain
+// of steps that bounds a batch of few tiles, and a tile of few columns wastes half as much; a batch that fills the units is
+// better off with two workgroups of four waves on each.  By the batch's load, 128-key steps of 64 columns per unit, against
+// workgroups of four waves (699 random batches of up to 256 tiles of 64 columns on 256 units, nine head layouts):
+// load up to 10: 0.80 of the time (0.54 .. 1.03); 10..15: 0.88, but tiles of 65 to 90 columns on long contexts, which two
+// workgroups then read twice, up to 1.21; 15..25: 0.95 with up to 64 tiles and few unused columns, 1.0 (up to 1.7) with more,
+// whose steps cannot be dealt out evenly any more; above 25 1.07 and worse.  Fewer than three steps (head_dim 64: two) do not
+// pay for the merge in LDS (one step 6.4 -> 8.3 us, two 11.2 -> 10.3, with few columns 9.9 -> 10.3).
+// "prefill_split" = 1, one workgroup per tile whatever its length, leaves only the chain: always.
+bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_lens, const int32_t *h_query_start_loc)
+{
+    const int rows = prefill_tile_rows(geo.Hq / geo.Hkv, 8 / kKeyGroups);
+    int64_t tiles = 0, steps = 0, longest = 0, widest = 0;
+    double cover = 0.0;   // (row, step) pairs that the tiles have room for, and that the chunks have
+    double used = 0.0;
+    for (int i = 0; i < num_seqs; ++i) {
+        const int64_t ql = (int64_t)h_query_start_loc[i + 1] - h_query_start_loc[i];
+        if (ql == 1) return false;
+        if (ql < 1) continue;
+        const int64_t t = (ql + rows - 1) / rows, s = ((int64_t)h_seq_lens[i] + 127) / 128;
+        tiles += t;
+        steps += t * s;
+        cover += (double)(t * rows) * (double)s;
+        used += (double)ql * (double)s;
+        longest = std::max(longest, s);
+        widest = std::max(widest, t);
+    }
+    if (tiles == 0 || geo.pf_groups_opt == kKeyGroups) return tiles > 0;
+    if (tiles * geo.Hkv > geo.num_cus || longest < (geo.hd == 128 ? 3 : 2)) return false;
+    if (geo.pf_split_opt > 0) return geo.pf_split_opt == 1;
+    const int64_t load = steps * geo.Hkv, cus = geo.num_cus;
+    return load <= 10 * cus || (load <= 25 * cus && 4 * tiles * geo.Hkv <= cus && (widest == 1 || cover <= 1.2 * used));
+}
+
 // Validates the length arrays and builds the plan.  Pure host code, no allocation.
 ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_lens,
                        const int32_t *h_query_start_loc, const int32_t *h_ctx_lens, const PlanStorage &store,
@@ -534,6 +604,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     // runs cut the line into equal lengths, so a run that starts several pieces streams correspondingly fewer
     // blocks (starting a piece costs a wave about as long as streaming three 8 KiB tiles).
     int64_t dec_blocks = 0, kv_blocks = 0, tiles = 0, tile_steps = 0, max_tile_steps = 1;
+    int64_t max_cols = 0;                        // query columns of the widest prefill tile
     int64_t dec_seqs = 0, max_dec_blocks = 0;    // decode sequences that hold at least one block, blocks of the longest
     double pf_pairs = 0.0;   // visible (query row, key) pairs of all prefill chunks
     const int64_t pad = geo.piece_pad < 0 ? default_piece_pad(geo.hd) : geo.piece_pad;
@@ -574,7 +645,11 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     out.lean = lean;
     const int pf_waves = geo.hd == 128 && (geo.pf_waves_opt == 8 || lean) ? 8 : 4;
     out.pf_waves = pf_waves;
-    const int tile_rows = prefill_tile_rows(geo.Hq / geo.Hkv, pf_waves);
+    const int g = geo.Hq / geo.Hkv;
+    if (geo.pf_groups_opt != 1 && !lean && !geo.fused && geo.pf_waves_opt == 0 && key_groups_pay(geo, num_seqs, h_seq_lens, h_query_start_loc))
+        out.pf_groups = kKeyGroups, out.pf_waves = 8;
+    const int step_keys = out.pf_step_keys();
+    const int tile_rows = prefill_tile_rows(geo.Hq / geo.Hkv, out.pf_col_waves());
     for (int i = 0; i < num_seqs; ++i) {
         const int64_t ql = (int64_t)h_query_start_loc[i + 1] - h_query_start_loc[i];
         if (ql < 0) return bad(OOCO_ESHAPE, "ooco_plan: query_start_loc decreases at sequence %d", i);
@@ -596,8 +671,9 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         if (ql > 1) {
             pf_pairs += (double)ql * (double)h_ctx_lens[i] + (double)ql * (double)(ql + 1) / 2.0;
             tiles += (ql + tile_rows - 1) / tile_rows;
+            max_cols = std::max(max_cols, std::min<int64_t>(ql, tile_rows) * g);
             for (int64_t t0 = 0; t0 < ql; t0 += tile_rows) {    // 64-key steps of every tile
-                const int64_t nstep = ((int64_t)h_ctx_lens[i] + std::min<int64_t>(ql, t0 + tile_rows) + 63) / 64;
+                const int64_t nstep = ((int64_t)h_ctx_lens[i] + std::min<int64_t>(ql, t0 + tile_rows) + step_keys - 1) / step_keys;
                 tile_steps += nstep;
                 max_tile_steps = std::max(max_tile_steps, nstep);
             }
@@ -632,7 +708,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     auto steps_of = [&](int32_t e) -> int64_t {   // 64-key steps of the tile a list entry names
         const int i = order[entry_chunk(e)];
         const int64_t ql = (int64_t)h_query_start_loc[i + 1] - h_query_start_loc[i], t0 = (int64_t)entry_tile(e) * tile_rows;
-        return ((int64_t)h_ctx_lens[i] + std::min<int64_t>(ql, t0 + tile_rows) + 63) / 64;
+        return ((int64_t)h_ctx_lens[i] + std::min<int64_t>(ql, t0 + tile_rows) + step_keys - 1) / step_keys;
     };
     // A launch of few tiles is as long as its unluckiest compute unit is busy, and the hardware hands workgroups out
     // in index order to whichever unit has room: the tiles of ALL chunks go out by decreasing number of 64-key
@@ -695,7 +771,7 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     out.near = lean && dec_blocks > 0 && max_dec_blocks * out.static_runs <= 32 * (int64_t)out.dec_blocks;
     // ---- prefill tiles cut along the context (see plan_prefill_parts)
     if (tiles > 0) {
-        const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, pf_waves, dec_blocks, kv_blocks, pf_pairs};
+        const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, out.pf_waves, max_cols, dec_blocks, kv_blocks, pf_pairs};
         plan_prefill_parts(geo, facts, store.pf + (2 * (size_t)out.num_pf + 1), out);
     }
     return OOCO_OK;
@@ -825,6 +901,7 @@ struct ooco_ctx {
     int64_t opt_append_parts = 0;   // KV append: workgroups per (sequence, block) pair, 0 = automatic
     int64_t opt_lean = 1;           // mixed batches: the register-lean kernels (0 never, 1 automatic, 2 always)
     int64_t opt_pf_waves = 0;       // waves per prefill workgroup: 0 = automatic, 4, 8
+    int64_t opt_pf_groups = 0;      // key groups per prefill workgroup: 0 = automatic, 1, 4
     int64_t opt_fused = 0;          // mixed batches in one launch (mixed kernel) instead of two kernels on two streams
     int64_t opt_coop = 1;           // cooperative decode workgroups (0 never, 1 by rule, 2 always)
     int64_t opt_step = 1;           // mixed batches in one launch of the step kernel (0 never, 1 by rule, 2 whenever it takes the plan)
@@ -1048,6 +1125,11 @@ ooco_status ooco_set_option(ooco_ctx *ctx, const char *name, int64_t value)
             return fail(ctx, OOCO_EINVAL, "ooco_set_option: prefill_waves must be 0 (automatic), 4 or 8");
         ctx->opt_pf_waves = value;
     }
+    else if (!strcmp(name, "prefill_groups")) {
+        if (value != 0 && value != 1 && value != kKeyGroups)
+            return fail(ctx, OOCO_EINVAL, "ooco_set_option: prefill_groups must be 0 (automatic), 1 or 4");
+        ctx->opt_pf_groups = value;
+    }
     else if (!strcmp(name, "mixed_lean"))
         ctx->opt_lean = value;
     else if (!strcmp(name, "decode_coop"))
@@ -1134,6 +1216,7 @@ ooco_status ooco_plan(ooco_ctx *ctx, int num_seqs, const int32_t *h_seq_lens, co
     geo.pf_split_opt = ctx->opt_pf_split;
     geo.piece_pad = ctx->opt_piece_pad;
     geo.pf_waves_opt = ctx->opt_pf_waves;
+    geo.pf_groups_opt = ctx->opt_pf_groups;
     geo.lean_opt = ctx->opt_lean;
     geo.coop_opt = ctx->opt_nbi ? 0 : ctx->opt_coop;   // (a forced number of blocks per step asks for single waves)
     geo.fused = ctx->opt_fused && ctx->opt_overlap;
@@ -1183,7 +1266,9 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
         geo.segments_opt = decode_segments;
         geo.tail_pct = decode_tail_pct;
         geo.tail_blocks = decode_tail_blocks;
-        geo.pf_split_opt = prefill_split;
+        const int64_t groups = prefill_split >> 16;
+        geo.pf_groups_opt = groups == 15 ? 0 : groups == kKeyGroups ? kKeyGroups : 1;
+        geo.pf_split_opt = prefill_split & 0xFFFF;
         geo.lean_opt = 1;   // (the default of a context)
         geo.piece_pad = decode_piece_pad;
         if (xcd_weights && !xcd_weights_to_cw(xcd_weights, geo.xcd_cw)) {
@@ -1215,7 +1300,7 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
         }
     if (prefill_tiles_out) {
         // in dispatch order, derived from the plan's arrays the way the prefill kernel derives them
-        const int tile_rows = prefill_tile_rows(num_q_heads / num_kv_heads, pl.pf_waves);
+        const int tile_rows = prefill_tile_rows(num_q_heads / num_kv_heads, pl.pf_col_waves());
         const int32_t *const pf = pl.pf;
         const int P = pl.num_pf;
         // (with the tile list a tile is listed where its first part is dispatched)
@@ -1238,7 +1323,7 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
             const int q0 = h_query_start_loc[i], ql = h_query_start_loc[i + 1] - q0, t0 = t * tile_rows;
             int32_t *o = prefill_tiles_out + 5 * idx++;
             o[0] = i, o[1] = q0 + t0, o[2] = std::min(tile_rows, ql - t0), o[3] = h_ctx_lens[i] + t0;
-            o[4] = (int32_t)std::min<int64_t>(parts, ((int64_t)o[3] + o[2] + 63) / 64);
+            o[4] = (int32_t)std::min<int64_t>(parts, ((int64_t)o[3] + o[2] + pl.pf_step_keys() - 1) / pl.pf_step_keys());
         }
     }
     return OOCO_OK;
@@ -1255,7 +1340,7 @@ ooco_status ooco_plan_info(const ooco_ctx *ctx, int64_t *decode_waves, int64_t *
     if (workspace_used) {
         size_t bytes = (size_t)ctx->plan.slots * (size_t)ctx->Hq * (ctx->hd + 2) * sizeof(float);
         if (ctx->plan.pf_split > 1)
-            bytes = (bytes + 255) / 256 * 256 + (size_t)ctx->plan.pf_slots * ctx->Hkv * (size_t)(32 * ctx->plan.pf_waves) *
+            bytes = (bytes + 255) / 256 * 256 + (size_t)ctx->plan.pf_slots * ctx->Hkv * (size_t)(32 * ctx->plan.pf_col_waves()) *
                                                     (ctx->hd + 2) * sizeof(float);
         *workspace_used = (int64_t)bytes;
     }
@@ -1288,7 +1373,7 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
         if (pf && pl.lean && pl.pf_waves == 8)
             snprintf(f, sizeof f, "prefill_kernel_lean<%d>", ctx->hd);
         else if (pf)
-            snprintf(f, sizeof f, "prefill_kernel<%d, %d>", ctx->hd, pl.pf_waves);
+            snprintf(f, sizeof f, pl.pf_groups > 1 ? "prefill_kernel<%d, %d, %d>" : "prefill_kernel<%d, %d>", ctx->hd, pl.pf_waves, pl.pf_groups);
     }
     snprintf(names, cap, "%s%s%s", d, d[0] && f[0] ? ";" : "", f);
     return OOCO_OK;
@@ -1367,13 +1452,13 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
         const size_t dec_floats = ((size_t)pl.slots * ctx->Hq * (ctx->hd + 2) + 63) / 64 * 64;   // 256-byte aligned
         const size_t parts = (size_t)pl.pf_slots * ctx->Hkv;   // (what the planner checked against the workspace)
         p.pf_acc = static_cast<float *>(ctx->ws) + dec_floats;
-        p.pf_ml = p.pf_acc + parts * (size_t)(32 * pl.pf_waves) * ctx->hd;
+        p.pf_ml = p.pf_acc + parts * (size_t)(32 * pl.pf_col_waves()) * ctx->hd;
         p.pf_counters = ctx->pf_counters;
         p.pf_split = pl.pf_split;
         p.pf_table = pl.pf_table;
         // (what the kernels will address, once more against what the context owns: a plan that does not fit is an error of
         // this library, reported instead of launched)
-        const size_t pf_end = (dec_floats + parts * (size_t)(32 * pl.pf_waves) * (ctx->hd + 2)) * sizeof(float);
+        const size_t pf_end = (dec_floats + parts * (size_t)(32 * pl.pf_col_waves()) * (ctx->hd + 2)) * sizeof(float);
         // (arrival counters: one per part-0 slot with the tile list, one per (tile, kv head) without it)
         const size_t pf_counters_used = pl.pf_table ? parts : (size_t)pl.n_tiles * ctx->Hkv;
         if ((pl.pf_split > 1 && (pf_end > ctx->ws_bytes || pf_counters_used > (size_t)kPrefillSplitUnits)) ||
@@ -1408,7 +1493,8 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     p.n_tiles = pl.n_tiles;
     p.num_pf = pl.num_pf;
     p.dec_cus = (int16_t)pl.dec_cus;
-    p.pf_waves = (int16_t)pl.pf_waves;
+    p.pf_waves = (int8_t)pl.pf_waves;
+    p.pf_groups = (int8_t)pl.pf_groups;
     p.nbi = ctx->opt_nbi ? (int32_t)ctx->opt_nbi : pl.nbi;
     p.rotate_heads = (int16_t)(ctx->opt_rotate != 0);
     p.coop = (int16_t)decode_coop(ctx);
@@ -1621,7 +1707,8 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.queue_base = 0;
     p.n_tiles = pl.n_tiles;
     p.num_pf = pl.num_pf;
-    p.pf_waves = (int16_t)pl.pf_waves;
+    p.pf_waves = (int8_t)pl.pf_waves;
+    p.pf_groups = (int8_t)pl.pf_groups;
     p.nbi = pl.nbi;
     p.coop = (int16_t)pl.coop;
     p.dec_near = (int16_t)pl.near;

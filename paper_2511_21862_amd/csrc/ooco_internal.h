@@ -35,6 +35,8 @@ constexpr int kBlockSize = 16;      // tokens per KV block (fixed by the cache l
 constexpr int kPrefillCols = 128;   // (row, head) query columns per four-wave prefill workgroup (eight waves: 256)
 constexpr int kInlineSeqs = 960;    // sequences whose cumulative array fits the kernel arguments
 constexpr int kMaxPrefillSplit = 16; // parts a prefill tile's keys may be cut into
+constexpr int kKeyGroups = 4;        // key groups of an eight-wave prefill workgroup that has them
+constexpr int kMaxGroupSplit = 64;   // parts of such a workgroup's tile (a list entry has 6 bits for the part)
 constexpr int kPrefillSplitUnits = 8192;   // (tile, kv head) pairs up to which the split is available
 constexpr int kListEntries = 896;    // (tile, part) entries the plan's tile list may have (it lives in the kernel arguments)
 constexpr int kSortedTiles = kListEntries;   // prefill tiles up to which the plan lists them one by one, most 64-key steps first
@@ -64,7 +66,8 @@ struct AttnParams {
     int32_t num_pf;             // prefill: number of chunks (entries of the prefill array, see below)
     int32_t dec_wgs;            // step kernel: its first workgroups, which decode (set by launch_step)
     int16_t dec_cus;            // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
-    int16_t pf_waves;           // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave)
+    int8_t pf_waves;            // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave of a key group)
+    int8_t pf_groups;           // prefill: key groups of a workgroup (1, or 2 or 4 in workgroups of eight waves)
     int16_t dec_wpw;            // step kernel: decode waves of such a workgroup (set by launch_step)
     int16_t dec_near;           // step kernel: they take items side by side (the kv heads of one run), else far apart
     int32_t nbi;                // tuning: KV blocks per softmax step of the decode kernel

@@ -94,6 +94,24 @@ OOCO_DEV float max32(const f32x16 &a, const f32x16 &b)
     return e;
 }
 
+// the same of 16 scores
+OOCO_DEV float max16(const f32x16 &a)
+{
+    float d;
+    asm("v_max3_f32 %0, %1, %2, %3\n\t"
+        "v_max3_f32 %0, %0, %4, %5\n\t"
+        "v_max3_f32 %0, %0, %6, %7\n\t"
+        "v_max3_f32 %0, %0, %8, %9\n\t"
+        "v_max3_f32 %0, %0, %10, %11\n\t"
+        "v_max3_f32 %0, %0, %12, %13\n\t"
+        "v_max3_f32 %0, %0, %14, %15\n\t"
+        "v_max_f32_e32 %0, %0, %16"
+        : "=&v"(d)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]),
+          "v"(a[10]), "v"(a[11]), "v"(a[12]), "v"(a[13]), "v"(a[14]), "v"(a[15]));
+    return d;
+}
+
 // acc + lo + hi of a packed bf16 pair (one v_dot2c_f32_bf16 against the pair (1, 1))
 OOCO_DEV float sum2_bf16(uint32_t pair, float acc)
 {
@@ -120,15 +138,17 @@ OOCO_DEV void store_dev4(float *ptr, f32x4 v)   // ptr is 16-byte aligned
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(ptr), "v"(v) : "memory");
 }
-// Device-scope 16-byte loads of one part of a split prefill tile as one lane sees it: four loads (1 KiB apart)
-// from each of MB pointers.  All loads and the wait for them sit in ONE asm statement, so that the compiler
-// never sees a register it believes loaded while the data is still on its way.
+// Sixteen device-scope 16-byte loads of a lane, N (1 KiB apart) from each of 16 / N pointers: pieces of the parts of a split
+// prefill tile.  All loads and the wait for them sit in ONE asm statement, so that the compiler never sees a register it
+// believes loaded while the data is still on its way.
 #define OOCO_LD4(o, a) \
     "global_load_dwordx4 %" #o ", %" #a ", off sc1\n\t"
 #define OOCO_LD4O(o, a, off) \
     "global_load_dwordx4 %" #o ", %" #a ", off offset:" #off " sc1\n\t"
+template <int N>
 OOCO_DEV void load_dev_part(f32x4 (&t)[16], const float *p0, const float *p1, const float *p2, const float *p3)
 {
+    static_assert(N == 4, "sixteen loads");
     asm volatile(OOCO_LD4(0, 16) OOCO_LD4O(1, 16, 1024) OOCO_LD4O(2, 16, 2048) OOCO_LD4O(3, 16, 3072)
                  OOCO_LD4(4, 17) OOCO_LD4O(5, 17, 1024) OOCO_LD4O(6, 17, 2048) OOCO_LD4O(7, 17, 3072)
                  OOCO_LD4(8, 18) OOCO_LD4O(9, 18, 1024) OOCO_LD4O(10, 18, 2048) OOCO_LD4O(11, 18, 3072)
@@ -139,13 +159,19 @@ OOCO_DEV void load_dev_part(f32x4 (&t)[16], const float *p0, const float *p1, co
                  : "v"(p0), "v"(p1), "v"(p2), "v"(p3)
                  : "memory");
 }
-OOCO_DEV void load_dev_part(f32x4 (&t)[8], const float *p0, const float *p1)
+template <int N>
+OOCO_DEV void load_dev_part(f32x4 (&t)[16], const float *p0, const float *p1, const float *p2, const float *p3, const float *p4,
+                            const float *p5, const float *p6, const float *p7)
 {
-    asm volatile(OOCO_LD4(0, 8) OOCO_LD4O(1, 8, 1024) OOCO_LD4O(2, 8, 2048) OOCO_LD4O(3, 8, 3072)
-                 OOCO_LD4(4, 9) OOCO_LD4O(5, 9, 1024) OOCO_LD4O(6, 9, 2048) OOCO_LD4O(7, 9, 3072)
+    static_assert(N == 2, "sixteen loads");
+    asm volatile(OOCO_LD4(0, 16) OOCO_LD4O(1, 16, 1024) OOCO_LD4(2, 17) OOCO_LD4O(3, 17, 1024)
+                 OOCO_LD4(4, 18) OOCO_LD4O(5, 18, 1024) OOCO_LD4(6, 19) OOCO_LD4O(7, 19, 1024)
+                 OOCO_LD4(8, 20) OOCO_LD4O(9, 20, 1024) OOCO_LD4(10, 21) OOCO_LD4O(11, 21, 1024)
+                 OOCO_LD4(12, 22) OOCO_LD4O(13, 22, 1024) OOCO_LD4(14, 23) OOCO_LD4O(15, 23, 1024)
                  "s_waitcnt vmcnt(0)"
-                 : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]), "=&v"(t[6]), "=&v"(t[7])
-                 : "v"(p0), "v"(p1)
+                 : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]), "=&v"(t[6]), "=&v"(t[7]),
+                   "=&v"(t[8]), "=&v"(t[9]), "=&v"(t[10]), "=&v"(t[11]), "=&v"(t[12]), "=&v"(t[13]), "=&v"(t[14]), "=&v"(t[15])
+                 : "v"(p0), "v"(p1), "v"(p2), "v"(p3), "v"(p4), "v"(p5), "v"(p6), "v"(p7)
                  : "memory");
 }
 #undef OOCO_LD4
@@ -845,11 +871,14 @@ OOCO_DEV int plan_entry(const KernArgs &a, int idx)
     return v;
 }
 
-// The K and V tiles of two steps, as one array (the cooperative decode workgroups of the step kernel use the same memory).
-template <int HD>
+// The K and V tiles of two steps, for KG key groups, as one array (the cooperative decode workgroups of the step kernel use
+// the same memory).
+template <int KG>
+constexpr int kPfGroupBlocks = KG == 1 ? kPfBlocks : 2 * kPfBlocks / KG;   // KV blocks a key group stages per step
+template <int HD, int KG = 1>
 OOCO_DEV u32x4 *stage_lds()
 {
-    __shared__ u32x4 lds[4 * kPfBlocks * HD * 2];
+    __shared__ u32x4 lds[4 * KG * kPfGroupBlocks<KG> * HD * 2];
     return lds;
 }
 
@@ -859,27 +888,40 @@ OOCO_DEV u32x4 *stage_lds()
 // threads of the workgroup call it together; every return is workgroup-uniform.
 // NW = waves per workgroup: 4 (128 query columns) or 8 (256 columns: the same K/V tiles in LDS serve twice as many
 // columns, which halves the traffic from L2 into the compute unit per unit of matrix work).
+// KG = key groups: with 4, the NW = 8 waves are four groups of two, 64 query columns, and each group stages and walks a
+// quarter (32) of every 128 keys with a pipeline of its own; only the barrier of a step is common.  The groups' results meet
+// in LDS (128 KiB, as much as their tiles: one workgroup per compute unit).  For batches of few tiles, which are bound by
+// the chain of steps and not by the matrix cores: a step takes about the time its loads need whatever it holds, 1.06 .. 1.36 us
+// for 128 keys in place of 1.08 .. 1.3 for 64, and a tile of few columns keeps a quarter of the waves idle instead of
+// three quarters.  Measured on MI355X against KG = 1 (us): 3 chunks of 3 rows on 17,000 cached tokens, 28/4 heads 42.6 -> 28.3,
+// 57 + 87 rows on 2000, 32/8 20.7 -> 18.0, 3 x 100 rows on 400 15.5 -> 12.5; two groups of 128 columns each gained nothing
+// (1 x 300 rows on 15,780 tokens 93.9 against 93.7, short contexts 2.5 us for the merge of 128 KiB).
 // PIPE = false: no software pipeline across steps (the scores of a step are computed in that step, one score
 // register set): fewer registers, so that two such waves and a decode wave share a SIMD; the overlap of matrix and
 // vector work then comes from the two waves of a SIMD rather than from within one wave.
 // `phases` (option "trace", prefill-only batches): receives four 16-bit times in units of 10 ns since `t_start`
 // (saturating), lowest first: tile looked up, first K/V loads sent off, first tiles arrived, last step done.
-template <int HD, int NW, bool PIPE, class CumAt>
+template <int HD, int NW, bool PIPE, int KG, class CumAt>
 OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint64_t *phases = nullptr,
                            const uint64_t t_start = 0)
 {
-    constexpr int THREADS = NW * 64;
-    constexpr int COLS = NW * 32;      // query columns per workgroup
+    constexpr int NC = NW / KG;        // waves per key group, 32 query columns each
+    constexpr int COLS = NC * 32;      // query columns per workgroup
     constexpr int KS = HD / 16;        // k-steps of QK
     constexpr int MB = HD / 32;        // 32-dim groups of the output
     constexpr int CH = HD * 2;         // 16-byte chunks per (block, kv head) tile
-    constexpr int STAGE = kPfBlocks * CH;               // chunks of one step's K (or V) tiles
-    constexpr int NCP = STAGE / THREADS;                // chunks each thread moves per stage
-    u32x4 (*const ldsK)[STAGE] = reinterpret_cast<u32x4 (*)[STAGE]>(stage_lds<HD>()), (*const ldsV)[STAGE] = ldsK + 2;
+    constexpr int BLK = kPfGroupBlocks<KG>;             // KV blocks of one step of a key group
+    constexpr int T = BLK * kBlockSize, HV = T / 32;    // tokens, and 32-token halves, of such a step
+    constexpr int STEP = KG * T;                        // tokens of one step of the workgroup
+    constexpr int STAGE = BLK * CH;                     // chunks of one step's K (or V) tiles of a key group
+    constexpr int NCP = STAGE / (NC * 64);              // chunks each thread moves per stage
+    constexpr int ITEMS = 4 * MB / KG;                  // 16-byte pieces of the merged output a thread ends up with
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = KG == 1 ? 0 : wave_id / NC, wave = KG == 1 ? wave_id : wave_id - kg * NC;   // key group, wave of the group
+    u32x4 (*const ldsK)[STAGE] = reinterpret_cast<u32x4 (*)[STAGE]>(stage_lds<HD, KG>()) + 4 * kg, (*const ldsV)[STAGE] = ldsK + 2;
     const int col = lane & 31;
     const int h = lane >> 5;
     const int g = p.g;
@@ -960,10 +1002,11 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     const int pos = pos0 + row;                          // this column's absolute position
     // the wave's columns span rows [w_row_lo, w_row_hi] (scalar)
     const int w_row_lo = min((wave * 32) / g, rows - 1), w_row_hi = min((wave * 32 + 31) / g, rows - 1);
-    const int w_pos_lo = pos0 + w_row_lo, w_pos_hi = pos0 + w_row_hi;
+    const bool w_used = wave * 32 < rows * g;            // (a narrow tile leaves the other waves without columns: they only stage)
+    const int w_pos_lo = pos0 + w_row_lo, w_pos_hi = w_used ? pos0 + w_row_hi : -1;
     const int kv_end = pos0 + rows;                      // keys visible to the tile: [0, kv_end)
     const int nblk = (kv_end + kBlockSize - 1) / kBlockSize;
-    const int nstep_all = (nblk + kPfBlocks - 1) / kPfBlocks;
+    const int nstep_all = (nblk + KG * BLK - 1) / (KG * BLK);
     // this workgroup's share of the steps: [st_lo, nstep); a unit with fewer steps than parts has fewer parts
     const int nparts = min(split, nstep_all);
     if (part >= nparts) return;                          // (the whole workgroup leaves: no barrier is pending)
@@ -1003,23 +1046,23 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     // (tile of kv head kvh of physical block pb) = cache + pb * blk_stride + kvh * tile_elems, in elements
     const uint16_t *const k_head = k_cache + (int64_t)kvh * tile_elems, *const v_head = v_cache + (int64_t)kvh * tile_elems;
     const uint32_t blk_stride = (uint32_t)Hkv * (uint32_t)tile_elems;
-    auto issue = [&](bool is_v, int slot, const int (&pb)[kPfBlocks]) {   // pb: physical ids of the step's blocks
+    auto issue = [&](bool is_v, int slot, const int (&pb)[BLK]) {   // pb: physical ids of the step's blocks
         static_assert(NCP == 4 || NCP == 2, "one asm statement per stage");
         const uint16_t *base[NCP];
         uint32_t voff[NCP], dst[NCP];
 #pragma unroll
         for (int n = 0; n < NCP; ++n) {
-            const int grp = wave + NW * n;                 // wave-uniform
+            const int grp = wave + NC * n;                 // wave-uniform
             const int cidx = grp * 64 + lane;
             // block of the step (wave-uniform).  Four waves and at least 256 chunks per tile: a compile-time
             // constant, which keeps pb[] in registers without select chains.  Eight waves (256 chunks per tile):
             // waves 0..3 move the even blocks' tiles, waves 4..7 the odd ones (one select, no indexed array).
             int which, pbw;
-            if constexpr (NW == 4) {
-                which = CH >= 256 ? (4 * n * 64) / CH : (grp * 64) / CH;
+            if constexpr (NC <= 4) {
+                which = CH >= NC * 64 ? (NC * n * 64) / CH : (grp * 64) / CH;
                 pbw = pb[which];
             } else {
-                static_assert(NW != 8 || CH == 256, "eight-wave workgroups: head_dim 128");
+                static_assert(NC != 8 || CH == 256, "eight waves on one step: head_dim 128");
                 which = 2 * n + (wave >> 2);
                 pbw = (wave >> 2) ? pb[2 * n + 1] : pb[2 * n];
             }
@@ -1058,26 +1101,26 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         for (int r = 0; r < 16; ++r) O[mb][r] = 0.f;
 
     // scores of one step: S[hh] register r is token st*64 + 32hh + 8h + 16(r/8) + r%8
-    auto qk = [&](f32x16 (&S)[2], int slot) {
+    auto qk = [&](f32x16 (&S)[HV], int slot) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
+        for (int hh = 0; hh < HV; ++hh)
 #pragma unroll
             for (int r = 0; r < 16; ++r) S[hh][r] = 0.f;
         // the two token halves alternate, so that consecutive MFMAs never wait for each other's result
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
+            for (int hh = 0; hh < HV; ++hh) {
                 const u32x4 kop = ldsK[slot][(2 * hh + ku) * CH + (2 * ks + h) * 16 + kslot];
                 S[hh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop),
                                                             __builtin_bit_cast(bf16x8, qb[ks]), S[hh], 0, 0, 0);
             }
     };
     // causal mask of a step that touches the diagonal
-    auto mask = [&](f32x16 (&S)[2], int st) {
-        const int room = pos - (st * 64 + 8 * h);        // visible iff 32hh + 16(r/8) + r%8 <= room
+    auto mask = [&](f32x16 (&S)[HV], int tok0) {
+        const int room = pos - (tok0 + 8 * h);           // visible iff 32hh + 16(r/8) + r%8 <= room
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
+        for (int hh = 0; hh < HV; ++hh)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 S[hh][r] = (32 * hh + 16 * (r / 8) + (r % 8) <= room) ? S[hh][r] : -INFINITY;
@@ -1088,7 +1131,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     // so the maximum can be taken before scaling).
     // The update comes in two halves so that the PV products of the first 32 tokens can run beside the
     // exponentials of the last 32: weights(S, P, q4, ...) turns the scores of tokens 16*q4 + 8h + 0..7 into P[q4].
-    auto weights = [&](const f32x16 (&S)[2], u32x4 (&P)[4], int q4, float m_ref, float &psum) {
+    auto weights = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], int q4, float m_ref, float &psum) {
         float e[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) e[r] = fast_exp2(__builtin_fmaf(S[q4 >> 1][8 * (q4 & 1) + r], c_log2e, -m_ref));
@@ -1097,8 +1140,12 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
 #pragma unroll
         for (int w = 0; w < 4; ++w) psum = sum2_bf16(P[q4][w], psum);
     };
-    auto softmax_first = [&](const f32x16 (&S)[2], u32x4 (&P)[4], float &alpha, bool &grow, float &psum) {
-        float mloc = max32(S[0], S[1]);
+    auto softmax_first = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], float &alpha, bool &grow, float &psum) {
+        float mloc;
+        if constexpr (HV == 2)
+            mloc = max32(S[0], S[1]);
+        else
+            mloc = max16(S[0]);
         {
             float x, y;
             swap32(mloc, x, y);
@@ -1115,20 +1162,20 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         alpha = fast_exp2(m - m_new);
         m = m_new;
         psum = 0.f;
-        weights(S, P, 0, m, psum);
-        weights(S, P, 1, m, psum);
+#pragma unroll
+        for (int q = 0; q < HV; ++q) weights(S, P, q, m, psum);
     };
-    auto softmax_second = [&](const f32x16 (&S)[2], u32x4 (&P)[4], float alpha, float psum) {
-        weights(S, P, 2, m, psum);
-        weights(S, P, 3, m, psum);
+    auto softmax_second = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], float alpha, float psum) {
+#pragma unroll
+        for (int q = HV; q < 2 * HV; ++q) weights(S, P, q, m, psum);
         lsum = lsum * alpha + psum;
     };
     // The MFMAs of tokens 0..31 (P[0], P[1]) are laid out beside the vector work that is still due when pv
     // starts (the second half of the softmax update), those of tokens 32..63 follow.
-    auto pv = [&](const u32x4 (&P)[4], int slot) {
+    auto pv = [&](const u32x4 (&P)[2 * HV], int slot) {
         const u32x4 *vp = &ldsV[slot][h * HD + col];
 #pragma unroll
-        for (int i = 0; i < 4 * MB; ++i) {
+        for (int i = 0; i < 2 * HV * MB; ++i) {
             const u32x4 vop = vp[(i / MB) * CH + 32 * (i % MB)];
             O[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vop),
                                                             __builtin_bit_cast(bf16x8, P[i / MB]), O[i % MB], 0, 0, 0);
@@ -1137,21 +1184,21 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         constexpr int kAhead = 4;
         __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
 #pragma unroll
-        for (int i = 0; i < 4 * MB - kAhead; ++i) {
+        for (int i = 0; i < 2 * HV * MB - kAhead; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (i < 2 * MB) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // (exponentials count as VALU here)
+            if (i < HV * MB) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // (exponentials count as VALU here)
         }
         __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
     };
     // Last step of a sequence only (workgroup-uniform): V slots at or past seq_len may hold anything; their
     // weights are 0, but 0*NaN is NaN, so they are zeroed in LDS before anybody multiplies with them.
-    auto scrub_v = [&](int slot, int st) {
+    auto scrub_v = [&](int slot, int tok0) {
 #pragma unroll
         for (int n = 0; n < NCP; ++n) {
-            const int cidx = n * THREADS + tid;              // chunk [block][token half][dim] of the stage
+            const int cidx = (n * NC + wave) * 64 + lane;    // chunk [block][token half][dim] of the stage
             const int blk = cidx / CH, half = (cidx % CH) / HD;
-            const int t0 = st * 64 + 16 * blk + 8 * half;    // tokens t0 .. t0+7
+            const int t0 = tok0 + 16 * blk + 8 * half;       // tokens t0 .. t0+7
             u32x4 mk;
 #pragma unroll
             for (int w = 0; w < 4; ++w)
@@ -1161,14 +1208,15 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         __syncthreads();
     };
 
-    int ids1[kPfBlocks], ids2[kPfBlocks];   // block ids of the steps st+1 and st+2
+    auto step_block = [&](int st, int b) -> int { return block_id(BLK * (KG * st + kg) + b); };
+    int ids1[BLK], ids2[BLK];   // block ids of the steps st+1 and st+2
     {
-        int ids0[kPfBlocks];
+        int ids0[BLK];
 #pragma unroll
-        for (int b = 0; b < kPfBlocks; ++b) {
-            ids0[b] = block_id(kPfBlocks * st_lo + b);
-            ids1[b] = block_id(kPfBlocks * (st_lo + 1) + b);
-            ids2[b] = block_id(kPfBlocks * (st_lo + 2) + b);
+        for (int b = 0; b < BLK; ++b) {
+            ids0[b] = step_block(st_lo, b);
+            ids1[b] = step_block(st_lo + 1, b);
+            ids2[b] = step_block(st_lo + 2, b);
         }
         issue(false, st_lo & 1, ids0);
         issue(true, st_lo & 1, ids0);
@@ -1176,23 +1224,24 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     }
     phase(1);
     // One step.  Sc: scores of step st (computed during step st-1), Sn: receives those of step st+1.
-    auto body = [&](f32x16 (&Sc)[2], f32x16 (&Sn)[2], int st) {
+    auto body = [&](f32x16 (&Sc)[HV], f32x16 (&Sn)[HV], int st) {
+        const int tok0 = st * STEP + kg * T;   // first token of this key group's share of the step
         // this wave's loads of K[st+1] and V[st] have landed, and after the barrier so have
         // everybody's; nobody reads K[st] or V[st-1] any more
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (st + 2 < nstep) issue(false, st & 1, ids2);
         if (st + 1 < nstep) issue(true, (st + 1) & 1, ids1);
-        if (st * 64 + 64 > seq_len) scrub_v(st & 1, st);
+        if (st * STEP + STEP > seq_len) scrub_v(st & 1, tok0);
 #pragma unroll
-        for (int b = 0; b < kPfBlocks; ++b) {
+        for (int b = 0; b < BLK; ++b) {
             ids1[b] = ids2[b];
-            ids2[b] = block_id(kPfBlocks * (st + 3) + b);
+            ids2[b] = step_block(st + 3, b);
         }
         // wave-uniform: some column of this wave sees keys of the step
-        if (st * 64 > w_pos_hi) return;
-        if (st * 64 + 63 > w_pos_lo) mask(Sc, st);   // the step touches the causal diagonal
-        u32x4 P[4];
+        if (tok0 > w_pos_hi) return;
+        if (tok0 + T - 1 > w_pos_lo) mask(Sc, tok0);   // the step touches the causal diagonal
+        u32x4 P[2 * HV];
         float alpha, psum;
         bool grow;
         // One straight-line region for the scheduler.  The scores of step st+1 are computed even
@@ -1201,9 +1250,9 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         qk(Sn, (st + 1) & 1);
         softmax_first(Sc, P, alpha, grow, psum);
         // the weights of the first 32 tokens are due here, inside the region of the score MFMAs ...
-        asm volatile("" : "+v"(P[0]));
-        asm volatile("" : "+v"(P[1]));
-        // ... and the region is laid out as 2*hd/16 x (MFMA, LDS read, a share of the vector work):
+#pragma unroll
+        for (int q = 0; q < HV; ++q) asm volatile("" : "+v"(P[q]));
+        // ... and the region is laid out as HV*hd/16 x (MFMA, LDS read, a share of the vector work):
         // the maximum is found next to the first MFMAs, the exponentials next to the others
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
@@ -1213,7 +1262,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
             __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
         }
 #pragma unroll
-        for (int i = KS / 2; i < 2 * KS; ++i) {
+        for (int i = KS / 2; i < HV * KS; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
@@ -1227,13 +1276,13 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         }
         // the second half of the update belongs to the region of the PV MFMAs: its scores pass through an empty
         // asm here so that nothing of it is moved up
-        asm volatile("" : "+v"(Sc[1]));
+        asm volatile("" : "+v"(Sc[HV - 1]));
         softmax_second(Sc, P, alpha, psum);
         pv(P, st & 1);
     };
 
     if constexpr (PIPE) {
-        f32x16 SA[2], SB[2];
+        f32x16 SA[HV], SB[HV];
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         phase(2);
@@ -1252,14 +1301,15 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
                 issue(false, (st + 1) & 1, ids1);
                 issue(true, (st + 1) & 1, ids1);
             }
-            if (st * 64 + 64 > seq_len) scrub_v(st & 1, st);
+            const int tok0 = st * STEP + kg * T;
+            if (st * STEP + STEP > seq_len) scrub_v(st & 1, tok0);
 #pragma unroll
-            for (int b = 0; b < kPfBlocks; ++b) ids1[b] = block_id(kPfBlocks * (st + 2) + b);
-            if (st * 64 > w_pos_hi) continue;   // wave-uniform: no column of this wave sees keys of the step
-            f32x16 S[2];
+            for (int b = 0; b < BLK; ++b) ids1[b] = step_block(st + 2, b);
+            if (tok0 > w_pos_hi) continue;   // wave-uniform: no column of this wave sees keys of the step
+            f32x16 S[HV];
             qk(S, st & 1);
-            if (st * 64 + 63 > w_pos_lo) mask(S, st);
-            u32x4 P[4];
+            if (tok0 + T - 1 > w_pos_lo) mask(S, tok0);
+            u32x4 P[2 * HV];
             float alpha, psum;
             bool grow;
             softmax_first(S, P, alpha, grow, psum);
@@ -1272,7 +1322,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
             softmax_second(S, P, alpha, psum);
             const u32x4 *vp = &ldsV[st & 1][h * HD + col];
 #pragma unroll
-            for (int i = 0; i < 4 * MB; ++i) {
+            for (int i = 0; i < 2 * HV * MB; ++i) {
                 const u32x4 vop = vp[(i / MB) * CH + 32 * (i % MB)];
                 O[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vop),
                                                                 __builtin_bit_cast(bf16x8, P[i / MB]), O[i % MB], 0, 0, 0);
@@ -1287,25 +1337,64 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         swap32(lsum, x, y);
         ltot = x + y;
     }
+    // Piece q of a wave's output (0 .. 4*MB-1) is, in lane (col, h), column 32*wave + col, dims 8q + 4h + 0..3: registers
+    // 4*(q % 4) .. + 3 of O[q / 4].  From here on a thread holds ITEMS pieces of its column, q0 .. q0 + ITEMS - 1.
+    const int q0 = KG == 1 ? 0 : kg * ITEMS;
+    f32x4 acc[ITEMS];
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) acc[i] = f32x4{O[i / 4][4 * (i % 4)], O[i / 4][4 * (i % 4) + 1], O[i / 4][4 * (i % 4) + 2], O[i / 4][4 * (i % 4) + 3]};
+    } else {
+        // The key groups' results meet in the stage memory, which they fill exactly: every wave writes all its pieces, and
+        // the KG waves of a column group each fold the pieces of one KG-th of the dims, in the order of the groups.
+        __shared__ f32x2 group_ml[NW][32];
+        static_assert(NW * 4 * MB * 64 == 4 * KG * STAGE, "the results fill the stage memory");
+        f32x4 (*const all)[4 * MB][64] = reinterpret_cast<f32x4 (*)[4 * MB][64]>(stage_lds<HD, KG>());
+        __syncthreads();   // nobody reads K or V tiles any more
+#pragma unroll
+        for (int q = 0; q < 4 * MB; ++q)
+            all[wave_id][q][lane] = f32x4{O[q / 4][4 * (q % 4)], O[q / 4][4 * (q % 4) + 1], O[q / 4][4 * (q % 4) + 2], O[q / 4][4 * (q % 4) + 3]};
+        if (h == 0) group_ml[wave_id][col] = f32x2{m, ltot};
+        __syncthreads();
+        f32x2 ml[KG];
+        float M = -1e30f;   // (finite: no group may have seen a key of this column, which then weighs nothing)
+#pragma unroll
+        for (int k = 0; k < KG; ++k) {
+            ml[k] = group_ml[k * NC + wave][col];
+            M = fmaxf(M, ml[k][0]);
+        }
+        ltot = 0.f;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KG; ++k) {
+            const float w = fast_exp2(ml[k][0] - M);
+            ltot += ml[k][1] * w;
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                const f32x4 o = all[k * NC + wave][q0 + i][lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][r] += o[r] * w;
+            }
+        }
+        m = M;
+    }
     if (nparts > 1) {
         // (one counter per (tile, kv head): the slot of its part 0 with the list, the unit's index without)
         const int counter_idx = p.pf_table ? slot0 : slot0 / split;
         // ---- partial result of this part, arrival count, merge by the part that arrives last (same
-        // device-scope accesses as the decode kernel).  Lane (col, h) of wave w owns column c = 32w + col,
-        // dims 32mb + 8q4 + 4h + 0..3.  m is the same in both lane halves; ltot already sums them.
-        // layout of a part: [wave][mb][q4][lane][4 floats], so that every store and load instruction of a wave
-        // covers 1 KiB of contiguous memory
-        auto part_ptr = [&](int64_t j, int mb) -> float * {
-            return p.pf_acc + ((((int64_t)(slot0 + (int)j * slot_step) * NW + wave) * MB + mb) * 4 * 64 + lane) * 4;
+        // device-scope accesses as the decode kernel).  Layout of a part: [wave of columns][piece][lane][4 floats], so that
+        // every store and load instruction of a wave covers 1 KiB of contiguous memory.  Waves without columns have nothing
+        // to store or merge (a chunk of 5 rows x 4 heads: one wave's 16 KiB instead of 64).
+        auto part_ptr = [&](int64_t j) -> float * {
+            return p.pf_acc + (((int64_t)(slot0 + (int)j * slot_step) * NC + wave) * 4 * MB + q0) * 256 + lane * 4;
         };
-        {
+        auto ml_ptr = [&](int64_t j) -> float * { return p.pf_ml + ((int64_t)(slot0 + (int)j * slot_step) * COLS + c) * 2; };
+        if (w_used) {
+            float *const pp = part_ptr(part);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    store_dev4(part_ptr(part, mb) + q4 * 256,
-                               f32x4{O[mb][4 * q4], O[mb][4 * q4 + 1], O[mb][4 * q4 + 2], O[mb][4 * q4 + 3]});
-            if (h == 0) store_dev2(p.pf_ml + ((int64_t)(slot0 + part * slot_step) * COLS + c) * 2, m, ltot);
+            for (int i = 0; i < ITEMS; ++i) store_dev4(pp + i * 256, acc[i]);
+            if (h == 0 && kg == 0) store_dev2(ml_ptr(part), m, ltot);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial has reached memory ...
         __syncthreads();                                    // ... and so have the other waves'
@@ -1314,50 +1403,56 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
             arrived = __hip_atomic_fetch_add(p.pf_counters + counter_idx, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (arrived != nparts - 1) return;
+        if (tid == 0)   // ready for the next call
+            __hip_atomic_store(p.pf_counters + counter_idx, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!w_used) return;
         float M = -INFINITY;
         ltot = 0.f;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int i = 0; i < ITEMS; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // in part order: the result does not depend on who is last.  16 loads of a lane on their way at a time: 16 / ITEMS parts.
+        constexpr int PB = 16 / ITEMS;
+        for (int j0 = 0; j0 < nparts; j0 += PB) {
+            f32x2 ml[PB];
+            f32x4 t[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) O[mb][r] = 0.f;
-        for (int j = 0; j < nparts; ++j) {                  // in part order: the result does not depend on who is last
-            const f32x2 ml = load_dev2(p.pf_ml + ((int64_t)(slot0 + j * slot_step) * COLS + c) * 2);
-            f32x4 t[4 * MB];   // t[4*mb + q4] = this lane's dims 32mb + 8q4 + 4h + 0..3 of part j
-            if constexpr (MB == 4)
-                load_dev_part(t, part_ptr(j, 0), part_ptr(j, 1), part_ptr(j, 2), part_ptr(j, 3));
+            for (int b = 0; b < PB; ++b) ml[b] = load_dev2(ml_ptr(min(j0 + b, nparts - 1)));
+            auto pp = [&](int b) -> const float * { return part_ptr(min(j0 + b, nparts - 1)); };
+            if constexpr (PB == 1)
+                load_dev_part<4>(t, pp(0), pp(0) + 1024, pp(0) + 2048, pp(0) + 3072);
+            else if constexpr (PB == 2)
+                load_dev_part<4>(t, pp(0), pp(0) + 1024, pp(1), pp(1) + 1024);
+            else if constexpr (PB == 4)
+                load_dev_part<4>(t, pp(0), pp(1), pp(2), pp(3));
             else
-                load_dev_part(t, part_ptr(j, 0), part_ptr(j, 1));
-            const float M_new = fmaxf(M, ml[0]);
-            const float w_old = fast_exp2(M - M_new), w_new = fast_exp2(ml[0] - M_new);
-            M = M_new;
-            ltot = ltot * w_old + ml[1] * w_new;
+                load_dev_part<2>(t, pp(0), pp(1), pp(2), pp(3), pp(4), pp(5), pp(6), pp(7));
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+            for (int b = 0; b < PB; ++b) {
+                if (j0 + b < nparts) {
+                    const float M_new = fmaxf(M, ml[b][0]);
+                    const float w_old = fast_exp2(M - M_new), w_new = fast_exp2(ml[b][0] - M_new);
+                    M = M_new;
+                    ltot = ltot * w_old + ml[b][1] * w_new;
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
+                    for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) O[mb][4 * q4 + r] = O[mb][4 * q4 + r] * w_old + t[4 * mb + q4][r] * w_new;
+                        for (int r = 0; r < 4; ++r) acc[i][r] = acc[i][r] * w_old + t[b * ITEMS + i][r] * w_new;
                 }
+            }
         }
-        if (tid == 0)   // ready for the next call
-            __hip_atomic_store(p.pf_counters + counter_idx, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (c_valid) {
         const float inv = 1.0f / ltot;
-        uint16_t *op = p.out + ((int64_t)(q_row0 + row) * p.Hq + head) * HD + 4 * h;
+        uint16_t *op = p.out + ((int64_t)(q_row0 + row) * p.Hq + head) * HD + 8 * q0 + 4 * h;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                // registers 4*q4 .. 4*q4+3: dims 32mb + 8*q4 + 4h + 0..3
-                u32x2 w = {pack2_bf16(O[mb][4 * q4] * inv, O[mb][4 * q4 + 1] * inv),
-                           pack2_bf16(O[mb][4 * q4 + 2] * inv, O[mb][4 * q4 + 3] * inv)};
-                *reinterpret_cast<u32x2 *>(op + mb * 32 + q4 * 8) = w;
-            }
+        for (int i = 0; i < ITEMS; ++i) {
+            u32x2 w = {pack2_bf16(acc[i][0] * inv, acc[i][1] * inv), pack2_bf16(acc[i][2] * inv, acc[i][3] * inv)};
+            *reinterpret_cast<u32x2 *>(op + 8 * i) = w;
+        }
     }
 }
 
-template <int HD, int NW>
+template <int HD, int NW, int KG = 1>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs a)
 {
     const AttnParams &p = a.p;
@@ -1370,7 +1465,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs
         trace[1] = (__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u) * 256u + ((__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 8) & 255u);
         trace[2] = 0;   // (a workgroup that leaves before its first step stores no phases)
     }
-    prefill_unit<HD, NW, true>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)blockIdx.x,
+    prefill_unit<HD, NW, true, KG>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)blockIdx.x,
                                trace ? trace + 2 : nullptr, t_start);
     if (trace) {
         __syncthreads();
@@ -1384,7 +1479,7 @@ template <int HD>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void prefill_kernel_lean(const KernArgs a)
 {
     const AttnParams &p = a.p;
-    prefill_unit<HD, 8, false>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)blockIdx.x);
+    prefill_unit<HD, 8, false, 1>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1438,7 +1533,7 @@ OOCO_DEV void step_body(const KernArgs &a)
         }
     } else {
         const int n_cum = p.num_seqs + 1;   // the prefill array follows the decode array
-        prefill_unit<HD, NW, PIPE>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, (int)blockIdx.x - p.dec_wgs);
+        prefill_unit<HD, NW, PIPE, 1>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, (int)blockIdx.x - p.dec_wgs);
     }
 }
 
@@ -1561,7 +1656,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void mixed_kernel(const KernArgs a)
                 __syncthreads();
                 const int vb = sh_item;
                 if (vb < 0) break;
-                prefill_unit<HD, 4, true>(p, pf_at, vb);
+                prefill_unit<HD, 4, true, 1>(p, pf_at, vb);
                 if (pass == 0) ++n_first; else ++n_second;
             }
         }
@@ -1867,7 +1962,11 @@ hipError_t launch_prefill(const KernArgs &a, hipStream_t s)
     if (a.p.n_tiles <= 0) return hipSuccess;
     const dim3 grid((unsigned)(a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
                                             : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1)));
-    if (a.p.hd == 128 && a.p.pf_waves == 8 && a.p.lean)
+    if (a.p.pf_groups > 1 && a.p.hd == 128)
+        hipLaunchKernelGGL((prefill_kernel<128, 8, kKeyGroups>), grid, dim3(512), 0, s, a);
+    else if (a.p.pf_groups > 1)
+        hipLaunchKernelGGL((prefill_kernel<64, 8, kKeyGroups>), grid, dim3(512), 0, s, a);
+    else if (a.p.hd == 128 && a.p.pf_waves == 8 && a.p.lean)
         hipLaunchKernelGGL((prefill_kernel_lean<128>), grid, dim3(512), 0, s, a);
     else if (a.p.hd == 128 && a.p.pf_waves == 8)
         hipLaunchKernelGGL((prefill_kernel<128, 8>), grid, dim3(512), 0, s, a);
