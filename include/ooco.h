@@ -139,9 +139,11 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *   "prefill_groups"      key groups of a prefill workgroup: 4 = workgroups of eight waves on 64 query columns whose
  *                         four groups walk a quarter of the keys each, 128 keys per step, and merge in LDS; 1 =
  *                         workgroups of four waves on 128 columns; 0 (default) = by the number and the length of the
- *                         tiles: a batch of few tiles takes half as many steps one after the other.  Batches without
- *                         decode sequences (4: any batch outside the register-lean pair); automatic "prefill_split"
- *                         then cuts a tile into up to 64 parts.
+ *                         tiles: a batch of few tiles takes half as many steps one after the other.  Beside decode
+ *                         sequences the decode workgroups then have eight waves too, and all of them together a compute
+ *                         unit each (step_kernel_groups).  Automatic "prefill_split" cuts such a tile into up to 64
+ *                         parts.  4 is taken wherever such a batch fits (not with the register-lean pair, a dynamic
+ *                         tail, XCD weights or "decode_coop" 0).
  *   "prefill_sorted"      0/1/2 (default 1): a batch of at most 896 prefill tiles dispatches the tiles of ALL its
  *                         chunks -- the parts of its tiles, if they are split -- by decreasing number of 64-key
  *                         steps (one list entry per tile or part, in the kernel arguments; at most 896 entries);

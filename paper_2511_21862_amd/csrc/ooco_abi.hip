@@ -123,6 +123,8 @@ struct HostPlan {
     bool two_streams = false;    // a batch with both kinds of work that runs faster as two kernels on two streams than in one launch
     bool near = false;           // step kernel: AttnParams::dec_near
     int32_t coop = 0;            // decode runs are worked on by workgroups of four waves (decode_coop_kernel); kCoopBySequence: run i is sequence i
+    int32_t coop_waves = 4;      // waves of such a workgroup
+    int32_t pf_units = 0;        // key groups beside decode work: the compute units that the prefill workgroups take
     int32_t nbi = 0;             // KV blocks per softmax step of the decode kernel that the plan asks for (0 = the kernel's default)
 };
 
@@ -225,15 +227,29 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     } else if (whole && wgs > cus) {
         whole = (geo.hd == 64 || !equal) && (pf_wgs > 0 || 2 * wgs <= 3 * cus || longest <= 32 * 128 || !skewed);
     }
-    if (coop_can && geo.coop_opt && geo.segments_opt == 0 && whole) {
+    if (out.pf_units > 0) {
+        // Beside prefill workgroups of key groups: workgroups of eight waves, one per unit that those leave.
+        const int64_t left = std::max<int64_t>(1, (cus - out.pf_units) / geo.Hkv);
+        out.coop_waves = 8;
+        out.nbi = geo.hd == 128 ? 2 : 0;
+        if (geo.segments_opt == 0 && longest <= 48 * 128 && num_seqs <= left) {
+            out.coop = kCoopBySequence;
+            out.static_runs = num_seqs;
+            out.static_blocks = (int32_t)dec_blocks;
+            return;
+        }
+        out.coop = 1;
+    } else if (coop_can && geo.coop_opt && geo.segments_opt == 0 && whole) {
         out.coop = kCoopBySequence;
         out.nbi = geo.hd == 128 ? 2 : 0;
         out.static_runs = num_seqs;
         out.static_blocks = (int32_t)dec_blocks;
         return;
     }
-    out.coop = coop_can && (geo.coop_opt >= 2 || (geo.coop_opt == 1 && coop_rule));
-    if (geo.hd == 128 && short_seqs)
+    if (out.pf_units == 0) out.coop = coop_can && (geo.coop_opt >= 2 || (geo.coop_opt == 1 && coop_rule));
+    if (out.pf_units > 0)
+        ;
+    else if (geo.hd == 128 && short_seqs)
         out.nbi = tiles <= 16384 ? 2 : 1;
     else if (geo.hd == 128 && small)
         out.nbi = 2;
@@ -241,14 +257,14 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     if (out.coop) {
         // (beside a prefill part longer runs, which leave it units: one sequence of 16,000 tokens, 4 kv heads, beside
         // 100 rows 23.4 -> 16.9 us)
-        wave_slots = per_unit;
+        wave_slots = out.pf_units > 0 ? std::max<int64_t>(1, (cus - out.pf_units) / geo.Hkv) : per_unit;
         min_blocks = kv_blocks > 512 * dec_seqs || (pf_wgs > 0 && kv_blocks > 256) ? 32 : pf_wgs > 0 || kv_blocks <= 16 || kv_blocks > 64 * dec_seqs ? 16 : 8;
         if (short_seqs) at_least = dec_seqs;
         // Starting a piece costs the whole workgroup, so it weighs more in the line: as much as 12 tiles of head_dim 128.
         // Pads of 3 / 6 / 12 / 24: sixteen sequences of 512..4096 tokens 31.5 / 31.1 / 30.6 / 30.5 us, sixteen of
         // 1000..2000 22.8 / 22.0 / 21.0 / 21.8; head_dim 64, pads of 6 / 12 / 24 / 36: 12.3 / 11.3 / 10.2 / 10.2.
         if (geo.piece_pad < 0) {
-            const int32_t more = 3 * default_piece_pad(geo.hd);
+            const int32_t more = (out.coop_waves == 8 ? 5 : 3) * default_piece_pad(geo.hd);
             int32_t added = 0;
             for (int i = 0; i < num_seqs; ++i) {
                 if (dcum[i + 1] + added > dcum[i]) added += more;   // (dcum[i] has its share already)
@@ -326,6 +342,8 @@ struct PrefillFacts {
     const int32_t *st;                           // with the tile list: steps of the listed tiles, in list order
     int pf_waves;
     int64_t max_cols;                            // query columns of the widest tile
+    int64_t dec_units;                           // units that the decode part needs, if it is planned later
+    size_t dec_reserve;                          // workspace that the decode part may take, if it is planned later
     int64_t dec_blocks, kv_blocks;               // decode part: units of its line, KV blocks
     double pf_pairs;                             // visible (query row, key) pairs of all chunks
 };
@@ -345,7 +363,7 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
     const int64_t units = tiles * geo.Hkv;
     int64_t split = 1;
     const size_t part_bytes = (size_t)(32 * out.pf_col_waves()) * (geo.hd + 2) * sizeof(float);
-    const size_t left = geo.ws_bytes - std::min(geo.ws_bytes, ((size_t)out.slots * slot_bytes(geo) + 255) / 256 * 256);
+    const size_t left = geo.ws_bytes - std::min(geo.ws_bytes, std::max(f.dec_reserve, ((size_t)out.slots * slot_bytes(geo) + 255) / 256 * 256));
     const double cus = (double)geo.num_cus;
     // Estimated time in microseconds of a launch of w workgroups in all, the longest of them `longest` 64-key steps,
     // fitted to sweeps of 28 batches of equal chunks x 8 forced splits on MI355X (the choice is within 2.5 % of the best
@@ -436,13 +454,21 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
                 const double step = !wide ? 0.78 + 0.2 * r : k > 1 ? 1.05 + 0.4 * r : 1.06 + 0.6 * std::max(0.0, r - 0.5);
                 return (wide ? 8.0 : 5.6) + (double)longest * step + (k > 1 ? (wide ? 2.0 : 1.5) + merge * (double)k : 0.0);
             };
-            double best = est_groups(units, max_tile_steps, 1);
+            // beside decode workgroups, one per unit that is left: the longer of the two
+            const double dec_bytes = (double)kv_blocks * BS * 2.0 * geo.Hkv * geo.hd * 2.0;
+            auto est_step = [&](int64_t wgs, int64_t longest, int64_t k) {
+                const double t = est_groups(wgs, longest, k);
+                if (kv_blocks == 0) return t;
+                const double left_units = std::max(1.0, cus - (double)wgs);
+                return std::max(t, 9.0 + dec_bytes / std::min(6.6e6, 0.030e6 * left_units)) + 0.1 * t;
+            };
+            double best = est_step(units, max_tile_steps, 1);
             int64_t worse = 0;
             for (int64_t k = 2; k <= kMaxGroupSplit && k <= max_tile_steps && worse < 8; ++k) {
                 int64_t split_ones = 0;
                 const int64_t e = entries_of(k, true, nullptr, &split_ones);
-                if (e * geo.Hkv > geo.num_cus || !list_fits(e, split_ones)) break;
-                const double t = est_groups(e * geo.Hkv, (max_tile_steps + k - 1) / k, k);
+                if (e * geo.Hkv > geo.num_cus - (kv_blocks > 0 ? f.dec_units : 0) || !list_fits(e, split_ones)) break;
+                const double t = est_step(e * geo.Hkv, (max_tile_steps + k - 1) / k, k);
                 if (t < best) {
                     best = t;
                     split = k;
@@ -538,40 +564,67 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
     }
 }
 
-// Whether the prefill part of a batch without decode work runs in workgroups of key groups: eight waves, 64 query columns,
-// each of the four groups walking a quarter of the keys, their results merged in LDS.  Such a workgroup has a compute unit to
-// itself and takes 1.06 .. 1.36 us for 128 keys (one of four waves and 128 columns 1.08 .. 1.3 for 64), so it halves the chain
-// of steps that bounds a batch of few tiles, and a tile of few columns wastes half as much; a batch that fills the units is
-// better off with two workgroups of four waves on each.  By the batch's load, 128-key steps of 64 columns per unit, against
-// workgroups of four waves (699 random batches of up to 256 tiles of 64 columns on 256 units, nine head layouts):
-// load up to 10: 0.80 of the time (0.54 .. 1.03); 10..15: 0.88, but tiles of 65 to 90 columns on long contexts, which two
-// workgroups then read twice, up to 1.21; 15..25: 0.95 with up to 64 tiles and few unused columns, 1.0 (up to 1.7) with more,
-// whose steps cannot be dealt out evenly any more; above 25 1.07 and worse.  Fewer than three steps (head_dim 64: two) do not
-// pay for the merge in LDS (one step 6.4 -> 8.3 us, two 11.2 -> 10.3, with few columns 9.9 -> 10.3).
-// "prefill_split" = 1, one workgroup per tile whatever its length, leaves only the chain: always.
+// Whether the prefill part of a batch runs in workgroups of key groups: eight waves, 64 query columns, each of the four groups
+// walking a quarter of the keys, their results merged in LDS.  Such a workgroup has a compute unit to itself and takes
+// 1.06 .. 1.36 us for 128 keys (one of four waves and 128 columns 1.08 .. 1.3 for 64), so it halves the chain of steps that
+// bounds a batch of few tiles, and a tile of few columns wastes half as much; a batch that fills the units is better off with
+// two workgroups of four waves on each.
+//   * Without decode work, by the batch's load, 128-key steps of 64 columns per unit, against workgroups of four waves (699
+//     random batches of up to 256 tiles of 64 columns on 256 units, nine head layouts): load up to 10: 0.80 of the time
+//     (0.54 .. 1.03); 10..15: 0.88, but tiles of 65 to 90 columns on long contexts, which two workgroups then read twice, up
+//     to 1.21; 15..25: 0.95 with up to 64 tiles and few unused columns, 1.0 (up to 1.7) with more, whose steps cannot be dealt
+//     out evenly any more; above 25 1.07 and worse.  Fewer than three steps (head_dim 64: two) do not pay for the merge in LDS
+//     (one step 6.4 -> 8.3 us, two 11.2 -> 10.3, with few columns 9.9 -> 10.3).
+//   * Beside decode work (the step kernel, whose decode workgroups then have eight waves and a unit each too): where every
+//     decode sequence finds a unit of its own or half of one, and the stream on the units that are left is no longer than the
+//     prefill part or hardly longer than on all; not where the decode part alone decides the time (1713 random batches: 836
+//     taken, 0.81 of the time, 39 of them more than 3 % slower, mostly by under a microsecond; one step more where one wave
+//     holds all columns).
+//   * "prefill_split" = 1, one workgroup per tile whatever its length, leaves only the chain, so any load (756 batches: 441
+//     taken, 0.62 of the time, six of them more than 6 % slower).
 bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_lens, const int32_t *h_query_start_loc)
 {
-    const int rows = prefill_tile_rows(geo.Hq / geo.Hkv, 8 / kKeyGroups);
-    int64_t tiles = 0, steps = 0, longest = 0, widest = 0;
-    double cover = 0.0;   // (row, step) pairs that the tiles have room for, and that the chunks have
-    double used = 0.0;
+    const int64_t g = geo.Hq / geo.Hkv, rows = prefill_tile_rows((int32_t)g, 8 / kKeyGroups);
+    int64_t tiles = 0, steps = 0, longest = 0, widest = 0, n_dec = 0, dec_blk = 0;
+    double cover = 0.0, used = 0.0;   // (row, step) pairs that the tiles have room for, and that the chunks have
     for (int i = 0; i < num_seqs; ++i) {
         const int64_t ql = (int64_t)h_query_start_loc[i + 1] - h_query_start_loc[i];
-        if (ql == 1) return false;
-        if (ql < 1) continue;
+        if (ql == 1) {
+            ++n_dec;
+            dec_blk += ((int64_t)h_seq_lens[i] + geo.BS - 1) / geo.BS;
+        }
+        if (ql <= 1) continue;
         const int64_t t = (ql + rows - 1) / rows, s = ((int64_t)h_seq_lens[i] + 127) / 128;
         tiles += t;
         steps += t * s;
         cover += (double)(t * rows) * (double)s;
         used += (double)ql * (double)s;
         longest = std::max(longest, s);
-        widest = std::max(widest, t);
+        widest = std::max(widest, ql);
     }
-    if (tiles == 0 || geo.pf_groups_opt == kKeyGroups) return tiles > 0;
-    if (tiles * geo.Hkv > geo.num_cus || longest < (geo.hd == 128 ? 3 : 2)) return false;
-    if (geo.pf_split_opt > 0) return geo.pf_split_opt == 1;
-    const int64_t load = steps * geo.Hkv, cus = geo.num_cus;
-    return load <= 10 * cus || (load <= 25 * cus && 4 * tiles * geo.Hkv <= cus && (widest == 1 || cover <= 1.2 * used));
+    const int64_t units = tiles * geo.Hkv, load = steps * geo.Hkv, cus = geo.num_cus;
+    const bool forced = geo.pf_groups_opt == kKeyGroups, whole = geo.pf_split_opt == 1;
+    if (tiles == 0) return false;
+    if (n_dec > 0) {
+        // (the decode part in cooperative workgroups of the default run layout)
+        if (!geo.coop_opt || geo.tail_pct || geo.xcd_cw[kXcds - 1] || num_seqs > kInlineSeqs / 2) return false;
+        if (units + n_dec * geo.Hkv > cus) return false;
+        if ((size_t)(cus / geo.Hkv + num_seqs + 1) * slot_bytes(geo) + 256 > geo.ws_bytes / 2) return false;
+    }
+    if (forced) return true;
+    const int64_t enough = (geo.hd == 128 ? 3 : 2) + (n_dec > 0 && widest * g <= 32);
+    if (units > cus || longest < enough || (geo.pf_split_opt > 0 && !whole)) return false;
+    if (n_dec > 0) {
+        // estimates in us, as in plan_prefill_parts
+        const double bytes = (double)dec_blk * geo.BS * 2.0 * geo.Hkv * geo.hd * 2.0;
+        const double dec_all = 9.0 + bytes / 6.6e6, dec_left = 9.0 + bytes / std::min(6.6e6, 0.030e6 * (double)(cus - units));
+        const int64_t parts = whole ? 1 : std::max<int64_t>(1, std::min<int64_t>(kMaxGroupSplit, 4 * (cus - units) / (5 * units)));
+        const double chain = (double)((longest + parts - 1) / parts), merge = parts > 1 ? 1.0 : 0.0, k = (double)parts;
+        const double pf = geo.hd == 128 ? 8.0 + 1.2 * chain + merge * (2.0 + 0.3 * k) : 5.6 + 0.9 * chain + merge * (1.5 + 0.2 * k);
+        if (dec_left > 1.35 * std::max(dec_all, pf) || pf < 0.7 * dec_all) return false;
+        if (!whole && parts == 1 && longest > 16) return false;   // (no unit left to cut a long tile)
+    }
+    return whole || load <= 10 * cus || (load <= 25 * cus && 4 * units <= cus && (n_dec > 0 || widest <= rows || cover <= 1.2 * used));
 }
 
 // Validates the length arrays and builds the plan.  Pure host code, no allocation.
@@ -763,16 +816,25 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         if (geo.dec_cus_opt == 99) dec = 99;   // every unit runs both kinds (one workgroup each): for measurements
         out.dec_cus = dec;
     }
-    // ---- run layout of the decode block line (see plan_decode_runs)
-    if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, max_dec_blocks, tiles * geo.Hkv, lean, dcum, out);
+    // ---- run layout of the decode block line (see plan_decode_runs); prefill tiles cut along the context (see
+    // plan_prefill_parts).  Prefill workgroups of key groups come first: the decode part gets the units that they leave.
+    const bool pf_first = out.pf_groups > 1 && dec_blocks > 0;
+    auto plan_decode = [&]() {
+        if (dec_blocks > 0) plan_decode_runs(geo, num_seqs, dec_blocks, kv_blocks, dec_seqs, max_dec_blocks, tiles * geo.Hkv, lean, dcum, out);
+    };
+    if (!pf_first) plan_decode();
     // The lean pair's decode waves of a workgroup side by side (half a percent of a long stream), but not where the longest
     // sequence is cut into more than 32 parts, whose merges then meet on one unit (see step_body): near / far by parts, 64/8
     // heads, 100,000 tokens: 16 0.99, 32 0.98, 43 1.04, 64 1.10, 128 1.17; 28/4 heads, 400,000: 32 1.02, 85 1.12, 128 1.24.
     out.near = lean && dec_blocks > 0 && max_dec_blocks * out.static_runs <= 32 * (int64_t)out.dec_blocks;
-    // ---- prefill tiles cut along the context (see plan_prefill_parts)
     if (tiles > 0) {
-        const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, out.pf_waves, max_cols, dec_blocks, kv_blocks, pf_pairs};
+        const size_t reserve = pf_first ? (size_t)(geo.num_cus / geo.Hkv + num_seqs + 1) * slot_bytes(geo) + 256 : 0;
+        const PrefillFacts facts = {tiles, tile_steps, max_tile_steps, n_order, st, out.pf_waves, max_cols, std::max<int64_t>(geo.Hkv, (dec_seqs * geo.Hkv + 1) / 2), reserve, dec_blocks, kv_blocks, pf_pairs};
         plan_prefill_parts(geo, facts, store.pf + (2 * (size_t)out.num_pf + 1), out);
+    }
+    if (pf_first) {
+        out.pf_units = (int32_t)(out.pf_table ? (int64_t)out.pf_table * geo.Hkv : tiles * geo.Hkv * out.pf_split);
+        plan_decode();
     }
     return OOCO_OK;
 }
@@ -783,7 +845,9 @@ bool step_fits(const HostPlan &pl, int hd, bool coop, int nbi)
 {
     return pl.n_tiles > 0 && pl.static_runs > 0 && pl.tail_runs == 0 && pl.cw[kXcds - 1] == 0 && pl.dec_cus == 0 &&
            (size_t)pl.num_seqs + 1 + pl.pf_size <= (size_t)kInlineSeqs + 1 &&
-           (pl.lean ? hd == 128 && pl.pf_waves == 8 : pl.pf_waves == 4 && (coop || nbi == 2 || (nbi == 1 && hd == 128)));
+           (pl.pf_groups > 1 ? coop && pl.coop_waves == 8
+            : pl.lean        ? hd == 128 && pl.pf_waves == 8
+                             : pl.pf_waves == 4 && (coop || nbi == 2 || (nbi == 1 && hd == 128)));
 }
 
 // Pieces of the decode line as the kernel walks them (host mirror of the device logic).
@@ -1359,7 +1423,7 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
     const int nbi = coop ? 256 / ctx->hd : decode_nbi(ctx);
     char d[64] = "", f[64] = "";
     if (runs_as_step(ctx))
-        snprintf(d, sizeof d, pl.lean ? "step_kernel_lean<%d>" : coop ? "step_kernel<%d, %d, true>" : "step_kernel<%d, %d, false>", ctx->hd,
+        snprintf(d, sizeof d, pl.pf_groups > 1 ? "step_kernel_groups<%d, %d>" : pl.lean ? "step_kernel_lean<%d>" : coop ? "step_kernel<%d, %d, true>" : "step_kernel<%d, %d, false>", ctx->hd,
                  nbi);
     else if (dec && pf && pl.dec_cus > 0)
         snprintf(d, sizeof d, "mixed_kernel<%d>", ctx->hd);
@@ -1367,7 +1431,7 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
         if (dec && pl.lean)
             snprintf(d, sizeof d, "decode_kernel_lean<%d>", ctx->hd);
         else if (dec && coop)
-            snprintf(d, sizeof d, "decode_coop_kernel<%d, %d>", ctx->hd, nbi);
+            snprintf(d, sizeof d, pl.coop_waves == 8 ? "decode_coop_kernel<%d, %d, 8>" : "decode_coop_kernel<%d, %d>", ctx->hd, nbi);
         else if (dec)
             snprintf(d, sizeof d, "decode_kernel<%d, %d>", ctx->hd, nbi);
         if (pf && pl.lean && pl.pf_waves == 8)
@@ -1497,7 +1561,8 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     p.pf_groups = (int8_t)pl.pf_groups;
     p.nbi = ctx->opt_nbi ? (int32_t)ctx->opt_nbi : pl.nbi;
     p.rotate_heads = (int16_t)(ctx->opt_rotate != 0);
-    p.coop = (int16_t)decode_coop(ctx);
+    p.coop = (int8_t)decode_coop(ctx);
+    p.coop_waves = (int8_t)pl.coop_waves;
     p.dec_near = (int16_t)pl.near;
     p.lean = (int16_t)pl.lean;
     for (int k = 0; k < kXcds; ++k) p.xcd_cw[k] = pl.cw[k];
@@ -1710,7 +1775,8 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.pf_waves = (int8_t)pl.pf_waves;
     p.pf_groups = (int8_t)pl.pf_groups;
     p.nbi = pl.nbi;
-    p.coop = (int16_t)pl.coop;
+    p.coop = (int8_t)pl.coop;
+    p.coop_waves = (int8_t)pl.coop_waves;
     p.dec_near = (int16_t)pl.near;
     p.rotate_heads = 1;
     p.pf_acc = nullptr;

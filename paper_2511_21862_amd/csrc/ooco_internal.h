@@ -72,7 +72,8 @@ struct AttnParams {
     int16_t dec_near;           // step kernel: they take items side by side (the kv heads of one run), else far apart
     int32_t nbi;                // tuning: KV blocks per softmax step of the decode kernel
     int16_t rotate_heads;       // tuning: kv head rotation across XCDs
-    int16_t coop;               // decode: workgroups of four waves that share every piece of a run (decode_coop_kernel): 1, kCoopBySequence, or 0
+    int8_t coop;                // decode: workgroups of waves that share every piece of a run (decode_coop_kernel): 1, kCoopBySequence, or 0
+    int8_t coop_waves;          // ... of so many waves: 4, or 8 beside prefill workgroups of key groups
     int16_t lean;               // mixed batches: the register-lean kernels (decode 128, prefill 8 waves x 192 registers)
     uint16_t xcd_cw[8];         // cumulative XCD weights of the static runs (RunLayout::cw); zeros = equal runs
     uint32_t queue_base;        // ticket value at which this launch's tail runs start

@@ -660,18 +660,20 @@ __global__ __launch_bounds__(64, 3) void decode_kernel_lean(const KernArgs a)
 template <int HD>
 constexpr int kCoopStride = HD + 16;   // floats from one head's partial output to the next in LDS (16-byte writes of four
                                        // heads' lanes then fall on 64 different banks)
-template <int HD>
-constexpr int kCoopFloats = 4 * 16 * kCoopStride<HD> + 4 * 16 * 2 + 4;   // LDS the four waves need
+template <int HD, int NWV>
+constexpr int kCoopFloats = NWV * 16 * kCoopStride<HD> + NWV * 16 * 2 + 4;   // LDS the waves need
 
-template <int HD, int NBI, class CumAt>
+// (NWV = waves of the workgroup: 4, or 8 beside prefill workgroups of key groups)
+template <int HD, int NBI, int NWV, class CumAt>
 OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, int run, int kvh, float *lds,
                               uint64_t *trace)
 {
     constexpr int NB = HD / 16;
     constexpr int STRIDE = kCoopStride<HD>;
-    constexpr int MAXU = (16 * HD / 4 + 255) / 256;   // 16-byte units of the output a thread may own
-    float *const l_ml = lds + 4 * 16 * STRIDE;
-    int *const l_last = reinterpret_cast<int *>(l_ml + 4 * 16 * 2);
+    constexpr int THREADS = NWV * 64;
+    constexpr int MAXU = (16 * HD / 4 + THREADS - 1) / THREADS;   // 16-byte units of the output a thread may own
+    float *const l_ml = lds + NWV * 16 * STRIDE;
+    int *const l_last = reinterpret_cast<int *>(l_ml + NWV * 16 * 2);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -690,7 +692,7 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
         seq = count_le(cum_at, p.num_seqs, lo, lane);
     }
     int pos = lo;
-    while (pos < hi) {   // (everything here is the same in all four waves)
+    while (pos < hi) {   // (everything here is the same in all waves)
         seq = __builtin_amdgcn_readfirstlane(seq);
         int cs = cum_at(seq), ce = cum_at(seq + 1);
         while (ce <= pos) {   // sequences without decode blocks
@@ -711,7 +713,7 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
         const int q_row = min(max(p.query_start_loc[seq], 0), p.total_q - 1);
         f32x4 O[NB];
         float m, lsum;
-        decode_stream<HD, NBI, 4>(p, kvh, seq, begin - first, stop - begin, seq_len, q_row, wave, lane, trace, first_piece, O, m,
+        decode_stream<HD, NBI, NWV>(p, kvh, seq, begin - first, stop - begin, seq_len, q_row, wave, lane, trace, first_piece, O, m,
                                   lsum);
         if (trace && stop == hi && lane == 0) trace[2] = wall_clock64();
         const float lw = rows_sum(lsum);
@@ -730,17 +732,19 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
         };
 #pragma unroll
         for (int i = 0; i < MAXU; ++i) {
-            const int u = tid + 256 * i;
+            const int u = tid + THREADS * i;
             if (u < units) {
                 const int hh = u / (HD / 4), d4 = u % (HD / 4);
-                f32x2 ml[4];
+                f32x2 ml[NWV];
 #pragma unroll
-                for (int w = 0; w < 4; ++w) ml[w] = *reinterpret_cast<const f32x2 *>(l_ml + (w * 16 + hh) * 2);
-                const float M = fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0]));
+                for (int w = 0; w < NWV; ++w) ml[w] = *reinterpret_cast<const f32x2 *>(l_ml + (w * 16 + hh) * 2);
+                float M = ml[0][0];
+#pragma unroll
+                for (int w = 1; w < NWV; ++w) M = fmaxf(M, ml[w][0]);
                 f32x4 acc = {0.f, 0.f, 0.f, 0.f};
                 float l = 0.f;
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {   // in wave order
+                for (int w = 0; w < NWV; ++w) {   // in wave order
                     const float wt = fast_exp2(ml[w][0] - M);
                     const f32x4 o = *reinterpret_cast<const f32x4 *>(lds + (w * 16 + hh) * STRIDE + 4 * d4);
                     l += ml[w][1] * wt;
@@ -767,7 +771,7 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
             if (*l_last) {   // last part of this (sequence, kv head): merge, in slot order
 #pragma unroll
                 for (int i = 0; i < MAXU; ++i) {
-                    const int u = tid + 256 * i;
+                    const int u = tid + THREADS * i;
                     if (u < units) {
                         const int hh = u / (HD / 4), d4 = u % (HD / 4);
                         float M = -INFINITY, l = 0.f;
@@ -809,11 +813,11 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
     }
 }
 
-template <int HD, int NBI>
-__global__ __launch_bounds__(256, 2) void decode_coop_kernel(const KernArgs a)
+template <int HD, int NBI, int NWV>
+__global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs a)
 {
     const AttnParams &p = a.p;
-    __shared__ __align__(16) float lds[kCoopFloats<HD>];
+    __shared__ __align__(16) float lds[kCoopFloats<HD, NWV>];
     asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens), "s"(p.query_start_loc),
                  "s"(p.cum_dev), "s"(p.trace), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),
                  "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks), "s"(p.static_runs), "s"(p.piece_pad),
@@ -823,7 +827,7 @@ __global__ __launch_bounds__(256, 2) void decode_coop_kernel(const KernArgs a)
     uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
     if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
     const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
-    decode_coop_run<HD, NBI>(p, [&](int idx) -> int { return p.cum_dev ? p.cum_dev[idx] : a.cum[idx]; }, L, run, kvh, lds, trace);
+    decode_coop_run<HD, NBI, NWV>(p, [&](int idx) -> int { return p.cum_dev ? p.cum_dev[idx] : a.cum[idx]; }, L, run, kvh, lds, trace);
     if (trace) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0) trace[3] = wall_clock64();
@@ -1492,18 +1496,18 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void 
 // rows + 128 decodes) and 1653 -> 1635 (2 x 2048 + 32 long decodes); in a loop of calls level, 266 / 268 and 1625 / 1630, but
 // 340 and 2170 on a context whose side stream shares a hardware queue with the caller's stream (one or two of eight contexts
 // made in a row), where the kernels run in sequence.  2 x 120 rows + 24 short decodes, in sequence before: 37.5 -> 29.
-template <int HD, int NBI, int MBATCH, int NW, bool PIPE, bool COOP>
+template <int HD, int NBI, int MBATCH, int NW, bool PIPE, bool COOP, int KG = 1>
 OOCO_DEV void step_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
     if (COOP && (int)blockIdx.x < p.dec_wgs) {   // cooperative decode workgroups
-        static_assert(kCoopFloats<HD> * sizeof(float) <= 4 * kPfBlocks * HD * 2 * sizeof(u32x4), "fits the stage memory");
+        static_assert(!COOP || kCoopFloats<HD, NW> * sizeof(float) <= 4 * KG * kPfGroupBlocks<KG> * HD * 2 * sizeof(u32x4), "fits the stage memory");
         const int run = (int)blockIdx.x / p.Hkv, slot = (int)blockIdx.x - run * p.Hkv;
         uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
         if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
         const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
-        decode_coop_run<HD, NBI>(p, [&](int idx) -> int { return a.cum[idx]; }, L, run, p.rotate_heads ? (slot + run) % p.Hkv : slot,
-                                 reinterpret_cast<float *>(stage_lds<HD>()), trace);
+        decode_coop_run<HD, NBI, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, L, run, p.rotate_heads ? (slot + run) % p.Hkv : slot,
+                                     reinterpret_cast<float *>(stage_lds<HD, KG>()), trace);
         if (trace) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (threadIdx.x == 0) trace[3] = wall_clock64();
@@ -1533,7 +1537,7 @@ OOCO_DEV void step_body(const KernArgs &a)
         }
     } else {
         const int n_cum = p.num_seqs + 1;   // the prefill array follows the decode array
-        prefill_unit<HD, NW, PIPE, 1>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, (int)blockIdx.x - p.dec_wgs);
+        prefill_unit<HD, NW, PIPE, KG>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, (int)blockIdx.x - p.dec_wgs);
     }
 }
 
@@ -1541,6 +1545,14 @@ template <int HD, int NBI, bool COOP>
 __global__ __launch_bounds__(kPfThreads, 2) void step_kernel(const KernArgs a)
 {
     step_body<HD, NBI, 3, 4, true, COOP>(a);
+}
+
+// The same with prefill workgroups of key groups and decode workgroups of eight waves, which have a compute unit each: small
+// batches whose workgroups all find one.
+template <int HD, int NBI>
+__global__ __launch_bounds__(512, 1) void step_kernel_groups(const KernArgs a)
+{
+    step_body<HD, NBI, 3, 8, true, true, kKeyGroups>(a);
 }
 
 // The register-lean pair in one launch: prefill workgroups of eight waves; of a decode workgroup's eight waves the
@@ -1925,10 +1937,14 @@ hipError_t launch_decode(const KernArgs &a, hipStream_t s)
     if (a.p.static_runs <= 0 || a.p.dec_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)((int64_t)a.p.static_runs * a.p.Hkv)), block(64);
     if (a.p.coop) {
-        if (a.p.hd == 128)
-            hipLaunchKernelGGL((decode_coop_kernel<128, 2>), grid, dim3(256), 0, s, a);
+        if (a.p.coop_waves == 8 && a.p.hd == 128)
+            hipLaunchKernelGGL((decode_coop_kernel<128, 2, 8>), grid, dim3(512), 0, s, a);
+        else if (a.p.coop_waves == 8)
+            hipLaunchKernelGGL((decode_coop_kernel<64, 4, 8>), grid, dim3(512), 0, s, a);
+        else if (a.p.hd == 128)
+            hipLaunchKernelGGL((decode_coop_kernel<128, 2, 4>), grid, dim3(256), 0, s, a);
         else
-            hipLaunchKernelGGL((decode_coop_kernel<64, 4>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((decode_coop_kernel<64, 4, 4>), grid, dim3(256), 0, s, a);
         return hipGetLastError();
     }
     if (a.p.lean && a.p.hd == 128) {
@@ -1989,7 +2005,12 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
                                     : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
     a.p.dec_wgs = (int32_t)dec;
     const dim3 grid((unsigned)(dec + pf));
-    if (a.p.lean)
+    if (a.p.pf_groups > 1 && (!a.p.coop || a.p.coop_waves != 8)) return hipErrorInvalidValue;
+    if (a.p.pf_groups > 1 && a.p.hd == 128)
+        hipLaunchKernelGGL((step_kernel_groups<128, 2>), grid, dim3(512), 0, s, a);
+    else if (a.p.pf_groups > 1)
+        hipLaunchKernelGGL((step_kernel_groups<64, 4>), grid, dim3(512), 0, s, a);
+    else if (a.p.lean)
         hipLaunchKernelGGL((step_kernel_lean<128>), grid, dim3(512), 0, s, a);
     else if (a.p.hd == 64 && a.p.coop)
         hipLaunchKernelGGL((step_kernel<64, 4, true>), grid, dim3(kPfThreads), 0, s, a);

@@ -55,8 +55,34 @@ def test_key_groups_are_planned_where_they_pay():
     assert rows4([512], [760]) == 16 and rows4([512], [900]) == 32
     assert rows4([128], [8192]) == 16 and rows4([144], [8192]) == 32
     assert rows4([64], [12000]) == 16 and rows4([16], [40000]) == 16 and rows4([18], [40000]) == 18 and rows4([18] * 4, [12000] * 4) == 18
-    # decode work beside it: the four-wave workgroups
-    assert rows4([40, 1], [1000, 50]) == 32
+    # beside decode work: where every decode sequence finds a unit, three steps (four where one wave holds all columns), and
+    # the decode part does not decide the time by itself; any load where tiles stay whole ("prefill_split" 1)
+    assert rows4([40, 1], [1000, 50]) == 16 and rows4([40, 1], [216, 50]) == 32 and rows4([8, 1], [370, 50]) == 8
+    assert dry((32, 8, 128), [8, 1], [370, 50], prefill_split=AUTO)["prefill_tiles"][0, 2] == 8
+    assert rows4([40] + [1] * 8, [1000] + [50] * 8) == 16 and rows4([40] + [1] * 30, [1000] + [50] * 30) == 32
+    assert rows4([40] + [1] * 4, [1000] + [8000] * 4) == 32
+    whole = lambda q, c: int(dry((32, 8, 128), q, c, prefill_split=AUTO + 1)["prefill_tiles"][:, 2].max())
+    assert rows4([300, 1], [16000, 50]) == 32 and whole([300, 1], [16000, 50]) == 16 and whole([300], [16000]) == 16
+    # what the cooperative decode workgroups do not take
+    assert dry((32, 8, 128), [40, 1], [1000, 50], prefill_split=AUTO, decode_tail_pct=20)["prefill_tiles"][:, 2].max() == 32
+
+
+@pytest.mark.parametrize("heads", HEADS, ids=str)
+def test_decode_parts_beside_key_groups_cover_every_block_on_the_units_that_are_left(heads):
+    rng = np.random.default_rng(5)
+    for n, top in ((1, 40), (3, 769), (9, 5000), (20, 300)):
+        if (n + 3) * heads[1] > 256:
+            continue
+        lens = rng.integers(1, top, size=n)
+        q, c = [3] + [1] * n, [3000] + [int(x) for x in lens]
+        for split in (FORCED, FORCED + 1):
+            r = dry(heads, q, c, prefill_split=split)
+            p = r["decode_pieces"]
+            for i in range(n):
+                mine = sorted((int(x[1]), int(x[2])) for x in p if x[0] == i + 1)
+                assert mine[0][0] == 0 and mine[-1][1] == (c[i + 1] + 1 + 15) // 16 and all(a[1] == b[0] for a, b in zip(mine, mine[1:]))
+            wgs = r["decode_runs"] * heads[1] + int(r["prefill_tiles"][:, 4].sum()) * heads[1]
+            assert wgs <= 256 and r["slots"] in (0, r["decode_runs"] + n + 1)
 
 
 def batch(heads, q_lens, ctx_lens, seed):
@@ -95,3 +121,28 @@ def test_more_parts_than_sixteen_and_a_small_workspace(heads, rows, ctx):
     assert all(np.array_equal(o, outs[0]) for o in outs[1:])
     for ws in (0, 1 << 20):
         assert_parity(run_gpu(b, workspace_bytes=ws or 256), want, f"workspace {ws}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", HEADS, ids=str)
+def test_step_of_key_groups_and_eight_wave_decode_workgroups(heads):
+    from gpu_util import assert_parity, run_gpu, say
+    g = heads[0] // heads[1]
+    # decode sequences whole, cut, of one block and of none of the waves' second step; an empty sequence; two chunks
+    for q, c in (([1, 5, 1, 0, 1], [15, 700, 255, 9, 256]), ([1, 64 // g + 1, 1, 2, 1], [5000, 1000, 767, 3000, 770])):
+        if (len(q) + 3) * heads[1] > 256:
+            continue
+        b = batch(heads, q, c, seed=63)
+        want = ref_c.attn_mixed(b.q, b.k_cache, b.v_cache, b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)
+        with B.Context(*heads, 16, b.num_blocks, b.max_blocks_per_seq) as ctx:
+            ctx.set_option("prefill_groups", 4)
+            ctx.plan(b.seq_lens, b.query_start_loc, b.ctx_lens)
+            assert ctx.plan_kernels() == [f"step_kernel_groups<{heads[2]}, {256 // heads[2]}>"]
+        outs = []
+        for opts in ({}, {"overlap": 0}, {"overlap": 2}, {"mixed_step": 0}, {"trace": 1}, {"prefill_split": 1}, {"prefill_split": 4}):
+            say(f"case: {heads} q={q} ctx={c} {opts}")
+            outs.append(run_gpu(b, options=dict(opts, prefill_groups=4)))
+            assert_parity(outs[-1], want, str(opts))
+        assert all(np.array_equal(o, outs[0]) for o in outs[1:5])       # one launch gives the bits of two
+        for ws in (1 << 20, 4096):                                       # too small for the plan: the four-wave workgroups
+            assert_parity(run_gpu(b, options={"prefill_groups": 4}, workspace_bytes=ws), want, f"workspace {ws}")
