@@ -241,6 +241,70 @@ OOCO_DEV int count_le(CumAt cum_at, int n, int x, int lane)
 }
 
 // ------------------------------------------------------------------------------------------
+// Equal runs of the decode line (RunLayout without XCD weights and tail, which only decode_kernel_general works on): the same
+// numbers as run_bounds and run_of by the reciprocal in double precision and an exact remainder.  The compiler's 64-bit
+// divisions -- a branch to a short and a long form each, and with the weighted form inlined eight of them per call -- made the
+// first 1100 instructions of a decode wave, and instruction fetch is what a small launch starts with.
+struct EqualRuns {
+    int32_t blocks, runs;
+    static OOCO_DEV double reciprocal(int n)   // 1 / n to the last place or two
+    {
+        const double d = (double)n, r0 = __builtin_amdgcn_rcp(d);
+        const double r1 = __builtin_fma(__builtin_fma(-d, r0, 1.0), r0, r0);
+        return __builtin_fma(__builtin_fma(-d, r1, 1.0), r1, r1);
+    }
+    // floor((a * b - c) / n), c = 0 or 1, the quotient below 2^30; wave-uniform
+    static OOCO_DEV int quotient(int a, int b, int c, int n, double inv)
+    {
+        int q = (int)(((double)a * (double)b - (double)c) * inv);   // off by one at most
+        const int64_t r = (int64_t)a * b - c - (int64_t)q * n;
+        q += r < 0 ? -1 : r >= n ? 1 : 0;
+        return __builtin_amdgcn_readfirstlane(q);
+    }
+    OOCO_DEV void bounds(int run, int &lo, int &hi) const
+    {
+        const double inv = reciprocal(runs);
+        lo = quotient(blocks, run, 0, runs, inv);
+        hi = quotient(blocks, run + 1, 0, runs, inv);
+    }
+    // runs that hold units x and y
+    OOCO_DEV void holding(int x, int y, int &rx, int &ry) const
+    {
+        const double inv = reciprocal(blocks);
+        rx = quotient(x + 1, runs, 1, blocks, inv);
+        ry = quotient(y + 1, runs, 1, blocks, inv);
+    }
+};
+struct GeneralRuns {
+    RunLayout L;
+    OOCO_DEV void bounds(int run, int &lo, int &hi) const { run_bounds(L, run, lo, hi); }
+    OOCO_DEV void holding(int x, int y, int &rx, int &ry) const
+    {
+        rx = run_of(L, x);
+        ry = run_of(L, y);
+    }
+};
+
+// The sequence i with cum[i] <= x < cum[i + 1], and those two values.  head: lane l holds cum[l + 1] (anything for l >= n),
+// loaded with the kernel's first loads; what it does not reach is read here.
+template <class CumAt>
+OOCO_DEV int locate(CumAt cum_at, int head, int n, int x, int lane, int &cs, int &ce)
+{
+    int before = 0;   // cum[base - 1]
+    for (int base = 1;; base += 64) {
+        const int idx = base + lane;
+        const int v = idx > n ? 0x7FFFFFFF : base == 1 ? head : cum_at(idx);
+        const int c = __popcll(__ballot(v <= x));
+        if (c < 64) {
+            cs = c ? __builtin_amdgcn_readlane(v, c - 1) : before;
+            ce = __builtin_amdgcn_readlane(v, c);
+            return base - 1 + c;
+        }
+        before = __builtin_amdgcn_readlane(v, 63);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Decode: one wave per (run k of the decode block line, kv head).  A wave walks the pieces of its
 // run one after the other; a piece is a range of KV blocks of one sequence.  Per 16-token block:
 //   S^T[16 tok][16 heads] = K[16 tok][hd] · Q^T[hd][16 heads]      (hd/32 x v_mfma_f32_16x16x32_bf16)
@@ -264,8 +328,9 @@ OOCO_DEV int count_le(CumAt cum_at, int n, int x, int lane)
 // waves that take steps of NBI blocks in turn: un-normalised output O, running maximum m (the same in the four rows of a
 // lane column) and this lane's share lsum of the sum, as laid out above.  A wave without a step has (0, -inf, 0), one whose
 // scores are all -inf (0, -FLT_MAX, 0); neither weighs anything beside one with a score.
+// q_row: the sequence's query row, read here (after the block ids have been asked for: one memory round trip for both).
 template <int HD, int NBI, int NW>
-OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin, int nblk, int seq_len, int q_row, int wave,
+OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin, int nblk, int &q_row, int wave,
                             int lane, uint64_t *trace, bool &first_piece, f32x4 (&O)[HD / 16], float &m, float &lsum)
 {
     constexpr int KC = HD / 32;
@@ -276,6 +341,18 @@ OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin
     const int64_t tile_elems = (int64_t)HD * kBlockSize;   // one (block, kv head) tile
     const int head = kvh * g + col;
     const int nstep = ((nblk + NBI - 1) / NBI - wave + NW - 1) / NW;   // of this wave
+    // block (of the piece) that is this wave's i-th
+    auto blk_of = [&](int i) -> int { return NW == 1 ? i : (i / NBI * NW + wave) * NBI + i % NBI; };
+
+    // rolling window of the physical ids of this wave's next 64 blocks, one per lane
+    const int32_t *table = p.block_tables + (int64_t)seq * p.max_blocks_per_seq + blk_begin;
+    int wbase = 0;
+    int idv = table[min(blk_of(lane), nblk - 1)];
+    int idn = table[min(blk_of(64 + lane), nblk - 1)];
+    const int q_raw = p.query_start_loc[seq], seq_len = p.seq_lens[seq];
+    // (sent off together, before anything waits for one of them)
+    __builtin_amdgcn_sched_barrier(kNoVmem);
+    q_row = min(max(q_raw, 0), p.total_q - 1);
     if (NW > 1 && nstep <= 0) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) O[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -283,9 +360,6 @@ OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin
         lsum = 0.f;
         return;
     }
-    // block (of the piece) that is this wave's i-th
-    auto blk_of = [&](int i) -> int { return NW == 1 ? i : (i / NBI * NW + wave) * NBI + i % NBI; };
-
     // Q as B operand: head col, dims 32c + 8kq .. +8
     u32x4 qb[KC];
     {
@@ -296,12 +370,6 @@ OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin
             qb[c] = (col < g) ? t : u32x4{0u, 0u, 0u, 0u};
         }
     }
-    // rolling window of the physical ids of this wave's next 64 blocks, one per lane
-    const int32_t *table = p.block_tables + (int64_t)seq * p.max_blocks_per_seq + blk_begin;
-    int wbase = 0;
-    int idv = table[min(blk_of(lane), nblk - 1)];
-    int idn = table[min(blk_of(64 + lane), nblk - 1)];
-
     u32x4 kreg[NBI][KC];
     u32x2 vreg[NBI][NB];
     int64_t offs[NBI];
@@ -423,8 +491,8 @@ OOCO_DEV void decode_stream(const AttnParams &p, int kvh, int seq, int blk_begin
 
 // One run of the decode line for one kv head, all its pieces, executed by one wave (see above).
 // `at_stream_end()` is called once the last piece of the run has been streamed, before its epilogue.
-template <int HD, int NBI, int MBATCH, class CumAt, class AtStreamEnd>
-OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, int run, int kvh, int lane, uint64_t *trace,
+template <int HD, int NBI, int MBATCH, class CumAt, class Runs, class AtStreamEnd>
+OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, int cum_head, const Runs &L, int run, int kvh, int lane, uint64_t *trace,
                          bool &first_piece, AtStreamEnd at_stream_end)
 {
     constexpr int NB = HD / 16;
@@ -433,17 +501,16 @@ OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, 
     const int g = p.g;
     const int head = kvh * g + col;
     int lo, hi;
-    run_bounds(L, run, lo, hi);
-    int seq = count_le(cum_at, p.num_seqs, lo, lane);
-    int pos = lo;
+    L.bounds(run, lo, hi);
+    int cs, ce, pos = lo;
+    int seq = locate(cum_at, cum_head, p.num_seqs, lo, lane, cs, ce);
     while (pos < hi) {
-        seq = __builtin_amdgcn_readfirstlane(seq);
-        int cs = cum_at(seq), ce = cum_at(seq + 1);
-        while (ce <= pos) {   // sequences without decode blocks
+        while (ce <= pos) {   // the next sequence with decode blocks
             ++seq;
             cs = ce;
             ce = cum_at(seq + 1);
         }
+        seq = __builtin_amdgcn_readfirstlane(seq);
         const int stop = min(hi, ce);
         // the sequence's blocks start piece_pad units into its stretch of the line
         const int first = cs + p.piece_pad;
@@ -456,12 +523,11 @@ OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, 
         const int blk_begin = begin - first;
         const int nblk = stop - begin;
         const bool whole = (begin == first) && (stop == ce);
-        const int seq_len = p.seq_lens[seq];
-        const int q_row = min(max(p.query_start_loc[seq], 0), p.total_q - 1);
 
         f32x4 O[NB];
         float m, lsum;
-        decode_stream<HD, NBI, 1>(p, kvh, seq, blk_begin, nblk, seq_len, q_row, 0, lane, trace, first_piece, O, m, lsum);
+        int q_row;
+        decode_stream<HD, NBI, 1>(p, kvh, seq, blk_begin, nblk, q_row, 0, lane, trace, first_piece, O, m, lsum);
 
         if (trace && stop == hi && lane == 0) trace[2] = wall_clock64();   // end of streaming
         if (stop == hi) at_stream_end();
@@ -478,8 +544,9 @@ OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, 
                 for (int nb = 0; nb < NB; ++nb) store_dev4(ap + nb * 16, O[nb]);
                 if (kq == 0) store_dev2(p.part_ml + row * 2, m, ltot);
             }
-            const int first_run = run_of(L, first);
-            const int nparts = run_of(L, (int64_t)ce - 1) - first_run + 1;
+            int first_run, last_run;
+            L.holding(first, ce - 1, first_run, last_run);
+            const int nparts = last_run - first_run + 1;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the partial has reached memory before the count
             int prev = 0;
             if (lane == 0)
@@ -566,67 +633,82 @@ OOCO_DEV void decode_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, 
                 *reinterpret_cast<u32x2 *>(op + nb * 16) = w;
             }
         }
-        pos = stop;
-        ++seq;
+        pos = stop;   // (the next piece's sequence is found at the top: ce <= pos unless the run ends here)
     }
 }
 
-template <int HD, int NBI, int MBATCH>
+// Entries of the decode array: lane l has entry l + 1 (for locate), and entry idx for the whole wave.  DEV: from device
+// memory, where the plan did not fit the kernel arguments.
+template <bool DEV>
+OOCO_DEV int cum_head(const KernArgs &a, int lane)
+{
+    return DEV ? a.p.cum_dev[min(1 + lane, a.p.num_seqs)] : a.cum[1 + lane];
+}
+template <bool DEV>
+OOCO_DEV int cum_entry(const KernArgs &a, int idx)
+{
+    return DEV ? a.p.cum_dev[idx] : a.cum[idx];
+}
+
+// GENERAL: XCD weights, a dynamic tail, or a plan in device memory (which equal runs without a tail may be, too).
+template <int HD, int NBI, int MBATCH, bool GENERAL>
 OOCO_DEV void decode_kernel_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
     // What a wave needs before its first KV tile is on its way comes from a dozen places of the kernel
     // arguments; asked for one after the other, each at its point of use, they cost a wave ten dependent
     // round trips to the scalar cache.  Naming them here makes the compiler fetch them together.
-    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens),
-                 "s"(p.query_start_loc), "s"(p.cum_dev), "s"(p.trace), "s"(p.queue), "s"(p.Hq), "s"(p.Hkv), "s"(p.g),
-                 "s"(p.max_blocks_per_seq), "s"(p.num_seqs), "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks),
-                 "s"(p.static_runs), "s"(p.tail_runs), "s"(p.piece_pad), "s"(p.rotate_heads), "s"(p.scale_log2e),
-                 "s"(p.queue_base), "s"(*reinterpret_cast<const uint64_t *>(&p.xcd_cw[0])),
-                 "s"(*reinterpret_cast<const uint64_t *>(&p.xcd_cw[4])));
     const int lane = threadIdx.x;
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens),
+                 "s"(p.query_start_loc), "s"(p.cum_dev), "s"(p.trace), "s"(p.Hq), "s"(p.Hkv), "s"(p.g),
+                 "s"(p.max_blocks_per_seq), "s"(p.num_seqs), "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks),
+                 "s"(p.static_runs), "s"(p.piece_pad), "s"(p.rotate_heads), "s"(p.scale_log2e));
     // Workgroups are handed to the XCDs round-robin and the kv heads of a block lie in adjacent
     // 4 KiB pieces of memory: rotating the head by the run index gives every XCD every kv head
     // in turn instead of pinning XCD x to head x.
     int run = blockIdx.x / p.Hkv;
     int kvh = p.rotate_heads ? (int)((blockIdx.x - run * p.Hkv + run) % p.Hkv) : (int)(blockIdx.x - run * p.Hkv);
-    if (p.xcd_cw[kXcds - 1]) {
-        // weighted runs: all kv heads of run v on XCD v % 8 (workgroup b runs on XCD b % 8)
-        const int x = blockIdx.x % kXcds, t = blockIdx.x / kXcds;
-        kvh = t % p.Hkv;
-        run = kXcds * (t / p.Hkv) + x;
-    }
-    auto cum_at = [&](int idx) -> int { return p.cum_dev ? p.cum_dev[idx] : a.cum[idx]; };
-    const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, p.tail_runs, p.xcd_cw};
-    const unsigned tail_tasks = (unsigned)p.tail_runs * (unsigned)p.Hkv;
-
+    const bool dev = GENERAL && p.cum_dev;
+    const int head = dev ? cum_head<true>(a, lane) : cum_head<false>(a, lane);
+    auto cum_at = [&](int idx) -> int { return dev ? cum_entry<true>(a, idx) : cum_entry<false>(a, idx); };
     uint64_t *trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;   // per-wave time stamps
     if (trace && lane == 0) trace[0] = wall_clock64();
     bool first_piece = true;
-
-  for (;;) {   // the wave's own run first, then tail runs by ticket
-    // The ticket for the next tail run is drawn when the last piece of this run has been streamed (whoever
-    // is done first gets the next run) and looked at after that piece's epilogue, which covers the round
-    // trip of the atomic.  (Every wave ends by drawing a ticket that tells it to stop; atomics on one address
-    // are served one after the other, about 13 ns each on MI355X, which is why the tail only pays on long
-    // kernels.)
-    unsigned ticket = 0xFFFFFFFFu;
-    bool drawn = false;
-    auto draw = [&]() {
-        if (lane == 0)
-            ticket = __hip_atomic_fetch_add(p.queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - p.queue_base;
-        drawn = true;
-    };
-    decode_run<HD, NBI, MBATCH>(p, cum_at, L, run, kvh, lane, trace, first_piece, [&]() {
-        if (tail_tasks) draw();
-    });
-    if (!tail_tasks) break;
-    if (!drawn) draw();   // (a run that held no block)
-    ticket = __builtin_amdgcn_readfirstlane(ticket);
-    if (ticket >= tail_tasks) break;
-    run = p.static_runs + (int)(ticket / (unsigned)p.Hkv);
-    kvh = (int)(ticket % (unsigned)p.Hkv);
-  }
+    if constexpr (!GENERAL) {
+        decode_run<HD, NBI, MBATCH>(p, cum_at, head, EqualRuns{p.static_blocks, p.static_runs}, run, kvh, lane, trace, first_piece, []() {});
+    } else {
+        if (p.xcd_cw[kXcds - 1]) {
+            // weighted runs: all kv heads of run v on XCD v % 8 (workgroup b runs on XCD b % 8)
+            const int x = blockIdx.x % kXcds, t = blockIdx.x / kXcds;
+            kvh = t % p.Hkv;
+            run = kXcds * (t / p.Hkv) + x;
+        }
+        const GeneralRuns L = {{p.dec_blocks, p.static_blocks, p.static_runs, p.tail_runs, p.xcd_cw}};
+        const unsigned tail_tasks = (unsigned)p.tail_runs * (unsigned)p.Hkv;
+        for (;;) {   // the wave's own run first, then tail runs by ticket
+            // The ticket for the next tail run is drawn when the last piece of this run has been streamed (whoever
+            // is done first gets the next run) and looked at after that piece's epilogue, which covers the round
+            // trip of the atomic.  (Every wave ends by drawing a ticket that tells it to stop; atomics on one address
+            // are served one after the other, about 13 ns each on MI355X, which is why the tail only pays on long
+            // kernels.)
+            unsigned ticket = 0xFFFFFFFFu;
+            bool drawn = false;
+            auto draw = [&]() {
+                if (lane == 0)
+                    ticket = __hip_atomic_fetch_add(p.queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - p.queue_base;
+                drawn = true;
+            };
+            decode_run<HD, NBI, MBATCH>(p, cum_at, head, L, run, kvh, lane, trace, first_piece, [&]() {
+                if (tail_tasks) draw();
+            });
+            if (!tail_tasks) break;
+            if (!drawn) draw();   // (a run that held no block)
+            ticket = __builtin_amdgcn_readfirstlane(ticket);
+            if (ticket >= tail_tasks) break;
+            run = p.static_runs + (int)(ticket / (unsigned)p.Hkv);
+            kvh = (int)(ticket % (unsigned)p.Hkv);
+        }
+    }
     if (trace) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (lane == 0) trace[3] = wall_clock64();
@@ -636,16 +718,21 @@ OOCO_DEV void decode_kernel_body(const KernArgs &a)
 template <int HD, int NBI>
 __global__ __launch_bounds__(64, 2) void decode_kernel(const KernArgs a)
 {
-    decode_kernel_body<HD, NBI, 3>(a);
+    decode_kernel_body<HD, NBI, 3, false>(a);
+}
+template <int HD, int NBI>
+__global__ __launch_bounds__(64, 2) void decode_kernel_general(const KernArgs a)
+{
+    decode_kernel_body<HD, NBI, 3, true>(a);
 }
 
 // The same kernel within 160 registers per wave (one KV block per step, one part per merge round trip), for
 // batches whose prefill workgroups need the rest of the register file: a SIMD then holds one decode wave beside
 // two prefill waves of 176 registers.
-template <int HD>
+template <int HD, bool GENERAL>
 __global__ __launch_bounds__(64, 3) void decode_kernel_lean(const KernArgs a)
 {
-    decode_kernel_body<HD, 1, 1>(a);
+    decode_kernel_body<HD, 1, 1, GENERAL>(a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -665,8 +752,7 @@ constexpr int kCoopFloats = NWV * 16 * kCoopStride<HD> + NWV * 16 * 2 + 4;   // 
 
 // (NWV = waves of the workgroup: 4, or 8 beside prefill workgroups of key groups)
 template <int HD, int NBI, int NWV, class CumAt>
-OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout &L, int run, int kvh, float *lds,
-                              uint64_t *trace)
+OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, int cum_head, int run, int kvh, float *lds, uint64_t *trace)
 {
     constexpr int NB = HD / 16;
     constexpr int STRIDE = kCoopStride<HD>;
@@ -681,25 +767,25 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
     const int g = p.g, units = g * (HD / 4);
     bool first_piece = wave == 0;
     if (wave != 0) trace = nullptr;
-    int lo, hi, seq;
+    const EqualRuns L = {p.static_blocks, p.static_runs};
+    int lo, hi, seq, cs, ce;
     if (p.coop == kCoopBySequence) {   // run i is sequence i, whole
         seq = run;
-        lo = cum_at(run);
-        hi = cum_at(run + 1);
+        cs = lo = cum_at(run);
+        ce = hi = cum_at(run + 1);
         if (trace && lo >= hi && lane == 0) trace[1] = trace[2] = wall_clock64();
     } else {
-        run_bounds(L, run, lo, hi);
-        seq = count_le(cum_at, p.num_seqs, lo, lane);
+        L.bounds(run, lo, hi);
+        seq = locate(cum_at, cum_head, p.num_seqs, lo, lane, cs, ce);
     }
     int pos = lo;
     while (pos < hi) {   // (everything here is the same in all waves)
-        seq = __builtin_amdgcn_readfirstlane(seq);
-        int cs = cum_at(seq), ce = cum_at(seq + 1);
-        while (ce <= pos) {   // sequences without decode blocks
+        while (ce <= pos) {   // the next sequence with decode blocks
             ++seq;
             cs = ce;
             ce = cum_at(seq + 1);
         }
+        seq = __builtin_amdgcn_readfirstlane(seq);
         const int stop = min(hi, ce);
         const int first = cs + p.piece_pad;
         const int begin = max(pos, first);
@@ -709,12 +795,10 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
             continue;
         }
         const bool whole = (begin == first) && (stop == ce);
-        const int seq_len = p.seq_lens[seq];
-        const int q_row = min(max(p.query_start_loc[seq], 0), p.total_q - 1);
         f32x4 O[NB];
         float m, lsum;
-        decode_stream<HD, NBI, NWV>(p, kvh, seq, begin - first, stop - begin, seq_len, q_row, wave, lane, trace, first_piece, O, m,
-                                  lsum);
+        int q_row;
+        decode_stream<HD, NBI, NWV>(p, kvh, seq, begin - first, stop - begin, q_row, wave, lane, trace, first_piece, O, m, lsum);
         if (trace && stop == hi && lane == 0) trace[2] = wall_clock64();
         const float lw = rows_sum(lsum);
         if (pos != lo) __syncthreads();   // the last piece's results have been read
@@ -761,8 +845,9 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
             }
         }
         if (!whole) {
-            const int first_run = run_of(L, first);
-            const int nparts = run_of(L, (int64_t)ce - 1) - first_run + 1;
+            int first_run, last_run;
+            L.holding(first, ce - 1, first_run, last_run);
+            const int nparts = last_run - first_run + 1;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial has reached memory ...
             __syncthreads();                                    // ... and so have the other waves'
             int32_t *const counter = p.counters + (int64_t)seq * p.Hkv + kvh;
@@ -809,11 +894,10 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, const RunLayout
             }
         }
         pos = stop;
-        ++seq;
     }
 }
 
-template <int HD, int NBI, int NWV>
+template <int HD, int NBI, int NWV, bool DEV>
 __global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs a)
 {
     const AttnParams &p = a.p;
@@ -826,8 +910,8 @@ __global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs
     const int kvh = p.rotate_heads ? (slot + run) % p.Hkv : slot;
     uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
     if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
-    const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
-    decode_coop_run<HD, NBI, NWV>(p, [&](int idx) -> int { return p.cum_dev ? p.cum_dev[idx] : a.cum[idx]; }, L, run, kvh, lds, trace);
+    decode_coop_run<HD, NBI, NWV>(p, [&](int idx) -> int { return cum_entry<DEV>(a, idx); }, cum_head<DEV>(a, threadIdx.x & 63), run, kvh,
+                                  lds, trace);
     if (trace) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0) trace[3] = wall_clock64();
@@ -1505,8 +1589,8 @@ OOCO_DEV void step_body(const KernArgs &a)
         const int run = (int)blockIdx.x / p.Hkv, slot = (int)blockIdx.x - run * p.Hkv;
         uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
         if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
-        const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
-        decode_coop_run<HD, NBI, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, L, run, p.rotate_heads ? (slot + run) % p.Hkv : slot,
+        decode_coop_run<HD, NBI, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + (threadIdx.x & 63)], run,
+                                     p.rotate_heads ? (slot + run) % p.Hkv : slot,
                                      reinterpret_cast<float *>(stage_lds<HD, KG>()), trace);
         if (trace) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1529,8 +1613,8 @@ OOCO_DEV void step_body(const KernArgs &a)
         uint64_t *const trace = p.trace ? p.trace + (int64_t)item * 4 : nullptr;
         if (trace && lane == 0) trace[0] = wall_clock64();
         bool first_piece = true;
-        const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
-        decode_run<HD, NBI, MBATCH>(p, [&](int idx) -> int { return a.cum[idx]; }, L, run, kvh, lane, trace, first_piece, []() {});
+        decode_run<HD, NBI, MBATCH>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + lane], EqualRuns{p.static_blocks, p.static_runs},
+                                    run, kvh, lane, trace, first_piece, []() {});
         if (trace) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane == 0) trace[3] = wall_clock64();
@@ -1599,7 +1683,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void mixed_kernel(const KernArgs a)
     int32_t *const claims = state, *const xcd_arrivals = state + kMixedClaims, *const pf_drawn = state + kMixedClaims + 8;
     int32_t *const dec_drawn = state + kMixedClaims + 16, *const left = state + kMixedClaims + 17;
     const int n_cum = p.num_seqs + 1;   // the prefill array follows the decode array
-    auto dcum_at = [&](int idx) -> int { return p.cum_dev ? p.cum_dev[idx] : a.cum[idx]; };
+    auto dcum_at = [&](int idx) -> int { return p.cum_dev ? cum_entry<true>(a, idx) : cum_entry<false>(a, idx); };
+    const int dcum_head = p.cum_dev ? cum_head<true>(a, lane) : cum_head<false>(a, lane);
     auto pf_at = [&](int idx) -> int { return plan_entry(a, n_cum + idx); };
     const unsigned xcc = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u;              // XCC_ID
     if (tid == 0) {
@@ -1636,7 +1721,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void mixed_kernel(const KernArgs a)
     }
     const int n_dec_items = p.static_runs * p.Hkv;
     const int n_vb = p.pf_table ? p.pf_table * p.Hkv : p.n_tiles * p.Hkv * p.pf_split;
-    const RunLayout L = {p.dec_blocks, p.static_blocks, p.static_runs, 0, p.xcd_cw};
+    const EqualRuns L = {p.static_blocks, p.static_runs};
     for (int pass = 0; pass < 2; ++pass, role ^= 1) {
         if (role == 0) {
             bool first_piece = false;
@@ -1647,7 +1732,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void mixed_kernel(const KernArgs a)
                 if (item >= n_dec_items) break;
                 const int run = item / p.Hkv;
                 const int kvh = (item - run * p.Hkv + run) % p.Hkv;   // kv heads rotate over the runs
-                decode_run<HD, (HD == 64 ? 2 : 1), 3>(p, dcum_at, L, run, kvh, lane, nullptr, first_piece, []() {});
+                decode_run<HD, (HD == 64 ? 2 : 1), 3>(p, dcum_at, dcum_head, L, run, kvh, lane, nullptr, first_piece, []() {});
                 if (pass == 0) ++n_first; else ++n_second;
             }
         } else {
@@ -1937,24 +2022,53 @@ hipError_t launch_decode(const KernArgs &a, hipStream_t s)
     if (a.p.static_runs <= 0 || a.p.dec_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)((int64_t)a.p.static_runs * a.p.Hkv)), block(64);
     if (a.p.coop) {
-        if (a.p.coop_waves == 8 && a.p.hd == 128)
-            hipLaunchKernelGGL((decode_coop_kernel<128, 2, 8>), grid, dim3(512), 0, s, a);
-        else if (a.p.coop_waves == 8)
-            hipLaunchKernelGGL((decode_coop_kernel<64, 4, 8>), grid, dim3(512), 0, s, a);
-        else if (a.p.hd == 128)
-            hipLaunchKernelGGL((decode_coop_kernel<128, 2, 4>), grid, dim3(256), 0, s, a);
+        auto launch = [&](auto dev) {
+            constexpr bool DEV = decltype(dev)::value;
+            if (a.p.coop_waves == 8 && a.p.hd == 128)
+                hipLaunchKernelGGL((decode_coop_kernel<128, 2, 8, DEV>), grid, dim3(512), 0, s, a);
+            else if (a.p.coop_waves == 8)
+                hipLaunchKernelGGL((decode_coop_kernel<64, 4, 8, DEV>), grid, dim3(512), 0, s, a);
+            else if (a.p.hd == 128)
+                hipLaunchKernelGGL((decode_coop_kernel<128, 2, 4, DEV>), grid, dim3(256), 0, s, a);
+            else
+                hipLaunchKernelGGL((decode_coop_kernel<64, 4, 4, DEV>), grid, dim3(256), 0, s, a);
+        };
+        if (a.p.cum_dev)
+            launch(std::true_type());
         else
-            hipLaunchKernelGGL((decode_coop_kernel<64, 4, 4>), grid, dim3(256), 0, s, a);
+            launch(std::false_type());
         return hipGetLastError();
     }
+    const bool general = a.p.tail_runs > 0 || a.p.xcd_cw[kXcds - 1] != 0 || a.p.cum_dev;
     if (a.p.lean && a.p.hd == 128) {
-        hipLaunchKernelGGL((decode_kernel_lean<128>), grid, block, 0, s, a);
+        if (general)
+            hipLaunchKernelGGL((decode_kernel_lean<128, true>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((decode_kernel_lean<128, false>), grid, block, 0, s, a);
         return hipGetLastError();
     }
     // KV blocks per softmax step: a wave keeps one step's tiles in flight, and 8 KiB per wave is what it takes
     // to saturate HBM with three waves per compute unit: one block for head_dim 128, two for head_dim 64
     // (measured: 56.9 % -> 72.2 % of the HBM peak on 256 sequences with head_dim 64; four blocks: 69.8 %)
     const int nbi = a.p.nbi ? a.p.nbi : (a.p.hd == 64 ? 2 : 1);
+    if (general) {
+        if (a.p.hd == 128) {
+            if (nbi == 2)
+                hipLaunchKernelGGL((decode_kernel_general<128, 2>), grid, block, 0, s, a);
+            else if (nbi == 4)
+                hipLaunchKernelGGL((decode_kernel_general<128, 4>), grid, block, 0, s, a);
+            else
+                hipLaunchKernelGGL((decode_kernel_general<128, 1>), grid, block, 0, s, a);
+        } else {
+            if (nbi == 2)
+                hipLaunchKernelGGL((decode_kernel_general<64, 2>), grid, block, 0, s, a);
+            else if (nbi == 4)
+                hipLaunchKernelGGL((decode_kernel_general<64, 4>), grid, block, 0, s, a);
+            else
+                hipLaunchKernelGGL((decode_kernel_general<64, 1>), grid, block, 0, s, a);
+        }
+        return hipGetLastError();
+    }
     if (a.p.hd == 128) {
         if (nbi == 2)
             hipLaunchKernelGGL((decode_kernel<128, 2>), grid, block, 0, s, a);
