@@ -624,7 +624,7 @@ bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_
         if (dec_left > 1.35 * std::max(dec_all, pf) || pf < 0.7 * dec_all) return false;
         if (!whole && parts == 1 && longest > 16) return false;   // (no unit left to cut a long tile)
     }
-    return whole || load <= 10 * cus || (load <= 25 * cus && 4 * units <= cus && (n_dec > 0 || widest <= rows || cover <= 1.2 * used));
+    return whole || load <= 10 * cus || (load <= 25 * cus && 4 * units <= cus && (widest <= rows || cover <= 1.2 * used));
 }
 
 // Validates the length arrays and builds the plan.  Pure host code, no allocation.
@@ -848,6 +848,28 @@ bool step_fits(const HostPlan &pl, int hd, bool coop, int nbi)
            (pl.pf_groups > 1 ? coop && pl.coop_waves == 8
             : pl.lean        ? hd == 128 && pl.pf_waves == 8
                              : pl.pf_waves == 4 && (coop || nbi == 2 || (nbi == 1 && hd == 128)));
+}
+
+// The plan's arrays in the kernel arguments, for kernels that take the decode part, the prefill part or both: the decode
+// array, then the prefill array, or, where the plan has a tile list, only that, from the other end (AttnParams::list_row).
+// The caller has seen to it that the arrays fit.
+void fill_plan(const HostPlan &pl, bool dec, bool pf, KernArgs &ka)
+{
+    AttnParams &p = ka.p;
+    const int64_t n_cum = dec ? (int64_t)pl.num_seqs + 1 : 0;
+    p.list_row = 0;
+    p.rows2d = 0;
+    p.list_by_seq = pf && pl.pf_table > 0;
+    if (dec) memcpy(ka.cum, pl.dcum, (size_t)n_cum * sizeof(int32_t));
+    if (!pf) return;
+    if (!pl.pf_table) {
+        memcpy(ka.cum + n_cum, pl.pf, pl.pf_size * sizeof(int32_t));
+        return;
+    }
+    if (dec && p.coop && n_cum + pl.static_runs + pl.pf_table <= kInlineSeqs + 1) p.rows2d = 1, p.list_row = (int16_t)pl.static_runs;
+    const int32_t *const tab = pl.pf + 2 * pl.num_pf + 1, *const seqs = pl.pf + pl.num_pf + 1;
+    int32_t *const top = ka.cum + kInlineSeqs - p.list_row;
+    for (int32_t e = 0; e < pl.pf_table; ++e) top[-e] = list_entry(seqs[entry_chunk(tab[e])], entry_tile(tab[e]), entry_part(tab[e]), entry_parts(tab[e]));
 }
 
 // Pieces of the decode line as the kernel walks them (host mirror of the device logic).
@@ -1518,8 +1540,8 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
         p.pf_acc = static_cast<float *>(ctx->ws) + dec_floats;
         p.pf_ml = p.pf_acc + parts * (size_t)(32 * pl.pf_col_waves()) * ctx->hd;
         p.pf_counters = ctx->pf_counters;
-        p.pf_split = pl.pf_split;
-        p.pf_table = pl.pf_table;
+        p.pf_split = (int16_t)pl.pf_split;
+        p.pf_table = (int16_t)pl.pf_table;
         // (what the kernels will address, once more against what the context owns: a plan that does not fit is an error of
         // this library, reported instead of launched)
         const size_t pf_end = (dec_floats + parts * (size_t)(32 * pl.pf_col_waves()) * (ctx->hd + 2)) * sizeof(float);
@@ -1542,6 +1564,7 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     p.Hq = ctx->Hq;
     p.Hkv = ctx->Hkv;
     p.g = ctx->g;
+    p.g_magic = (uint16_t)(32768 / ctx->g + 1);
     p.hd = ctx->hd;
     p.max_blocks_per_seq = ctx->max_blocks_per_seq;
     p.scale_log2e = ctx->scale * 1.4426950408889634f;
@@ -1556,15 +1579,15 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     p.queue_base = ctx->queue_base;
     p.n_tiles = pl.n_tiles;
     p.num_pf = pl.num_pf;
-    p.dec_cus = (int16_t)pl.dec_cus;
+    p.dec_cus = (int8_t)pl.dec_cus;
     p.pf_waves = (int8_t)pl.pf_waves;
     p.pf_groups = (int8_t)pl.pf_groups;
-    p.nbi = ctx->opt_nbi ? (int32_t)ctx->opt_nbi : pl.nbi;
-    p.rotate_heads = (int16_t)(ctx->opt_rotate != 0);
+    p.nbi = (int8_t)std::min<int64_t>(ctx->opt_nbi ? ctx->opt_nbi : pl.nbi, 100);
+    p.rotate_heads = (int8_t)(ctx->opt_rotate != 0);
     p.coop = (int8_t)decode_coop(ctx);
     p.coop_waves = (int8_t)pl.coop_waves;
-    p.dec_near = (int16_t)pl.near;
-    p.lean = (int16_t)pl.lean;
+    p.dec_near = (int8_t)pl.near;
+    p.lean = (int8_t)pl.lean;
     for (int k = 0; k < kXcds; ++k) p.xcd_cw[k] = pl.cw[k];
 
     if (pl.tail_runs > 0) {
@@ -1611,7 +1634,8 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     auto run_prefill = [&]() {
         if (e == hipSuccess && pl.n_tiles > 0) {
             p.cum_dev = inline_cum ? nullptr : ctx->plan_d + n_cum;
-            if (inline_cum) memcpy(ka.cum, pl.pf, n_pf * sizeof(int32_t));
+            p.list_by_seq = 0;
+            if (inline_cum) fill_plan(pl, false, true, ka);
         }
         mark(2, ps);
         if (e == hipSuccess && pl.n_tiles > 0) e = launch_prefill(ka, ps);
@@ -1620,7 +1644,7 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     auto run_decode = [&]() {
         if (e == hipSuccess && pl.static_runs > 0) {
             p.cum_dev = inline_cum ? nullptr : ctx->plan_d;
-            if (inline_cum) memcpy(ka.cum, pl.dcum, n_cum * sizeof(int32_t));
+            if (inline_cum) fill_plan(pl, true, false, ka);
         }
         mark(0, s);
         if (e == hipSuccess && pl.static_runs > 0) {
@@ -1634,9 +1658,14 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     mark(4, s);
     if (fused || step) {
         p.cum_dev = inline_cum ? nullptr : ctx->plan_d;
-        if (inline_cum) {
-            memcpy(ka.cum, pl.dcum, n_cum * sizeof(int32_t));
-            memcpy(ka.cum + n_cum, pl.pf, n_pf * sizeof(int32_t));
+        if (step) {
+            fill_plan(pl, true, true, ka);
+        } else {
+            p.list_by_seq = 0;   // (the mixed kernel takes the arrays one behind the other, as in device memory)
+            if (inline_cum) {
+                memcpy(ka.cum, pl.dcum, n_cum * sizeof(int32_t));
+                memcpy(ka.cum + n_cum, pl.pf, n_pf * sizeof(int32_t));
+            }
         }
         mark(0, s);
         mark(2, s);
@@ -1758,6 +1787,7 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.Hq = num_q_heads;
     p.Hkv = num_kv_heads;
     p.g = num_q_heads / num_kv_heads;
+    p.g_magic = (uint16_t)(32768 / p.g + 1);
     p.hd = head_dim;
     p.max_blocks_per_seq = max_blocks_per_seq;
     p.scale_log2e = (softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)head_dim)) * 1.4426950408889634f;
@@ -1774,16 +1804,16 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.num_pf = pl.num_pf;
     p.pf_waves = (int8_t)pl.pf_waves;
     p.pf_groups = (int8_t)pl.pf_groups;
-    p.nbi = pl.nbi;
+    p.nbi = (int8_t)pl.nbi;
     p.coop = (int8_t)pl.coop;
     p.coop_waves = (int8_t)pl.coop_waves;
-    p.dec_near = (int16_t)pl.near;
+    p.dec_near = (int8_t)pl.near;
     p.rotate_heads = 1;
     p.pf_acc = nullptr;
     p.pf_ml = nullptr;
     p.pf_counters = nullptr;
     p.pf_split = 1;
-    p.pf_table = pl.pf_table;
+    p.pf_table = (int16_t)pl.pf_table;
 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // The array keeps whatever the last call on this GPU left: the arrival counters this call will count in
@@ -1792,16 +1822,15 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     if (e == hipSuccess && step_fits(pl, head_dim, pl.coop, pl.nbi ? pl.nbi : (head_dim == 64 ? 2 : 1))) {
         // both kinds of work side by side in one launch: a step of four decodes and one prompt 16.6 -> 11.4 us (7.5 with
         // whole sequences)
-        memcpy(ka.cum, pl.dcum, ((size_t)num_seqs + 1) * sizeof(int32_t));
-        memcpy(ka.cum + num_seqs + 1, pl.pf, pl.pf_size * sizeof(int32_t));
+        fill_plan(pl, true, true, ka);
         e = launch_step(ka, dev.num_cus, s);
     } else {
         if (e == hipSuccess && pl.n_tiles > 0) {
-            memcpy(ka.cum, pl.pf, pl.pf_size * sizeof(int32_t));
+            fill_plan(pl, false, true, ka);
             e = launch_prefill(ka, s);
         }
         if (e == hipSuccess && pl.static_runs > 0) {
-            memcpy(ka.cum, pl.dcum, ((size_t)num_seqs + 1) * sizeof(int32_t));
+            fill_plan(pl, true, false, ka);
             e = launch_decode(ka, s);
         }
     }

@@ -65,16 +65,16 @@ struct AttnParams {
     int32_t n_tiles;            // prefill: tiles per kv head
     int32_t num_pf;             // prefill: number of chunks (entries of the prefill array, see below)
     int32_t dec_wgs;            // step kernel: its first workgroups, which decode (set by launch_step)
-    int16_t dec_cus;            // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
+    int8_t dec_cus;             // mixed kernel: compute units per XCD that run decode waves (the others run prefill tiles)
     int8_t pf_waves;            // prefill: waves per workgroup, 4 or 8 (a tile has 32 query columns per wave of a key group)
-    int8_t pf_groups;           // prefill: key groups of a workgroup (1, or 2 or 4 in workgroups of eight waves)
-    int16_t dec_wpw;            // step kernel: decode waves of such a workgroup (set by launch_step)
-    int16_t dec_near;           // step kernel: they take items side by side (the kv heads of one run), else far apart
-    int32_t nbi;                // tuning: KV blocks per softmax step of the decode kernel
-    int16_t rotate_heads;       // tuning: kv head rotation across XCDs
+    int8_t pf_groups;           // prefill: key groups of a workgroup (1, or kKeyGroups in workgroups of eight waves)
+    int8_t dec_wpw;             // step kernel: decode waves of such a workgroup (set by launch_step)
+    int8_t dec_near;            // step kernel: they take items side by side (the kv heads of one run), else far apart
+    int8_t nbi;                 // tuning: KV blocks per softmax step of the decode kernel
+    int8_t rotate_heads;        // tuning: kv head rotation across XCDs
     int8_t coop;                // decode: workgroups of waves that share every piece of a run (decode_coop_kernel): 1, kCoopBySequence, or 0
     int8_t coop_waves;          // ... of so many waves: 4, or 8 beside prefill workgroups of key groups
-    int16_t lean;               // mixed batches: the register-lean kernels (decode 128, prefill 8 waves x 192 registers)
+    int8_t lean;                // mixed batches: the register-lean kernels (decode 127, prefill 8 waves x 166 registers)
     uint16_t xcd_cw[8];         // cumulative XCD weights of the static runs (RunLayout::cw); zeros = equal runs
     uint32_t queue_base;        // ticket value at which this launch's tail runs start
     uint32_t *queue;            // ticket counter for the tail runs (monotonic across launches)
@@ -83,13 +83,21 @@ struct AttnParams {
     float *pf_acc;
     float *pf_ml;
     int32_t *pf_counters;
-    int32_t pf_split;
+    int16_t pf_split;
     // > 0: the prefill array continues with that many entries, one per (tile, part of its keys) in dispatch order
     // (see list_entry): the parts of all tiles ordered by their number of 64-key steps, the longest first, the parts
     // of one tile next to each other in part order.  Workgroup b works on entry b / Hkv for kv head b % Hkv; part j
     // of the tile whose part 0 is entry e0 writes partial slot (e0 + j) * Hkv + kv head, and pf_counters[e0 * Hkv +
     // kv head] counts the arrivals.  Every tile has its own number of parts (pf_split is the largest).
-    int32_t pf_table;
+    int16_t pf_table;
+    // The tile list in the arguments: entry e is cum[kInlineSeqs - list_row - e] and names the sequence where list_entry has
+    // the chunk (list_by_seq), so that a workgroup of row y of a two-dimensional grid (x = kv head) finds its tile at
+    // cum[kInlineSeqs - y], whatever else the arguments say: the word comes with its first loads.  (A plan in device memory
+    // and the mixed kernel have the list behind the prefill array, with chunks.)
+    int16_t list_row;           // rows of the grid in front of the list's: the step kernel's cooperative decode runs
+    uint16_t g_magic;           // 32768 / g + 1: c / g = (c * g_magic) >> 15 for c < 512
+    int8_t rows2d;              // step kernel: the grid has rows
+    int8_t list_by_seq;
 };
 
 // Entry of the tile list: chunk of the prefill array (10 bits), tile of the chunk (10 bits), part (6 bits), parts of

@@ -662,7 +662,7 @@ OOCO_DEV void decode_kernel_body(const KernArgs &a)
     asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens),
                  "s"(p.query_start_loc), "s"(p.cum_dev), "s"(p.trace), "s"(p.Hq), "s"(p.Hkv), "s"(p.g),
                  "s"(p.max_blocks_per_seq), "s"(p.num_seqs), "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks),
-                 "s"(p.static_runs), "s"(p.piece_pad), "s"(p.rotate_heads), "s"(p.scale_log2e));
+                 "s"(p.static_runs), "s"(p.piece_pad), "s"((int)p.rotate_heads), "s"(p.scale_log2e));
     // Workgroups are handed to the XCDs round-robin and the kv heads of a block lie in adjacent
     // 4 KiB pieces of memory: rotating the head by the run index gives every XCD every kv head
     // in turn instead of pinning XCD x to head x.
@@ -905,7 +905,7 @@ __global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs
     asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens), "s"(p.query_start_loc),
                  "s"(p.cum_dev), "s"(p.trace), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),
                  "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks), "s"(p.static_runs), "s"(p.piece_pad),
-                 "s"(p.rotate_heads), "s"(p.scale_log2e));
+                 "s"((int)p.rotate_heads), "s"(p.scale_log2e));
     const int run = blockIdx.x / p.Hkv, slot = blockIdx.x - run * p.Hkv;
     const int kvh = p.rotate_heads ? (slot + run) % p.Hkv : slot;
     uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
@@ -989,9 +989,10 @@ OOCO_DEV u32x4 *stage_lds()
 // vector work then comes from the two waves of a SIMD rather than from within one wave.
 // `phases` (option "trace", prefill-only batches): receives four 16-bit times in units of 10 ns since `t_start`
 // (saturating), lowest first: tile looked up, first K/V loads sent off, first tiles arrived, last step done.
+// `list_word`: with the tile list, the word of the workgroup's entry vb / Hkv.
 template <int HD, int NW, bool PIPE, int KG, class CumAt>
-OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint64_t *phases = nullptr,
-                           const uint64_t t_start = 0)
+OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, const int entry, const int list_kvh, const int list_word,
+                           uint64_t *phases = nullptr, const uint64_t t_start = 0)
 {
     constexpr int NC = NW / KG;        // waves per key group, 32 query columns each
     constexpr int COLS = NC * 32;      // query columns per workgroup
@@ -1023,58 +1024,63 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     // workgroup -> (tile, kv head, part of the tile's keys, parts the tile has), and the partial-result slot of
     // part 0 of that (tile, kv head) with the distance between the slots of consecutive parts.  With the tile list
     // every tile has its own number of parts; without it vb = ((tile * Hkv) + kv head) * pf_split + part.
-    int split, part, tile_idx, kvh, list_raw = 0;
+    int split, part, kvh, seq, t;
     int slot0, slot_step;   // (at most kPrefillSplitUnits * kMaxPrefillSplit slots)
-    if (p.pf_table) {
-        const int entry = min(vb / p.Hkv, p.pf_table - 1);
-        kvh = vb - (vb / p.Hkv) * p.Hkv;
-        list_raw = cum_at(2 * p.num_pf + 1 + entry);
-        const int list_e = __builtin_amdgcn_readfirstlane(list_raw);   // (the same in every lane)
+    if (p.pf_table) {   // the plan lists the (tile, part) pairs one by one
+        const int list_e = __builtin_amdgcn_readfirstlane(list_word);   // (the same in every lane)
+        kvh = __builtin_amdgcn_readfirstlane(list_kvh);
         part = entry_part(list_e);
         split = entry_parts(list_e);
-        tile_idx = 0;   // (looked up from the entry below)
         slot0 = (entry - part) * p.Hkv + kvh;
         slot_step = p.Hkv;
+        t = entry_tile(list_e);
+        seq = p.list_by_seq ? entry_chunk(list_e) : cum_at(p.num_pf + 1 + min(entry_chunk(list_e), p.num_pf - 1));
     } else {
         split = p.pf_split;
         const int unit = vb / split;
-        part = vb - unit * split;
-        tile_idx = unit / p.Hkv;
-        kvh = unit - tile_idx * p.Hkv;
+        part = __builtin_amdgcn_readfirstlane(vb - unit * split);
+        const int tile_idx = unit / p.Hkv;
+        kvh = __builtin_amdgcn_readfirstlane(unit - tile_idx * p.Hkv);
         slot0 = unit * split;
         slot_step = 1;
+        // tile -> (sequence, tile of the sequence); tiles of a sequence are taken last-first because
+        // the later rows of a chunk see more keys and the hardware dispatches in index order
+        const int chunk = __builtin_amdgcn_readfirstlane(count_le(cum_at, p.num_pf, tile_idx, lane));
+        t = __builtin_amdgcn_readfirstlane((cum_at(chunk + 1) - 1) - tile_idx);   // reversed order inside the sequence
+        seq = cum_at(p.num_pf + 1 + chunk);
     }
-
-    // tile -> (sequence, tile of the sequence); tiles of a sequence are taken last-first because
-    // the later rows of a chunk see more keys and the hardware dispatches in index order
-    int seq, q_row0, rows, pos0, seq_len;
+    seq = __builtin_amdgcn_readfirstlane(min(max(seq, 0), p.num_seqs - 1));
+    // The sequence's lengths, and the block ids of the first three steps where the workgroup starts at the first key, in one
+    // round trip (through the constant address space: scalar loads, which the waits on the vector-memory counter do not see).
+    // Ids past the tile's last block may be anything until they are replaced below.
+    typedef const __attribute__((address_space(4))) int32_t *const_i32_ptr;
+    const const_i32_ptr ctable = (const_i32_ptr)(uintptr_t)(p.block_tables + (int64_t)seq * p.max_blocks_per_seq);
+    int ids0[BLK], ids1[BLK], ids2[BLK];   // block ids of the steps st, st + 1 and st + 2
+    const int id_first = ctable[0];
     {
-        int chunk, t;
-        if (p.pf_table) {   // the plan lists the (tile, part) pairs one by one
-            chunk = min(entry_chunk(list_raw), p.num_pf - 1);
-            t = entry_tile(list_raw);
-        } else {
-            chunk = __builtin_amdgcn_readfirstlane(count_le(cum_at, p.num_pf, tile_idx, lane));
-            t = (cum_at(chunk + 1) - 1) - tile_idx;       // reversed order inside the sequence
+        const int last = p.max_blocks_per_seq - 1;
+#pragma unroll
+        for (int b = 0; b < BLK; ++b) {
+            ids0[b] = ctable[min(BLK * kg + b, last)];
+            ids1[b] = ctable[min(BLK * (KG + kg) + b, last)];
+            ids2[b] = ctable[min(BLK * (2 * KG + kg) + b, last)];
         }
-        seq = min(max(cum_at(p.num_pf + 1 + chunk), 0), p.num_seqs - 1);
-        const int q0 = p.query_start_loc[seq];
-        const int q_len = p.query_start_loc[seq + 1] - q0;
-        const int tile_rows = max(1, COLS / g);
+    }
+    int q_row0, rows, pos0, seq_len;
+    {
+        const const_i32_ptr qsl = (const_i32_ptr)(uintptr_t)p.query_start_loc;
+        const int q0 = qsl[seq], q1 = qsl[seq + 1];
+        const int ctx = ((const_i32_ptr)(uintptr_t)p.ctx_lens)[seq];
+        seq_len = ((const_i32_ptr)(uintptr_t)p.seq_lens)[seq];
+        const int q_len = q1 - q0;
+        const int tile_rows = max(1, (COLS * (int)p.g_magic) >> 15);
         const int t0 = t * tile_rows;
         q_row0 = min(max(q0 + t0, 0), p.total_q - 1);
         rows = max(1, min(min(tile_rows, q_len - t0), p.total_q - q_row0));
-        seq_len = p.seq_lens[seq];
         // keys beyond what the plan allotted to this sequence are never touched
         const int cap = p.max_blocks_per_seq * kBlockSize;
-        pos0 = min(max(p.ctx_lens[seq] + t0, 0), cap - rows);
+        pos0 = min(max(ctx + t0, 0), cap - rows);
         seq_len = min(seq_len, cap);
-        // all of these are the same in every lane: keep them in scalar registers
-        seq = __builtin_amdgcn_readfirstlane(seq);
-        q_row0 = __builtin_amdgcn_readfirstlane(q_row0);
-        rows = __builtin_amdgcn_readfirstlane(rows);
-        pos0 = __builtin_amdgcn_readfirstlane(pos0);
-        seq_len = __builtin_amdgcn_readfirstlane(seq_len);
     }
     const uint16_t *const k_cache = p.k_cache, *const v_cache = p.v_cache;
     const int Hkv = p.Hkv;
@@ -1083,13 +1089,13 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     const uint32_t ldsV_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&ldsV[0][0];
     // this lane's query column
     const int c = wave * 32 + col;
-    const int c_row = c / g, c_head = c - c_row * g;
+    const int c_row = (int)((uint32_t)c * p.g_magic >> 15), c_head = c - c_row * g;
     const bool c_valid = c_row < rows;
     const int row = min(c_row, rows - 1);
     const int head = kvh * g + c_head;
     const int pos = pos0 + row;                          // this column's absolute position
     // the wave's columns span rows [w_row_lo, w_row_hi] (scalar)
-    const int w_row_lo = min((wave * 32) / g, rows - 1), w_row_hi = min((wave * 32 + 31) / g, rows - 1);
+    const int w_row_lo = min((wave * 32 * (int)p.g_magic) >> 15, rows - 1), w_row_hi = min(((wave * 32 + 31) * (int)p.g_magic) >> 15, rows - 1);
     const bool w_used = wave * 32 < rows * g;            // (a narrow tile leaves the other waves without columns: they only stage)
     const int w_pos_lo = pos0 + w_row_lo, w_pos_hi = w_used ? pos0 + w_row_hi : -1;
     const int kv_end = pos0 + rows;                      // keys visible to the tile: [0, kv_end)
@@ -1107,13 +1113,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
         const u32x4 *qp = reinterpret_cast<const u32x4 *>(p.q + ((int64_t)(q_row0 + row) * p.Hq + head) * HD);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qb[ks] = qp[2 * ks + h];
-        // Passing the registers through an empty asm makes the compiler wait for these loads here,
-        // before the loop, instead of counting them down inside it (which would also wait for the
-        // global->LDS loads it does not know about).
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qb[ks]));
     }
-    const int32_t *table = p.block_tables + (int64_t)seq * p.max_blocks_per_seq;
     const int64_t tile_elems = (int64_t)HD * kBlockSize;
     // K operand row col -> block (col>>4) of the half, slot with bits 2,3 of (col&15) swapped
     const int ku = col >> 4;
@@ -1126,10 +1126,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     //   K: cache chunk cidx%CH   (same order as the cache)
     //   V: LDS position r = half*HD + dim  <-  cache chunk 2*dim + half
     // The instruction is issued through inline asm so that the waits stay under this code's
-    // control.  (The block table is read through the constant address space: scalar loads, which
-    // the waits on the vector-memory counter do not see.)
-    typedef const __attribute__((address_space(4))) int32_t *const_i32_ptr;
-    const const_i32_ptr ctable = (const_i32_ptr)(uintptr_t)table;
+    // control.
     auto block_id = [&](int b) -> int { return ctable[min(b, nblk - 1)]; };
     // (tile of kv head kvh of physical block pb) = cache + pb * blk_stride + kvh * tile_elems, in elements
     const uint16_t *const k_head = k_cache + (int64_t)kvh * tile_elems, *const v_head = v_cache + (int64_t)kvh * tile_elems;
@@ -1297,18 +1294,30 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     };
 
     auto step_block = [&](int st, int b) -> int { return block_id(BLK * (KG * st + kg) + b); };
-    int ids1[BLK], ids2[BLK];   // block ids of the steps st+1 and st+2
     {
-        int ids0[BLK];
+        if (st_lo == 0) {   // (the ids are here; steps past the tile's last block take any valid one)
 #pragma unroll
-        for (int b = 0; b < BLK; ++b) {
-            ids0[b] = step_block(st_lo, b);
-            ids1[b] = step_block(st_lo + 1, b);
-            ids2[b] = step_block(st_lo + 2, b);
+            for (int b = 0; b < BLK; ++b) {
+                if (BLK * kg + b >= nblk) ids0[b] = id_first;
+                if (BLK * (KG + kg) + b >= nblk) ids1[b] = id_first;
+                if (BLK * (2 * KG + kg) + b >= nblk) ids2[b] = id_first;
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < BLK; ++b) {
+                ids0[b] = step_block(st_lo, b);
+                ids1[b] = step_block(st_lo + 1, b);
+                ids2[b] = step_block(st_lo + 2, b);
+            }
         }
         issue(false, st_lo & 1, ids0);
         issue(true, st_lo & 1, ids0);
         if (PIPE && st_lo + 1 < nstep) issue(false, (st_lo + 1) & 1, ids1);
+        // Passing the query registers through an empty asm makes the compiler wait for their loads here, behind the first
+        // tiles' loads and before the loop, instead of counting them down inside it (which would also wait for the
+        // global->LDS loads it does not know about).
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qb[ks]));
     }
     phase(1);
     // One step.  Sc: scores of step st (computed during step st-1), Sn: receives those of step st+1.
@@ -1540,21 +1549,35 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, uint
     }
 }
 
+// The tile list's word of this workgroup's row (see AttnParams::list_row): its address needs no other argument.
+OOCO_DEV int row_word(const KernArgs &a) { return a.cum[kInlineSeqs - min((int)blockIdx.y, kInlineSeqs)]; }
+// (What a prefill workgroup needs of the arguments before its first tile, asked for together: see decode_kernel_body.)
+OOCO_DEV void prefill_args(const AttnParams &p)
+{
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens), "s"(p.query_start_loc),
+                 "s"(p.ctx_lens), "s"(p.trace), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),
+                 "s"(p.total_q), "s"(p.scale_log2e), "s"((int)p.pf_table), "s"((int)p.g_magic), "s"((int)p.list_by_seq));
+}
+
 template <int HD, int NW, int KG = 1>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs a)
 {
     const AttnParams &p = a.p;
+    int tile_word = row_word(a);
+    prefill_args(p);
+    const int vb = (int)(blockIdx.y * (unsigned)p.Hkv + blockIdx.x);
     // option "trace" on a batch without decode work: per workgroup (start, XCD * 256 + compute unit id, times of
     // four phases since the start, end)
-    uint64_t *const trace = (p.trace && p.static_runs == 0) ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
+    uint64_t *const trace = (p.trace && p.static_runs == 0) ? p.trace + (int64_t)vb * 4 : nullptr;
     const uint64_t t_start = trace ? wall_clock64() : 0;
     if (trace && threadIdx.x == 0) {
         trace[0] = t_start;
         trace[1] = (__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u) * 256u + ((__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 8) & 255u);
         trace[2] = 0;   // (a workgroup that leaves before its first step stores no phases)
     }
-    prefill_unit<HD, NW, true, KG>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)blockIdx.x,
-                               trace ? trace + 2 : nullptr, t_start);
+    if (!p.list_by_seq && p.pf_table) tile_word = plan_entry(a, 2 * p.num_pf + 1 + (int)blockIdx.y);
+    prefill_unit<HD, NW, true, KG>(p, [&](int idx) -> int { return plan_entry(a, idx); }, vb, (int)blockIdx.y, (int)blockIdx.x, tile_word,
+                                   trace ? trace + 2 : nullptr, t_start);
     if (trace) {
         __syncthreads();
         if (threadIdx.x == 0) trace[3] = wall_clock64();
@@ -1567,7 +1590,11 @@ template <int HD>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void prefill_kernel_lean(const KernArgs a)
 {
     const AttnParams &p = a.p;
-    prefill_unit<HD, 8, false, 1>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)blockIdx.x);
+    int tile_word = row_word(a);
+    prefill_args(p);
+    if (!p.list_by_seq && p.pf_table) tile_word = plan_entry(a, 2 * p.num_pf + 1 + (int)blockIdx.y);
+    prefill_unit<HD, 8, false, 1>(p, [&](int idx) -> int { return plan_entry(a, idx); }, (int)(blockIdx.y * (unsigned)p.Hkv + blockIdx.x),
+                                  (int)blockIdx.y, (int)blockIdx.x, tile_word);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1584,10 +1611,13 @@ template <int HD, int NBI, int MBATCH, int NW, bool PIPE, bool COOP, int KG = 1>
 OOCO_DEV void step_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
-    if (COOP && (int)blockIdx.x < p.dec_wgs) {   // cooperative decode workgroups
+    int tile_word = row_word(a);
+    prefill_args(p);
+    const int wg = p.rows2d ? (int)(blockIdx.y * (unsigned)p.Hkv + blockIdx.x) : (int)blockIdx.x;
+    if (COOP && wg < p.dec_wgs) {   // cooperative decode workgroups
         static_assert(!COOP || kCoopFloats<HD, NW> * sizeof(float) <= 4 * KG * kPfGroupBlocks<KG> * HD * 2 * sizeof(u32x4), "fits the stage memory");
-        const int run = (int)blockIdx.x / p.Hkv, slot = (int)blockIdx.x - run * p.Hkv;
-        uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
+        const int run = p.rows2d ? (int)blockIdx.y : wg / p.Hkv, slot = wg - run * p.Hkv;
+        uint64_t *const trace = p.trace ? p.trace + (int64_t)wg * 4 : nullptr;
         if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
         decode_coop_run<HD, NBI, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + (threadIdx.x & 63)], run,
                                      p.rotate_heads ? (slot + run) % p.Hkv : slot,
@@ -1596,17 +1626,17 @@ OOCO_DEV void step_body(const KernArgs &a)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (threadIdx.x == 0) trace[3] = wall_clock64();
         }
-    } else if (!COOP && (int)blockIdx.x < p.dec_wgs) {
+    } else if (!COOP && wg < p.dec_wgs) {
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
         // (the waves of a workgroup take items far apart: side by side they hold the kv heads of one run, finish together and
         // merge one long sequence's parts on one unit, which reads no faster for three waves than for one -- a sequence of
         // 73,000 tokens in 80 parts, 64/8 heads: 52 us from the last step to the end, and 26 apart)
-        const int item = p.dec_near ? (int)blockIdx.x * p.dec_wpw + wave : wave * p.dec_wgs + (int)blockIdx.x;
+        const int item = p.dec_near ? wg * p.dec_wpw + wave : wave * p.dec_wgs + wg;
         if (wave >= p.dec_wpw || item >= p.static_runs * p.Hkv) return;
         asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.block_tables), "s"(p.seq_lens),
                      "s"(p.query_start_loc), "s"(p.Hq), "s"(p.Hkv), "s"(p.g), "s"(p.max_blocks_per_seq), "s"(p.num_seqs),
                      "s"(p.total_q), "s"(p.dec_blocks), "s"(p.static_blocks), "s"(p.static_runs), "s"(p.piece_pad),
-                     "s"(p.rotate_heads), "s"(p.scale_log2e), "s"(p.trace));
+                     "s"((int)p.rotate_heads), "s"(p.scale_log2e), "s"(p.trace));
         const int lane = (int)threadIdx.x & 63;
         const int run = item / p.Hkv, slot = item - run * p.Hkv;
         const int kvh = p.rotate_heads ? (slot + run) % p.Hkv : slot;
@@ -1621,7 +1651,14 @@ OOCO_DEV void step_body(const KernArgs &a)
         }
     } else {
         const int n_cum = p.num_seqs + 1;   // the prefill array follows the decode array
-        prefill_unit<HD, NW, PIPE, KG>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, (int)blockIdx.x - p.dec_wgs);
+        const int vb = wg - p.dec_wgs;
+        int entry = (int)blockIdx.y - p.list_row, kvh = (int)blockIdx.x;
+        if (!p.rows2d && p.pf_table) {
+            entry = vb / p.Hkv;
+            kvh = vb - entry * p.Hkv;
+            tile_word = a.cum[kInlineSeqs - p.list_row - entry];
+        }
+        prefill_unit<HD, NW, PIPE, KG>(p, [&](int idx) -> int { return a.cum[n_cum + idx]; }, vb, entry, kvh, tile_word);
     }
 }
 
@@ -1753,7 +1790,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void mixed_kernel(const KernArgs a)
                 __syncthreads();
                 const int vb = sh_item;
                 if (vb < 0) break;
-                prefill_unit<HD, 4, true, 1>(p, pf_at, vb);
+                const int entry = p.pf_table ? min(vb / p.Hkv, p.pf_table - 1) : 0;
+                prefill_unit<HD, 4, true, 1>(p, pf_at, vb, entry, vb - entry * p.Hkv, p.pf_table ? pf_at(2 * p.num_pf + 1 + entry) : 0);
                 if (pass == 0) ++n_first; else ++n_second;
             }
         }
@@ -2090,8 +2128,8 @@ hipError_t launch_decode(const KernArgs &a, hipStream_t s)
 hipError_t launch_prefill(const KernArgs &a, hipStream_t s)
 {
     if (a.p.n_tiles <= 0) return hipSuccess;
-    const dim3 grid((unsigned)(a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
-                                            : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1)));
+    const dim3 grid = a.p.pf_table ? dim3((unsigned)a.p.Hkv, (unsigned)a.p.pf_table)
+                                   : dim3((unsigned)((int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1)));
     if (a.p.pf_groups > 1 && a.p.hd == 128)
         hipLaunchKernelGGL((prefill_kernel<128, 8, kKeyGroups>), grid, dim3(512), 0, s, a);
     else if (a.p.pf_groups > 1)
@@ -2113,12 +2151,14 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
     // Decode waves of a workgroup: as few as put a decode workgroup on every unit, at most one per SIMD.  (24 sequences,
     // 384 waves: four to a workgroup the stream has the vector-memory paths of 96 units only)
     const int64_t items = (int64_t)a.p.static_runs * a.p.Hkv;
-    a.p.dec_wpw = a.p.coop ? 1 : (int16_t)std::min<int64_t>(kStepDecWaves, (items + num_cus - 1) / num_cus);
+    a.p.dec_wpw = a.p.coop ? 1 : (int8_t)std::min<int64_t>(kStepDecWaves, (items + num_cus - 1) / num_cus);
     const int64_t dec = (items + a.p.dec_wpw - 1) / a.p.dec_wpw;
     const int64_t pf = a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
                                     : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
     a.p.dec_wgs = (int32_t)dec;
-    const dim3 grid((unsigned)(dec + pf));
+    // rows: the decode runs of cooperative workgroups, then the tile list's entries
+    if (a.p.rows2d && (!a.p.coop || !a.p.pf_table || a.p.list_row != a.p.static_runs)) return hipErrorInvalidValue;
+    const dim3 grid = a.p.rows2d ? dim3((unsigned)a.p.Hkv, (unsigned)(a.p.static_runs + a.p.pf_table)) : dim3((unsigned)(dec + pf));
     if (a.p.pf_groups > 1 && (!a.p.coop || a.p.coop_waves != 8)) return hipErrorInvalidValue;
     if (a.p.pf_groups > 1 && a.p.hd == 128)
         hipLaunchKernelGGL((step_kernel_groups<128, 2>), grid, dim3(512), 0, s, a);
