@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libooco.so: argument marshalling only.
+"""Thin binding over libooco.so: argument marshalling only, through ctypes and, for the plain form of the per-step calls,
+through the native module `_binding` (csrc/ooco_py.cpp).
 
 Function names equal the C entry points of include/ooco.h.  Device arguments are torch
 tensors (used purely as device allocations: `.data_ptr()`), host arguments numpy int32 arrays.
@@ -86,6 +87,34 @@ _lib.ooco_mix_decoding_select.argtypes = ([ctypes.POINTER(ModelParams)] + [ctype
                                           ctypes.c_char_p, ctypes.c_size_t])
 
 
+# The per-step calls' arguments in native code: each of those functions tries it first and goes the general way when it
+# answers NotImplemented (anything but contiguous GPU tensors and int32 arrays).  Small calls in a loop on MI355X, the general
+# way -> native: plan 1.7 -> 0.3 us, plan and attention of five short sequences 7.8 -> 5.0 (the kernel's time), the static entry
+# 8.0 -> 5.0, KV append 5.7 -> 3.8, block copy 5.3 -> 3.5.
+_native = None
+if torch is not None:
+    try:
+        from paper_2511_21862_amd import _binding as _native
+        _native.bind(_P, *[ctypes.cast(f, _P).value for f in (_lib.ooco_plan, _lib.ooco_attn_mixed, _lib.ooco_attn_mixed_static,
+                                                              _lib.ooco_kv_append, _lib.ooco_kv_block_copy)])
+    except ImportError as e:      # not built, or built for another torch: the general way alone
+        import warnings
+
+        _native = None
+        warnings.warn(f"native argument marshalling is not available ({e}); build it with `python -m paper_2511_21862_amd.build`",
+                      RuntimeWarning, stacklevel=2)
+
+
+def _not_native(*args):
+    return NotImplemented
+
+
+_OF_TENSOR = getattr(_native, "OF_TENSOR", None)     # for a size: the native module reads it off the tensor
+_plan_fast, _attn_fast, _static_fast, _append_fast, _copy_fast = (
+    (_native.plan, _native.attn_mixed, _native.attn_mixed_static, _native.kv_append, _native.kv_block_copy)
+    if _native is not None else (_not_native,) * 5)
+
+
 class OocoError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"{_STATUS_NAMES.get(status, status)}: {message}")
@@ -137,7 +166,7 @@ def ooco_last_error(ctx) -> str:
     return s.decode() if s else ""
 
 
-def _check(ctx, status: int):
+def _check(ctx, status: int) -> None:
     if status != OOCO_OK:
         raise OocoError(status, ooco_last_error(ctx))
 
@@ -160,6 +189,9 @@ def ooco_set_option(ctx, name: str, value: int) -> None:
 
 
 def ooco_plan(ctx, num_seqs, h_seq_lens, h_query_start_loc, h_ctx_lens) -> None:
+    st = _plan_fast(ctx, num_seqs, h_seq_lens, h_query_start_loc, h_ctx_lens)
+    if st is not NotImplemented:
+        return _check(ctx, st)
     a, pa = _host_i32(h_seq_lens)
     b, pb = _host_i32(h_query_start_loc)
     c, pc = _host_i32(h_ctx_lens)
@@ -235,6 +267,9 @@ def ooco_profile_read(ctx) -> dict:
 
 def ooco_attn_mixed(ctx, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc, ctx_lens, out, num_seqs,
                     total_q_tokens, stream=None) -> None:
+    st = _attn_fast(ctx, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc, ctx_lens, out, num_seqs, total_q_tokens, stream)
+    if st is not NotImplemented:
+        return _check(ctx, st)
     _check(ctx, _lib.ooco_attn_mixed(ctx, _dev(q), _dev(k_cache), _dev(v_cache), _dev(block_tables), _dev(seq_lens),
                                      _dev(query_start_loc), _dev(ctx_lens), _dev(out), num_seqs, total_q_tokens,
                                      _stream_handle(stream)))
@@ -243,6 +278,13 @@ def ooco_attn_mixed(ctx, q, k_cache, v_cache, block_tables, seq_lens, query_star
 def ooco_attn_mixed_static(num_q_heads, num_kv_heads, head_dim, block_size, max_blocks_per_seq, softmax_scale, h_seq_lens,
                            h_query_start_loc, h_ctx_lens, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc,
                            ctx_lens, out, num_seqs, total_q_tokens, stream=None) -> None:
+    st = _static_fast(num_q_heads, num_kv_heads, head_dim, block_size, max_blocks_per_seq, softmax_scale, h_seq_lens, h_query_start_loc,
+                      h_ctx_lens, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc, ctx_lens, out, num_seqs, total_q_tokens,
+                      stream)
+    if st is not NotImplemented:
+        if st != OOCO_OK:
+            raise OocoError(*st)
+        return
     a, pa = _host_i32(h_seq_lens)
     b, pb = _host_i32(h_query_start_loc)
     c, pc = _host_i32(h_ctx_lens)
@@ -256,12 +298,18 @@ def ooco_attn_mixed_static(num_q_heads, num_kv_heads, head_dim, block_size, max_
 
 
 def ooco_kv_block_copy(ctx, k_src, v_src, k_dst, v_dst, src_block_ids, dst_block_ids, num_pairs, stream=None) -> None:
+    st = _copy_fast(ctx, k_src, v_src, k_dst, v_dst, src_block_ids, dst_block_ids, num_pairs, stream)
+    if st is not NotImplemented:
+        return _check(ctx, st)
     _check(ctx, _lib.ooco_kv_block_copy(ctx, _dev(k_src), _dev(v_src), _dev(k_dst), _dev(v_dst), _dev(src_block_ids),
                                         _dev(dst_block_ids), num_pairs, _stream_handle(stream)))
 
 
 def ooco_kv_append(ctx, k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, num_seqs,
                    total_q_tokens, stream=None) -> None:
+    st = _append_fast(ctx, k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, num_seqs, total_q_tokens, stream)
+    if st is not NotImplemented:
+        return _check(ctx, st)
     _check(ctx, _lib.ooco_kv_append(ctx, _dev(k_new), _dev(v_new), _dev(k_cache), _dev(v_cache), _dev(block_tables),
                                     _dev(query_start_loc), _dev(ctx_lens), num_seqs, total_q_tokens,
                                     _stream_handle(stream)))
@@ -415,12 +463,21 @@ class Context:
         return ooco_trace_read(self.h)
 
     def attn_mixed(self, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc, ctx_lens, out, stream=None):
+        st = _attn_fast(self.h, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc, ctx_lens, out, _OF_TENSOR, _OF_TENSOR, stream)
+        if st is not NotImplemented:
+            return _check(self.h, st)
         ooco_attn_mixed(self.h, q, k_cache, v_cache, block_tables, seq_lens, query_start_loc, ctx_lens, out,
                         int(seq_lens.shape[0]), int(q.shape[0]), stream)
 
     def kv_append(self, k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, stream=None):
+        st = _append_fast(self.h, k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, _OF_TENSOR, _OF_TENSOR, stream)
+        if st is not NotImplemented:
+            return _check(self.h, st)
         ooco_kv_append(self.h, k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens,
                        int(ctx_lens.shape[0]), int(k_new.shape[0]), stream)
 
     def kv_block_copy(self, k_src, v_src, k_dst, v_dst, src_ids, dst_ids, stream=None):
+        st = _copy_fast(self.h, k_src, v_src, k_dst, v_dst, src_ids, dst_ids, _OF_TENSOR, stream)
+        if st is not NotImplemented:
+            return _check(self.h, st)
         ooco_kv_block_copy(self.h, k_src, v_src, k_dst, v_dst, src_ids, dst_ids, int(src_ids.shape[0]), stream)

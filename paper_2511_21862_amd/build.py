@@ -1,4 +1,4 @@
-"""Builds libooco.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Builds libooco.so (HIP kernels + C ABI) for gfx950 with hipcc, and the native half of the Python binding, in-tree.
 
     python -m paper_2511_21862_amd.build
 """
@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -19,6 +20,35 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
+
+MARSHAL = os.path.join(HERE, "_binding.so")
+MARSHAL_SRC = os.path.join(CSRC, "ooco_py.cpp")
+
+
+def build_marshalling(force: bool = True, verbose: bool = False) -> str | None:
+    """The binding's native argument marshalling (host code against this Python, numpy and torch); without torch the
+    binding is used for host functions only and does without."""
+    try:
+        import numpy
+        import torch
+    except ImportError:
+        return None
+    if not force and os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL) >= max(os.path.getmtime(f) for f in [MARSHAL_SRC, HEADERS[1]]):
+        return MARSHAL
+    tinc, tlib = (os.path.join(os.path.dirname(torch.__file__), d) for d in ("include", "lib"))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for d in (tinc, os.path.join(tinc, "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"], numpy.get_include(),
+              "/opt/rocm/include"):
+        cmd += ["-isystem", d]
+    cmd += ["-I", os.path.join(HERE, "..", "include"), "-Wall", "-o", MARSHAL, MARSHAL_SRC,
+            "-L", tlib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed:\n{res.stderr}\n{res.stdout}")
+    return MARSHAL
 
 
 def build_library(force: bool = True, verbose: bool = False) -> str:
@@ -43,3 +73,4 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build_library(force=True, verbose=True))
+    print(build_marshalling(force=True, verbose=True))
