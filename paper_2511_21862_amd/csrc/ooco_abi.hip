@@ -1628,6 +1628,10 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     const bool step = runs_as_step(ctx);
     const bool overlap = mixed && !fused && !step && ctx->side_stream && (ctx->opt_overlap >= 2 || (ctx->opt_overlap == 1 && !pl.brief));
     hipStream_t ps = overlap ? ctx->side_stream : s;   // the stream of the prefill kernel
+    // A split tile's merge is shared among its parts where all workgroups of the launch find a place at once (launch_step adds
+    // its decode workgroups): two of four waves per compute unit.
+    const int64_t pf_wgs = pl.pf_table ? (int64_t)pl.pf_table * ctx->Hkv : (int64_t)pl.n_tiles * ctx->Hkv * pl.pf_split;
+    p.pf_share = pl.pf_split > 1 && pl.pf_waves == 4 && (step || !mixed) && pf_wgs <= 2 * (int64_t)ctx->num_cus;
     auto mark = [&](int k, hipStream_t st) {
         if (ev && e == hipSuccess) e = hipEventRecord(ev[k], st);
     };
@@ -1813,6 +1817,7 @@ ooco_status ooco_attn_mixed_static(int num_q_heads, int num_kv_heads, int head_d
     p.pf_ml = nullptr;
     p.pf_counters = nullptr;
     p.pf_split = 1;
+    p.pf_share = 0;
     p.pf_table = (int16_t)pl.pf_table;
 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);

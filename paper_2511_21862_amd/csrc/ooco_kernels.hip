@@ -946,6 +946,9 @@ __global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs
 // 64 KiB LDS each).
 constexpr int kPfThreads = 256;   // threads of the four-wave workgroup (the eight-wave one has 512)
 constexpr int kPfBlocks = 4;    // KV blocks per step
+constexpr int kMergeSlices = 4;        // shared merge of a split tile (see prefill_unit): slices of the dims,
+constexpr int kSharedMergeParts = 4;   // parts from which it pays,
+constexpr int kMergePolls = 12;        // looks at the counter before a part leaves it to the others
 
 // Entry idx of the plan's array: from device memory if the plan did not fit the kernel arguments, else from the
 // argument block.  The two loads must stay two loads: merged into one load through a selected pointer, the argument
@@ -1476,6 +1479,18 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         }
         m = M;
     }
+    // this thread's pieces first .. of its column, divided by the sum, to the output
+    auto put = [&](const auto &a, int first) {
+        if (c_valid) {
+            const float inv = 1.0f / ltot;
+            uint16_t *op = p.out + ((int64_t)(q_row0 + row) * p.Hq + head) * HD + 8 * (q0 + first) + 4 * h;
+#pragma unroll
+            for (int i = 0; i < (int)std::extent_v<std::remove_reference_t<decltype(a)>>; ++i) {
+                u32x2 w = {pack2_bf16(a[i][0] * inv, a[i][1] * inv), pack2_bf16(a[i][2] * inv, a[i][3] * inv)};
+                *reinterpret_cast<u32x2 *>(op + 8 * i) = w;
+            }
+        }
+    };
     if (nparts > 1) {
         // (one counter per (tile, kv head): the slot of its part 0 with the list, the unit's index without)
         const int counter_idx = p.pf_table ? slot0 : slot0 / split;
@@ -1495,58 +1510,114 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partial has reached memory ...
         __syncthreads();                                    // ... and so have the other waves'
+        // Pieces first .. first + N - 1 (of this thread's) of all parts, in part order: the result does not depend on who is
+        // last or who merges.  16 loads of a lane on their way at a time: 16 / N parts.
+        auto merge = [&](auto &a, int first) {
+            constexpr int N = std::extent_v<std::remove_reference_t<decltype(a)>>, PB = 16 / N;
+            float M = -INFINITY;
+            ltot = 0.f;
+#pragma unroll
+            for (int i = 0; i < N; ++i) a[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j0 = 0; j0 < nparts; j0 += PB) {
+                f32x2 ml[PB];
+                f32x4 t[16];
+#pragma unroll
+                for (int b = 0; b < PB; ++b) ml[b] = load_dev2(ml_ptr(min(j0 + b, nparts - 1)));
+                auto pp = [&](int b) -> const float * { return part_ptr(min(j0 + b, nparts - 1)) + first * 256; };
+                if constexpr (PB == 1)
+                    load_dev_part<4>(t, pp(0), pp(0) + 1024, pp(0) + 2048, pp(0) + 3072);
+                else if constexpr (PB == 2)
+                    load_dev_part<4>(t, pp(0), pp(0) + 1024, pp(1), pp(1) + 1024);
+                else if constexpr (PB == 4)
+                    load_dev_part<4>(t, pp(0), pp(1), pp(2), pp(3));
+                else
+                    load_dev_part<2>(t, pp(0), pp(1), pp(2), pp(3), pp(4), pp(5), pp(6), pp(7));
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    if (j0 + b < nparts) {
+                        const float M_new = fmaxf(M, ml[b][0]);
+                        const float w_old = fast_exp2(M - M_new), w_new = fast_exp2(ml[b][0] - M_new);
+                        M = M_new;
+                        // (the fused multiply-adds are spelled out: every N gives the same bits)
+                        ltot = __builtin_fmaf(ltot, w_old, ml[b][1] * w_new);
+#pragma unroll
+                        for (int i = 0; i < N; ++i)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) a[i][r] = __builtin_fmaf(a[i][r], w_old, t[b * N + i][r] * w_new);
+                    }
+                }
+            }
+        };
         __shared__ int arrived;
-        if (tid == 0)
-            arrived = __hip_atomic_fetch_add(p.pf_counters + counter_idx, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (arrived != nparts - 1) return;
-        if (tid == 0)   // ready for the next call
-            __hip_atomic_store(p.pf_counters + counter_idx, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!w_used) return;
-        float M = -INFINITY;
-        ltot = 0.f;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // in part order: the result does not depend on who is last.  16 loads of a lane on their way at a time: 16 / ITEMS parts.
-        constexpr int PB = 16 / ITEMS;
-        for (int j0 = 0; j0 < nparts; j0 += PB) {
-            f32x2 ml[PB];
-            f32x4 t[16];
-#pragma unroll
-            for (int b = 0; b < PB; ++b) ml[b] = load_dev2(ml_ptr(min(j0 + b, nparts - 1)));
-            auto pp = [&](int b) -> const float * { return part_ptr(min(j0 + b, nparts - 1)); };
-            if constexpr (PB == 1)
-                load_dev_part<4>(t, pp(0), pp(0) + 1024, pp(0) + 2048, pp(0) + 3072);
-            else if constexpr (PB == 2)
-                load_dev_part<4>(t, pp(0), pp(0) + 1024, pp(1), pp(1) + 1024);
-            else if constexpr (PB == 4)
-                load_dev_part<4>(t, pp(0), pp(1), pp(2), pp(3));
-            else
-                load_dev_part<2>(t, pp(0), pp(1), pp(2), pp(3), pp(4), pp(5), pp(6), pp(7));
-#pragma unroll
-            for (int b = 0; b < PB; ++b) {
-                if (j0 + b < nparts) {
-                    const float M_new = fmaxf(M, ml[b][0]);
-                    const float w_old = fast_exp2(M - M_new), w_new = fast_exp2(ml[b][0] - M_new);
-                    M = M_new;
-                    ltot = ltot * w_old + ml[b][1] * w_new;
-#pragma unroll
-                    for (int i = 0; i < ITEMS; ++i)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[i][r] = acc[i][r] * w_old + t[b * ITEMS + i][r] * w_new;
+        int32_t *const counter = p.pf_counters + counter_idx;
+        if constexpr (KG == 1 && PIPE) {
+            if (p.pf_share && nparts >= kSharedMergeParts) {
+                // The merge of a tile of many parts is shared: the parts end within a few microseconds of each other, and one
+                // unit reads 64 KB of partial results in 1.2 us, a part after the other (six parts 8 .. 11 us at the end of
+                // the launch, eleven 15).  So a part that ends early waits, for a bounded time, until the last one has arrived;
+                // the dims fall into kMergeSlices slices, the last part takes the first and whoever is there draws the others.
+                // Only where all workgroups of the launch are resident, so that nobody waits for the place of one that waits.
+                // MI355X (us, one merging part -> shared): 11 parts, 2 x 74 rows on 13,000 tokens, 28/4 heads 45.5 -> 42.0; drawn
+                // batches of 5 .. 16 parts 13.0 -> 11.8, 39.2 -> 36.7, 86.0 -> 79.6; six parts of 80 tiles, whose 32 MB of partial
+                // results are a matter of HBM as well, 87.8 -> 86.9.  Eight slices lose half of that; looks at the counter every
+                // 1.2 us instead of 2 slow down the parts that still work (67 -> 70 us for the steps of those six parts).
+                // The counter's bytes: arrivals, draws, parts that left without waiting any longer.  Every part ends with one
+                // event of its own -- a draw that finds no slice, or leaving --, and the last event of all resets the counter:
+                // nobody touches it any more.
+                constexpr int kDraw = 1 << 8, kLeave = 1 << 16, PI = ITEMS / kMergeSlices;
+                static_assert(kMaxPrefillSplit + kMergeSlices < 256, "a byte each");
+                const int events = kMergeSlices - 1 + nparts;
+                auto event = [&](int what) -> int {   // draws and leaves before this one
+                    const int w = __hip_atomic_fetch_add(counter, what, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int draws = (w >> 8) & 255, leaves = (w >> 16) & 255;
+                    if (draws + leaves + 1 == events) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return draws;
+                };
+                auto draw = [&]() -> int {   // the slice, or -1
+                    const int d = event(kDraw);
+                    return d < kMergeSlices - 1 ? d + 1 : -1;
+                };
+                if (tid == 0) {
+                    const int w = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    int mine = 0;
+                    if ((w & 255) != nparts - 1) {
+                        bool all = false;
+                        for (int i = 0; i < kMergePolls && !all; ++i) {   // (a load and a pause: 2 us or so)
+                            __builtin_amdgcn_s_sleep(40);
+                            all = (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 255) == nparts;
+                        }
+                        if (all) {
+                            mine = draw();
+                        } else {
+                            (void)event(kLeave);
+                            mine = -1;
+                        }
+                    }
+                    arrived = mine;
+                }
+                for (;;) {
+                    __syncthreads();
+                    const int slice = __builtin_amdgcn_readfirstlane(arrived);
+                    if (slice < 0) return;
+                    if (w_used) {
+                        f32x4 a[PI];
+                        merge(a, slice * PI);
+                        put(a, slice * PI);
+                    }
+                    __syncthreads();   // everybody has read `arrived`
+                    if (tid == 0) arrived = draw();
                 }
             }
         }
+        if (tid == 0) arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (arrived != nparts - 1) return;
+        if (tid == 0)   // ready for the next call
+            __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!w_used) return;
+        merge(acc, 0);
     }
-    if (c_valid) {
-        const float inv = 1.0f / ltot;
-        uint16_t *op = p.out + ((int64_t)(q_row0 + row) * p.Hq + head) * HD + 8 * q0 + 4 * h;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            u32x2 w = {pack2_bf16(acc[i][0] * inv, acc[i][1] * inv), pack2_bf16(acc[i][2] * inv, acc[i][3] * inv)};
-            *reinterpret_cast<u32x2 *>(op + 8 * i) = w;
-        }
-    }
+    put(acc, 0);
 }
 
 // The tile list's word of this workgroup's row (see AttnParams::list_row): its address needs no other argument.
@@ -2156,6 +2227,7 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
     const int64_t pf = a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
                                     : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
     a.p.dec_wgs = (int32_t)dec;
+    a.p.pf_share = a.p.pf_share && dec + pf <= 2 * (int64_t)num_cus;   // (two workgroups of four waves fit a unit)
     // rows: the decode runs of cooperative workgroups, then the tile list's entries
     if (a.p.rows2d && (!a.p.coop || !a.p.pf_table || a.p.list_row != a.p.static_runs)) return hipErrorInvalidValue;
     const dim3 grid = a.p.rows2d ? dim3((unsigned)a.p.Hkv, (unsigned)(a.p.static_runs + a.p.pf_table)) : dim3((unsigned)(dec + pf));
