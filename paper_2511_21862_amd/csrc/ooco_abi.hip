@@ -409,6 +409,24 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
         }
         return std::max(average, longest * step_us(beside)) + merge + 2.5 * std::ceil(std::min(r, 2.0));
     };
+    // The same for k parts at head_dim 64, for batches without decode work: a workgroup has half the registers and LDS, so a unit
+    // holds three; a step takes 0.95 us alone and hardly more beside others, the unit's steps 0.61 us at least whoever they
+    // belong to, and the merge of a part reads half as much.  Fitted to 63 random batches of up to 512 tiles x 13 forced splits
+    // (the choice is 2.3 % above the best of them on average, 14 % at worst; by the estimate above it was 7.6 and 54 %).  MI355X,
+    // 32/4 heads (us): 615 rows on 1500 tokens 34.8 -> 21.9, 1036 on 1598 45.2 -> 34.7, 8 x 114 on 3800 66.0 -> 47.4.
+    auto est64 = [&](double w, double w_parts, double longest, double k) {
+        const double r = w / cus, beside = std::min(std::min(r, 1.15 * all_steps / (longest * cus)), 3.0);
+        double body = std::max(longest * (beside <= 1.0 ? 0.945 : 0.95 + std::min(beside - 1.0, 0.15) / 3.0), all_steps / cus * 0.61);
+        double rounds = r / 3.0;
+        if (rounds > 1.0) {   // (parts are equally long: up to three rounds of them count whole)
+            if (w_parts > 0.0 && rounds <= 3.0) rounds = std::ceil(rounds - 1e-9);
+            body = std::max(body, rounds * all_steps / w * 0.82);
+        }
+        const double merge = w_parts > 0.0 ? std::max(1.5 + 0.3 * k, 0.64 + 0.29 * k + 2.03 * w_parts / cus) : 0.0;
+        return 4.1 + 1.93 * std::min(r, 3.0) + body + merge;
+    };
+    // (below 16 steps the merge is most of what a split costs, and two workgroups keep a unit busy: the estimate above)
+    const bool use64 = geo.hd == 64 && dec_blocks == 0 && out.pf_waves == 4 && max_tile_steps >= 16 && units < 2 * (int64_t)geo.num_cus;
     // With the tile list every tile gets parts by its own number of steps: the longest tile k parts, the others as
     // many as keep their parts no longer than that tile's (a tile of a short chunk stays whole beside a long one).
     // Without it (more than kSortedTiles tiles, or a forced value) every tile gets the same number.
@@ -481,7 +499,9 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
             by_steps = true;
             int64_t big = 0, split_ones = 0;
             (void)entries_of(1, true, &big);
-            double best = est((double)units, (double)(big * geo.Hkv), 0.0, (double)max_tile_steps) * 0.97;   // a split must win 3 %
+            double best = use64 ? est64((double)units, 0.0, (double)max_tile_steps, 1.0)
+                                : est((double)units, (double)(big * geo.Hkv), 0.0, (double)max_tile_steps);
+            best *= 0.97;   // a split must win 3 %
             // (a launch of two or more workgroups per unit whose longest tile is no longer than the units' average
             // load cannot gain from more workgroups)
             // Beside a decode part that lasts longer anyway, parts beyond what hides the prefill part behind it only add
@@ -495,8 +515,9 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
             for (int64_t k = 2; !full && k <= kMaxPrefillSplit && k <= max_tile_steps; ++k) {
                 const int64_t e = entries_of(k, true, &big, &split_ones);
                 if (!list_fits(e, split_ones)) break;
-                const double t = est((double)(e * geo.Hkv), (double)(big * geo.Hkv), (double)(split_ones * geo.Hkv),
-                                     (double)((max_tile_steps + k - 1) / k));
+                const double longest = (double)((max_tile_steps + k - 1) / k);
+                const double t = use64 ? est64((double)(e * geo.Hkv), (double)(split_ones * geo.Hkv), longest, (double)k)
+                                       : est((double)(e * geo.Hkv), (double)(big * geo.Hkv), (double)(split_ones * geo.Hkv), longest);
                 if (t < best) {
                     best = t;
                     split = k;

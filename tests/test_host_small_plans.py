@@ -146,3 +146,17 @@ def test_run_bounds_by_reciprocal_equal_the_divisions():
                 q = ((a.astype(np.float64) * b.astype(np.float64) - c) * inv).astype(np.int64)
                 r = np.array([int(x) * int(y) - c - int(u) * int(z) for x, y, z, u in zip(a, b, n, q)])
                 assert (q + np.where(r < 0, -1, np.where(r >= n, 1, 0)) == want).all()
+
+
+def test_parts_of_prefill_tiles_at_head_dim_64():
+    # 32/4 heads of 64: whole tiles below 16 steps and from two workgroups per unit on, parts in between, never past three
+    # workgroups per unit by more than one part per tile
+    def plan(n, rows, ctx):
+        ql, cx = np.full(n, rows, np.int32), np.full(n, ctx, np.int32)
+        qsl = np.arange(n + 1, dtype=np.int32) * rows
+        return B.ooco_plan_dry_run(32, 4, 64, 16, 4096, 256, 256 << 20, cx + ql, qsl, cx)
+    for n, rows, ctx, want in ((1, 615, 1500, 3), (1, 1036, 1598, 2), (8, 112, 3800, 2), (8, 256, 768, 1), (8, 250, 700, 1)):
+        r = plan(n, rows, ctx)
+        t = r["prefill_tiles"]
+        assert r["prefill_parts"] == want, (n, rows, ctx, r["prefill_parts"])
+        assert t[:, 2].sum() == n * rows and t[:, 4].sum() * 4 <= 3 * 256 + 4 * len(t)
