@@ -603,6 +603,10 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
 //     holds all columns).
 //   * "prefill_split" = 1, one workgroup per tile whatever its length, leaves only the chain, so any load (756 batches: 441
 //     taken, 0.62 of the time, six of them more than 6 % slower).
+//     With eight steps or more that chain decides the time also where the decode sequences have to share the units that
+//     are left (120 batches of ooco_attn_mixed_static with more sequences than units: 48 taken, 0.61 of the time; us: 59
+//     decodes of up to 1534 tokens beside 53 + 65 rows on 4728, 28/4 heads 95 -> 58; 128 beside 61 + 76 on 4518 107 -> 55;
+//     with three or four steps 13.8 -> 15.8 .. 17.8, as they then wait for one another).
 bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_lens, const int32_t *h_query_start_loc)
 {
     const int64_t g = geo.Hq / geo.Hkv, rows = prefill_tile_rows((int32_t)g, 8 / kKeyGroups);
@@ -629,7 +633,7 @@ bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_
     if (n_dec > 0) {
         // (the decode part in cooperative workgroups of the default run layout)
         if (!geo.coop_opt || geo.tail_pct || geo.xcd_cw[kXcds - 1] || num_seqs > kInlineSeqs / 2) return false;
-        if (units + n_dec * geo.Hkv > cus) return false;
+        if (units + (whole && longest >= 8 ? 1 : n_dec) * geo.Hkv > cus) return false;
         if ((size_t)(cus / geo.Hkv + num_seqs + 1) * slot_bytes(geo) + 256 > geo.ws_bytes / 2) return false;
     }
     if (forced) return true;

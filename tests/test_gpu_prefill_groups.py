@@ -146,3 +146,30 @@ def test_step_of_key_groups_and_eight_wave_decode_workgroups(heads):
         assert all(np.array_equal(o, outs[0]) for o in outs[1:5])       # one launch gives the bits of two
         for ws in (1 << 20, 4096):                                       # too small for the plan: the four-wave workgroups
             assert_parity(run_gpu(b, options={"prefill_groups": 4}, workspace_bytes=ws), want, f"workspace {ws}")
+
+
+# (one workgroup per tile whatever its length: key groups from eight steps of 128 keys on also beside more decode sequences
+# than units; 7 and 8 steps, decodes whole and cut, of one block and empty)
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", [(32, 8, 128), (28, 4, 128), (32, 4, 64), (64, 8, 128)], ids=str)
+@pytest.mark.parametrize("keys", [896, 897, 2500])
+def test_static_entry_with_more_decode_sequences_than_units(heads, keys):
+    import torch
+    from gpu_util import assert_parity, device_meta, say
+    rng = np.random.default_rng(keys)
+    n = 256 // heads[1] + 9
+    q = [1] * n + [2, 21]
+    ctx = rng.integers(0, 300, size=n).tolist() + [keys - 2, keys - 700]
+    ctx[3], ctx[5] = 0, 1900
+    ql, cx = np.asarray(q), np.asarray(ctx)
+    b = W.build_batch(Hq=heads[0], Hkv=heads[1], hd=heads[2], q_lens=q, ctx_lens=ctx, num_blocks=int(((ql + cx + 15) // 16).sum()) + 5,
+                      seed=91, poison=True)
+    want = ref_c.attn_mixed(b.q, b.k_cache, b.v_cache, b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)
+    d, meta = W.to_device(b), device_meta(b)
+    for _ in range(3):
+        say(f"case: {heads} {n} decodes, {keys} keys")
+        out = torch.full((b.total_q, b.Hq, b.hd), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.ooco_attn_mixed_static(*heads, 16, b.max_blocks_per_seq, 0.0, b.seq_lens, b.query_start_loc, b.ctx_lens, d.q, d.k_cache,
+                                 d.v_cache, *meta, out, b.num_seqs, b.total_q)
+        torch.cuda.synchronize()
+        assert_parity(out.view(torch.int16).cpu().numpy().view(np.uint16), want, "static")
