@@ -143,6 +143,8 @@ bool xcd_weights_to_cw(const int32_t *w, uint16_t *cw)
 }
 
 size_t slot_bytes(const PlanGeometry &geo) { return (size_t)geo.Hq * (geo.hd + 2) * sizeof(float); }
+// (one part of a split prefill tile, for one kv head)
+size_t pf_part_bytes(const PlanGeometry &geo, const HostPlan &pl) { return (size_t)(32 * pl.pf_col_waves()) * (geo.hd + 2) * sizeof(float); }
 
 // Where build_plan puts the plan's arrays: room for `seqs_cap` sequences, i.e. dcum [seqs_cap + 1],
 // pf [2 * seqs_cap + 1 + kListEntries] and a work array order [seqs_cap].  build_plan itself allocates nothing.
@@ -305,6 +307,9 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     int64_t runs = geo.segments_opt > 0 ? geo.segments_opt
                                         : std::min<int64_t>(wave_slots, std::max<int64_t>((kv_blocks + min_blocks - 1) / min_blocks, at_least));
     runs = std::max<int64_t>(1, std::min<int64_t>(runs, dec_blocks));
+    // (what prefill parts that were planned first leave of the workspace: they lie behind the slots, 256-byte aligned)
+    const size_t pf_bytes = (size_t)out.pf_slots * geo.Hkv * pf_part_bytes(geo, out);
+    const size_t ws_bytes = pf_bytes ? (geo.ws_bytes - std::min(geo.ws_bytes, pf_bytes)) / 256 * 256 : geo.ws_bytes;
     for (;;) {
         // weighted runs come in groups of one run per XCD
         bool weighted = geo.xcd_cw[kXcds - 1] != 0 && runs >= kXcds && out.dec_cus == 0;
@@ -320,8 +325,8 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         if (dec_blocks - tail_blk < 16 * runs) weighted = false;
         // partial slots: (run index) + seq < runs + tails + num_seqs; one run never splits a sequence
         const int64_t slots = (runs + tails > 1) ? runs + tails + num_seqs : 0;
-        if ((size_t)slots * slot_bytes(geo) <= geo.ws_bytes || runs == 1) {
-            if ((size_t)slots * slot_bytes(geo) > geo.ws_bytes) {   // a single run, no tail, needs no slots
+        if ((size_t)slots * slot_bytes(geo) <= ws_bytes || runs == 1) {
+            if ((size_t)slots * slot_bytes(geo) > ws_bytes) {   // a single run, no tail, needs no slots
                 tail_blk = tails = 0;
             }
             out.static_runs = (int32_t)runs;
@@ -362,7 +367,7 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
     const int BS = geo.BS;
     const int64_t units = tiles * geo.Hkv;
     int64_t split = 1;
-    const size_t part_bytes = (size_t)(32 * out.pf_col_waves()) * (geo.hd + 2) * sizeof(float);
+    const size_t part_bytes = pf_part_bytes(geo, out);
     const size_t left = geo.ws_bytes - std::min(geo.ws_bytes, std::max(f.dec_reserve, ((size_t)out.slots * slot_bytes(geo) + 255) / 256 * 256));
     const double cus = (double)geo.num_cus;
     // Estimated time in microseconds of a launch of w workgroups in all, the longest of them `longest` 64-key steps,
@@ -631,7 +636,9 @@ bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_
     const bool forced = geo.pf_groups_opt == kKeyGroups, whole = geo.pf_split_opt == 1;
     if (tiles == 0) return false;
     if (n_dec > 0) {
-        // (the decode part in cooperative workgroups of the default run layout)
+        // (the decode part in cooperative workgroups of the default run layout; a number of runs asked for is planned first,
+        // with all of the workspace)
+        if (geo.segments_opt && !forced) return false;
         if (!geo.coop_opt || geo.tail_pct || geo.xcd_cw[kXcds - 1] || num_seqs > kInlineSeqs / 2) return false;
         if (units + (whole && longest >= 8 ? 1 : n_dec) * geo.Hkv > cus) return false;
         if ((size_t)(cus / geo.Hkv + num_seqs + 1) * slot_bytes(geo) + 256 > geo.ws_bytes / 2) return false;
