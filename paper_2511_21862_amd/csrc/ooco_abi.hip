@@ -871,6 +871,14 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     return OOCO_OK;
 }
 
+// Whether the plan's arrays ride in the kernel arguments (the mixed kernel, dec_cus > 0, takes both at once; the two separate
+// kernels one each); else the kernels read them from device memory.
+bool plan_in_args(const HostPlan &pl)
+{
+    const size_t n_cum = (size_t)pl.num_seqs + 1, room = (size_t)kInlineSeqs + 1;
+    return pl.dec_cus > 0 ? n_cum + pl.pf_size <= room : n_cum <= room && pl.pf_size <= room;
+}
+
 // Whether the step kernel can run the plan: both kinds of work, both arrays together in the kernel arguments, no
 // dynamic tail and no XCD weights, and decode waves that it is instantiated for (nbi: KV blocks per softmax step).
 bool step_fits(const HostPlan &pl, int hd, bool coop, int nbi)
@@ -1471,10 +1479,12 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
     if (!ctx) return OOCO_EINVAL;
     if (!ctx->plan_made) return fail(ctx, OOCO_EINVAL, "ooco_plan_kernels: no plan has been made");
     if (!names || cap == 0) return fail(ctx, OOCO_EINVAL, "ooco_plan_kernels: no buffer");
+    // (by the conditions of launch_decode, launch_prefill and launch_step)
     const HostPlan &pl = ctx->plan;
     const bool dec = pl.static_runs > 0, pf = pl.n_tiles > 0;
-    const bool coop = decode_coop(ctx) != 0;
-    const int nbi = coop ? 256 / ctx->hd : decode_nbi(ctx);
+    const bool coop = decode_coop(ctx) != 0, in_args = plan_in_args(pl), lean = pl.lean && ctx->hd == 128;
+    const bool general = !in_args || (!coop && (pl.tail_runs > 0 || pl.cw[kXcds - 1] != 0));
+    const int wanted = decode_nbi(ctx), nbi = coop ? 256 / ctx->hd : wanted == 2 || wanted == 4 ? wanted : 1;
     char d[64] = "", f[64] = "";
     if (runs_as_step(ctx))
         snprintf(d, sizeof d, pl.pf_groups > 1 ? "step_kernel_groups<%d, %d>" : pl.lean ? "step_kernel_lean<%d>" : coop ? "step_kernel<%d, %d, true>" : "step_kernel<%d, %d, false>", ctx->hd,
@@ -1482,16 +1492,16 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
     else if (dec && pf && pl.dec_cus > 0)
         snprintf(d, sizeof d, "mixed_kernel<%d>", ctx->hd);
     else {
-        if (dec && pl.lean)
-            snprintf(d, sizeof d, "decode_kernel_lean<%d>", ctx->hd);
-        else if (dec && coop)
-            snprintf(d, sizeof d, pl.coop_waves == 8 ? "decode_coop_kernel<%d, %d, 8>" : "decode_coop_kernel<%d, %d>", ctx->hd, nbi);
+        if (dec && coop)
+            snprintf(d, sizeof d, "decode_coop_kernel%s<%d, %d>", pl.coop_waves == 8 ? "_groups" : general ? "_general" : "", ctx->hd, nbi);
+        else if (dec && lean)
+            snprintf(d, sizeof d, "decode_kernel_lean%s<%d>", general ? "_general" : "", ctx->hd);
         else if (dec)
-            snprintf(d, sizeof d, "decode_kernel<%d, %d>", ctx->hd, nbi);
-        if (pf && pl.lean && pl.pf_waves == 8)
-            snprintf(f, sizeof f, "prefill_kernel_lean<%d>", ctx->hd);
+            snprintf(d, sizeof d, "decode_kernel%s<%d, %d>", general ? "_general" : "", ctx->hd, nbi);
+        if (pf && (pl.pf_groups > 1 || (lean && pl.pf_waves == 8)))
+            snprintf(f, sizeof f, pl.pf_groups > 1 ? "prefill_kernel_groups<%d>" : "prefill_kernel_lean<%d>", ctx->hd);
         else if (pf)
-            snprintf(f, sizeof f, pl.pf_groups > 1 ? "prefill_kernel<%d, %d, %d>" : "prefill_kernel<%d, %d>", ctx->hd, pl.pf_waves, pl.pf_groups);
+            snprintf(f, sizeof f, "prefill_kernel<%d, %d>", ctx->hd, pl.pf_waves);
     }
     snprintf(names, cap, "%s%s%s", d, d[0] && f[0] ? ";" : "", f);
     return OOCO_OK;
@@ -1539,9 +1549,7 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
 
     // The cumulative arrays ride in the kernel arguments; only very large batches need a copy.
     const size_t n_cum = (size_t)num_seqs + 1, n_pf = pl.pf_size;
-    // (the mixed kernel, pl.dec_cus > 0, takes both arrays at once; the two separate kernels one each)
-    const bool inline_cum = pl.dec_cus > 0 ? n_cum + n_pf <= (size_t)kInlineSeqs + 1
-                                           : n_cum <= (size_t)kInlineSeqs + 1 && n_pf <= (size_t)kInlineSeqs + 1;
+    const bool inline_cum = plan_in_args(pl);
     if (!inline_cum && ctx->plan_dirty) {
         if (ctx->upload_pending) (void)hipEventSynchronize(ctx->upload_done);
         memcpy(ctx->plan_h, pl.dcum, n_cum * sizeof(int32_t));

@@ -729,10 +729,15 @@ __global__ __launch_bounds__(64, 2) void decode_kernel_general(const KernArgs a)
 // The same kernel within 160 registers per wave (one KV block per step, one part per merge round trip), for
 // batches whose prefill workgroups need the rest of the register file: a SIMD then holds one decode wave beside
 // two prefill waves of 176 registers.
-template <int HD, bool GENERAL>
+template <int HD>
 __global__ __launch_bounds__(64, 3) void decode_kernel_lean(const KernArgs a)
 {
-    decode_kernel_body<HD, 1, 1, GENERAL>(a);
+    decode_kernel_body<HD, 1, 1, false>(a);
+}
+template <int HD>
+__global__ __launch_bounds__(64, 3) void decode_kernel_lean_general(const KernArgs a)
+{
+    decode_kernel_body<HD, 1, 1, true>(a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -898,7 +903,7 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, int cum_head, i
 }
 
 template <int HD, int NBI, int NWV, bool DEV>
-__global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs a)
+OOCO_DEV void decode_coop_kernel_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
     __shared__ __align__(16) float lds[kCoopFloats<HD, NWV>];
@@ -916,6 +921,21 @@ __global__ __launch_bounds__(NWV * 64, 2) void decode_coop_kernel(const KernArgs
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0) trace[3] = wall_clock64();
     }
+}
+template <int HD, int NBI>
+__global__ __launch_bounds__(256, 2) void decode_coop_kernel(const KernArgs a)
+{
+    decode_coop_kernel_body<HD, NBI, 4, false>(a);
+}
+template <int HD, int NBI>
+__global__ __launch_bounds__(256, 2) void decode_coop_kernel_general(const KernArgs a)   // a plan in device memory
+{
+    decode_coop_kernel_body<HD, NBI, 4, true>(a);
+}
+template <int HD, int NBI>
+__global__ __launch_bounds__(512, 2) void decode_coop_kernel_groups(const KernArgs a)   // eight waves, beside key groups
+{
+    decode_coop_kernel_body<HD, NBI, 8, false>(a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1630,8 +1650,8 @@ OOCO_DEV void prefill_args(const AttnParams &p)
                  "s"(p.total_q), "s"(p.scale_log2e), "s"((int)p.pf_table), "s"((int)p.g_magic), "s"((int)p.list_by_seq));
 }
 
-template <int HD, int NW, int KG = 1>
-__global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs a)
+template <int HD, int NW, int KG>
+OOCO_DEV void prefill_kernel_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
     int tile_word = row_word(a);
@@ -1653,6 +1673,16 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs
         __syncthreads();
         if (threadIdx.x == 0) trace[3] = wall_clock64();
     }
+}
+template <int HD, int NW>
+__global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs a)
+{
+    prefill_kernel_body<HD, NW, 1>(a);
+}
+template <int HD>
+__global__ __launch_bounds__(512, 1) void prefill_kernel_groups(const KernArgs a)
+{
+    prefill_kernel_body<HD, 8, kKeyGroups>(a);
 }
 
 // Eight waves, 256 query columns, no software pipeline, at most 176 registers per wave: the prefill kernel of
@@ -2131,29 +2161,30 @@ hipError_t launch_decode(const KernArgs &a, hipStream_t s)
     if (a.p.static_runs <= 0 || a.p.dec_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)((int64_t)a.p.static_runs * a.p.Hkv)), block(64);
     if (a.p.coop) {
-        auto launch = [&](auto dev) {
-            constexpr bool DEV = decltype(dev)::value;
-            if (a.p.coop_waves == 8 && a.p.hd == 128)
-                hipLaunchKernelGGL((decode_coop_kernel<128, 2, 8, DEV>), grid, dim3(512), 0, s, a);
-            else if (a.p.coop_waves == 8)
-                hipLaunchKernelGGL((decode_coop_kernel<64, 4, 8, DEV>), grid, dim3(512), 0, s, a);
-            else if (a.p.hd == 128)
-                hipLaunchKernelGGL((decode_coop_kernel<128, 2, 4, DEV>), grid, dim3(256), 0, s, a);
+        if (a.p.coop_waves == 8) {   // (planned for batches whose arrays fit the arguments only)
+            if (a.p.cum_dev) return hipErrorInvalidValue;
+            if (a.p.hd == 128)
+                hipLaunchKernelGGL((decode_coop_kernel_groups<128, 2>), grid, dim3(512), 0, s, a);
             else
-                hipLaunchKernelGGL((decode_coop_kernel<64, 4, 4, DEV>), grid, dim3(256), 0, s, a);
-        };
-        if (a.p.cum_dev)
-            launch(std::true_type());
-        else
-            launch(std::false_type());
+                hipLaunchKernelGGL((decode_coop_kernel_groups<64, 4>), grid, dim3(512), 0, s, a);
+        } else if (a.p.cum_dev) {
+            if (a.p.hd == 128)
+                hipLaunchKernelGGL((decode_coop_kernel_general<128, 2>), grid, dim3(256), 0, s, a);
+            else
+                hipLaunchKernelGGL((decode_coop_kernel_general<64, 4>), grid, dim3(256), 0, s, a);
+        } else if (a.p.hd == 128) {
+            hipLaunchKernelGGL((decode_coop_kernel<128, 2>), grid, dim3(256), 0, s, a);
+        } else {
+            hipLaunchKernelGGL((decode_coop_kernel<64, 4>), grid, dim3(256), 0, s, a);
+        }
         return hipGetLastError();
     }
     const bool general = a.p.tail_runs > 0 || a.p.xcd_cw[kXcds - 1] != 0 || a.p.cum_dev;
     if (a.p.lean && a.p.hd == 128) {
         if (general)
-            hipLaunchKernelGGL((decode_kernel_lean<128, true>), grid, block, 0, s, a);
+            hipLaunchKernelGGL((decode_kernel_lean_general<128>), grid, block, 0, s, a);
         else
-            hipLaunchKernelGGL((decode_kernel_lean<128, false>), grid, block, 0, s, a);
+            hipLaunchKernelGGL((decode_kernel_lean<128>), grid, block, 0, s, a);
         return hipGetLastError();
     }
     // KV blocks per softmax step: a wave keeps one step's tiles in flight, and 8 KiB per wave is what it takes
@@ -2202,9 +2233,9 @@ hipError_t launch_prefill(const KernArgs &a, hipStream_t s)
     const dim3 grid = a.p.pf_table ? dim3((unsigned)a.p.Hkv, (unsigned)a.p.pf_table)
                                    : dim3((unsigned)((int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1)));
     if (a.p.pf_groups > 1 && a.p.hd == 128)
-        hipLaunchKernelGGL((prefill_kernel<128, 8, kKeyGroups>), grid, dim3(512), 0, s, a);
+        hipLaunchKernelGGL((prefill_kernel_groups<128>), grid, dim3(512), 0, s, a);
     else if (a.p.pf_groups > 1)
-        hipLaunchKernelGGL((prefill_kernel<64, 8, kKeyGroups>), grid, dim3(512), 0, s, a);
+        hipLaunchKernelGGL((prefill_kernel_groups<64>), grid, dim3(512), 0, s, a);
     else if (a.p.hd == 128 && a.p.pf_waves == 8 && a.p.lean)
         hipLaunchKernelGGL((prefill_kernel_lean<128>), grid, dim3(512), 0, s, a);
     else if (a.p.hd == 128 && a.p.pf_waves == 8)

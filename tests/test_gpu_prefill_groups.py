@@ -114,7 +114,7 @@ def test_more_parts_than_sixteen_and_a_small_workspace(heads, rows, ctx):
     want = ref_c.attn_mixed(b.q, b.k_cache, b.v_cache, b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)
     with B.Context(*heads, 16, b.num_blocks, b.max_blocks_per_seq) as ctx_:
         ctx_.plan(b.seq_lens, b.query_start_loc, b.ctx_lens)
-        assert ctx_.plan_info()["prefill_parts"] > 16 and ctx_.plan_kernels() == [f"prefill_kernel<{heads[2]}, 8, 4>"]
+        assert ctx_.plan_info()["prefill_parts"] > 16 and ctx_.plan_kernels() == [f"prefill_kernel_groups<{heads[2]}>"]
         say(f"case: {heads} {rows} rows on {ctx} tokens, {ctx_.plan_info()}")
         outs = [run_gpu(b, ctx=ctx_) for _ in range(3)]       # (the arrival counters are clean for every call)
     assert_parity(outs[0], want, "many parts")
