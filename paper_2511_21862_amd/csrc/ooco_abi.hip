@@ -124,7 +124,7 @@ struct HostPlan {
     bool near = false;           // step kernel: AttnParams::dec_near
     int32_t coop = 0;            // decode runs are worked on by workgroups of four waves (decode_coop_kernel); kCoopBySequence: run i is sequence i
     int32_t coop_waves = 4;      // waves of such a workgroup
-    int32_t pf_units = 0;        // key groups beside decode work: the compute units that the prefill workgroups take
+    int32_t pf_units = 0;        // key groups beside decode work in one launch: the compute units that the prefill workgroups take
     int32_t nbi = 0;             // KV blocks per softmax step of the decode kernel that the plan asks for (0 = the kernel's default)
 };
 
@@ -865,7 +865,11 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         plan_prefill_parts(geo, facts, store.pf + (2 * (size_t)out.num_pf + 1), out);
     }
     if (pf_first) {
-        out.pf_units = (int32_t)(out.pf_table ? (int64_t)out.pf_table * geo.Hkv : tiles * geo.Hkv * out.pf_split);
+        // (where the arrays do not fit the kernel arguments together the parts run as two kernels, which have all units each:
+        // ooco_attn_mixed_static, 16/1 heads, 159 decodes of 60..124 tokens beside 245 chunks of 2..4 rows on 1000..2500,
+        // decode runs for the units that are left -> for all: 101 -> 47 us; four-wave prefill workgroups 56)
+        if ((size_t)num_seqs + 1 + out.pf_size <= (size_t)kInlineSeqs + 1)
+            out.pf_units = (int32_t)(out.pf_table ? (int64_t)out.pf_table * geo.Hkv : tiles * geo.Hkv * out.pf_split);
         plan_decode();
     }
     return OOCO_OK;

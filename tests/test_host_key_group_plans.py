@@ -48,3 +48,38 @@ def test_random_plans_fit_the_workspace_and_cover_every_block():
         for i in range(len(q) - n, len(q)):
             mine = sorted((int(p[1]), int(p[2])) for p in r["decode_pieces"] if p[0] == i)
             assert mine[0][0] == 0 and mine[-1][1] == (c[i] + 16) // 16 and all(a[1] == b[0] for a, b in zip(mine, mine[1:]))
+
+
+# 16/1 heads: chunks of a tile each; arrays of num_seqs + 1 and 2 * chunks + 1 + tiles entries, together up to 961
+def two_kernels(chunks, decodes):
+    return [3] * chunks + [1] * decodes, [1500 - 7 * i % 500 for i in range(chunks)] + [60 + 9 * i % 300 for i in range(decodes)]
+
+
+@pytest.mark.parametrize("chunks,decodes,fit", [(180, 239, True), (180, 240, False), (235, 159, False)])
+def test_decode_runs_of_plans_in_two_kernels_are_those_of_all_units(chunks, decodes, fit):
+    q, c = two_kernels(chunks, decodes)
+    r, four = (dry((16, 1, 128), q, c, prefill_split=groups + 1, workspace=32 << 20) for groups in (AUTO, 0))
+    assert chunks + decodes + 1 + 3 * chunks + 1 <= 961 if fit else chunks + decodes + 1 + 3 * chunks + 1 > 961
+    assert r["decode_runs"] == 256 - chunks if fit else (r["decode_pieces"] == four["decode_pieces"]).all()
+
+
+@pytest.mark.gpu
+def test_two_kernels_beside_key_groups():
+    import torch
+    from gpu_util import assert_parity, device_meta, run_gpu, say
+    from oracle import ref_c
+    from paper_2511_21862_amd import workloads as W
+    q, c = two_kernels(235, 159)
+    b = W.build_batch(Hq=16, Hkv=1, hd=128, q_lens=q, ctx_lens=c, num_blocks=sum((x + y + 15) // 16 for x, y in zip(q, c)) + 5, seed=92,
+                      poison=True)
+    want = ref_c.attn_mixed(b.q, b.k_cache, b.v_cache, b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)
+    d, meta = W.to_device(b), device_meta(b)
+    say("case: static entry, arrays too large for one launch")
+    out = torch.full((b.total_q, b.Hq, b.hd), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.ooco_attn_mixed_static(16, 1, 128, 16, b.max_blocks_per_seq, 0.0, b.seq_lens, b.query_start_loc, b.ctx_lens, d.q, d.k_cache, d.v_cache,
+                             *meta, out, b.num_seqs, b.total_q)
+    torch.cuda.synchronize()
+    assert_parity(out.view(torch.int16).cpu().numpy().view(np.uint16), want, "static")
+    for opts in ({}, {"prefill_groups": 4}, {"prefill_split": 1}):
+        say(f"case: plan {opts}")
+        assert_parity(run_gpu(b, options=opts), want, str(opts))
