@@ -611,7 +611,11 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
 //     With eight steps or more that chain decides the time also where the decode sequences have to share the units that
 //     are left (120 batches of ooco_attn_mixed_static with more sequences than units: 48 taken, 0.61 of the time; us: 59
 //     decodes of up to 1534 tokens beside 53 + 65 rows on 4728, 28/4 heads 95 -> 58; 128 beside 61 + 76 on 4518 107 -> 55;
-//     with three or four steps 13.8 -> 15.8 .. 17.8, as they then wait for one another).
+//     with three or four steps 13.8 -> 15.8 .. 17.8, as they then wait for one another).  Where the decode part is the longer
+//     one (54 batches at that edge, 0.78 of the time), it also takes ten steps at head_dim 128 (eight and nine: 0.85 .. 1.10,
+//     us: 156 of up to 294 tokens beside 21 + 16 rows on 970, 28/4 heads 24.3 -> 26.6), and units enough that the decode part
+//     takes less than 1.5 times as long as on all of them (71 on the 40 that 55 + 69 + 83 rows on 1700 leave, 64/8 heads 42.6
+//     -> 50.0).
 bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_lens, const int32_t *h_query_start_loc)
 {
     const int64_t g = geo.Hq / geo.Hkv, rows = prefill_tile_rows((int32_t)g, 8 / kKeyGroups);
@@ -654,6 +658,8 @@ bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_
         const double chain = (double)((longest + parts - 1) / parts), merge = parts > 1 ? 1.0 : 0.0, k = (double)parts;
         const double pf = geo.hd == 128 ? 8.0 + 1.2 * chain + merge * (2.0 + 0.3 * k) : 5.6 + 0.9 * chain + merge * (1.5 + 0.2 * k);
         if (dec_left > 1.35 * std::max(dec_all, pf) || pf < 0.7 * dec_all) return false;
+        const bool shared_units = units + n_dec * geo.Hkv > cus;
+        if (shared_units && dec_left > pf && (dec_left > 1.5 * dec_all || (geo.hd == 128 && longest < 10))) return false;
         if (!whole && parts == 1 && longest > 16) return false;   // (no unit left to cut a long tile)
     }
     return whole || load <= 10 * cus || (load <= 25 * cus && 4 * units <= cus && (widest <= rows || cover <= 1.2 * used));

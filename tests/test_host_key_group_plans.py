@@ -50,6 +50,17 @@ def test_random_plans_fit_the_workspace_and_cover_every_block():
             assert mine[0][0] == 0 and mine[-1][1] == (c[i] + 16) // 16 and all(a[1] == b[0] for a, b in zip(mine, mine[1:]))
 
 
+@pytest.mark.parametrize("heads,chunks,cached,decodes,longest,taken", [
+    ((32, 8, 128), [6], 1057, 42, 850, False), ((32, 8, 128), [6], 1250, 42, 850, True), ((32, 4, 64), [6], 1057, 84, 850, True),
+    ((28, 4, 128), [21, 16], 970, 156, 290, False), ((28, 4, 128), [21, 16], 970, 120, 200, True),
+    ((64, 8, 128), [55, 69, 83], 1700, 71, 118, False), ((64, 8, 128), [15, 19, 13], 1700, 71, 118, True)])
+def test_key_groups_whose_decode_part_would_be_the_longer_one(heads, chunks, cached, decodes, longest, taken):
+    # whole tiles beside more decode sequences than units: chains of eight and nine steps, and of more with few units left
+    q, c = chunks + [1] * decodes, [cached] * len(chunks) + [longest // 4 + i * longest * 3 // (4 * decodes) for i in range(decodes)]
+    plans = [dry(heads, q, c, prefill_split=split)["decode_pieces"].tolist() for split in (AUTO + 1, 1)]
+    assert (plans[0] != plans[1]) == taken
+
+
 # 16/1 heads: chunks of a tile each; arrays of num_seqs + 1 and 2 * chunks + 1 + tiles entries, together up to 961
 def two_kernels(chunks, decodes):
     return [3] * chunks + [1] * decodes, [1500 - 7 * i % 500 for i in range(chunks)] + [60 + 9 * i % 300 for i in range(decodes)]
