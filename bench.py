@@ -413,10 +413,14 @@ def wg_timeline(ctx, b, run_step, torch, reps=5):
     over `reps` launches of every figure, in microseconds from the first workgroup's start."""
     from paper_2511_21862_amd import binding as B
 
+    run_step()
+    # workgroups of four waves: steps of 64 keys, two to a compute unit; of key groups: 128 keys, one to a unit
+    groups = any("groups" in k for k in ctx.plan_kernels())
+    step_keys, per_cu = (128, 1) if groups else (64, 2)
     tiles = B.ooco_plan_dry_run(b.Hq, b.Hkv, b.hd, b.BS, b.max_blocks_per_seq, torch.cuda.get_device_properties(0).multi_processor_count,
                                 512 << 20, h_seq_lens=b.seq_lens, h_query_start_loc=b.query_start_loc,
-                                h_ctx_lens=b.ctx_lens)["prefill_tiles"]
-    steps_tile = (tiles[:, 3] + tiles[:, 2] + 63) // 64
+                                h_ctx_lens=b.ctx_lens, prefill_groups=4 if groups else 1)["prefill_tiles"]
+    steps_tile = (tiles[:, 3] + tiles[:, 2] + step_keys - 1) // step_keys
     ctx.set_option("trace", 1)
     rows = []
     for _ in range(reps):
@@ -432,8 +436,8 @@ def wg_timeline(ctx, b, run_step, torch, reps=5):
         # (with split tiles the list holds (tile, part) entries in an order of its own: no per-workgroup steps then, -1)
         steps = np.repeat(steps_tile, n // len(steps_tile)) if n == len(steps_tile) * b.Hkv else np.full(n, -1.0)
         r = {"workgroups": n, "compute_units": int(len(np.unique(cu))), "span_us": float(t1.max()),
-             "all_first_round_started_by_us": float(np.sort(t0)[min(n, 2 * len(np.unique(cu))) - 1]),
-             "slot_busy_us_mean": float((t1 - t0).sum() / (2 * len(np.unique(cu)))),
+             "all_first_round_started_by_us": float(np.sort(t0)[min(n, per_cu * len(np.unique(cu))) - 1]),
+             "slot_busy_us_mean": float((t1 - t0).sum() / (per_cu * len(np.unique(cu)))),
              "steps_total": int(steps_tile.sum()) * b.Hkv}
         ends = np.array([t1[cu == c].max() for c in np.unique(cu)])
         r["cu_last_end_us_min_mean_max"] = [float(ends.min()), float(ends.mean()), float(ends.max())]
@@ -449,8 +453,8 @@ def wg_timeline(ctx, b, run_step, torch, reps=5):
         x = raw[:, 2].astype(np.uint64)
         ph = np.stack([((x >> np.uint64(16 * k)) & np.uint64(0xFFFF)).astype(np.float64) / 100.0 for k in range(4)], axis=1)
         order = np.argsort(t0, kind="stable")
-        first = order[: min(n, 2 * len(np.unique(cu)))]
-        later = order[min(n, 2 * len(np.unique(cu))):]
+        first = order[: min(n, per_cu * len(np.unique(cu)))]
+        later = order[min(n, per_cu * len(np.unique(cu))):]
         for name, idx in (("first_round", first), ("later_rounds", later)):
             idx = idx[x[idx] != 0]
             if len(idx):

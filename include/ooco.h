@@ -271,15 +271,16 @@ ooco_status ooco_plan(ooco_ctx *ctx, int num_seqs, const int32_t *h_seq_lens /*H
  *     -1 when the piece covers the whole sequence and writes the output directly
  *   prefill_tiles_out: HOST int32 [prefill_cap][5] = (seq, q_row0, rows, pos0, parts), in the order in which
  *     the tiles (their first parts) are dispatched; a tile holds up to 128 / (num_q_heads/num_kv_heads) query rows
- *     (256 / ... in the eight-wave kernel) and runs once per kv head; parts = workgroups its key range is cut into
+ *     (256 / ... in the eight-wave kernel, 64 / ... in workgroups of key groups) and runs once per kv head; parts =
+ *     workgroups its key range is cut into
  *   counts: HOST int64 [6] = (decode pieces, prefill tiles, static decode runs, partial-result
  *     slots, dynamically fetched tail runs, the most parts a prefill tile's key range is cut into);
  *     runs are numbered static first, then tail
  *   msg: HOST buffer of msg_cap bytes receiving the error text.  Any output pointer may be NULL.
  *   xcd_weights: NULL for equal static runs, else the relative run lengths per XCD that option
  *     "xcd_weights" would set (static run v then belongs to XCD v % 8).
- *   prefill_split: what option "prefill_split" would set (0 = automatic), in the low 16 bits; what option
- *     "prefill_groups" would set above them, 0 standing for 1 here (workgroups of four waves) and 15 for automatic.
+ *   prefill_split: what option "prefill_split" would set (0 = automatic) in the low 32 bits, and above them what option
+ *     "prefill_groups" would set: 0 (automatic, as in a context), 1 or 4; other values -> OOCO_EINVAL.
  *   decode_piece_pad: what option "decode_piece_pad" would set; negative = the default. */
 ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, int block_size,
                               int max_blocks_per_seq, int num_cus, size_t workspace_bytes,

@@ -1402,9 +1402,12 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
         geo.segments_opt = decode_segments;
         geo.tail_pct = decode_tail_pct;
         geo.tail_blocks = decode_tail_blocks;
-        const int64_t groups = prefill_split >> 16;
-        geo.pf_groups_opt = groups == 15 ? 0 : groups == kKeyGroups ? kKeyGroups : 1;
-        geo.pf_split_opt = prefill_split & 0xFFFF;
+        geo.pf_groups_opt = prefill_split >> 32;
+        geo.pf_split_opt = prefill_split & 0xFFFFFFFF;
+        if (geo.pf_groups_opt != 0 && geo.pf_groups_opt != 1 && geo.pf_groups_opt != kKeyGroups) {
+            snprintf(err, sizeof err, "ooco_plan_dry_run: prefill groups (above bit 32 of prefill_split) must be 0 (automatic), 1 or 4");
+            st = OOCO_EINVAL;
+        }
         geo.lean_opt = 1;   // (the default of a context)
         geo.piece_pad = decode_piece_pad;
         if (xcd_weights && !xcd_weights_to_cw(xcd_weights, geo.xcd_cw)) {

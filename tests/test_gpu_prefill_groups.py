@@ -8,7 +8,7 @@ from paper_2511_21862_amd import binding as B
 from paper_2511_21862_amd import workloads as W
 
 HEADS = [(32, 8, 128), (28, 4, 128), (16, 1, 128), (4, 4, 128), (32, 4, 64), (4, 1, 64)]
-FORCED, AUTO = 4 << 16, 15 << 16          # "prefill_groups" in the dry run's prefill_split
+FORCED, AUTO = 4 << 32, 0          # "prefill_groups" in the dry run's prefill_split
 
 
 def dry(heads, q_lens, ctx_lens, **kw):
@@ -31,7 +31,7 @@ def test_tiles_of_64_columns_cover_every_row_once(heads):
                 mine = mine[np.argsort(mine[:, 1])]
                 assert mine[:, 2].sum() == n and (mine[:, 3] == cx + np.r_[0, np.cumsum(mine[:-1, 2])]).all()
                 steps = (mine[:, 3] + mine[:, 2] + 127) // 128
-                if split >> 16 == 4:
+                if split >> 32 == 4:
                     assert (mine[:-1, 2] == rows).all() and (mine[:, 4] >= 1).all() and (mine[:, 4] <= np.minimum(steps, 64)).all()
                     assert parts == 0 or (mine[:, 4] == np.minimum(parts, steps)).all()
             # the parts fit the units, and the workspace bounds them
@@ -45,7 +45,7 @@ def test_tiles_of_64_columns_cover_every_row_once(heads):
 def test_key_groups_are_planned_where_they_pay():
     rows4 = lambda q, c, heads=(32, 8, 128), **kw: int(dry(heads, q, c, prefill_split=AUTO, **kw)["prefill_tiles"][:, 2].max())
     # the dry run without them keeps the four-wave tiles
-    assert dry((32, 8, 128), [40], [1000])["prefill_tiles"][:, 2].max() == 32
+    assert dry((32, 8, 128), [40], [1000], prefill_groups=1)["prefill_tiles"][:, 2].max() == 32
     assert rows4([40], [1000]) == 16
     # three steps (head_dim 64: two) at least, at most one workgroup per unit
     assert rows4([40], [216]) == 32 and rows4([40], [217]) == 16

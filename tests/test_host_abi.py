@@ -270,7 +270,8 @@ def test_small_workspace_reduces_the_number_of_runs():
 
 
 def prefill_parts(n, c, prior, **kw):
-    return dry([prior + c] * n, [i * c for i in range(n + 1)], [prior] * n, **kw)["prefill_parts"]
+    """Parts of the longest tile of four-wave workgroups."""
+    return dry([prior + c] * n, [i * c for i in range(n + 1)], [prior] * n, prefill_groups=1, **kw)["prefill_parts"]
 
 
 def test_prefill_tiles_are_split_only_when_the_batch_cannot_occupy_the_gpu():
@@ -337,7 +338,7 @@ def test_planned_parts_match_the_measured_best_on_the_profiled_batches():
         ql, cx = np.asarray(ql, np.int32), np.asarray(cx, np.int32)
         qsl = np.zeros(len(ql) + 1, np.int32)
         qsl[1:] = np.cumsum(ql)
-        t = dry(cx + ql, qsl, cx)["prefill_tiles"]
+        t = dry(cx + ql, qsl, cx, prefill_groups=1)["prefill_tiles"]      # (measured with workgroups of four waves)
         return {int(i): sorted(set(t[t[:, 0] == i][:, 4].tolist())) for i in np.flatnonzero(ql > 1)}, int(t[:, 2].max())
     for (n, c, pc), want in (((1, 128, 8192), 8), ((1, 128, 32768), 16), ((4, 128, 8192), 4), ((1, 512, 8192), 4),
                              ((2, 512, 4096), 2), ((2, 512, 1000), 1), ((8, 128, 2048), 1), ((10, 128, 8192), 1),

@@ -1,11 +1,11 @@
-"""Plans of key groups beside decode work (CPU: the planner's dry run): what the kernels will write of partial results lies
-inside the workspace, whatever "decode_segments" asks for."""
+"""Plans of key groups (CPU: the planner's dry run): the dry run is what a context plans, and what the kernels will write of
+partial results lies inside the workspace, whatever "decode_segments" asks for."""
 import numpy as np
 import pytest
 
 from paper_2511_21862_amd import binding as B
 
-FORCED, AUTO = 4 << 16, 15 << 16          # "prefill_groups" in the dry run's prefill_split
+FORCED, OFF, AUTO = 4 << 32, 1 << 32, 0          # "prefill_groups" in the dry run's prefill_split
 
 
 def dry(heads, q_lens, ctx_lens, **kw):
@@ -57,8 +57,41 @@ def test_random_plans_fit_the_workspace_and_cover_every_block():
 def test_key_groups_whose_decode_part_would_be_the_longer_one(heads, chunks, cached, decodes, longest, taken):
     # whole tiles beside more decode sequences than units: chains of eight and nine steps, and of more with few units left
     q, c = chunks + [1] * decodes, [cached] * len(chunks) + [longest // 4 + i * longest * 3 // (4 * decodes) for i in range(decodes)]
-    plans = [dry(heads, q, c, prefill_split=split)["decode_pieces"].tolist() for split in (AUTO + 1, 1)]
+    plans = [dry(heads, q, c, prefill_split=split)["decode_pieces"].tolist() for split in (AUTO + 1, OFF + 1)]
     assert (plans[0] != plans[1]) == taken
+
+
+def test_the_dry_run_takes_key_groups_as_a_context_does():
+    rows = lambda **kw: int(dry((32, 8, 128), [40], [1000], **kw)["prefill_tiles"][:, 2].max())
+    assert rows() == rows(prefill_groups=0) == rows(prefill_groups=4) == 16 and rows(prefill_groups=1) == 32
+    assert rows(prefill_split=70000) == 32          # (forced parts: four waves, however many are asked for)
+    for groups in (2, 3, 5, 15, 1 << 20):
+        with pytest.raises(B.OocoError) as e:
+            rows(prefill_groups=groups)
+        assert e.value.status == B.OOCO_EINVAL
+
+
+@pytest.mark.gpu
+def test_the_dry_run_is_what_a_context_plans():
+    import torch
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(20257)
+    for case in range(150):
+        heads = [(32, 8, 128), (28, 4, 128), (64, 8, 128), (16, 1, 128), (32, 4, 64), (4, 1, 64)][rng.integers(6)]
+        q = [int(x) for x in np.exp(rng.uniform(np.log(2), np.log(600), size=rng.integers(0, 4)))] + [1] * int(rng.integers(0, 60))
+        q = np.asarray(q or [1], np.int32)
+        c = (2.0 ** rng.uniform(2, 14, size=len(q))).astype(np.int32)
+        args = q + c, np.r_[0, np.cumsum(q)].astype(np.int32), c
+        opts = dict(prefill_groups=int(rng.choice([0, 0, 1, 4])), prefill_split=int(rng.choice([0, 0, 1, 3])),
+                    decode_segments=int(rng.choice([0, 0, 20])))
+        r = B.ooco_plan_dry_run(*heads, 16, 2048, units, 128 << 20, *args, **opts)
+        with B.Context(*heads, 16, 64, 2048) as ctx:
+            for k, v in opts.items():
+                ctx.set_option(k, v)
+            ctx.plan(*args)
+            info = ctx.plan_info()
+        got = (info["decode_waves"], info["prefill_tiles"], info["prefill_parts"])
+        assert got == (r["decode_runs"], len(r["prefill_tiles"]), r["prefill_parts"]), (case, heads, q, c, opts)
 
 
 # 16/1 heads: chunks of a tile each; arrays of num_seqs + 1 and 2 * chunks + 1 + tiles entries, together up to 961
@@ -69,7 +102,7 @@ def two_kernels(chunks, decodes):
 @pytest.mark.parametrize("chunks,decodes,fit", [(180, 239, True), (180, 240, False), (235, 159, False)])
 def test_decode_runs_of_plans_in_two_kernels_are_those_of_all_units(chunks, decodes, fit):
     q, c = two_kernels(chunks, decodes)
-    r, four = (dry((16, 1, 128), q, c, prefill_split=groups + 1, workspace=32 << 20) for groups in (AUTO, 0))
+    r, four = (dry((16, 1, 128), q, c, prefill_split=groups + 1, workspace=32 << 20) for groups in (AUTO, OFF))
     assert chunks + decodes + 1 + 3 * chunks + 1 <= 961 if fit else chunks + decodes + 1 + 3 * chunks + 1 > 961
     assert r["decode_runs"] == 256 - chunks if fit else (r["decode_pieces"] == four["decode_pieces"]).all()
 

@@ -99,9 +99,9 @@ def test_lines_with_larger_pads_cover_every_block_once(heads, workspace):
 
 def test_prefill_parts_hidden_behind_a_long_decode_part_stay_few():
     dec = [2250] * 48
-    alone = dry((32, 8, 128), [60] * 4, [1500] * 4)["prefill_parts"]
-    beside = dry((32, 8, 128), [60] * 4 + [1] * 48, [1500] * 4 + dec)["prefill_parts"]
-    few = dry((32, 8, 128), [60] * 4 + [1] * 8, [1500] * 4 + dec[:8])["prefill_parts"]
+    alone = dry((32, 8, 128), [60] * 4, [1500] * 4, prefill_groups=1)["prefill_parts"]
+    beside = dry((32, 8, 128), [60] * 4 + [1] * 48, [1500] * 4 + dec, prefill_groups=1)["prefill_parts"]
+    few = dry((32, 8, 128), [60] * 4 + [1] * 8, [1500] * 4 + dec[:8], prefill_groups=1)["prefill_parts"]
     assert beside < min(alone, few)
     # ... but a chunk that would outlast the decode part is still cut
     assert dry((32, 8, 128), [100] + [1] * 48, [10000] + dec)["prefill_parts"] >= 5
