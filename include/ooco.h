@@ -198,6 +198,14 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                loop of calls level (268 / 266, 1630 / 1625), but 340 and 2170 in a context whose side stream shares
  *                a hardware queue with the caller's stream, so that its kernels run in sequence (one or two of eight
  *                contexts made in a row); 2 x 120 rows beside 24 short ones 29 / 45 (37.5 in sequence)
+ *   "prefill_merge_looks"  0..100 (default 12): where all workgroups of a launch find a place on an idle GPU at once, the
+ *                parts of a prefill tile cut into four or more (of four waves) share its merge, and one that ends early
+ *                waits for the last, at most this many looks at the arrival counter of about 2 us each.  It holds its
+ *                place meanwhile; where other streams' work fills the GPU beside such a launch, parts may wait in
+ *                vain for one that has no place yet, no longer than that.  0 = nobody waits, the last part merges
+ *                alone.  Output bits do not depend on it.  MI355X, us, 12 / 0 looks: 300 rows on 14,700 tokens, six
+ *                parts, 85 / 92.5, in turns with 64 decodes on another stream 186 / 193.5 for both; 2 x 74 rows in
+ *                twelve parts 44 / 55, 145 / 156
  *   "decode_first"  0/1 (default 1): with "overlap", enqueue the decode kernel before the prefill
  *                kernel (0: the other way round)
  *   "profile"    0/1: every ooco_attn_mixed records HIP events around its two kernels (each on the

@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libooco.so")
 SOURCES = ["ooco_abi.hip", "ooco_kernels.hip", "ooco_model.hip", "ooco_sort.hip"]
-HEADERS = [os.path.join(CSRC, "ooco_internal.h"), os.path.join(HERE, "..", "include", "ooco.h")]
+HEADERS = [os.path.join(CSRC, "ooco_internal.h"), os.path.join(HERE, "..", "include", "ooco.h"), os.path.join(CSRC, "ooco_arith.h")]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # never let the compiler form packed-fp32 VALU ops

@@ -1038,6 +1038,7 @@ struct ooco_ctx {
     int64_t opt_lean = 1;           // mixed batches: the register-lean kernels (0 never, 1 automatic, 2 always)
     int64_t opt_pf_waves = 0;       // waves per prefill workgroup: 0 = automatic, 4, 8
     int64_t opt_pf_groups = 0;      // key groups per prefill workgroup: 0 = automatic, 1, 4
+    int64_t opt_merge_looks = 12;   // shared merge of a split tile: looks at the counter before an early part leaves
     int64_t opt_fused = 0;          // mixed batches in one launch (mixed kernel) instead of two kernels on two streams
     int64_t opt_coop = 1;           // cooperative decode workgroups (0 never, 1 by rule, 2 always)
     int64_t opt_step = 1;           // mixed batches in one launch of the step kernel (0 never, 1 by rule, 2 whenever it takes the plan)
@@ -1302,6 +1303,10 @@ ooco_status ooco_set_option(ooco_ctx *ctx, const char *name, int64_t value)
         return OOCO_OK;
     } else if (!strcmp(name, "overlap")) {
         ctx->opt_overlap = value;
+        return OOCO_OK;
+    } else if (!strcmp(name, "prefill_merge_looks")) {
+        if (value > 100) return fail(ctx, OOCO_EINVAL, "ooco_set_option: prefill_merge_looks must be 0..100");
+        ctx->opt_merge_looks = value;
         return OOCO_OK;
     } else if (!strcmp(name, "mixed_step")) {
         ctx->opt_step = value;
@@ -1684,7 +1689,7 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     // A split tile's merge is shared among its parts where all workgroups of the launch find a place at once (launch_step adds
     // its decode workgroups): two of four waves per compute unit.
     const int64_t pf_wgs = pl.pf_table ? (int64_t)pl.pf_table * ctx->Hkv : (int64_t)pl.n_tiles * ctx->Hkv * pl.pf_split;
-    p.pf_share = pl.pf_split > 1 && pl.pf_waves == 4 && (step || !mixed) && pf_wgs <= 2 * (int64_t)ctx->num_cus;
+    p.pf_share = pl.pf_split > 1 && pl.pf_waves == 4 && (step || !mixed) && pf_wgs <= 2 * (int64_t)ctx->num_cus ? (int8_t)(1 + ctx->opt_merge_looks) : (int8_t)0;
     auto mark = [&](int k, hipStream_t st) {
         if (ev && e == hipSuccess) e = hipEventRecord(ev[k], st);
     };

@@ -29,6 +29,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ooco_arith.h"
+
 namespace ooco {
 
 constexpr int kBlockSize = 16;      // tokens per KV block (fixed by the cache layout)
@@ -98,7 +100,8 @@ struct AttnParams {
     uint16_t g_magic;           // 32768 / g + 1: c / g = (c * g_magic) >> 15 for c < 512
     int8_t rows2d;              // step kernel: the grid has rows
     int8_t list_by_seq;
-    int8_t pf_share;            // prefill: the parts of a split tile may share its merge (all workgroups of the launch are resident)
+    int8_t pf_share;            // prefill: > 0, the parts of a split tile share its merge (all workgroups of the launch find a
+                                // place at once), and one that ends early waits for pf_share - 1 looks at the counter
 };
 
 // Entry of the tile list: chunk of the prefill array (10 bits), tile of the chunk (10 bits), part (6 bits), parts of

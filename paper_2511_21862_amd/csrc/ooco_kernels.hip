@@ -253,13 +253,9 @@ struct EqualRuns {
         const double r1 = __builtin_fma(__builtin_fma(-d, r0, 1.0), r0, r0);
         return __builtin_fma(__builtin_fma(-d, r1, 1.0), r1, r1);
     }
-    // floor((a * b - c) / n), c = 0 or 1, the quotient below 2^30; wave-uniform
-    static OOCO_DEV int quotient(int a, int b, int c, int n, double inv)
+    static OOCO_DEV int quotient(int a, int b, int c, int n, double inv)   // wave-uniform
     {
-        int q = (int)(((double)a * (double)b - (double)c) * inv);   // off by one at most
-        const int64_t r = (int64_t)a * b - c - (int64_t)q * n;
-        q += r < 0 ? -1 : r >= n ? 1 : 0;
-        return __builtin_amdgcn_readfirstlane(q);
+        return __builtin_amdgcn_readfirstlane(quotient_by_reciprocal(a, b, c, n, inv));
     }
     OOCO_DEV void bounds(int run, int &lo, int &hi) const
     {
@@ -966,9 +962,7 @@ __global__ __launch_bounds__(512, 2) void decode_coop_kernel_groups(const KernAr
 // 64 KiB LDS each).
 constexpr int kPfThreads = 256;   // threads of the four-wave workgroup (the eight-wave one has 512)
 constexpr int kPfBlocks = 4;    // KV blocks per step
-constexpr int kMergeSlices = 4;        // shared merge of a split tile (see prefill_unit): slices of the dims,
-constexpr int kSharedMergeParts = 4;   // parts from which it pays,
-constexpr int kMergePolls = 12;        // looks at the counter before a part leaves it to the others
+constexpr int kSharedMergeParts = 4;   // parts from which sharing the merge of a split tile pays (see prefill_unit)
 
 // Entry idx of the plan's array: from device memory if the plan did not fit the kernel arguments, else from the
 // argument block.  The two loads must stay two loads: merged into one load through a selected pointer, the argument
@@ -1575,41 +1569,34 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
                 // The merge of a tile of many parts is shared: the parts end within a few microseconds of each other, and one
                 // unit reads 64 KB of partial results in 1.2 us, a part after the other (six parts 8 .. 11 us at the end of
                 // the launch, eleven 15).  So a part that ends early waits, for a bounded time, until the last one has arrived;
-                // the dims fall into kMergeSlices slices, the last part takes the first and whoever is there draws the others.
-                // Only where all workgroups of the launch are resident, so that nobody waits for the place of one that waits.
+                // the dims fall into MergeWord::kSlices slices, the last part takes the first and whoever is there draws the others.
+                // Only where all workgroups of the launch find a place at once, so that nobody waits for the place of one that
+                // waits -- unless another stream's work holds units: hence the bound.
                 // MI355X (us, one merging part -> shared): 11 parts, 2 x 74 rows on 13,000 tokens, 28/4 heads 45.5 -> 42.0; drawn
                 // batches of 5 .. 16 parts 13.0 -> 11.8, 39.2 -> 36.7, 86.0 -> 79.6; six parts of 80 tiles, whose 32 MB of partial
                 // results are a matter of HBM as well, 87.8 -> 86.9.  Eight slices lose half of that; looks at the counter every
                 // 1.2 us instead of 2 slow down the parts that still work (67 -> 70 us for the steps of those six parts).
-                // The counter's bytes: arrivals, draws, parts that left without waiting any longer.  Every part ends with one
-                // event of its own -- a draw that finds no slice, or leaving --, and the last event of all resets the counter:
-                // nobody touches it any more.
-                constexpr int kDraw = 1 << 8, kLeave = 1 << 16, PI = ITEMS / kMergeSlices;
-                static_assert(kMaxPrefillSplit + kMergeSlices < 256, "a byte each");
-                const int events = kMergeSlices - 1 + nparts;
-                auto event = [&](int what) -> int {   // draws and leaves before this one
+                constexpr int PI = ITEMS / MergeWord::kSlices;
+                static_assert(kMaxPrefillSplit + MergeWord::kSlices < 256, "a byte each");
+                auto event = [&](int what) -> int {   // the word that it found
                     const int w = __hip_atomic_fetch_add(counter, what, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const int draws = (w >> 8) & 255, leaves = (w >> 16) & 255;
-                    if (draws + leaves + 1 == events) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    return draws;
+                    if (MergeWord::last_event(w, nparts)) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return w;
                 };
-                auto draw = [&]() -> int {   // the slice, or -1
-                    const int d = event(kDraw);
-                    return d < kMergeSlices - 1 ? d + 1 : -1;
-                };
+                auto draw = [&]() -> int { return MergeWord::slice(event(MergeWord::kDraw)); };
                 if (tid == 0) {
-                    const int w = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int w = __hip_atomic_fetch_add(counter, MergeWord::kArrive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     int mine = 0;
-                    if ((w & 255) != nparts - 1) {
+                    if (!MergeWord::arrived_last(w, nparts)) {
                         bool all = false;
-                        for (int i = 0; i < kMergePolls && !all; ++i) {   // (a load and a pause: 2 us or so)
+                        for (int i = 1; i < p.pf_share && !all; ++i) {   // (a load and a pause: 2 us or so)
                             __builtin_amdgcn_s_sleep(40);
-                            all = (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 255) == nparts;
+                            all = MergeWord::arrivals(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == nparts;
                         }
                         if (all) {
                             mine = draw();
                         } else {
-                            (void)event(kLeave);
+                            (void)event(MergeWord::kLeave);
                             mine = -1;
                         }
                     }
@@ -2258,7 +2245,7 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
     const int64_t pf = a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
                                     : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
     a.p.dec_wgs = (int32_t)dec;
-    a.p.pf_share = a.p.pf_share && dec + pf <= 2 * (int64_t)num_cus;   // (two workgroups of four waves fit a unit)
+    if (dec + pf > 2 * (int64_t)num_cus) a.p.pf_share = 0;   // (two workgroups of four waves fit a unit)
     // rows: the decode runs of cooperative workgroups, then the tile list's entries
     if (a.p.rows2d && (!a.p.coop || !a.p.pf_table || a.p.list_row != a.p.static_runs)) return hipErrorInvalidValue;
     const dim3 grid = a.p.rows2d ? dim3((unsigned)a.p.Hkv, (unsigned)(a.p.static_runs + a.p.pf_table)) : dim3((unsigned)(dec + pf));

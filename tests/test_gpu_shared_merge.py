@@ -1,6 +1,6 @@
 """Split prefill tiles whose parts share the merge: the float64 oracle at the fewest and the most parts, tiles with unused
-columns and parts without visible keys, one bit pattern whoever merges, counters ready for the next call and under replay,
-and a launch too large for it."""
+columns and parts without visible keys, one bit pattern whoever merges -- also where early parts leave at once or after one
+look --, counters ready for the next call and under replay, and a launch too large for it."""
 import numpy as np
 import pytest
 import torch
@@ -32,7 +32,8 @@ def test_parity_and_the_same_bits_every_time(heads, parts):
         ctx.plan(b.seq_lens, b.query_start_loc, b.ctx_lens)
         say(f"case: {heads} {parts} parts {ctx.plan_kernels()}")
         outs = []
-        for _ in range(12):
+        for looks in (12, 0, 12, 1, 0, 1, 100, 0, 3, 12, 12, 12):
+            ctx.set_option("prefill_merge_looks", looks)
             out = torch.full((b.total_q, b.Hq, b.hd), float("nan"), dtype=torch.bfloat16, device="cuda")
             ctx.attn_mixed(d.q, d.k_cache, d.v_cache, *meta, out)
             outs.append(out)
@@ -45,7 +46,7 @@ def test_parity_and_the_same_bits_every_time(heads, parts):
 def test_replays_and_a_launch_that_is_too_large():
     from gpu_util import assert_parity, device_meta, say
     heads = (32, 8, 128)
-    for n, parts in ((2, 8), (12, 6)):                    # 128 workgroups; 576, more than 256 units hold
+    for n, parts, looks in ((2, 8, 12), (2, 8, 0), (2, 8, 1), (12, 6, 12)):      # 128 workgroups; 576, more than 256 units hold
         b = batch(heads, [20] * n, [1500 + 64 * i for i in range(n)], seed=84)
         want = ref_c.attn_mixed(b.q, b.k_cache, b.v_cache, b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)
         d, meta = W.to_device(b), device_meta(b)
@@ -53,8 +54,9 @@ def test_replays_and_a_launch_that_is_too_large():
         with B.Context(*heads, 16, b.num_blocks, b.max_blocks_per_seq) as ctx:
             for k, v in dict(prefill_groups=1, prefill_split=parts, plan_persistent=1).items():
                 ctx.set_option(k, v)
+            ctx.set_option("prefill_merge_looks", looks)
             ctx.plan(b.seq_lens, b.query_start_loc, b.ctx_lens)
-            say(f"case: {n} chunks in {parts} parts {ctx.plan_info()}")
+            say(f"case: {n} chunks in {parts} parts, {looks} looks, {ctx.plan_info()}")
             side = torch.cuda.Stream()
             with torch.cuda.stream(side):
                 ctx.attn_mixed(d.q, d.k_cache, d.v_cache, *meta, out)

@@ -131,23 +131,6 @@ def test_one_long_sequence_among_short_ones_is_not_cut_into_crumbs(heads):
         assert 4 <= parts <= (40 if longest == 8000 else 20), (longest, parts)
 
 
-def test_run_bounds_by_reciprocal_equal_the_divisions():
-    # EqualRuns::quotient of the kernels: floor((a * b - c) / n) by the reciprocal in doubles (up to two units in its last place
-    # off) and one exact correction step, for quotients below 2^30
-    rng = np.random.default_rng(8)
-    n = np.concatenate([np.arange(1, 400), np.exp(rng.uniform(0, np.log(2 ** 30), size=20000)).astype(np.int64)])
-    a = np.minimum(np.exp(rng.uniform(0, np.log(2 ** 30), size=len(n))).astype(np.int64) + 1, 2 ** 30)
-    for b in (np.minimum(n, a), n, np.maximum(1, (n * rng.random(len(n))).astype(np.int64)), np.ones_like(n)):
-        for c in (0, 1):
-            want = np.array([(int(x) * int(y) - c) // int(z) for x, y, z in zip(a, b, n)])
-            for ulp in (-2, 0, 2):
-                inv = 1.0 / n.astype(np.float64)
-                inv = inv + ulp * np.spacing(inv)
-                q = ((a.astype(np.float64) * b.astype(np.float64) - c) * inv).astype(np.int64)
-                r = np.array([int(x) * int(y) - c - int(u) * int(z) for x, y, z, u in zip(a, b, n, q)])
-                assert (q + np.where(r < 0, -1, np.where(r >= n, 1, 0)) == want).all()
-
-
 def test_parts_of_prefill_tiles_at_head_dim_64():
     # 32/4 heads of 64: whole tiles below 16 steps and from two workgroups per unit on, parts in between, never past three
     # workgroups per unit by more than one part per tile
