@@ -59,6 +59,32 @@ def general(monkeypatch):
 
 
 @pytest.mark.gpu
+def test_plain_calls_are_taken():
+    """Every native function accepts its plain form (else both ways below would be the general one), with sizes given and read
+    off the tensors, on the current stream and on one given by its handle."""
+    b = W.config1(poison=True)
+    d = W.to_device(b, "cuda:0")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    tabs = [t(x) for x in (b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)]
+    n, host = len(b.seq_lens), (b.seq_lens, b.query_start_loc, b.ctx_lens)
+    kn = torch.randn(b.total_q, b.Hkv, b.hd, device="cuda").bfloat16()
+    ids, dst = torch.tensor([1, 2, 3], device="cuda"), torch.tensor([2, 0, 1], device="cuda")
+    kd, vd = torch.zeros_like(d.k_cache[:4]), torch.zeros_like(d.v_cache[:4])
+    out = torch.zeros((b.total_q, b.Hq, b.hd), dtype=torch.bfloat16, device="cuda")
+    with B.Context(b.Hq, b.Hkv, b.hd, b.BS, b.num_blocks, b.max_blocks_per_seq) as ctx:
+        for stream in (None, torch.cuda.current_stream().cuda_stream):
+            for sizes in ((n, b.total_q), (N.OF_TENSOR, N.OF_TENSOR)):
+                assert N.kv_append(ctx.h, kn, kn, d.k_cache, d.v_cache, tabs[0], tabs[2], tabs[3], *sizes, stream) == B.OOCO_OK
+                assert N.plan(ctx.h, n, *host) == B.OOCO_OK
+                assert N.attn_mixed(ctx.h, d.q, d.k_cache, d.v_cache, *tabs, out, *sizes, stream) == B.OOCO_OK
+            for pairs in (3, N.OF_TENSOR):
+                assert N.kv_block_copy(ctx.h, d.k_cache, d.v_cache, kd, vd, ids, dst, pairs, stream) == B.OOCO_OK
+            assert N.attn_mixed_static(b.Hq, b.Hkv, b.hd, b.BS, b.max_blocks_per_seq, 0.0, *host, d.q, d.k_cache, d.v_cache, *tabs,
+                                       torch.zeros_like(out), n, b.total_q, stream) == B.OOCO_OK
+        torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
 def test_both_ways_agree(general):
     b = W.config1(poison=True)
     d = W.to_device(b, "cuda:0")
