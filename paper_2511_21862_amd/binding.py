@@ -95,6 +95,10 @@ _native = None
 if torch is not None:
     try:
         from paper_2511_21862_amd import _binding as _native
+        from paper_2511_21862_amd.build import built_for as _built_for
+
+        if getattr(_native, "BUILT_FOR", None) != _built_for(torch):
+            raise ImportError(f"built as '{getattr(_native, 'BUILT_FOR', None)}'")
         _native.bind(_P, *[ctypes.cast(f, _P).value for f in (_lib.ooco_plan, _lib.ooco_attn_mixed, _lib.ooco_attn_mixed_static,
                                                               _lib.ooco_kv_append, _lib.ooco_kv_block_copy)])
     except ImportError as e:      # not built, or built for another torch: the general way alone

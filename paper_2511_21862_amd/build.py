@@ -25,6 +25,16 @@ MARSHAL = os.path.join(HERE, "_binding.so")
 MARSHAL_SRC = os.path.join(CSRC, "ooco_py.cpp")
 
 
+def built_for(torch) -> str:
+    """What the marshalling module is compiled against, whose objects it reads directly (numpy checks its version by itself)."""
+    return f"ooco_binding for torch {torch.__version__}, python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
+def has_stamp(path: str, stamp: str) -> bool:
+    with open(path, "rb") as f:
+        return stamp.encode() + b"\0" in f.read()
+
+
 def build_marshalling(force: bool = True, verbose: bool = False) -> str | None:
     """The binding's native argument marshalling (host code against this Python, numpy and torch); without torch the
     binding is used for host functions only and does without."""
@@ -33,11 +43,14 @@ def build_marshalling(force: bool = True, verbose: bool = False) -> str | None:
         import torch
     except ImportError:
         return None
-    if not force and os.path.exists(MARSHAL) and os.path.getmtime(MARSHAL) >= max(os.path.getmtime(f) for f in [MARSHAL_SRC, HEADERS[1]]):
-        return MARSHAL
+    stamp = built_for(torch)
+    if not force and os.path.exists(MARSHAL) and has_stamp(MARSHAL, stamp):
+        if os.path.getmtime(MARSHAL) >= max(os.path.getmtime(f) for f in [MARSHAL_SRC, HEADERS[1]]):
+            return MARSHAL
     tinc, tlib = (os.path.join(os.path.dirname(torch.__file__), d) for d in ("include", "lib"))
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f'-DOOCO_BUILT_FOR="{stamp}"',
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     for d in (tinc, os.path.join(tinc, "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"], numpy.get_include(),
               "/opt/rocm/include"):
         cmd += ["-isystem", d]

@@ -247,7 +247,7 @@ PyMODINIT_FUNC PyInit__binding(void)
     import_array();
     PyObject *const m = PyModule_Create(&module);
     if (m && !of_tensor) of_tensor = PyObject_CallNoArgs(reinterpret_cast<PyObject *>(&PyBaseObject_Type));
-    if (m && (!of_tensor || PyModule_AddObjectRef(m, "OF_TENSOR", of_tensor) != 0)) {
+    if (m && (!of_tensor || PyModule_AddObjectRef(m, "OF_TENSOR", of_tensor) != 0 || PyModule_AddStringConstant(m, "BUILT_FOR", OOCO_BUILT_FOR) != 0)) {
         Py_DECREF(m);
         return nullptr;
     }

@@ -17,6 +17,32 @@ def test_the_native_module_is_there():
     assert N is not None
 
 
+def test_a_module_for_another_torch_is_not_used(tmp_path):
+    """... and is built again: it reads torch's objects directly."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+
+    from paper_2511_21862_amd import build
+    stamp = build.built_for(torch)
+    assert N.BUILT_FOR == stamp and torch.__version__ in stamp and build.has_stamp(build.MARSHAL, stamp)
+    other = tmp_path / "_binding.so"
+    code = open(build.MARSHAL, "rb").read()
+    other.write_bytes(code.replace(stamp.encode(), stamp.replace("torch " + torch.__version__[0], "torch 9").encode()))
+    assert not build.has_stamp(str(other), stamp)
+    # a copy of the package with that module: the general way, and a warning that says why
+    pkg = tmp_path / "paper_2511_21862_amd"
+    pkg.mkdir()
+    for f in os.listdir(build.HERE):
+        if f.endswith((".py", ".so")):
+            shutil.copy(os.path.join(build.HERE, f), pkg / f)
+    shutil.copy(other, pkg / "_binding.so")
+    res = subprocess.run([sys.executable, "-c", "from paper_2511_21862_amd import binding as B; assert B._native is None; "
+                          "assert B._plan_fast is B._not_native"], cwd=tmp_path, capture_output=True, text=True)
+    assert res.returncode == 0 and "torch 9" in res.stderr, res.stderr
+
+
 @pytest.mark.parametrize("seq", [[3, 5], np.array([3, 5], np.int64), np.array([3, 5, 7, 9], np.int32)[::2], np.array([3, 5], ">i4"),
                                  None, np.array([3, 5], np.uint32), torch.tensor([3, 5], dtype=torch.int32)])
 def test_other_length_arrays_are_left_to_the_general_way(seq):
