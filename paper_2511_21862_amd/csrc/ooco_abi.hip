@@ -649,7 +649,9 @@ bool key_groups_pay(const PlanGeometry &geo, int num_seqs, const int32_t *h_seq_
     }
     if (forced) return true;
     const int64_t enough = (geo.hd == 128 ? 3 : 2) + (n_dec > 0 && widest * g <= 32);
-    if (units > cus || longest < enough || (geo.pf_split_opt > 0 && !whole)) return false;
+    // (without the tile list the parts of a tile are chosen for four waves: one chunk of 186 rows on 2760 tokens, 32/4 heads of
+    // 64, five parts 21.8 us, key groups in one 24.2)
+    if (units > cus || longest < enough || (geo.pf_split_opt > 0 && !whole) || !geo.pf_table_opt) return false;
     if (n_dec > 0) {
         // estimates in us, as in plan_prefill_parts
         const double bytes = (double)dec_blk * geo.BS * 2.0 * geo.Hkv * geo.hd * 2.0;
@@ -1687,9 +1689,12 @@ ooco_status ooco_attn_mixed(ooco_ctx *ctx, const void *q, const void *k_cache, c
     const bool overlap = mixed && !fused && !step && ctx->side_stream && (ctx->opt_overlap >= 2 || (ctx->opt_overlap == 1 && !pl.brief));
     hipStream_t ps = overlap ? ctx->side_stream : s;   // the stream of the prefill kernel
     // A split tile's merge is shared among its parts where all workgroups of the launch find a place at once (launch_step adds
-    // its decode workgroups): two of four waves per compute unit.
+    // its decode workgroups): two of four waves per compute unit.  Only with the tile list, whose counters lie a tile's parts
+    // apart: without it those of 32 tiles share a line, and the waiting parts' looks delay the others (option "prefill_sorted" 0,
+    // us, one merging part -> shared: 25 + 27 rows on 7000 tokens, 32/8 heads, 15 parts 31.4 -> 38.8; 32 + 40 on 6500, 64/8 heads,
+    // six parts 34.6 -> 39.1).
     const int64_t pf_wgs = pl.pf_table ? (int64_t)pl.pf_table * ctx->Hkv : (int64_t)pl.n_tiles * ctx->Hkv * pl.pf_split;
-    p.pf_share = pl.pf_split > 1 && pl.pf_waves == 4 && (step || !mixed) && pf_wgs <= 2 * (int64_t)ctx->num_cus ? (int8_t)(1 + ctx->opt_merge_looks) : (int8_t)0;
+    p.pf_share = pl.pf_table && pl.pf_split > 1 && pl.pf_waves == 4 && (step || !mixed) && pf_wgs <= 2 * (int64_t)ctx->num_cus ? (int8_t)(1 + ctx->opt_merge_looks) : (int8_t)0;
     auto mark = [&](int k, hipStream_t st) {
         if (ev && e == hipSuccess) e = hipEventRecord(ev[k], st);
     };

@@ -27,6 +27,8 @@ CASES = [
     ((32, 4, 64), [64], [10], {}, "prefill_kernel<64, 4>"),
     ((32, 8, 128), [64], [10], {"prefill_waves": 8}, "prefill_kernel<128, 8>"),
     ((32, 8, 128), [40], [1000], {}, "prefill_kernel_groups<128>"),
+    ((32, 8, 128), [40], [1000], {"prefill_sorted": 0}, "prefill_kernel<128, 4>"),
+    ((32, 8, 128), [40], [1000], {"prefill_sorted": 0, "prefill_groups": 4}, "prefill_kernel_groups<128>"),
     ((32, 8, 128), *SMALL, {}, "step_kernel_groups<128, 2>"),
     ((32, 8, 128), *SMALL, {"overlap": 0}, "decode_coop_kernel_groups<128, 2>;prefill_kernel_groups<128>"),
     ((32, 4, 64), *SMALL, {"overlap": 0, "prefill_groups": 4}, "decode_coop_kernel_groups<64, 4>;prefill_kernel_groups<64>"),
