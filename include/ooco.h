@@ -124,8 +124,9 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                         this many blocks less than a run that holds none, so that all waves
  *                         finish together.  Unset: 3 * 128 / head_dim (a wave needs about 3 us
  *                         from one piece to the first tile of the next), four times that in runs that
- *                         workgroups of four waves share ("decode_coop"); 0 = runs of equal
- *                         block counts; at most 64.  A value that is set holds for both.
+ *                         workgroups of four waves share ("decode_coop"), six times in those of eight waves beside
+ *                         "prefill_groups"; 0 = runs of equal
+ *                         block counts; at most 64.  A value that is set holds for all.
  * Prefill tiles (takes effect at the next ooco_plan):
  *   "prefill_split"       parts a prefill tile's key range is cut into, 1..16 (more is taken as 16); every part is
  *                         a workgroup of its own and the last one to finish merges their partial
@@ -244,8 +245,8 @@ ooco_status ooco_profile_read_calls(ooco_ctx *ctx, double *per_call_ms /*HOST*/,
  * wave start, first K/V tiles arrived, end of KV streaming, wave end (after partial results and
  * merge).  ooco_trace_read waits for the streams the context's calls were given and copies the stamps of the last
  * traced call:
- *   stamps: HOST uint64 [cap_waves][4], wave index = run * num_kv_heads + kv head (a workgroup of four waves that
- *   share a run stamps once, its first wave);
+ *   stamps: HOST uint64 [cap_waves][4], wave index = run * num_kv_heads + kv head (a workgroup of four or eight waves
+ *   that share a run stamps once, its first wave);
  *   waves: HOST, receives the number of decode waves of that call.
  * A traced batch WITHOUT decode sequences stores per prefill workgroup instead (workgroup index = (tile in
  * dispatch order * num_kv_heads + kv head) * parts + part): start, XCD * 256 + compute-unit id, phases, end; `waves`
@@ -301,7 +302,7 @@ ooco_status ooco_plan_dry_run(int num_q_heads, int num_kv_heads, int head_dim, i
                               const int32_t *xcd_weights /*HOST, 8 values in 1..255, or NULL*/,
                               int64_t prefill_split, int64_t decode_piece_pad);
 
-/* Numbers describing the last plan made, current or used up (any pointer may be NULL): decode runs (waves, or workgroups of four, per kv head),
+/* Numbers describing the last plan made, current or used up (any pointer may be NULL): decode runs (waves, or workgroups of four or eight, per kv head),
  * prefill tiles, KV blocks of all decode sequences, bytes of workspace the partial results use,
  * the most parts a prefill tile's key range is cut into (1 = no tile is split). */
 ooco_status ooco_plan_info(const ooco_ctx *ctx, int64_t *decode_waves, int64_t *prefill_tiles,

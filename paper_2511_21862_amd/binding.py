@@ -90,7 +90,7 @@ _lib.ooco_mix_decoding_select.argtypes = ([ctypes.POINTER(ModelParams)] + [ctype
 # The per-step calls' arguments in native code: each of those functions tries it first and goes the general way when it
 # answers NotImplemented (anything but contiguous GPU tensors and int32 arrays).  Small calls in a loop on MI355X, the general
 # way -> native: plan 1.7 -> 0.3 us, plan and attention of five short sequences 7.8 -> 5.0 (the kernel's time), the static entry
-# 8.0 -> 5.0, KV append 5.7 -> 3.8, block copy 5.3 -> 3.5.
+# 7.9 -> 5.3 (7.4 .. 8.0 on several cards), KV append 5.7 -> 3.8, block copy 5.3 -> 3.5.
 _native = None
 if torch is not None:
     try:

@@ -265,6 +265,9 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         // Starting a piece costs the whole workgroup, so it weighs more in the line: as much as 12 tiles of head_dim 128.
         // Pads of 3 / 6 / 12 / 24: sixteen sequences of 512..4096 tokens 31.5 / 31.1 / 30.6 / 30.5 us, sixteen of
         // 1000..2000 22.8 / 22.0 / 21.0 / 21.8; head_dim 64, pads of 6 / 12 / 24 / 36: 12.3 / 11.3 / 10.2 / 10.2.
+        // Eight waves, beside key groups: 18 tiles.  60 random batches whose runs hold several pieces, time over the best of seven
+        // pads of 3 / 6 / 9 / 12 / 18 / 24 / 30: 1.087 / 1.064 / 1.050 / 1.033 / 1.015 / 1.009 / 1.010, head_dim 64 (twice as many
+        // units) 1.141 / 1.076 / 1.046 / 1.027 / 1.013 / 1.012 / 1.035.
         if (geo.piece_pad < 0) {
             const int32_t more = (out.coop_waves == 8 ? 5 : 3) * default_piece_pad(geo.hd);
             int32_t added = 0;

@@ -81,7 +81,8 @@ struct AttnParams {
     uint32_t queue_base;        // ticket value at which this launch's tail runs start
     uint32_t *queue;            // ticket counter for the tail runs (monotonic across launches)
     // prefill tiles split along the context (pf_split > 1): part j of unit u = (tile, kv head) writes
-    // pf_acc[(u*pf_split + j)][128 columns][hd] and pf_ml[..][128][2]; pf_counters[u] counts arrivals
+    // pf_acc[(u*pf_split + j)][columns][hd] and pf_ml[..][columns][2], 32 columns per wave of a key group; pf_counters[u]
+    // counts arrivals
     float *pf_acc;
     float *pf_ml;
     int32_t *pf_counters;
