@@ -144,7 +144,8 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                         sequences the decode workgroups then have eight waves too, and all of them together a compute
  *                         unit each (step_kernel_groups).  Automatic "prefill_split" cuts such a tile into up to 64
  *                         parts.  4 is taken wherever such a batch fits (not with the register-lean pair, a dynamic
- *                         tail, XCD weights or "decode_coop" 0).
+ *                         tail, XCD weights or "decode_coop" 0); 0 takes them neither with "prefill_sorted" 0 nor,
+ *                         beside decode sequences, where "decode_segments" asks for a number of runs.
  *   "prefill_sorted"      0/1/2 (default 1): a batch of at most 896 prefill tiles dispatches the tiles of ALL its
  *                         chunks -- the parts of its tiles, if they are split -- by decreasing number of 64-key
  *                         steps (one list entry per tile or part, in the kernel arguments; at most 896 entries);
