@@ -943,23 +943,28 @@ __global__ __launch_bounds__(512, 2) void decode_coop_kernel_groups(const KernAr
 // global->LDS loads, one barrier per step.  Per wave and step, for each 32-token half:
 //   S^T[32 tok][32 cols] = K · Q^T    (hd/16 x v_mfma_f32_32x32x16_bf16, K operand from LDS)
 //   O^T[hd][32 cols]    += V^T · P^T  (hd/32 x 2 x v_mfma_f32_32x32x16_bf16, V operand from LDS)
-// with one softmax update over the 64 scores of a column.  The loop is software pipelined: the
-// score MFMAs of step st+1 are issued together with the softmax arithmetic of step st (two score
-// register sets that swap roles every step), so that the matrix core works on the next scores
-// while the vector ALU exponentiates the current ones; K therefore runs one step ahead of V:
-// at the top of step st the loads of K[st+2] and V[st+1] are sent off.
+// The loop is software pipelined over halves of 32 tokens: a region of 16 MFMAs multiplies the weights of one half by V and
+// computes the scores of a half two further on, while the vector ALU turns the scores of the half between them into weights,
+// a score or so per MFMA.  K therefore runs one step ahead of V: in step st the loads of K[st+2] and V[st+1] are sent off.
 // Lane l = 32*h + col.  MFMA row i of the K operand is fed with token (i with bits 2 and 3
 // swapped) of its block, so that S^T register r of lane (col, h) is token 16(r/8) + 8h + r%8 of
 // the half: eight consecutive tokens per block, which is what one 16-byte V operand holds.
 // LDS (16-byte units, CH = 2*hd per tile): K tiles keep the cache order [hd/8][16 slots]; V tiles
 // are stored [token half][dim] so that the 16 lanes of a quarter wave read 256 contiguous bytes
 // (no bank conflicts).
-// The SIMD's VALU issue port is shared with the matrix core (a 32x32x16 MFMA holds it for half of
-// its 32 cycles), so the kernel is tuned for few vector instructions per MFMA: 64-token steps
-// halve the per-step bookkeeping, maxima use v_max3, row sums v_dot2c on the packed weights,
-// the causal mask runs only on steps that touch the diagonal; at the end of a sequence the unused V
-// slots are zeroed once in LDS instead of masking operands.  Two workgroups fit a CU (<= 256 VGPRs,
-// 64 KiB LDS each).
+// What bounds it, by stamps of the clock counter and loops of the same instruction mix on their own (cycles per 32x32x16 MFMA,
+// which takes 32, of two waves on a SIMD): on zeros the issue of everything around the matrix cores, on random data the power
+// that they draw, which brings the clock from 2.4 to 1.6 .. 1.75 GHz.  Both ask for few instructions per MFMA, at even distances:
+//   * an exponential, its fma and half a conversion per MFMA run beside it (67 cycles per pair of MFMAs); v_dot2c_f32_bf16 does
+//     not (84), so the sums of the weights are a small matrix product (73);
+//   * no maximum: weights are computed against the reference as it stands, and their sums show when it has to move;
+//   * the loads of a step are issued between MFMAs: all at its start they took a wave 860 of 3500 cycles; a wave's pieces lie in
+//     one block, so that a step asks it for one block id, two tile addresses and two settings of M0;
+//   * the barrier of a step sits where the last operands of the step before it are on their way to registers.
+// MI355X (us, before -> after): 2 x 2048 rows on 4096 tokens, 64/8 heads 602 -> 574 (on zeros 448 -> 400), 8 x 512 rows on up to
+// 2048, 32/8 heads 85.7 -> 81.1, 300 rows on 14,683 tokens 87.0 -> 82.5.
+// The causal mask runs only on halves that touch the diagonal; at the end of a sequence the unused V slots are zeroed once in LDS
+// instead of masking operands.  Two workgroups fit a CU (<= 256 VGPRs, 64 KiB LDS each).
 constexpr int kPfThreads = 256;   // threads of the four-wave workgroup (the eight-wave one has 512)
 constexpr int kPfBlocks = 4;    // KV blocks per step
 constexpr int kSharedMergeParts = 4;   // parts from which sharing the merge of a split tile pays (see prefill_unit)
@@ -1072,15 +1077,23 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
     // Ids past the tile's last block may be anything until they are replaced below.
     typedef const __attribute__((address_space(4))) int32_t *const_i32_ptr;
     const const_i32_ptr ctable = (const_i32_ptr)(uintptr_t)(p.block_tables + (int64_t)seq * p.max_blocks_per_seq);
-    int ids0[BLK], ids1[BLK], ids2[BLK];   // block ids of the steps st, st + 1 and st + 2
+    // A wave moves NCP consecutive 64-chunk pieces of a stage, which lie in one block: the first is chunk piece_chunk of block
+    // piece_block of the step.  (APART: the wave's two pieces are the same quarter of two blocks, two apart; see issue.)
+    constexpr bool APART = !PIPE;
+    const int piece_block = APART ? wave >> 2 : wave * NCP * 64 / CH, piece_chunk = APART ? (wave & 3) * 64 : wave * NCP * 64 % CH;
+    static_assert(CH % (NCP * 64) == 0 && (!APART || (NC == 8 && CH == 256)), "where the pieces of a wave lie");
+    auto wave_block = [&](int st) -> int { return BLK * (KG * st + kg) + piece_block; };   // of the sequence
+    int id0, id1, id2;   // physical ids of this wave's blocks of the steps st, st + 1 and st + 2
+    int id0b, id1b;      // (APART: of the second blocks of the steps st and st + 1)
     const int id_first = ctable[0];
     {
         const int last = p.max_blocks_per_seq - 1;
-#pragma unroll
-        for (int b = 0; b < BLK; ++b) {
-            ids0[b] = ctable[min(BLK * kg + b, last)];
-            ids1[b] = ctable[min(BLK * (KG + kg) + b, last)];
-            ids2[b] = ctable[min(BLK * (2 * KG + kg) + b, last)];
+        id0 = ctable[min(wave_block(0), last)];
+        id1 = ctable[min(wave_block(1), last)];
+        id2 = ctable[min(wave_block(2), last)];
+        if constexpr (APART) {
+            id0b = ctable[min(wave_block(0) + 2, last)];
+            id1b = ctable[min(wave_block(1) + 2, last)];
         }
     }
     int q_row0, rows, pos0, seq_len;
@@ -1136,162 +1149,102 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
     const int ku = col >> 4;
     const int kslot = (col & 3) | ((col & 4) << 1) | ((col & 8) >> 1);
 
-    // One stage (the K or the V tiles of a step) goes from global memory straight into LDS
-    // (global_load_lds_dwordx4: every lane gives a 16-byte global address, the wave's 64 pieces land
-    // contiguously at the LDS address in M0).  Wave w moves the 64-chunk groups w, w+4, ...; chunk
-    // cidx of the stage belongs to block cidx/CH of the step and comes from
-    //   K: cache chunk cidx%CH   (same order as the cache)
-    //   V: LDS position r = half*HD + dim  <-  cache chunk 2*dim + half
-    // The instruction is issued through inline asm so that the waits stay under this code's
-    // control.
-    auto block_id = [&](int b) -> int { return ctable[min(b, nblk - 1)]; };
-    // (tile of kv head kvh of physical block pb) = cache + pb * blk_stride + kvh * tile_elems, in elements
-    const uint16_t *const k_head = k_cache + (int64_t)kvh * tile_elems, *const v_head = v_cache + (int64_t)kvh * tile_elems;
-    const uint32_t blk_stride = (uint32_t)Hkv * (uint32_t)tile_elems;
-    auto issue = [&](bool is_v, int slot, const int (&pb)[BLK]) {   // pb: physical ids of the step's blocks
-        static_assert(NCP == 4 || NCP == 2, "one asm statement per stage");
-        const uint16_t *base[NCP];
-        uint32_t voff[NCP], dst[NCP];
+    // One stage (the K or the V tiles of a step) goes from global memory straight into LDS (global_load_lds_dwordx4: every lane
+    // gives a 16-byte global address, the wave's 64 pieces land contiguously at the LDS address in M0; the instruction's offset
+    // counts for both).  Chunk c of a block's tile in LDS comes from
+    //   K: cache chunk c   (same order as the cache)
+    //   V: half = c / HD, dim = c % HD  <-  cache chunk 2*dim + half
+    // The instructions are issued through inline asm so that the waits stay under this code's control.
+    const uint32_t blk_bytes = (uint32_t)Hkv * (uint32_t)tile_elems * 2u;
+    constexpr int kBias = 2048;   // keeps the V offsets below positive
+    const char *const k_head = reinterpret_cast<const char *>(k_cache + (int64_t)kvh * tile_elems);
+    const char *const v_head = reinterpret_cast<const char *>(v_cache + (int64_t)kvh * tile_elems) - kBias;
+    const uint32_t k_off = (uint32_t)(piece_chunk + lane) * 16u;
+    uint32_t v_off[NCP];
 #pragma unroll
-        for (int n = 0; n < NCP; ++n) {
-            const int grp = wave + NC * n;                 // wave-uniform
-            const int cidx = grp * 64 + lane;
-            // block of the step (wave-uniform).  Four waves and at least 256 chunks per tile: a compile-time
-            // constant, which keeps pb[] in registers without select chains.  Eight waves (256 chunks per tile):
-            // waves 0..3 move the even blocks' tiles, waves 4..7 the odd ones (one select, no indexed array).
-            int which, pbw;
-            if constexpr (NC <= 4) {
-                which = CH >= NC * 64 ? (NC * n * 64) / CH : (grp * 64) / CH;
-                pbw = pb[which];
-            } else {
-                static_assert(NC != 8 || CH == 256, "eight waves on one step: head_dim 128");
-                which = 2 * n + (wave >> 2);
-                pbw = (wave >> 2) ? pb[2 * n + 1] : pb[2 * n];
-            }
-            const int r = cidx - which * CH;
-            // scalar tile address + 32-bit lane offset (bytes)
-            base[n] = (is_v ? v_head : k_head) + (uint64_t)(uint32_t)pbw * blk_stride;
-            voff[n] = (uint32_t)(is_v ? 2 * (r % HD) + r / HD : r) * 16u;
-            dst[n] = (is_v ? ldsV_base : ldsK_base) + (uint32_t)((slot * STAGE + grp * 64) * 16);
-        }
+    for (int n = 0; n < NCP; ++n) {
+        const int c = piece_chunk + (APART ? 0 : n * 64) + lane;
+        v_off[n] = (uint32_t)((2 * (c % HD) + c / HD) * 16 - (APART ? 0 : n * 1024) + kBias);
+    }
+    // all pieces of this wave, of block id (scalar tile address + 32-bit lane offset)
+    auto issue = [&](bool is_v, int slot, int id) {
+        const char *const base = (is_v ? v_head : k_head) + (uint64_t)(uint32_t)id * blk_bytes;
+        const uint32_t dst = (is_v ? ldsV_base : ldsK_base) + (uint32_t)((slot * STAGE + wave * NCP * 64) * 16);
+        uint32_t off[4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) off[n] = is_v ? v_off[n % NCP] : k_off;
         uint32_t saved_m0;   // M0 is restored: the compiler may keep a value of its own there
         if constexpr (NCP == 4)
-            asm volatile("s_mov_b32 %0, m0\n\t"
-                         "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %9\n\t"
-                         "s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %10\n\t"
-                         "s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %7, %11\n\t"
-                         "s_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %8, %12\n\t"
-                         "s_mov_b32 m0, %0"
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %6\n\tglobal_load_lds_dwordx4 %3, %6 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %4, %6 offset:2048\n\tglobal_load_lds_dwordx4 %5, %6 offset:3072\n\ts_mov_b32 m0, %0"
                          : "=&s"(saved_m0)
-                         : "s"(dst[0]), "s"(dst[1]), "s"(dst[2]), "s"(dst[3]), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]),
-                           "v"(voff[3]), "s"(base[0]), "s"(base[1]), "s"(base[2]), "s"(base[3])
+                         : "s"(dst), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base)
                          : "memory");
         else
-            asm volatile("s_mov_b32 %0, m0\n\t"
-                         "s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
-                         "s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %6\n\t"
-                         "s_mov_b32 m0, %0"
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                         "global_load_lds_dwordx4 %2, %4\n\tglobal_load_lds_dwordx4 %3, %4 offset:1024\n\ts_mov_b32 m0, %0"
                          : "=&s"(saved_m0)
-                         : "s"(dst[0]), "s"(dst[1]), "v"(voff[0]), "v"(voff[1]), "s"(base[0]), "s"(base[1])
+                         : "s"(dst), "v"(off[0]), "v"(off[1]), "s"(base)
                          : "memory");
+        static_assert(NCP == 2 || NCP == 4, "one asm statement");
     };
-
+    // With eight waves and no pipeline, beside decode waves, the quarters of a block are fetched by four waves side by side, one load
+    // from each of two blocks, as fast as a wave can: two pieces of one block per wave cost the decode stream 0.8 % (MI355X, 2 x
+    // 2048 rows and 32 long decodes 1648 -> 1659 us, 8 x 512 and 128 262.6 -> 265.3).
+    auto issue_apart = [&](bool is_v, int slot, int ida, int idb) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const char *const base = (is_v ? v_head : k_head) + (uint64_t)(uint32_t)(n ? idb : ida) * blk_bytes;
+            const uint32_t dst = (is_v ? ldsV_base : ldsK_base) + (uint32_t)((slot * STAGE + (2 * n + piece_block) * CH + piece_chunk) * 16);
+            const uint32_t off = is_v ? v_off[0] : k_off;
+            uint32_t saved_m0;
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+                         : "=&s"(saved_m0)
+                         : "s"(dst), "v"(off), "s"(base)
+                         : "memory");
+        }
+    };
     f32x16 O[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) O[mb][r] = 0.f;
 
-    // scores of one step: S[hh] register r is token st*64 + 32hh + 8h + 16(r/8) + r%8
-    auto qk = [&](f32x16 (&S)[HV], int slot) {
+    // scores of 32 tokens: S register r is token 8h + 16(r/8) + r%8 of them
+    float m = -1e30f;   // (finite, so that a half of which a column sees nothing gives it weights of 0 and not inf - inf)
+    // The sums of the weights come from the matrix cores too (v_mfma_f32_16x16x32_bf16): as an operand of that product the 16
+    // rounded weights of a lane pair are 16 columns by 32 rows, of which rows 0..7 and 16..23 belong to columns 0..15 of the wave
+    // and the others to columns 16..31, so a first operand of ones and zeros gives both sums, in every lane those of columns
+    // lane % 16 and 16 + lane % 16.  (v_dot2c_f32_bf16 does not run beside matrix instructions: two waves per SIMD of MFMA + LDS
+    // read + a score's exponential 84 cycles per pair of MFMAs with it, 73 with this product, 67 without any sum.)
+    u32x4 ones;
 #pragma unroll
-        for (int hh = 0; hh < HV; ++hh)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) S[hh][r] = 0.f;
-        // the two token halves alternate, so that consecutive MFMAs never wait for each other's result
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int hh = 0; hh < HV; ++hh) {
-                const u32x4 kop = ldsK[slot][(2 * hh + ku) * CH + (2 * ks + h) * 16 + kslot];
-                S[hh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop),
-                                                            __builtin_bit_cast(bf16x8, qb[ks]), S[hh], 0, 0, 0);
-            }
+    for (int w = 0; w < 4; ++w) ones[w] = ((lane >> 4) & 1) == (lane & 1) ? 0x3F803F80u : 0u;
+    auto add_weights = [&](const u32x4 &P, f32x4 &sums) {
+        sums = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones), __builtin_bit_cast(bf16x8, P), sums, 0, 0, 0);
     };
-    // causal mask of a step that touches the diagonal
-    auto mask = [&](f32x16 (&S)[HV], int tok0) {
-        const int room = pos - (tok0 + 8 * h);           // visible iff 32hh + 16(r/8) + r%8 <= room
+    // Weights are computed against the reference m as it stands.  It only has to keep them in range (the final division cancels
+    // it, weights above 1 are as exact in bf16 and fp32 as below), so it moves when the weights of a column's half step sum to
+    // more than kMaxWeights, or to infinity or NaN: rarely, and then the half is done again (move_reference).
+    constexpr float kMaxWeights = 256.0f;
+    auto weights16 = [&](const f32x16 &S, u32x4 (&P)[2], f32x4 &sums) {
+        sums = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int hh = 0; hh < HV; ++hh)
+        for (int q = 0; q < 2; ++q) {
+            float e[8];
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                S[hh][r] = (32 * hh + 16 * (r / 8) + (r % 8) <= room) ? S[hh][r] : -INFINITY;
-    };
-    float m = -INFINITY, lsum = 0.f;
-    // online-softmax update with the raw scores of one step; P[2hh+u] holds the packed weights of
-    // tokens 32hh + 16u + 8h + 0..7.  The softmax scale rides in the fma that feeds exp2 (scale > 0,
-    // so the maximum can be taken before scaling).
-    // The update comes in two halves so that the PV products of the first 32 tokens can run beside the
-    // exponentials of the last 32: weights(S, P, q4, ...) turns the scores of tokens 16*q4 + 8h + 0..7 into P[q4].
-    auto weights = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], int q4, float m_ref, float &psum) {
-        float e[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) e[r] = fast_exp2(__builtin_fmaf(S[q4 >> 1][8 * (q4 & 1) + r], c_log2e, -m_ref));
-        P[q4] = u32x4{pack2_bf16(e[0], e[1]), pack2_bf16(e[2], e[3]), pack2_bf16(e[4], e[5]), pack2_bf16(e[6], e[7])};
-        // the denominator sums the same rounded weights that enter the PV product
-#pragma unroll
-        for (int w = 0; w < 4; ++w) psum = sum2_bf16(P[q4][w], psum);
-    };
-    auto softmax_first = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], float &alpha, bool &grow, float &psum) {
-        float mloc;
-        if constexpr (HV == 2)
-            mloc = max32(S[0], S[1]);
-        else
-            mloc = max16(S[0]);
-        {
-            float x, y;
-            swap32(mloc, x, y);
-            mloc = max2(x, y) * c_log2e;
+            for (int r = 0; r < 8; ++r) e[r] = fast_exp2(__builtin_fmaf(S[8 * q + r], c_log2e, -m));
+            P[q] = u32x4{pack2_bf16(e[0], e[1]), pack2_bf16(e[2], e[3]), pack2_bf16(e[4], e[5]), pack2_bf16(e[6], e[7])};
+            add_weights(P[q], sums);
         }
-        // (floored: a part of a split tile may start with steps that a column does not see at all; its maximum
-        // then stays at the floor, its weights and sum at 0, instead of running into inf - inf)
-        // The reference point m only has to stay within 2^8 of the true running maximum (weights up to 256 are
-        // exact enough in bf16 and harmless in the fp32 sums; the final division cancels the reference), so it
-        // moves, and the accumulators are rescaled, only when a step's maximum exceeds it by more than 8.
-        const float m_cand = floor_m1e30(mloc);
-        grow = m_cand > m + 8.0f;
-        const float m_new = grow ? m_cand : m;
-        alpha = fast_exp2(m - m_new);
-        m = m_new;
-        psum = 0.f;
-#pragma unroll
-        for (int q = 0; q < HV; ++q) weights(S, P, q, m, psum);
     };
-    auto softmax_second = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], float alpha, float psum) {
+    auto too_large = [&](const f32x4 &sums) -> bool { return !__all(sums[0] <= kMaxWeights && sums[1] <= kMaxWeights); };   // (or NaN)
+    float lsum_lo = 0.f, lsum_hi = 0.f;   // running sums of columns lane % 16 and 16 + lane % 16
+    auto mask16 = [&](f32x16 &S, int tok0) {   // tok0: first token of the 32
+        const int room = pos - (tok0 + 8 * h);
 #pragma unroll
-        for (int q = HV; q < 2 * HV; ++q) weights(S, P, q, m, psum);
-        lsum = lsum * alpha + psum;
-    };
-    // The MFMAs of tokens 0..31 (P[0], P[1]) are laid out beside the vector work that is still due when pv
-    // starts (the second half of the softmax update), those of tokens 32..63 follow.
-    auto pv = [&](const u32x4 (&P)[2 * HV], int slot) {
-        const u32x4 *vp = &ldsV[slot][h * HD + col];
-#pragma unroll
-        for (int i = 0; i < 2 * HV * MB; ++i) {
-            const u32x4 vop = vp[(i / MB) * CH + 32 * (i % MB)];
-            O[i % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vop),
-                                                            __builtin_bit_cast(bf16x8, P[i / MB]), O[i % MB], 0, 0, 0);
-        }
-        // every operand is requested kAhead MFMAs before the MFMA that uses it
-        constexpr int kAhead = 4;
-        __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
-#pragma unroll
-        for (int i = 0; i < 2 * HV * MB - kAhead; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (i < HV * MB) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // (exponentials count as VALU here)
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+        for (int r = 0; r < 16; ++r) S[r] = (16 * (r / 8) + (r % 8) <= room) ? S[r] : -INFINITY;
     };
     // Last step of a sequence only (workgroup-uniform): V slots at or past seq_len may hold anything; their
     // weights are 0, but 0*NaN is NaN, so they are zeroed in LDS before anybody multiplies with them.
@@ -1310,26 +1263,48 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         __syncthreads();
     };
 
-    auto step_block = [&](int st, int b) -> int { return block_id(BLK * (KG * st + kg) + b); };
+    // Block ids of further steps: lane l holds this wave's block of step id_base + l, and of step id_base + 64 + l.
+    const int32_t *const vtable = p.block_tables + (int64_t)seq * p.max_blocks_per_seq;
+    int id_base = st_lo + 3, idv = 0, idn = 0;
+    auto next_id = [&](int st) -> int {   // st is wave-uniform and does not decrease
+        if (st - id_base >= 64) {
+            id_base += 64;
+            idv = idn;
+            asm volatile("" : "+v"(idv));   // (waited for here, in the rare path)
+            idn = vtable[min(wave_block(id_base + 64 + lane), nblk - 1)];
+        }
+        return __builtin_amdgcn_readlane(idv, st - id_base);
+    };
     {
         if (st_lo == 0) {   // (the ids are here; steps past the tile's last block take any valid one)
-#pragma unroll
-            for (int b = 0; b < BLK; ++b) {
-                if (BLK * kg + b >= nblk) ids0[b] = id_first;
-                if (BLK * (KG + kg) + b >= nblk) ids1[b] = id_first;
-                if (BLK * (2 * KG + kg) + b >= nblk) ids2[b] = id_first;
+            if (wave_block(0) >= nblk) id0 = id_first;
+            if (wave_block(1) >= nblk) id1 = id_first;
+            if (wave_block(2) >= nblk) id2 = id_first;
+            if constexpr (APART) {
+                if (wave_block(0) + 2 >= nblk) id0b = id_first;
+                if (wave_block(1) + 2 >= nblk) id1b = id_first;
             }
         } else {
-#pragma unroll
-            for (int b = 0; b < BLK; ++b) {
-                ids0[b] = step_block(st_lo, b);
-                ids1[b] = step_block(st_lo + 1, b);
-                ids2[b] = step_block(st_lo + 2, b);
+            id0 = ctable[min(wave_block(st_lo), nblk - 1)];
+            id1 = ctable[min(wave_block(st_lo + 1), nblk - 1)];
+            id2 = ctable[min(wave_block(st_lo + 2), nblk - 1)];
+            if constexpr (APART) {
+                id0b = ctable[min(wave_block(st_lo) + 2, nblk - 1)];
+                id1b = ctable[min(wave_block(st_lo + 1) + 2, nblk - 1)];
             }
         }
-        issue(false, st_lo & 1, ids0);
-        issue(true, st_lo & 1, ids0);
-        if (PIPE && st_lo + 1 < nstep) issue(false, (st_lo + 1) & 1, ids1);
+        if constexpr (APART) {
+            issue_apart(false, st_lo & 1, id0, id0b);
+            issue_apart(true, st_lo & 1, id0, id0b);
+        } else {
+            issue(false, st_lo & 1, id0);
+            issue(true, st_lo & 1, id0);
+            if (st_lo + 1 < nstep) issue(false, (st_lo + 1) & 1, id1);
+        }
+        if constexpr (PIPE) {
+            idv = vtable[min(wave_block(id_base + lane), nblk - 1)];
+            idn = vtable[min(wave_block(id_base + 64 + lane), nblk - 1)];
+        }
         // Passing the query registers through an empty asm makes the compiler wait for their loads here, behind the first
         // tiles' loads and before the loop, instead of counting them down inside it (which would also wait for the
         // global->LDS loads it does not know about).
@@ -1337,88 +1312,352 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qb[ks]));
     }
     phase(1);
-    // One step.  Sc: scores of step st (computed during step st-1), Sn: receives those of step st+1.
-    auto body = [&](f32x16 (&Sc)[HV], f32x16 (&Sn)[HV], int st) {
-        const int tok0 = st * STEP + kg * T;   // first token of this key group's share of the step
-        // this wave's loads of K[st+1] and V[st] have landed, and after the barrier so have
-        // everybody's; nobody reads K[st] or V[st-1] any more
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (st + 2 < nstep) issue(false, st & 1, ids2);
-        if (st + 1 < nstep) issue(true, (st + 1) & 1, ids1);
-        if (st * STEP + STEP > seq_len) scrub_v(st & 1, tok0);
-#pragma unroll
-        for (int b = 0; b < BLK; ++b) {
-            ids1[b] = ids2[b];
-            ids2[b] = step_block(st + 3, b);
+    // A region: the weights Pu of 32 tokens by V (PV), the scores Ss of 32 others turned into the weights Pn (NEXT), and the scores
+    // Sq of 32 more (QK), hd/16 MFMAs for each of the two products, in turn, with the vector work spread evenly between them.
+    // Every LDS operand is asked for AHEAD MFMAs before its own, the first of a region by the region before it.
+    constexpr int AHEAD = 4;
+    u32x4 ring[AHEAD];
+    auto operand = [&](auto pv, auto qk, int i, int vslot, int vhalf, int kslot_q, int khalf) -> u32x4 {   // of MFMA i of a region
+        constexpr bool PV = decltype(pv)::value, QK = decltype(qk)::value;
+        const int j = PV && QK ? i / 2 : i;
+        if (QK && (!PV || (i & 1) == 0)) return ldsK[kslot_q][(2 * khalf + ku) * CH + h * 16 + kslot + j * 32];
+        return ldsV[vslot][(2 * vhalf + j / MB) * CH + h * HD + col + 32 * (j % MB)];
+    };
+    // prefetch(i): asks for operand i of the next region; beside(i): called once MFMA i has been issued
+    auto region = [&](auto pv, auto qk, auto next, u32x4 (&Pu)[2], f32x4 &sums_u, int vslot, int vhalf, f32x16 &Ss, u32x4 (&Pn)[2],
+                      f32x4 &sums_n, f32x16 &Sq, int kslot_q, int khalf, auto &&prefetch, auto &&beside) {
+        constexpr bool PV = decltype(pv)::value, QK = decltype(qk)::value, NEXT = decltype(next)::value;
+        constexpr int NM = (PV ? KS : 0) + (QK ? KS : 0);
+        static_assert(2 * MB == KS, "as many products of each kind");
+        if constexpr (PV) {
+            lsum_lo += sums_u[0];
+            lsum_hi += sums_u[1];
         }
-        // wave-uniform: some column of this wave sees keys of the step
-        if (tok0 > w_pos_hi) return;
-        if (tok0 + T - 1 > w_pos_lo) mask(Sc, tok0);   // the step touches the causal diagonal
-        u32x4 P[2 * HV];
-        float alpha, psum;
-        bool grow;
-        // One straight-line region for the scheduler.  The scores of step st+1 are computed even
-        // when nothing will use them (last step of the tile, or no column of the wave sees that
-        // step): the K slot then holds an older step's tiles, and the result is dropped.
-        qk(Sn, (st + 1) & 1);
-        softmax_first(Sc, P, alpha, grow, psum);
-        // the weights of the first 32 tokens are due here, inside the region of the score MFMAs ...
+        float e[16];
+        f32x4 sums = {0.f, 0.f, 0.f, 0.f};
+        // the vector work of score r, one stage later per two scores: scaled and referenced, exponentiated, packed and summed
+        auto vector_work = [&](int r) {
+            if (r < 16) e[r] = __builtin_fmaf(Ss[r], c_log2e, -m);
+            const int x = r - 2;
+            if (x >= 0 && x < 16) e[x] = fast_exp2(e[x]);
+            const int y = r - 4;
+            if (y >= 0 && y < 16 && (y & 1)) {
+                Pn[y / 8][(y % 8) / 2] = pack2_bf16(e[y - 1], e[y]);
+                if (y % 8 == 7) add_weights(Pn[y / 8], sums);
+            }
+        };
+        constexpr int CALLS = 20, OVER = NM - 2;   // calls of vector_work for 16 scores, MFMAs that they are spread over
 #pragma unroll
-        for (int q = 0; q < HV; ++q) asm volatile("" : "+v"(P[q]));
-        // ... and the region is laid out as HV*hd/16 x (MFMA, LDS read, a share of the vector work):
-        // the maximum is found next to the first MFMAs, the exponentials next to the others
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        for (int i = 0; i < NM; ++i) {
+            const int j = PV && QK ? i / 2 : i;
+            const u32x4 op = ring[i % AHEAD];
+            if (QK && (!PV || (i & 1) == 0)) {
+                f32x16 z;
 #pragma unroll
-        for (int i = 0; i < KS / 2; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                for (int r = 0; r < 16; ++r) z[r] = 0.f;
+                Sq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op), __builtin_bit_cast(bf16x8, qb[j]),
+                                                             j == 0 ? z : Sq, 0, 0, 0);
+            } else {
+                O[j % MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op), __builtin_bit_cast(bf16x8, Pu[j / MB]),
+                                                                    O[j % MB], 0, 0, 0);
+            }
+            beside(i);
+            if (i + AHEAD < NM)
+                ring[i % AHEAD] = operand(pv, qk, i + AHEAD, vslot, vhalf, kslot_q, khalf);
+            else
+                prefetch(i + AHEAD - NM);
+            if constexpr (NEXT) {
+#pragma unroll
+                for (int r = i * CALLS / OVER; r < (i + 1) * CALLS / OVER; ++r)
+                    if (r < CALLS) vector_work(r);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
+        if constexpr (NEXT) sums_n = sums;
+    };
+    // The reference that the weights of a half were computed with was too low for some column of the wave: move it to the
+    // maximum of the half and compute the weights again.
+    auto move_reference = [&](const f32x16 &Ss, u32x4 (&Pn)[2], f32x4 &sums_n) {
+        float x, y;
+        swap32(max16(Ss), x, y);
+        const float m_new = max2(m, floor_m1e30(max2(x, y) * c_log2e));
+        const float alpha = fast_exp2(m - m_new);
+        m = m_new;
+        weights16(Ss, Pn, sums_n);
+        lsum_lo *= __shfl(alpha, lane & 15);
+        lsum_hi *= __shfl(alpha, 16 + (lane & 15));
 #pragma unroll
-        for (int i = KS / 2; i < HV * KS; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-            __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-        }
-        if (__any(grow)) {
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) O[mb][r] *= alpha;
-        }
-        // the second half of the update belongs to the region of the PV MFMAs: its scores pass through an empty
-        // asm here so that nothing of it is moved up
-        asm volatile("" : "+v"(Sc[HV - 1]));
-        softmax_second(Sc, P, alpha, psum);
-        pv(P, st & 1);
+            for (int r = 0; r < 16; ++r) O[mb][r] *= alpha;
     };
 
-    if constexpr (PIPE) {
-        f32x16 SA[HV], SB[HV];
+    const auto yes = std::true_type();
+    const auto no = std::false_type();
+    auto nothing = [](int) {};
+    auto first_operands = [&](auto pv, auto qk, int vslot, int vhalf, int kslot_q, int khalf) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) ring[i] = operand(pv, qk, i, vslot, vhalf, kslot_q, khalf);
+    };
+    // The loads of a step, a wave's pieces of K beside the first MFMA of a region and those of V beside MFMA `later`: all of them at
+    // once, at the start of a step, hold up the waves that issue them (860 cycles a step) and those of the unit's other workgroup.
+    auto spread_issue = [&](int later, int i, int kslot_q, int k_id, int vslot, int v_id) {
+        if (i == 0) issue(false, kslot_q, k_id);
+        if (i == later) issue(true, vslot, v_id);
+    };
+    // the reference of the first half
+    auto first_reference = [&](const f32x16 &S) {
+        float x, y;
+        swap32(max16(S), x, y);
+        m = floor_m1e30(max2(x, y) * c_log2e);
+    };
+
+    if constexpr (PIPE && HV == 2) {
+        // Two halves of 32 tokens per step.  P0, P1: weights of the halves of step st; S0, S1: their scores, and those of step st + 1
+        // once the former have been used.  K runs one step ahead of V.
+        f32x16 S0, S1;
+        u32x4 P0[2], P1[2];
+        f32x4 sums0, sums1;
+        // Everybody's loads of K[st + 1] and V[st] have landed, and everybody is done with K[st] and V[st - 1].
+        auto arrive = [&](int st) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (st * STEP + STEP > seq_len) scrub_v(st & 1, st * STEP);
+        };
+        auto roll_ids = [&](int st) {
+            id1 = id2;
+            id2 = next_id(st + 3);
+        };
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("" : "+v"(idv), "+v"(idn));   // (arrived, and not to be waited for in the loop)
         __syncthreads();
         phase(2);
-        qk(SA, st_lo & 1);
-        for (int st = st_lo; st < nstep; st += 2) {
-            body(SA, SB, st);
-            if (st + 1 < nstep) body(SB, SA, st + 1);
+        first_operands(no, yes, 0, 0, st_lo & 1, 0);
+        region(no, yes, no, P0, sums0, 0, 0, S0, P0, sums0, S0, st_lo & 1, 0, [&](int i) { ring[i] = operand(no, yes, i, 0, 0, st_lo & 1, 1); }, nothing);
+        mask16(S0, st_lo * STEP);
+        first_reference(S0);
+        region(no, yes, yes, P0, sums0, 0, 0, S0, P0, sums0, S1, st_lo & 1, 1, nothing, nothing);
+        // w_last: the last step that this wave has columns for; the loop runs to the one before
+        const int w_last = w_used ? min(nstep - 1, w_pos_hi / T) : st_lo - 1;
+        int st = st_lo;
+        arrive(st);
+        if (st < w_last) first_operands(yes, yes, st & 1, 0, (st + 1) & 1, 0);
+        for (; st < w_last; ++st) {
+            const int tok0 = st * STEP, cur = st & 1, nxt = (st + 1) & 1;
+            if (tok0 + 63 > w_pos_lo) mask16(S1, tok0 + 32);
+            // (the loads of K[st + 2], of any block if there is no such step, and V[st + 1])
+            region(yes, yes, yes, P0, sums0, cur, 0, S1, P1, sums1, S0, nxt, 0, [&](int i) { ring[i] = operand(yes, yes, i, cur, 1, nxt, 1); },
+                   [&](int i) { spread_issue(KS, i, cur, id2, nxt, id1); });
+            if (too_large(sums1)) move_reference(S1, P1, sums1);
+            roll_ids(st);
+            if (tok0 + 95 > w_pos_lo) mask16(S0, tok0 + 64);
+            // (the step's last operands are on their way when the next step's are waited for, whose first then follow them)
+            region(yes, yes, yes, P1, sums1, cur, 1, S0, P0, sums0, S1, nxt, 1, [&](int i) { ring[i] = operand(yes, yes, i, nxt, 0, cur, 0); },
+                   [&](int i) {
+                       if (i == 2 * KS - AHEAD) arrive(st + 1);
+                   });
+            if (too_large(sums0)) move_reference(S0, P0, sums0);
+        }
+        if (st == w_last) {
+            const int tok0 = st * STEP, cur = st & 1;
+            if (st + 2 < nstep) issue(false, cur, id2);
+            if (st + 1 < nstep) issue(true, (st + 1) & 1, id1);
+            roll_ids(st);
+            first_operands(yes, no, cur, 0, 0, 0);
+            if (tok0 + 63 > w_pos_lo) mask16(S1, tok0 + 32);
+            region(yes, no, yes, P0, sums0, cur, 0, S1, P1, sums1, S0, 0, 0, [&](int i) { ring[i] = operand(yes, no, i, cur, 1, 0, 0); }, nothing);
+            if (too_large(sums1)) move_reference(S1, P1, sums1);
+            region(yes, no, no, P1, sums1, cur, 1, S0, P0, sums0, S1, 0, 0, nothing, nothing);
+            ++st;
+            if (st < nstep) arrive(st);
+        }
+        for (; st < nstep; ++st) {   // steps that other waves have columns for: this one stages only
+            if (st + 2 < nstep) issue(false, st & 1, id2);
+            if (st + 1 < nstep) {
+                issue(true, (st + 1) & 1, id1);
+                roll_ids(st);
+                arrive(st + 1);
+            }
+        }
+    } else if constexpr (PIPE) {
+        // One half per step.  Step st multiplies the weights of step st - 1, turns the scores of step st into weights and computes
+        // those of step st + 1: V runs two steps behind K.
+        static_assert(HV == 1, "a half per step");
+        f32x16 SA, SB;
+        u32x4 PA[2], PB[2];
+        f32x4 sumsA, sumsB;
+        // Everybody's loads of K[st + 1] and V[st - 1] have landed, and everybody is done with K[st] and V[st - 2].
+        auto arrive = [&](int st) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (st > st_lo && st * STEP > seq_len) scrub_v((st - 1) & 1, (st - 1) * STEP + kg * T);
+        };
+        auto roll_ids = [&](int st) {
+            id0 = id1;
+            id1 = id2;
+            id2 = next_id(st + 3);
+        };
+        auto load_step = [&](int st) {   // K[st + 2] and V[st]
+            if (st + 2 < nstep) issue(false, st & 1, id2);
+            if (st > st_lo && st < nstep) issue(true, st & 1, id0);
+            roll_ids(st);
+        };
+        auto mask_step = [&](f32x16 &S, int st) {
+            if (st * STEP + kg * T + T - 1 > w_pos_lo) mask16(S, st * STEP + kg * T);
+        };
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("" : "+v"(idv), "+v"(idn));
+        __syncthreads();
+        phase(2);
+        first_operands(no, yes, 0, 0, st_lo & 1, 0);
+        region(no, yes, no, PA, sumsA, 0, 0, SA, PA, sumsA, SA, st_lo & 1, 0, nothing, nothing);
+        // w_last: the last step that this wave has columns for
+        const int w_last = w_pos_hi >= kg * T ? min(nstep - 1, (w_pos_hi - kg * T) / STEP) : st_lo - 1;
+        int st = st_lo;
+        arrive(st);
+        if (st <= w_last) {
+            mask_step(SA, st);
+            first_reference(SA);
+            if (st < w_last) {
+                first_operands(no, yes, 0, 0, (st + 1) & 1, 0);
+                load_step(st);
+                region(no, yes, yes, PA, sumsA, 0, 0, SA, PA, sumsA, SB, (st + 1) & 1, 0, nothing, nothing);
+                ++st;
+                arrive(st);
+                if (st < w_last) first_operands(yes, yes, (st - 1) & 1, 0, (st + 1) & 1, 0);
+                // one step: scores Ss and weights Pu of the step before, which leave scores Sq and weights Pn; the loads are K[st + 2] (of
+                // any block if there is no such step) and V[st]
+                auto full = [&](f32x16 &Ss, f32x16 &Sq, u32x4 (&Pu)[2], f32x4 &sums_u, u32x4 (&Pn)[2], f32x4 &sums_n) {
+                    const int cur = st & 1, nxt = (st + 1) & 1;
+                    mask_step(Ss, st);
+                    region(yes, yes, yes, Pu, sums_u, nxt, 0, Ss, Pn, sums_n, Sq, nxt, 0, [&](int i) { ring[i] = operand(yes, yes, i, cur, 0, cur, 0); },
+                           [&](int i) {
+                               spread_issue(KS / 2, i, cur, id2, cur, id0);
+                               if (i == 2 * KS - AHEAD) arrive(st + 1);
+                           });
+                    if (too_large(sums_n)) move_reference(Ss, Pn, sums_n);
+                    roll_ids(st);
+                    ++st;
+                };
+                while (st < w_last) {
+                    full(SB, SA, PA, sumsA, PB, sumsB);
+                    if (st >= w_last) {
+                        SB = SA;
+                        PA[0] = PB[0];
+                        PA[1] = PB[1];
+                        sumsA = sumsB;
+                        break;
+                    }
+                    full(SA, SB, PB, sumsB, PA, sumsA);
+                }
+                first_operands(yes, no, (st - 1) & 1, 0, 0, 0);
+                load_step(st);
+                mask_step(SB, st);
+                region(yes, no, yes, PA, sumsA, (st - 1) & 1, 0, SB, PB, sumsB, SA, 0, 0, nothing, nothing);
+                if (too_large(sumsB)) move_reference(SB, PB, sumsB);
+            } else {
+                load_step(st);
+                weights16(SA, PB, sumsB);
+            }
+            ++st;
+            arrive(st);
+            first_operands(yes, no, (st - 1) & 1, 0, 0, 0);
+            load_step(st);
+            region(yes, no, no, PB, sumsB, (st - 1) & 1, 0, SA, PB, sumsB, SB, 0, 0, nothing, nothing);
+        } else {
+            load_step(st);
+        }
+        for (; st < nstep; ++st) {   // steps that other waves have columns for: this one stages only
+            arrive(st + 1);
+            load_step(st + 1);
         }
     } else {
+        // No pipeline across steps (few registers, see prefill_kernel_lean): scores, weights and product of a step one after the other,
+        // the overlap of matrix and vector work comes from the two waves of a SIMD.
+        float lsum = 0.f;
+        m = -INFINITY;
+        // scores of one step: S[hh] register r is token st*64 + 32hh + 8h + 16(r/8) + r%8
+        auto qk = [&](f32x16 (&S)[HV], int slot) {
+#pragma unroll
+            for (int hh = 0; hh < HV; ++hh)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) S[hh][r] = 0.f;
+            // the two token halves alternate, so that consecutive MFMAs never wait for each other's result
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int hh = 0; hh < HV; ++hh) {
+                    const u32x4 kop = ldsK[slot][(2 * hh + ku) * CH + (2 * ks + h) * 16 + kslot];
+                    S[hh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop),
+                                                                __builtin_bit_cast(bf16x8, qb[ks]), S[hh], 0, 0, 0);
+                }
+        };
+        // causal mask of a step that touches the diagonal
+        auto mask = [&](f32x16 (&S)[HV], int tok0) {
+            const int room = pos - (tok0 + 8 * h);           // visible iff 32hh + 16(r/8) + r%8 <= room
+#pragma unroll
+            for (int hh = 0; hh < HV; ++hh)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    S[hh][r] = (32 * hh + 16 * (r / 8) + (r % 8) <= room) ? S[hh][r] : -INFINITY;
+        };
+        // online-softmax update with the raw scores of one step; P[2hh+u] holds the packed weights of
+        // tokens 32hh + 16u + 8h + 0..7.  The softmax scale rides in the fma that feeds exp2 (scale > 0,
+        // so the maximum can be taken before scaling).
+        // The update comes in two halves so that the PV products of the first 32 tokens can run beside the
+        // exponentials of the last 32: weights(S, P, q4, ...) turns the scores of tokens 16*q4 + 8h + 0..7 into P[q4].
+        auto weights = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], int q4, float m_ref, float &psum) {
+            float e[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) e[r] = fast_exp2(__builtin_fmaf(S[q4 >> 1][8 * (q4 & 1) + r], c_log2e, -m_ref));
+            P[q4] = u32x4{pack2_bf16(e[0], e[1]), pack2_bf16(e[2], e[3]), pack2_bf16(e[4], e[5]), pack2_bf16(e[6], e[7])};
+            // the denominator sums the same rounded weights that enter the PV product
+#pragma unroll
+            for (int w = 0; w < 4; ++w) psum = sum2_bf16(P[q4][w], psum);
+        };
+        auto softmax_first = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], float &alpha, bool &grow, float &psum) {
+            float mloc;
+            if constexpr (HV == 2)
+                mloc = max32(S[0], S[1]);
+            else
+                mloc = max16(S[0]);
+            {
+                float x, y;
+                swap32(mloc, x, y);
+                mloc = max2(x, y) * c_log2e;
+            }
+            // (floored: a part of a split tile may start with steps that a column does not see at all; its maximum
+            // then stays at the floor, its weights and sum at 0, instead of running into inf - inf)
+            // The reference point m only has to stay within 2^8 of the true running maximum (weights up to 256 are
+            // exact enough in bf16 and harmless in the fp32 sums; the final division cancels the reference), so it
+            // moves, and the accumulators are rescaled, only when a step's maximum exceeds it by more than 8.
+            const float m_cand = floor_m1e30(mloc);
+            grow = m_cand > m + 8.0f;
+            const float m_new = grow ? m_cand : m;
+            alpha = fast_exp2(m - m_new);
+            m = m_new;
+            psum = 0.f;
+#pragma unroll
+            for (int q = 0; q < HV; ++q) weights(S, P, q, m, psum);
+        };
+        auto softmax_second = [&](const f32x16 (&S)[HV], u32x4 (&P)[2 * HV], float alpha, float psum) {
+#pragma unroll
+            for (int q = HV; q < 2 * HV; ++q) weights(S, P, q, m, psum);
+            lsum = lsum * alpha + psum;
+        };
         for (int st = st_lo; st < nstep; ++st) {
             // the loads of K[st] and V[st] have landed (everybody's, after the barrier); nobody reads the tiles of
             // step st-1 any more, so the loads of step st+1 may overwrite them
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (st + 1 < nstep) {
-                issue(false, (st + 1) & 1, ids1);
-                issue(true, (st + 1) & 1, ids1);
+                issue_apart(false, (st + 1) & 1, id1, id1b);
+                issue_apart(true, (st + 1) & 1, id1, id1b);
             }
             const int tok0 = st * STEP + kg * T;
             if (st * STEP + STEP > seq_len) scrub_v(st & 1, tok0);
-#pragma unroll
-            for (int b = 0; b < BLK; ++b) ids1[b] = step_block(st + 2, b);
+            id1 = ctable[min(wave_block(st + 2), nblk - 1)];
+            id1b = ctable[min(wave_block(st + 2) + 2, nblk - 1)];
             if (tok0 > w_pos_hi) continue;   // wave-uniform: no column of this wave sees keys of the step
             f32x16 S[HV];
             qk(S, st & 1);
@@ -1442,15 +1681,13 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
                                                                 __builtin_bit_cast(bf16x8, P[i / MB]), O[i % MB], 0, 0, 0);
             }
         }
-    }
-    phase(3);
-    if (phases && tid == 0) *phases = phase_bits;
-    float ltot;
-    {
         float x, y;
         swap32(lsum, x, y);
-        ltot = x + y;
+        lsum_lo = lsum_hi = x + y;
     }
+    float ltot = (lane & 16) ? lsum_hi : lsum_lo;
+    phase(3);
+    if (phases && tid == 0) *phases = phase_bits;
     // Piece q of a wave's output (0 .. 4*MB-1) is, in lane (col, h), column 32*wave + col, dims 8q + 4h + 0..3: registers
     // 4*(q % 4) .. + 3 of O[q / 4].  From here on a thread holds ITEMS pieces of its column, q0 .. q0 + ITEMS - 1.
     const int q0 = KG == 1 ? 0 : kg * ITEMS;
