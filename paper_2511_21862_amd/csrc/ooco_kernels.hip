@@ -1120,7 +1120,6 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
     // this lane's query column
     const int c = wave * 32 + col;
     const int c_row = (int)((uint32_t)c * p.g_magic >> 15), c_head = c - c_row * g;
-    const bool c_valid = c_row < rows;
     const int row = min(c_row, rows - 1);
     const int head = kvh * g + c_head;
     const int pos = pos0 + row;                          // this column's absolute position
@@ -1730,21 +1729,43 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         }
         m = M;
     }
-    // this thread's pieces first .. of its column, divided by the sum, to the output
+    // This wave's pieces first .. of its columns, divided by the sums, to the output: through LDS, so that a store instruction
+    // writes whole rows (pieces of one wave are side by side) and not 16 bytes of each of 32.  The stage memory is free.  A piece
+    // is 16 bytes of the output; those of a column lie in LDS with their index permuted by the column, which spreads a wave's
+    // writes over the banks.
+    // Stores of 8 bytes per lane, 16 to a row of 256 bytes, made complete lines only in L2, where a line often had to leave earlier,
+    // and what was still there when the kernel ended was written back then; the rows leave at once, past the caches (`nt`).
+    // MI355X (us), 8 bytes per lane -> rows -> rows, nt: 8 x 512 rows beside 128 decodes 262.0 -> 257.6 -> 242.6, 2 x 2048 rows beside
+    // 32 long decodes 1647 -> 1631 -> 1559, 8 x 512 rows alone 81.5 -> 79.4 -> 78.4, six prompts of 295 rows 16.2 -> 14.4 -> 13.0;
+    // without any output stores the first two take 226 and 1533.  (Key groups, whose waves have a quarter of each row: 2 x 133 rows on
+    // 1231 tokens 17.9 -> 17.3; 24 decodes beside 237 rows lose 1.6 % with `nt` on such quarters.)
     auto put = [&](const auto &a, int first) {
-        if (c_valid) {
-            const float inv = 1.0f / ltot;
-            uint16_t *op = p.out + ((int64_t)(q_row0 + row) * p.Hq + head) * HD + 8 * (q0 + first) + 4 * h;
+        constexpr int N = std::extent_v<std::remove_reference_t<decltype(a)>>, PASS = 64 / N;   // rows of a store instruction
+        static_assert(N >= 2 && N <= 16 && (N & (N - 1)) == 0, "a permutation of N pieces");
+        auto place = [&](int column, int piece) -> int { return column * N + (piece ^ ((column / (16 / N)) & (N - 1))); };
+        u32x4 *const rows_lds = stage_lds<HD, KG>() + wave_id * 32 * N;
+        const float inv = 1.0f / ltot;
 #pragma unroll
-            for (int i = 0; i < (int)std::extent_v<std::remove_reference_t<decltype(a)>>; ++i) {
-                u32x2 w = {pack2_bf16(a[i][0] * inv, a[i][1] * inv), pack2_bf16(a[i][2] * inv, a[i][3] * inv)};
-                *reinterpret_cast<u32x2 *>(op + 8 * i) = w;
-                // The stores stay in this order, a line after the other.  Left to the compiler the last piece of every quarter, or all
-                // pieces q, q + 4, .. came together, and lines were written in two goes.  MI355X (us), compiler's order -> this one:
-                // 8 x 512 rows, 64/8 heads 85.4 -> 79.2; 2 x 2048 rows beside 32 long decodes 1677 -> 1668.
-                asm volatile("" ::: "memory");
+        for (int i = 0; i < N; ++i)
+            reinterpret_cast<u32x2 *>(rows_lds + place(col, i))[h] =
+                u32x2{pack2_bf16(a[i][0] * inv, a[i][1] * inv), pack2_bf16(a[i][2] * inv, a[i][3] * inv)};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int n = 0; n < 32 / PASS; ++n) {
+            const int r = n * PASS + lane / N, piece = lane % N;
+            const u32x4 w = rows_lds[place(r, piece)];
+            const int cc = wave * 32 + r, cc_row = (int)((uint32_t)cc * p.g_magic >> 15), cc_head = cc - cc_row * g;
+            if (cc_row < rows) {
+                u32x4 *const dst = reinterpret_cast<u32x4 *>(p.out + ((int64_t)(q_row0 + cc_row) * p.Hq + kvh * g + cc_head) * HD + 8 * (q0 + first + piece));
+                if constexpr (KG == 1)
+                    __builtin_nontemporal_store(w, dst);
+                else   // (a quarter of a row: 64 bytes of a line)
+                    *dst = w;
             }
         }
+        __builtin_amdgcn_wave_barrier();   // (before the next pieces)
     };
     if (nparts > 1) {
         // (one counter per (tile, kv head): the slot of its part 0 with the list, the unit's index without)
@@ -1864,6 +1885,8 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
             __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (!w_used) return;
         merge(acc, 0);
+    } else {
+        __syncthreads();   // nobody reads the stage memory any more
     }
     put(acc, 0);
 }
