@@ -2282,6 +2282,9 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
     const uint16_t *const k_src = k_new + row0 * row_elems, *const v_src = v_new + row0 * row_elems;
     u32x4 *const k_dst = reinterpret_cast<u32x4 *>(k_cache) + (int64_t)blk * chunks * kBlockSize + slot0;
     uint16_t *const v_dst = v_cache + (int64_t)blk * row_elems * kBlockSize;   // slot 0 of the first cache row
+    // Stores of 16 bytes go past the caches (`nt`): what lies in L2 at the end of the kernel is written back then.  MI355X (us): 8 x
+    // 512 rows and 128 decodes 10.44 -> 9.74, 2 x 2048 rows 7.91 -> 7.36; the 2-byte stores of a decode row's V lose by it (64
+    // decodes 4.4 -> 5.5).
     if (nrow == kBlockSize) {   // a whole block
         // K: thread -> (row r = tid % 16, 16-byte chunk c = tid / 16 + 16 i): the 16 rows of a chunk are adjacent in
         // the cache, so a wave's stores cover 4 chunks x 256 contiguous bytes
@@ -2298,7 +2301,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int c = c0 + i * kSlice * parts;
-                if (c < chunks && blk_ok) dst[(int64_t)c * kBlockSize] = v[i];
+                if (c < chunks && blk_ok) __builtin_nontemporal_store(v[i], &dst[(int64_t)c * kBlockSize]);
             }
         }
         // V: thread -> element e = (kv head, dim) of all rows, 32 contiguous bytes of the cache.  (Two adjacent elements
@@ -2312,8 +2315,8 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
                 x[r] = (uint32_t)s[(int64_t)(2 * r) * row_elems] | ((uint32_t)s[(int64_t)(2 * r + 1) * row_elems] << 16);
             u32x4 *d4 = reinterpret_cast<u32x4 *>(v_dst + (int64_t)e * kBlockSize);
             if (blk_ok) {
-                d4[0] = u32x4{x[0], x[1], x[2], x[3]};
-                d4[1] = u32x4{x[4], x[5], x[6], x[7]};
+                __builtin_nontemporal_store(u32x4{x[0], x[1], x[2], x[3]}, d4);
+                __builtin_nontemporal_store(u32x4{x[4], x[5], x[6], x[7]}, d4 + 1);
             }
         }
         return;
@@ -2348,7 +2351,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
             if (!blk_ok) continue;
 #pragma unroll
             for (int i = 0; i < KI; ++i)
-                if (r < nrow && c0 + 16 * i < chunks) k_dst[(int64_t)(c0 + 16 * i) * kBlockSize + r] = kv[i];
+                if (r < nrow && c0 + 16 * i < chunks) __builtin_nontemporal_store(kv[i], &k_dst[(int64_t)(c0 + 16 * i) * kBlockSize + r]);
             if (e < row_elems) {
                 // quarters of a cache row (4 slots = 8 bytes) that the step covers whole are written with one store
                 // each, the ragged ends slot by slot
