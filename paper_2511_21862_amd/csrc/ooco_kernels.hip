@@ -1529,14 +1529,14 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
                 auto full = [&](f32x16 &Ss, f32x16 &Sq, u32x4 (&Pu)[2], f32x4 &sums_u, u32x4 (&Pn)[2], f32x4 &sums_n) {
                     const int cur = st & 1, nxt = (st + 1) & 1;
                     mask_step(Ss, st);
-                    region(yes, yes, yes, Pu, sums_u, nxt, 0, Ss, Pn, sums_n, Sq, nxt, 0, [&](int i) { ring[i] = operand(yes, yes, i, cur, 0, cur, 0); },
-                           [&](int i) {
-                               spread_issue(KS / 2, i, cur, id2, cur, id0);
-                               if (i == 2 * KS - AHEAD) arrive(st + 1);
-                           });
+                    // (the loads have one step: they are waited for at its end, not where the last operands are on their way, 0.95 of the
+                    // time on long contexts)
+                    region(yes, yes, yes, Pu, sums_u, nxt, 0, Ss, Pn, sums_n, Sq, nxt, 0, nothing, [&](int i) { spread_issue(KS / 2, i, cur, id2, cur, id0); });
                     if (too_large(sums_n)) move_reference(Ss, Pn, sums_n);
                     roll_ids(st);
                     ++st;
+                    arrive(st);
+                    if (st < w_last) first_operands(yes, yes, cur, 0, cur, 0);
                 };
                 while (st < w_last) {
                     full(SB, SA, PA, sumsA, PB, sumsB);
