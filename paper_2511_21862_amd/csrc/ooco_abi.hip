@@ -179,9 +179,11 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     // with its own start (query vectors, first tiles): four waves per compute unit hide those better than three, and
     // one block per step wastes no padded step.  512 sequences of 128 tokens 58.5 -> 50.9 us, 900 of 64 71.9 -> 62.0,
     // 2048 of 256 403 -> 382, 1024 of 384 285 -> 275; 4096 of 512 tokens are faster with three waves (1430 / 1449 us).
-    // Up to 16,384 tiles of them two blocks per step, and as many runs as sequences even if those hold fewer than 16
-    // blocks: 32 sequences of 128 tokens 13.0 -> 10.2 us, 64 of 256 15.2 -> 13.2, 128 of 128 17.7 -> 14.8; 128 of 384
-    // tokens, 24,576 tiles: 34.5 / 33.7 us.
+    // Up to 16,384 tiles of them as many runs as sequences even if those hold fewer than 16 blocks, and, while there are fewer
+    // than 2.5 waves per unit, two blocks per step: 32 sequences of 128 tokens 13.0 -> 10.2 us, 64 of 256 15.2 -> 13.2; 56 of 214
+    // with one block 1.26 of the time, 64 of 166, 64/8 heads, 1.21.  More waves hide a piece's start by themselves, and a step
+    // of one block has no empty half: 99 sequences of 169 tokens 13.5 -> 12.8, 216 of 202, 28/4 heads, 17.6 -> 16.8, 371 of 20..41,
+    // 64/8 heads, 23.7 -> 21.2, 31 such batches 0.89 .. 1.0; 128 of 384 tokens, 24,576 tiles: 34.5 / 33.7 us.
     // A SMALL batch (at most 36,864 tiles, a tile being a (block, kv head) pair's 8 KiB of head_dim 128: with head_dim 64
     // twice as many blocks) cannot keep HBM busy anyway: what counts is the chain start -> steps of a wave -> partial
     // result -> merge.
@@ -252,7 +254,7 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     if (out.pf_units > 0)
         ;
     else if (geo.hd == 128 && short_seqs)
-        out.nbi = tiles <= 16384 ? 2 : 1;
+        out.nbi = tiles <= 16384 && 2 * dec_seqs * geo.Hkv < 5 * cus ? 2 : 1;
     else if (geo.hd == 128 && small)
         out.nbi = 2;
     int64_t min_blocks = 16 * 128 / geo.hd, at_least = 0;   // blocks of a run; runs whatever they hold

@@ -752,9 +752,16 @@ template <int HD, int NWV>
 constexpr int kCoopFloats = NWV * 16 * kCoopStride<HD> + NWV * 16 * 2 + 4;   // LDS the waves need
 
 // (NWV = waves of the workgroup: 4, or 8 beside prefill workgroups of key groups)
-template <int HD, int NBI, int NWV, class CumAt>
+// AHEAD = KV blocks that a wave's loads in flight belong to, those of the step at hand (V) and of the next (K): a step takes half
+// of them, 8 KiB of tiles.  With steps of 16 KiB a wave has half as many, so the last of them is half empty more often, and the
+// waves of a workgroup end further apart.  MI355X (us), steps of 16 -> 8 KiB: 24 decodes beside 237 rows, 28/4 heads 22.6 -> 20.1
+// (148 workgroups of eight waves, 3.25 steps -> 6.5), four layers of 16 decodes 146.8 -> 138.7, 38 drawn batches 0.963 (0.885 ..
+// 1.007); 4 KiB at head_dim 64 0.89 .. 1.11.
+template <int HD, int AHEAD, int NWV, class CumAt>
 OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, int cum_head, int run, int kvh, float *lds, uint64_t *trace)
 {
+    static_assert(AHEAD * HD == 256, "steps of 8 KiB");
+    constexpr int NBI = AHEAD / 2;
     constexpr int NB = HD / 16;
     constexpr int STRIDE = kCoopStride<HD>;
     constexpr int THREADS = NWV * 64;
@@ -1971,7 +1978,7 @@ OOCO_DEV void step_body(const KernArgs &a)
         const int run = p.rows2d ? (int)blockIdx.y : wg / p.Hkv, slot = wg - run * p.Hkv;
         uint64_t *const trace = p.trace ? p.trace + (int64_t)wg * 4 : nullptr;
         if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
-        decode_coop_run<HD, NBI, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + (threadIdx.x & 63)], run,
+        decode_coop_run<HD, COOP ? NBI : 256 / HD, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + (threadIdx.x & 63)], run,
                                      p.rotate_heads ? (slot + run) % p.Hkv : slot,
                                      reinterpret_cast<float *>(stage_lds<HD, KG>()), trace);
         if (trace) {
