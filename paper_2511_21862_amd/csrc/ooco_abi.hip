@@ -187,25 +187,32 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     // A SMALL batch (at most 36,864 tiles, a tile being a (block, kv head) pair's 8 KiB of head_dim 128: with head_dim 64
     // twice as many blocks) cannot keep HBM busy anyway: what counts is the chain start -> steps of a wave -> partial
     // result -> merge.
-    //   * One sequence, or sequences of more than 384 tokens on average with at most one beginning per two runs -- per run
-    //     beside a prefill part, whose workgroups hold units that single waves would want too --: its work is shared by the four waves of a workgroup
-    //     (decode_coop_kernel), one workgroup per unit: one sequence of 1000 tokens 11.1 -> 7.8 us, of 4000 14.1 -> 10.0,
-    //     of 16,000 24.1 -> 18.8, four of 2000..4000 20.1 -> 16.2, sixteen of 1250..5000 39.8 -> 36.1
-    //     (28/4 heads, 28 of them: 41.0 -> 39.2); the more pieces, the more of their starts cost four waves each: level at
-    //     32 to 40 sequences of 8 kv heads.
+    //   * One sequence, or sequences of more than 384 tokens on average of which at most two begin per run: its work is shared by
+    //     the four waves of a workgroup (decode_coop_kernel), one workgroup per unit: one sequence of 1000 tokens 11.1 -> 7.8 us,
+    //     of 4000 14.1 -> 10.0, of 16,000 24.1 -> 18.8, four of 2000..4000 20.1 -> 16.2.  Time over that of single waves, up to 0.5 /
+    //     1 / 2 / more beginnings per run: 0.87 / 0.88 / 0.95 / 0.98 (head_dim 64: 1.05), us: 39 of 477..1908, 28/4 heads, 21.0 -> 18.3,
+    //     24 of 885..1771, 64/8 heads, 27.6 -> 24.8; equal lengths of head_dim 128 1.02 .. 1.26 beyond 0.5, as single waves in as many
+    //     runs cut nothing.  Larger batches: 0.90 / 0.94 / 0.96 / 0.97 up to 70,000 tiles, 0.99 from there to 80,000 (head_dim 64: 0.99 and
+    //     0.98, equal lengths 1.0), then 1.0 and more.
+    //     Beside a prefill part, whose workgroups hold units that single waves would want too, up to one beginning per run: 0.81 ..
+    //     1.0; more 0.98 .. 1.05.
     //     Runs hold at least 16 blocks -- 8 where the sequences are of 64 blocks or fewer on average and so have few parts
     //     to merge (four of 500..1000 tokens 11.3 -> 8.5 us, but one of 4000 10.0 -> 12.3); 32 for sequences of more than
     //     512 blocks on average, whose many parts cost more than the shorter chain gains (one of 16,000 tokens, 64/8 heads,
     //     runs of 16 / 32 / 64 blocks 25.0 / 18.9 / 19.3), and beside a prefill part from 256 blocks on.
-    //   * Else single waves, two blocks per step, two waves per unit: 32 sequences of 1000..2000 tokens 37.6 -> 36.1,
-    //     64 of 300..900 35.0 -> 31.8.
+    //   * Else single waves, two blocks per step, two waves per unit.
     const int64_t tiles = kv_blocks * geo.Hkv * geo.hd / 128;
     const bool plain = !lean && out.dec_cus == 0 && dec_seqs > 0;
     const bool short_seqs = plain && kv_blocks <= 24 * dec_seqs;
     const bool small = plain && tiles <= 36864;
     const int64_t per_unit = std::max<int64_t>(1, (int64_t)geo.num_cus / geo.Hkv);   // runs that put one workgroup (of one kv head) on every unit
     const bool coop_can = plain && geo.tail_pct == 0 && geo.xcd_cw[kXcds - 1] == 0;
-    const bool coop_rule = small && (short_seqs ? dec_seqs == 1 : dec_seqs * (pf_wgs > 0 ? 1 : 2) <= per_unit);
+    const bool equal = max_blocks * dec_seqs == kv_blocks;
+    const bool unequal = 8 * max_blocks * dec_seqs > 9 * kv_blocks;   // (by more than the cut of a run's ends)
+    const bool coop_rule = short_seqs ? small && dec_seqs == 1
+                           : pf_wgs > 0 ? tiles <= 70000 && dec_seqs <= per_unit
+                           : small ? dec_seqs * (unequal ? 1 : 4) <= 2 * per_unit
+                                   : tiles <= 70000 && (geo.hd == 128 || unequal);
     // A batch of short sequences takes one workgroup per (sequence, kv head) and cuts nothing: no partial results, no arrival
     // counters, no merge through memory.  Sequences of up to 768 tokens (48 blocks of head_dim 128: six steps of the four
     // waves; one of 1000 tokens is faster cut, 13.0 against 7.8 us), and by the number of workgroups per unit, against
@@ -223,7 +230,7 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     //     (0.8..0.98).
     const int64_t wgs = (int64_t)num_seqs * geo.Hkv, cus = geo.num_cus, g = geo.Hq / geo.Hkv;
     const int64_t longest = max_blocks * geo.hd;   // (in blocks of head_dim 1)
-    const bool equal = max_blocks * dec_seqs == kv_blocks, skewed = 5 * kv_blocks < 2 * max_blocks * dec_seqs;
+    const bool skewed = 5 * kv_blocks < 2 * max_blocks * dec_seqs;
     bool whole = longest <= 48 * 128;
     if (whole && wgs > 2 * cus) {
         const int64_t up_to = geo.hd == 64 ? (g >= 4 ? 32 : 8) : g >= 6 || (g >= 4 && 2 * wgs <= 5 * cus) ? 48 : 8;
