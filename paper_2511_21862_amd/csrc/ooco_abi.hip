@@ -720,12 +720,12 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     // The register-lean pair for batches with both kinds of work (lean_opt 2 = whenever the batch is mixed; 1 = when
     // it pays: every compute unit gets at least one eight-wave prefill workgroup -- counting the parts of 16 or more
     // 64-key steps that tiles on a long context can be cut into --, and the prefill part, by itself,
-    // would take between 0.30 and 4 times as long as the decode part -- estimated from the batch's FLOPs and bytes
-    // at 1.05 PFLOP/s and 6.8 TB/s).  Measured on MI355X, 32/8 heads, 128 decode sequences of 1.4 GB in all: beside
-    // 2 x 2048 rows 319 -> 291 us, beside 8 x 512 rows 286 -> 270 us, but beside 4 x 512 rows 257 -> 263 us and beside
-    // 1 x 512 rows 242 -> 266 us (alone the lean decode kernel is 3 % slower than the stand-alone one, which a short
-    // prefill part does not repay; alone the lean prefill kernel is 5 % slower, so a batch that is nearly all prefill
-    // keeps the stand-alone pair too); the long-context batch of 64/8 heads 1.75 -> 1.62 ms.
+    // would take between 0.30 and 2 times as long as the decode part -- estimated from the batch's FLOPs and bytes at 1.05 PFLOP/s
+    // and 6.8 TB/s --, 0.50 with fewer than two workgroups per unit beside a decode part of up to 150 us).  MI355X, 500 random
+    // batches, time of four-wave workgroups in one launch over that of the pair: 1.01 .. 1.08 inside those bounds; 0.93 .. 0.97 from
+    // twice the decode part on (the pair's prefill workgroups have no software pipeline: 9 % slower alone), 0.94 (0.83 .. 1.03)
+    // with few workgroups and short decode parts (its decode waves are 4 % slower alone).  32/8 heads, 128 decodes of 1.4 GB in
+    // all beside 8 x 512 rows 247 us; the long-context batch of 64/8 heads 1.57 ms, with two kernels on two streams 1.8.
     bool lean = false;
     if (geo.lean_opt && geo.hd == 128 && !geo.fused && num_seqs > 0) {
         const int rows8 = prefill_tile_rows(geo.Hq / geo.Hkv, 8);
@@ -744,7 +744,8 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         }
         const double t_pf = 4.0 * geo.Hq * geo.hd * pairs / 1.05e15;
         const double t_dec = (double)dec_blk * BS * 2.0 * geo.Hkv * geo.hd * 2.0 / 6.8e12;
-        const bool pays = wgs8 * geo.Hkv >= (int64_t)geo.num_cus && t_pf >= 0.30 * t_dec && t_pf <= 4.0 * t_dec;
+        const double least = tiles8 * geo.Hkv >= 2 * (int64_t)geo.num_cus || t_dec > 150e-6 ? 0.30 : 0.50;
+        const bool pays = wgs8 * geo.Hkv >= (int64_t)geo.num_cus && t_pf >= least * t_dec && t_pf <= 2.0 * t_dec;
         lean = n_dec > 0 && tiles8 > 0 && (geo.lean_opt >= 2 || pays);
     }
     out.lean = lean;
