@@ -1320,8 +1320,11 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
     phase(1);
     // A region: the weights Pu of 32 tokens by V (PV), the scores Ss of 32 others turned into the weights Pn (NEXT), and the scores
     // Sq of 32 more (QK), hd/16 MFMAs for each of the two products, in turn, with the vector work spread evenly between them.
-    // Every LDS operand is asked for AHEAD MFMAs before its own, the first of a region by the region before it.
-    constexpr int AHEAD = 4;
+    // Every LDS operand is asked for AHEAD MFMAs before its own, the first of a region by the region before it.  Two are enough, and
+    // hold fewer registers: at head_dim 64 a SIMD then has three waves (158 registers for 172).  MI355X (us), four -> two: 2 x 2048 rows
+    // on 4096 tokens, 64/8 heads 580.6 -> 576.0, 4 chunks of 700..1100, 28/4 heads 95.9 -> 93.6; head_dim 64: 8 x 450 rows 43.8 -> 42.4,
+    // ten drawn batches 0.97; key groups of head_dim 128, 2 x 133 rows on 1231 tokens 16.8 -> 16.9.
+    constexpr int AHEAD = KG > 1 && HD == 128 ? 4 : 2;
     u32x4 ring[AHEAD];
     auto operand = [&](auto pv, auto qk, int i, int vslot, int vhalf, int kslot_q, int khalf) -> u32x4 {   // of MFMA i of a region
         constexpr bool PV = decltype(pv)::value, QK = decltype(qk)::value;
@@ -1933,7 +1936,7 @@ OOCO_DEV void prefill_kernel_body(const KernArgs &a)
     }
 }
 template <int HD, int NW>
-__global__ __launch_bounds__(NW * 64, 8 / NW) void prefill_kernel(const KernArgs a)
+__global__ __launch_bounds__(NW * 64, HD == 64 ? 3 : 8 / NW) void prefill_kernel(const KernArgs a)
 {
     prefill_kernel_body<HD, NW, 1>(a);
 }
@@ -2022,7 +2025,7 @@ OOCO_DEV void step_body(const KernArgs &a)
 }
 
 template <int HD, int NBI, bool COOP>
-__global__ __launch_bounds__(kPfThreads, 2) void step_kernel(const KernArgs a)
+__global__ __launch_bounds__(kPfThreads, HD == 64 ? 3 : 2) void step_kernel(const KernArgs a)
 {
     step_body<HD, NBI, 3, 4, true, COOP>(a);
 }
