@@ -160,11 +160,14 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                         four per compute unit, so that a SIMD holds two prefill waves and a decode wave at once.
  *                         1 (default) = automatic: when the prefill part gives every compute unit at least one
  *                         eight-wave workgroup and, by the batch's FLOPs and bytes, would by itself take between
- *                         0.30 and 4 times as long as the decode part (a shorter one does not repay the lean
- *                         decode kernel's 3 %, a longer one not the lean prefill kernel's 5 %); 0 = never (the
+ *                         0.30 and 2 times as long as the decode part (0.50 with fewer than two such workgroups per
+ *                         unit beside a decode part of up to 150 us; a shorter one does not repay the lean decode
+ *                         kernel's 4 %, a longer one not the lean prefill kernel's 9 %); 0 = never (the
  *                         stand-alone kernels side by side); 2 = whenever the batch holds both kinds of work.
- *   "decode_coop"         0/1/2 (default 1; batches without XCD weights or a dynamic tail): 1 = small batches run in
- *                         workgroups of four waves that share every piece of a run and merge in LDS, and batches of
+ *   "decode_coop"         0/1/2 (default 1; batches without XCD weights or a dynamic tail): 1 = batches of up to two
+ *                         beginnings of sequences per run (one beside a prefill part; half a one for equal lengths) and
+ *                         70,000 (block, kv head) tiles run in workgroups of four waves that share every piece of a run and
+ *                         merge in LDS, and batches of
  *                         sequences of at most 768 tokens (1536 with head_dim 64) take one such workgroup per
  *                         sequence and kv head while that is one per compute unit -- or up to four, where that is
  *                         measured faster than single waves; 0 = single waves; 2 = such workgroups always.  (Forcing "decode_nbi"

@@ -969,7 +969,8 @@ __global__ __launch_bounds__(512, 2) void decode_coop_kernel_groups(const KernAr
 //     one block, so that a step asks it for one block id, two tile addresses and two settings of M0;
 //   * the barrier of a step sits where the last operands of the step before it are on their way to registers.
 // MI355X (us, before -> after): 2 x 2048 rows on 4096 tokens, 64/8 heads 602 -> 574 (on zeros 448 -> 400), 8 x 512 rows on up to
-// 2048, 32/8 heads 85.7 -> 81.1, 300 rows on 14,683 tokens 87.0 -> 82.5.
+// 2048, 32/8 heads 85.7 -> 81.1, 300 rows on 14,683 tokens 87.0 -> 82.5.  (Calls as a whole, with the output stores and the
+// operands below as well: 608 -> 576, 89.3 -> 78.5, 256 rows on 8192 tokens 86.6 -> 81.5.)
 // The causal mask runs only on halves that touch the diagonal; at the end of a sequence the unused V slots are zeroed once in LDS
 // instead of masking operands.  Two workgroups fit a CU (<= 256 VGPRs, 64 KiB LDS each).
 constexpr int kPfThreads = 256;   // threads of the four-wave workgroup (the eight-wave one has 512)
@@ -1008,8 +1009,8 @@ OOCO_DEV u32x4 *stage_lds()
 // KG = key groups: with 4, the NW = 8 waves are four groups of two, 64 query columns, and each group stages and walks a
 // quarter (32) of every 128 keys with a pipeline of its own; only the barrier of a step is common.  The groups' results meet
 // in LDS (128 KiB, as much as their tiles: one workgroup per compute unit).  For batches of few tiles, which are bound by
-// the chain of steps and not by the matrix cores: a step takes about the time its loads need whatever it holds, 1.06 .. 1.36 us
-// for 128 keys in place of 1.08 .. 1.3 for 64, and a tile of few columns keeps a quarter of the waves idle instead of
+// the chain of steps and not by the matrix cores: a step takes about the time its loads need whatever it holds (1.06 .. 1.36 us
+// for 128 keys in place of 1.08 .. 1.3 for 64 when the rule was measured; both became 5 to 12 % shorter since), and a tile of few columns keeps a quarter of the waves idle instead of
 // three quarters.  Measured on MI355X against KG = 1 (us): 3 chunks of 3 rows on 17,000 cached tokens, 28/4 heads 42.6 -> 28.3,
 // 57 + 87 rows on 2000, 32/8 20.7 -> 18.0, 3 x 100 rows on 400 15.5 -> 12.5; two groups of 128 columns each gained nothing
 // (1 x 300 rows on 15,780 tokens 93.9 against 93.7, short contexts 2.5 us for the merge of 128 KiB).

@@ -23,7 +23,7 @@ def test_rows_land_where_they_belong(heads, opts):
     d, meta = W.to_device(b), device_meta(b)
     n, guard = b.total_q * Hq * hd, 512
     got = []
-    for shift in (0, 4):                # elements: 0 and 8 bytes past a 16-byte boundary
+    for shift in (0, 4, 1):             # elements: 0, 8 and 2 bytes past a 16-byte boundary
         buf = torch.full((n + 2 * guard,), 7.0, dtype=torch.bfloat16, device="cuda")
         out = buf[guard + shift: guard + shift + n].view(b.total_q, Hq, hd)
         with B.Context(Hq, Hkv, hd, 16, b.num_blocks, b.max_blocks_per_seq) as ctx:
@@ -37,4 +37,4 @@ def test_rows_land_where_they_belong(heads, opts):
     e = errors(got[0], want)
     say(f"  {heads} {opts}: {e}")
     assert e["finite"] and e["rel_l2"] <= REL_L2
-    assert np.array_equal(got[0], got[1])
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
