@@ -2228,14 +2228,16 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
                                                                    const int32_t *block_tables,
                                                                    const int32_t *query_start_loc, const int32_t *ctx_lens,
                                                                    int num_seqs, int total_q, int Hkv, int hd,
-                                                                   int max_blocks_per_seq, int64_t num_blocks, int parts)
+                                                                   int max_blocks_per_seq, int64_t num_blocks, int parts, int by_rows)
 {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     // `parts` workgroups share a (sequence, block) pair: each takes every parts-th slice of the rows' elements, so that a pair whose rows cover its block only partly (many narrow stores) does not end last
     const int w = blockIdx.x / parts;
     const int part = blockIdx.x - w * parts;
-    auto g_at = [&](int idx) -> int { return query_start_loc[idx] / kBlockSize + 2 * idx; };
+    // first pair of a sequence, by where its rows start: with `by_rows` it owns a pair per row (rows never touch more blocks)
+    auto g_of = [&](int start, int idx) -> int { return by_rows ? start : start / kBlockSize + 2 * idx; };
+    auto g_at = [&](int idx) -> int { return g_of(query_start_loc[idx], idx); };
     int seq, q0, q_len, ctx;
     if (num_seqs <= 4 * 64) {
         // up to 256 sequences: the four 64-lane looks are independent loads (one memory round trip), where
@@ -2253,7 +2255,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass) {
             const int idx = 1 + 64 * pass + lane;
-            const int v = idx <= num_seqs ? qv[pass] / kBlockSize + 2 * idx : 0x7FFFFFFF;
+            const int v = idx <= num_seqs ? g_of(qv[pass], idx) : 0x7FFFFFFF;
             cnt += __popcll(__ballot(v <= w));
         }
         seq = __builtin_amdgcn_readfirstlane(min(cnt, num_seqs - 1));
@@ -2276,7 +2278,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
         ctx = ctx_lens[seq];
     }
     if (q_len <= 0 || ctx < 0 || q0 < 0 || q0 + q_len > total_q) return;   // nothing to write / inconsistent arrays
-    const int j = w - (q0 / kBlockSize + 2 * seq);          // which of the touched blocks
+    const int j = w - g_of(q0, seq);          // which of the touched blocks
     const int bidx = ctx / kBlockSize + j;
     if (j < 0 || bidx > (ctx + q_len - 1) / kBlockSize) return;   // beyond the sequence's last touched block
     if (bidx >= max_blocks_per_seq) return;                 // beyond the block table: nothing is written
@@ -2399,10 +2401,16 @@ hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache,
     // One workgroup per 512 elements of a row.  8 kv heads x 128, 4,224 tokens, 1 / 2 / 4 / 8 parts: 12.7 / 10.4 / 13.1 /
     // 16.5 us; 32 x 128, 16 decodes: 18.2 / 10.2 / 6.6 / 4.7, 4096 chunk rows: 61 / 41 / 36 / 32.
     const int parts = parts_opt > 0 ? std::min(parts_opt, 8) : std::max(1, std::min(8, Hkv * hd / (2 * kAppendThreads)));
-    const unsigned grid = (unsigned)((total_q / kBlockSize + 2 * (int64_t)num_seqs + 1) * parts);
+    // Workgroups without a block to write cost their start all the same.  A sequence owns two (sequence, block) pairs and one more per
+    // 16 rows before its end, twice what a batch of decode rows needs; where nearly all sequences have one row, and the pairs are
+    // more than one per compute unit, it owns a pair per row.  MI355X (us): 200 decodes, 8 kv heads of 128 7.18 -> 6.34, 400 of 4
+    // heads 7.39 -> 6.62, 150 of 8 heads of 64 5.25 -> 4.60, 64 of 8 heads of 128 level; 91 of 4 heads, under 256 pairs, 5.14 -> 5.23.
+    const int64_t pairs = total_q / kBlockSize + 2 * (int64_t)num_seqs + 1;
+    const bool by_rows = 4 * (int64_t)total_q <= 5 * (int64_t)num_seqs && pairs * parts > 256;
+    const unsigned grid = (unsigned)((by_rows ? total_q : pairs) * parts);
     hipLaunchKernelGGL(kv_append_kernel, dim3(grid), dim3(kAppendThreads), 0, s, (const uint16_t *)k_new,
                        (const uint16_t *)v_new, (uint16_t *)k_cache, (uint16_t *)v_cache, block_tables, query_start_loc,
-                       ctx_lens, num_seqs, total_q, Hkv, hd, max_blocks_per_seq, num_blocks, parts);
+                       ctx_lens, num_seqs, total_q, Hkv, hd, max_blocks_per_seq, num_blocks, parts, (int)by_rows);
     return hipGetLastError();
 }
 

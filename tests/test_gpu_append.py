@@ -126,3 +126,31 @@ def test_append_of_partly_covered_blocks(Hkv, hd):
             ctx.kv_append(k_dev, v_flat[odd:].view(b.total_q, Hkv, hd), d.k_cache, d.v_cache, bt, qsl, cl)
             torch.cuda.synchronize()
         assert (bits(d.k_cache) == k_ref).all() and (bits(d.v_cache) == v_ref).all(), odd
+
+
+@pytest.mark.parametrize("hd, q_lens", [(128, [1] * 62 + [0, 0, 1, 2]),              # one look at the lengths, a pair per row
+                                        (128, [0] * 3 + [1] * 60 + [17]),           # 4 * 77 rows <= 5 * 64 sequences, a chunk of 17 rows
+                                        (64, [1] * 300 + [0] * 30 + [33, 2]),       # more than 256 sequences
+                                        (64, [0] * 20 + [1] * 250 + [38] + [0] * 9),
+                                        (128, [1] * 60 + [18, 2])], ids=str)        # just past the bound: pairs of blocks
+def test_append_of_decode_rows(hd, q_lens):
+    # a pair of (sequence, block) per row, sequences without rows first, between and last, chunks that start and end inside blocks
+    Hkv = 8
+    ctx = [(37 * i + 15) % 71 for i in range(len(q_lens))]
+    need = int(sum((q + c + 15) // 16 for q, c in zip(q_lens, ctx)))
+    b = W.build_batch(Hq=Hkv, Hkv=Hkv, hd=hd, q_lens=q_lens, ctx_lens=ctx, num_blocks=need + 7, seed=91)
+    say(f"case: append of decode rows {hd} {len(q_lens)} {b.total_q}")
+    rng = np.random.default_rng(5)
+    k_new, v_new = (rng.integers(0, 65536, size=(b.total_q, Hkv, hd)).astype(np.uint16) for _ in range(2))
+    k_ref, v_ref = b.k_cache.copy(), b.v_cache.copy()
+    ref_numpy.kv_append(k_new, v_new, k_ref, v_ref, b.block_tables, b.query_start_loc, b.ctx_lens)
+    d = W.to_device(b)
+    bt, sl, qsl, cl = device_meta(b)
+    to_dev = lambda a: torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
+    for parts in (0, 8):
+        k, v = d.k_cache.clone(), d.v_cache.clone()
+        with B.Context(Hkv, Hkv, hd, b.BS, b.num_blocks, b.max_blocks_per_seq) as c:
+            c.set_option("append_parts", parts)
+            c.kv_append(to_dev(k_new), to_dev(v_new), k, v, bt, qsl, cl)
+            torch.cuda.synchronize()
+        assert (bits(k) == k_ref).all() and (bits(v) == v_ref).all()
