@@ -1385,6 +1385,32 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         }
         if constexpr (NEXT) sums_n = sums;
     };
+    // A half with weights that are infinite or NaN.  In add_weights both columns of a pair would lose their sums, as 0 * inf and
+    // 0 * NaN are NaN: a column whose own sum, of its two lanes, is not finite takes part in the product with weights of 0, and its
+    // own sum is put in its place.  The other column's sum has the bits that it has beside finite weights.  Once the reference has
+    // moved only a score of NaN or +inf comes to that, and the column's running sum is NaN from here on: its query becomes 0, so
+    // that the halves to come do not end here again.
+    auto keep_apart = [&](const u32x4 (&P)[2], f32x4 &sums) {
+        float own = 0.f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) own = sum2_bf16(P[q][w], own);
+        float x, y;
+        swap32(own, x, y);
+        own = x + y;
+        const bool lost = !(own <= 3.402823466e38f);   // (weights are not negative)
+        sums = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) add_weights(u32x4{lost ? 0u : P[q][0], lost ? 0u : P[q][1], lost ? 0u : P[q][2], lost ? 0u : P[q][3]}, sums);
+        own = lost ? own : 0.f;
+        sums[0] += __shfl(own, lane & 15);
+        sums[1] += __shfl(own, 16 + (lane & 15));
+        m = lost ? 0.f : m;
+        const uint32_t keep = lost ? 0u : ~0u;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qb[ks] &= keep;
+    };
     // The reference that the weights of a half were computed with was too low for some column of the wave: move it to the
     // maximum of the half and compute the weights again.
     auto move_reference = [&](const f32x16 &Ss, u32x4 (&Pn)[2], f32x4 &sums_n) {
@@ -1394,6 +1420,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         const float alpha = fast_exp2(m - m_new);
         m = m_new;
         weights16(Ss, Pn, sums_n);
+        keep_apart(Pn, sums_n);
         lsum_lo *= __shfl(alpha, lane & 15);
         lsum_hi *= __shfl(alpha, 16 + (lane & 15));
 #pragma unroll
@@ -1447,6 +1474,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
         mask16(S0, st_lo * STEP);
         first_reference(S0);
         region(no, yes, yes, P0, sums0, 0, 0, S0, P0, sums0, S1, st_lo & 1, 1, nothing, nothing);
+        if (too_large(sums0)) keep_apart(P0, sums0);
         // w_last: the last step that this wave has columns for; the loop runs to the one before
         const int w_last = w_used ? min(nstep - 1, w_pos_hi / T) : st_lo - 1;
         int st = st_lo;
@@ -1532,6 +1560,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
                 first_operands(no, yes, 0, 0, (st + 1) & 1, 0);
                 load_step(st);
                 region(no, yes, yes, PA, sumsA, 0, 0, SA, PA, sumsA, SB, (st + 1) & 1, 0, nothing, nothing);
+                if (too_large(sumsA)) keep_apart(PA, sumsA);
                 ++st;
                 arrive(st);
                 if (st < w_last) first_operands(yes, yes, (st - 1) & 1, 0, (st + 1) & 1, 0);
@@ -1568,6 +1597,7 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
             } else {
                 load_step(st);
                 weights16(SA, PB, sumsB);
+                if (too_large(sumsB)) keep_apart(PB, sumsB);
             }
             ++st;
             arrive(st);
