@@ -1233,8 +1233,8 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
     };
     // Weights are computed against the reference m as it stands.  It only has to keep them in range (the final division cancels
     // it, weights above 1 are as exact in bf16 and fp32 as below), so it moves when the weights of a column's half step sum to
-    // more than kMaxWeights, or to infinity or NaN: rarely, and then the half is done again (move_reference).
-    constexpr float kMaxWeights = 256.0f;
+    // more than kMaxWeights, or to infinity or NaN, and then the half is done again (move_reference).
+    constexpr float kMaxWeights = 256.0f, kMargin = 8.0f;
     auto weights16 = [&](const f32x16 &S, u32x4 (&P)[2], f32x4 &sums) {
         sums = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1411,22 +1411,30 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qb[ks] &= keep;
     };
-    // The reference that the weights of a half were computed with was too low for some column of the wave: move it to the
-    // maximum of the half and compute the weights again.
+    // The reference that the weights of a half were computed with was too low for some column of the wave: move that of all its
+    // columns to the maximum of the half and a margin, and compute the weights again.  With the margin scores may rise by 2^11 to
+    // 2^16 before the next move.  The maximum itself keeps a weight that is a power of two, without a rounding error: moves by
+    // powers of two, of weights that are only scaled, were faster yet (677 us for the last column below), but their errors on rising
+    // scores 2 to 11 % larger.  All columns move together because every move costs the wave the same: columns that each move by
+    // themselves took 715 / 634 us for the first two columns below.  So the rounding of an output can depend on the scores of the
+    // other rows and heads of its wave, where those rise that far.
+    // MI355X (us), 2 x 2048 rows on 4096 tokens, 64/8 heads; scores that rise by 2^72 over all keys / of deviation 4 / that rise by
+    // 2^32 in every half / of deviation 1: maxima of every step and a rescale where one grew by 2^8, as the lean kernels do,
+    // 585 / 613 / 581 / 598; no margin 558 / 592 / 741 / 560; as here 541 / 575 / 751 / 559.
     auto move_reference = [&](const f32x16 &Ss, u32x4 (&Pn)[2], f32x4 &sums_n) {
         float x, y;
         swap32(max16(Ss), x, y);
-        const float m_new = max2(m, floor_m1e30(max2(x, y) * c_log2e));
+        const float m_new = max2(m, floor_m1e30(max2(x, y) * c_log2e) + kMargin);
         const float alpha = fast_exp2(m - m_new);
         m = m_new;
         weights16(Ss, Pn, sums_n);
-        keep_apart(Pn, sums_n);
         lsum_lo *= __shfl(alpha, lane & 15);
         lsum_hi *= __shfl(alpha, 16 + (lane & 15));
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) O[mb][r] *= alpha;
+        if (too_large(sums_n)) keep_apart(Pn, sums_n);
     };
 
     const auto yes = std::true_type();
@@ -1593,12 +1601,12 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
                 load_step(st);
                 mask_step(SB, st);
                 region(yes, no, yes, PA, sumsA, (st - 1) & 1, 0, SB, PB, sumsB, SA, 0, 0, nothing, nothing);
-                if (too_large(sumsB)) move_reference(SB, PB, sumsB);
             } else {
                 load_step(st);
-                weights16(SA, PB, sumsB);
-                if (too_large(sumsB)) keep_apart(PB, sumsB);
+                SB = SA;
+                weights16(SB, PB, sumsB);
             }
+            if (too_large(sumsB)) move_reference(SB, PB, sumsB);
             ++st;
             arrive(st);
             first_operands(yes, no, (st - 1) & 1, 0, 0, 0);
