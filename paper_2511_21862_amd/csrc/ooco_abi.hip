@@ -2017,7 +2017,7 @@ ooco_status ooco_kv_append(ooco_ctx *ctx, const void *k_new, const void *v_new, 
         return fail(ctx, OOCO_EINVAL, "ooco_kv_append: NULL pointer argument");
     hipError_t e = launch_kv_append(k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, num_seqs,
                                     total_q_tokens, ctx->Hkv, ctx->hd, ctx->max_blocks_per_seq, ctx->num_blocks,
-                                    (int)ctx->opt_append_parts, reinterpret_cast<hipStream_t>(stream));
+                                    (int)ctx->opt_append_parts, ctx->num_cus, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(ctx, OOCO_EHIP, "ooco_kv_append: kernel launch: %s", hipGetErrorString(e));
     return OOCO_OK;
 }

@@ -38,4 +38,11 @@ struct MergeWord {
     static OOCO_HD bool last_event(int w, int nparts) { return draws(w) + leaves(w) + 1 == kSlices - 1 + nparts; }
 };
 
+// The KV append's choice of workgroups: of the two (sequence, block) pairs per sequence and one per 16 rows, or of one per row, which
+// is half as many where nearly all sequences have one row.  `workgroups` is the former number with all parts.
+OOCO_HD bool append_by_rows(int total_q, int num_seqs, int64_t workgroups, int num_cus)
+{
+    return 4 * (int64_t)total_q <= 5 * (int64_t)num_seqs && workgroups > num_cus;
+}
+
 }  // namespace ooco

@@ -2433,7 +2433,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
 
 hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache, void *v_cache, const int32_t *block_tables,
                             const int32_t *query_start_loc, const int32_t *ctx_lens, int num_seqs, int total_q, int Hkv,
-                            int hd, int max_blocks_per_seq, int64_t num_blocks, int parts_opt, hipStream_t s)
+                            int hd, int max_blocks_per_seq, int64_t num_blocks, int parts_opt, int num_cus, hipStream_t s)
 {
     if (total_q <= 0 || num_seqs <= 0) return hipSuccess;
     // One workgroup per 512 elements of a row.  8 kv heads x 128, 4,224 tokens, 1 / 2 / 4 / 8 parts: 12.7 / 10.4 / 13.1 /
@@ -2444,7 +2444,7 @@ hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache,
     // more than one per compute unit, it owns a pair per row.  MI355X (us): 200 decodes, 8 kv heads of 128 7.18 -> 6.34, 400 of 4
     // heads 7.39 -> 6.62, 150 of 8 heads of 64 5.25 -> 4.60, 64 of 8 heads of 128 level; 91 of 4 heads, under 256 pairs, 5.14 -> 5.23.
     const int64_t pairs = total_q / kBlockSize + 2 * (int64_t)num_seqs + 1;
-    const bool by_rows = 4 * (int64_t)total_q <= 5 * (int64_t)num_seqs && pairs * parts > 256;
+    const bool by_rows = append_by_rows(total_q, num_seqs, pairs * parts, num_cus);
     const unsigned grid = (unsigned)((by_rows ? total_q : pairs) * parts);
     hipLaunchKernelGGL(kv_append_kernel, dim3(grid), dim3(kAppendThreads), 0, s, (const uint16_t *)k_new,
                        (const uint16_t *)v_new, (uint16_t *)k_cache, (uint16_t *)v_cache, block_tables, query_start_loc,

@@ -30,6 +30,7 @@ int arrivals(int w) { return MergeWord::arrivals(w); }
 int arrived_last(int w, int nparts) { return MergeWord::arrived_last(w, nparts); }
 int slice(int w) { return MergeWord::slice(w); }
 int last_event(int w, int nparts) { return MergeWord::last_event(w, nparts); }
+int by_rows(int total_q, int num_seqs, int64_t workgroups, int num_cus) { return ooco::append_by_rows(total_q, num_seqs, workgroups, num_cus); }
 }
 """
 
@@ -60,6 +61,15 @@ def test_run_bounds_by_reciprocal_equal_the_divisions(lib):
         for c in (0, 1):
             for ulps in (-2, -1, 0, 1, 2):
                 assert lib.wrong_quotients(x.ctypes.data, y.ctypes.data, z.ctypes.data, c, ulps, len(x)) == 0
+
+
+# (sequences, rows, parts, compute units, a workgroup per row)
+@pytest.mark.parametrize("n, rows, parts, cus, want", [(64, 64, 2, 256, True), (63, 63, 2, 256, True), (62, 62, 2, 256, False), (64, 64, 1, 256, False),
+                                                       (16, 16, 2, 64, True), (15, 15, 2, 64, False), (62, 62, 2, 128, True), (300, 300, 2, 304, True),
+                                                       (70, 70, 2, 304, False), (64, 80, 2, 256, True), (64, 81, 2, 256, False), (8, 512, 8, 64, False)])
+def test_append_takes_a_workgroup_per_row_past_one_per_compute_unit(lib, n, rows, parts, cus, want):
+    lib.by_rows.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
+    assert bool(lib.by_rows(rows, n, (rows // 16 + 2 * n + 1) * parts, cus)) == want
 
 
 # A part: "work" before it arrives, "wait" while it looks at the counter, "merge" while it holds a slice, "gone".  An atomic is
