@@ -125,7 +125,7 @@ struct HostPlan {
     int32_t coop = 0;            // decode runs are worked on by workgroups of four waves (decode_coop_kernel); kCoopBySequence: run i is sequence i
     int32_t coop_waves = 4;      // waves of such a workgroup
     int32_t pf_units = 0;        // key groups beside decode work in one launch: the compute units that the prefill workgroups take
-    int32_t nbi = 0;             // KV blocks per softmax step of the decode kernel that the plan asks for (0 = the kernel's default)
+    int32_t nbi = 0;             // KV blocks per softmax step that the plan asks single decode waves for (0 = the kernel's default)
 };
 
 // XCD weights -> cumulative form; false if a weight is outside 1..255 or they differ by more than 4x.
@@ -242,7 +242,6 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         // Beside prefill workgroups of key groups: workgroups of eight waves, one per unit that those leave.
         const int64_t left = std::max<int64_t>(1, (cus - out.pf_units) / geo.Hkv);
         out.coop_waves = 8;
-        out.nbi = geo.hd == 128 ? 2 : 0;
         if (geo.segments_opt == 0 && longest <= 48 * 128 && num_seqs <= left) {
             out.coop = kCoopBySequence;
             out.static_runs = num_seqs;
@@ -252,17 +251,14 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
         out.coop = 1;
     } else if (coop_can && geo.coop_opt && geo.segments_opt == 0 && whole) {
         out.coop = kCoopBySequence;
-        out.nbi = geo.hd == 128 ? 2 : 0;
         out.static_runs = num_seqs;
         out.static_blocks = (int32_t)dec_blocks;
         return;
     }
     if (out.pf_units == 0) out.coop = coop_can && (geo.coop_opt >= 2 || (geo.coop_opt == 1 && coop_rule));
-    if (out.pf_units > 0)
-        ;
-    else if (geo.hd == 128 && short_seqs)
+    if (!out.coop && geo.hd == 128 && short_seqs)
         out.nbi = tiles <= 16384 && 2 * dec_seqs * geo.Hkv < 5 * cus ? 2 : 1;
-    else if (geo.hd == 128 && small)
+    else if (!out.coop && geo.hd == 128 && small)
         out.nbi = 2;
     int64_t min_blocks = 16 * 128 / geo.hd, at_least = 0;   // blocks of a run; runs whatever they hold
     if (out.coop) {
@@ -442,7 +438,8 @@ void plan_prefill_parts(const PlanGeometry &geo, const PrefillFacts &f, int32_t 
         const double merge = w_parts > 0.0 ? std::max(1.5 + 0.3 * k, 0.64 + 0.29 * k + 2.03 * w_parts / cus) : 0.0;
         return 4.1 + 1.93 * std::min(r, 3.0) + body + merge;
     };
-    // (below 16 steps the merge is most of what a split costs, and two workgroups keep a unit busy: the estimate above)
+    // (below 16 steps the merge is most of what a split costs, and two workgroups keep a unit busy: the estimate above.  So it is
+    // beside decode work, whose workgroups hold units as well: there the count of two per unit is kept, it was not fitted for three)
     const bool use64 = geo.hd == 64 && dec_blocks == 0 && out.pf_waves == 4 && max_tile_steps >= 16 && units < 2 * (int64_t)geo.num_cus;
     // With the tile list every tile gets parts by its own number of steps: the longest tile k parts, the others as
     // many as keep their parts no longer than that tile's (a tile of a short chunk stays whole beside a long one).
@@ -1517,20 +1514,20 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names, size_t cap)
     const bool dec = pl.static_runs > 0, pf = pl.n_tiles > 0;
     const bool coop = decode_coop(ctx) != 0, in_args = plan_in_args(pl), lean = pl.lean && ctx->hd == 128;
     const bool general = !in_args || (!coop && (pl.tail_runs > 0 || pl.cw[kXcds - 1] != 0));
-    const int wanted = decode_nbi(ctx), nbi = coop ? 256 / ctx->hd : wanted == 2 || wanted == 4 ? wanted : 1;
+    const int wanted = decode_nbi(ctx), blocks = coop ? 256 / ctx->hd : wanted == 2 || wanted == 4 ? wanted : 1;   // (in flight; of a step)
     char d[64] = "", f[64] = "";
     if (runs_as_step(ctx))
         snprintf(d, sizeof d, pl.pf_groups > 1 ? "step_kernel_groups<%d, %d>" : pl.lean ? "step_kernel_lean<%d>" : coop ? "step_kernel<%d, %d, true>" : "step_kernel<%d, %d, false>", ctx->hd,
-                 nbi);
+                 blocks);
     else if (dec && pf && pl.dec_cus > 0)
         snprintf(d, sizeof d, "mixed_kernel<%d>", ctx->hd);
     else {
         if (dec && coop)
-            snprintf(d, sizeof d, "decode_coop_kernel%s<%d, %d>", pl.coop_waves == 8 ? "_groups" : general ? "_general" : "", ctx->hd, nbi);
+            snprintf(d, sizeof d, "decode_coop_kernel%s<%d, %d>", pl.coop_waves == 8 ? "_groups" : general ? "_general" : "", ctx->hd, blocks);
         else if (dec && lean)
             snprintf(d, sizeof d, "decode_kernel_lean%s<%d>", general ? "_general" : "", ctx->hd);
         else if (dec)
-            snprintf(d, sizeof d, "decode_kernel%s<%d, %d>", general ? "_general" : "", ctx->hd, nbi);
+            snprintf(d, sizeof d, "decode_kernel%s<%d, %d>", general ? "_general" : "", ctx->hd, blocks);
         if (pf && (pl.pf_groups > 1 || (lean && pl.pf_waves == 8)))
             snprintf(f, sizeof f, pl.pf_groups > 1 ? "prefill_kernel_groups<%d>" : "prefill_kernel_lean<%d>", ctx->hd);
         else if (pf)

@@ -905,7 +905,7 @@ OOCO_DEV void decode_coop_run(const AttnParams &p, CumAt cum_at, int cum_head, i
     }
 }
 
-template <int HD, int NBI, int NWV, bool DEV>
+template <int HD, int AHEAD, int NWV, bool DEV>
 OOCO_DEV void decode_coop_kernel_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
@@ -918,27 +918,27 @@ OOCO_DEV void decode_coop_kernel_body(const KernArgs &a)
     const int kvh = p.rotate_heads ? (slot + run) % p.Hkv : slot;
     uint64_t *const trace = p.trace ? p.trace + (int64_t)blockIdx.x * 4 : nullptr;
     if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
-    decode_coop_run<HD, NBI, NWV>(p, [&](int idx) -> int { return cum_entry<DEV>(a, idx); }, cum_head<DEV>(a, threadIdx.x & 63), run, kvh,
+    decode_coop_run<HD, AHEAD, NWV>(p, [&](int idx) -> int { return cum_entry<DEV>(a, idx); }, cum_head<DEV>(a, threadIdx.x & 63), run, kvh,
                                   lds, trace);
     if (trace) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0) trace[3] = wall_clock64();
     }
 }
-template <int HD, int NBI>
+template <int HD, int AHEAD>
 __global__ __launch_bounds__(256, 2) void decode_coop_kernel(const KernArgs a)
 {
-    decode_coop_kernel_body<HD, NBI, 4, false>(a);
+    decode_coop_kernel_body<HD, AHEAD, 4, false>(a);
 }
-template <int HD, int NBI>
+template <int HD, int AHEAD>
 __global__ __launch_bounds__(256, 2) void decode_coop_kernel_general(const KernArgs a)   // a plan in device memory
 {
-    decode_coop_kernel_body<HD, NBI, 4, true>(a);
+    decode_coop_kernel_body<HD, AHEAD, 4, true>(a);
 }
-template <int HD, int NBI>
+template <int HD, int AHEAD>
 __global__ __launch_bounds__(512, 2) void decode_coop_kernel_groups(const KernArgs a)   // eight waves, beside key groups
 {
-    decode_coop_kernel_body<HD, NBI, 8, false>(a);
+    decode_coop_kernel_body<HD, AHEAD, 8, false>(a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -972,7 +972,7 @@ __global__ __launch_bounds__(512, 2) void decode_coop_kernel_groups(const KernAr
 // 2048, 32/8 heads 85.7 -> 81.1, 300 rows on 14,683 tokens 87.0 -> 82.5.  (Calls as a whole, with the output stores and the
 // operands below as well: 608 -> 576, 89.3 -> 78.5, 256 rows on 8192 tokens 86.6 -> 81.5.)
 // The causal mask runs only on halves that touch the diagonal; at the end of a sequence the unused V slots are zeroed once in LDS
-// instead of masking operands.  Two workgroups fit a CU (<= 256 VGPRs, 64 KiB LDS each).
+// instead of masking operands.  Two workgroups fit a CU (<= 256 VGPRs, 64 KiB LDS each), three of head_dim 64 (<= 168, 32 KiB).
 constexpr int kPfThreads = 256;   // threads of the four-wave workgroup (the eight-wave one has 512)
 constexpr int kPfBlocks = 4;    // KV blocks per step
 constexpr int kSharedMergeParts = 4;   // parts from which sharing the merge of a split tile pays (see prefill_unit)
@@ -2008,7 +2008,8 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_num_vgpr(168))) void 
 // rows + 128 decodes) and 1653 -> 1635 (2 x 2048 + 32 long decodes); in a loop of calls level, 266 / 268 and 1625 / 1630, but
 // 340 and 2170 on a context whose side stream shares a hardware queue with the caller's stream (one or two of eight contexts
 // made in a row), where the kernels run in sequence.  2 x 120 rows + 24 short decodes, in sequence before: 37.5 -> 29.
-template <int HD, int NBI, int MBATCH, int NW, bool PIPE, bool COOP, int KG = 1>
+// DEC = decode's KV blocks: of a step (single waves), or in flight (cooperative workgroups, see decode_coop_run).
+template <int HD, int DEC, int MBATCH, int NW, bool PIPE, bool COOP, int KG = 1>
 OOCO_DEV void step_body(const KernArgs &a)
 {
     const AttnParams &p = a.p;
@@ -2020,7 +2021,7 @@ OOCO_DEV void step_body(const KernArgs &a)
         const int run = p.rows2d ? (int)blockIdx.y : wg / p.Hkv, slot = wg - run * p.Hkv;
         uint64_t *const trace = p.trace ? p.trace + (int64_t)wg * 4 : nullptr;
         if (trace && threadIdx.x == 0) trace[0] = wall_clock64();
-        decode_coop_run<HD, COOP ? NBI : 256 / HD, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + (threadIdx.x & 63)], run,
+        decode_coop_run<HD, COOP ? DEC : 256 / HD, NW>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + (threadIdx.x & 63)], run,
                                      p.rotate_heads ? (slot + run) % p.Hkv : slot,
                                      reinterpret_cast<float *>(stage_lds<HD, KG>()), trace);
         if (trace) {
@@ -2044,7 +2045,7 @@ OOCO_DEV void step_body(const KernArgs &a)
         uint64_t *const trace = p.trace ? p.trace + (int64_t)item * 4 : nullptr;
         if (trace && lane == 0) trace[0] = wall_clock64();
         bool first_piece = true;
-        decode_run<HD, NBI, MBATCH>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + lane], EqualRuns{p.static_blocks, p.static_runs},
+        decode_run<HD, DEC, MBATCH>(p, [&](int idx) -> int { return a.cum[idx]; }, a.cum[1 + lane], EqualRuns{p.static_blocks, p.static_runs},
                                     run, kvh, lane, trace, first_piece, []() {});
         if (trace) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -2063,18 +2064,18 @@ OOCO_DEV void step_body(const KernArgs &a)
     }
 }
 
-template <int HD, int NBI, bool COOP>
+template <int HD, int DEC, bool COOP>
 __global__ __launch_bounds__(kPfThreads, HD == 64 ? 3 : 2) void step_kernel(const KernArgs a)
 {
-    step_body<HD, NBI, 3, 4, true, COOP>(a);
+    step_body<HD, DEC, 3, 4, true, COOP>(a);
 }
 
 // The same with prefill workgroups of key groups and decode workgroups of eight waves, which have a compute unit each: small
 // batches whose workgroups all find one.
-template <int HD, int NBI>
+template <int HD, int DEC>
 __global__ __launch_bounds__(512, 1) void step_kernel_groups(const KernArgs a)
 {
-    step_body<HD, NBI, 3, 8, true, true, kKeyGroups>(a);
+    step_body<HD, DEC, 3, 8, true, true, kKeyGroups>(a);
 }
 
 // The register-lean pair in one launch: prefill workgroups of eight waves; of a decode workgroup's eight waves the
@@ -2569,7 +2570,7 @@ hipError_t launch_step(KernArgs &a, int num_cus, hipStream_t s)
     const int64_t pf = a.p.pf_table ? (int64_t)a.p.pf_table * a.p.Hkv
                                     : (int64_t)a.p.n_tiles * a.p.Hkv * (a.p.pf_split > 0 ? a.p.pf_split : 1);
     a.p.dec_wgs = (int32_t)dec;
-    if (dec + pf > 2 * (int64_t)num_cus) a.p.pf_share = 0;   // (two workgroups of four waves fit a unit)
+    if (dec + pf > 2 * (int64_t)num_cus) a.p.pf_share = 0;   // (two workgroups of four waves fit a unit, of either head_dim)
     // rows: the decode runs of cooperative workgroups, then the tile list's entries
     if (a.p.rows2d && (!a.p.coop || !a.p.pf_table || a.p.list_row != a.p.static_runs)) return hipErrorInvalidValue;
     const dim3 grid = a.p.rows2d ? dim3((unsigned)a.p.Hkv, (unsigned)(a.p.static_runs + a.p.pf_table)) : dim3((unsigned)(dec + pf));
