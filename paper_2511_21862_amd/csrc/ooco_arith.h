@@ -45,4 +45,10 @@ OOCO_HD bool append_by_rows(int total_q, int num_seqs, int64_t workgroups, int n
     return 4 * (int64_t)total_q <= 5 * (int64_t)num_seqs && workgroups > num_cus;
 }
 
+// Whether the KV append's 16-byte stores go past the caches, by the bytes of K and V that it writes (see launch_kv_append).
+OOCO_HD bool append_past_caches(int total_q, int num_seqs, int64_t bytes)
+{
+    return bytes > 8 * (1 << 20) || (num_seqs >= 16 && total_q < 100 * (int64_t)num_seqs);
+}
+
 }  // namespace ooco

@@ -2262,12 +2262,10 @@ __global__ __launch_bounds__(kCopyThreads) void block_copy_kernel(const u32x4 *k
 // (q_len / 16 + 2); the grid has total_q / 16 + 2 num_seqs + 1 workgroups and those beyond a sequence's last
 // block leave at once.  Every workgroup finds its sequence with one 64-lane look at query_start_loc.
 constexpr int kAppendThreads = 256;
-__global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_t *k_new, const uint16_t *v_new,
-                                                                   uint16_t *k_cache, uint16_t *v_cache,
-                                                                   const int32_t *block_tables,
-                                                                   const int32_t *query_start_loc, const int32_t *ctx_lens,
-                                                                   int num_seqs, int total_q, int Hkv, int hd,
-                                                                   int max_blocks_per_seq, int64_t num_blocks, int parts, int by_rows)
+template <bool PAST>   // 16-byte stores past the caches
+OOCO_DEV void kv_append_body(const uint16_t *k_new, const uint16_t *v_new, uint16_t *k_cache, uint16_t *v_cache, const int32_t *block_tables,
+                             const int32_t *query_start_loc, const int32_t *ctx_lens, int num_seqs, int total_q, int Hkv, int hd,
+                             int max_blocks_per_seq, int64_t num_blocks, int parts, int by_rows)
 {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -2334,9 +2332,13 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
     const uint16_t *const k_src = k_new + row0 * row_elems, *const v_src = v_new + row0 * row_elems;
     u32x4 *const k_dst = reinterpret_cast<u32x4 *>(k_cache) + (int64_t)blk * chunks * kBlockSize + slot0;
     uint16_t *const v_dst = v_cache + (int64_t)blk * row_elems * kBlockSize;   // slot 0 of the first cache row
-    // Stores of 16 bytes go past the caches (`nt`): what lies in L2 at the end of the kernel is written back then.  MI355X (us): 8 x
-    // 512 rows and 128 decodes 10.44 -> 9.74, 2 x 2048 rows 7.91 -> 7.36; the 2-byte stores of a decode row's V lose by it (64
-    // decodes 4.4 -> 5.5).
+    // (the 2-byte stores of a decode row's V lose past the caches: 64 decodes 4.4 -> 5.5 us)
+    auto store16 = [](const u32x4 &v, u32x4 *d) {
+        if constexpr (PAST)
+            __builtin_nontemporal_store(v, d);
+        else
+            *d = v;
+    };
     if (nrow == kBlockSize) {   // a whole block
         // K: thread -> (row r = tid % 16, 16-byte chunk c = tid / 16 + 16 i): the 16 rows of a chunk are adjacent in
         // the cache, so a wave's stores cover 4 chunks x 256 contiguous bytes
@@ -2353,7 +2355,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int c = c0 + i * kSlice * parts;
-                if (c < chunks && blk_ok) __builtin_nontemporal_store(v[i], &dst[(int64_t)c * kBlockSize]);
+                if (c < chunks && blk_ok) store16(v[i], &dst[(int64_t)c * kBlockSize]);
             }
         }
         // V: thread -> element e = (kv head, dim) of all rows, 32 contiguous bytes of the cache.  (Two adjacent elements
@@ -2367,8 +2369,8 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
                 x[r] = (uint32_t)s[(int64_t)(2 * r) * row_elems] | ((uint32_t)s[(int64_t)(2 * r + 1) * row_elems] << 16);
             u32x4 *d4 = reinterpret_cast<u32x4 *>(v_dst + (int64_t)e * kBlockSize);
             if (blk_ok) {
-                __builtin_nontemporal_store(u32x4{x[0], x[1], x[2], x[3]}, d4);
-                __builtin_nontemporal_store(u32x4{x[4], x[5], x[6], x[7]}, d4 + 1);
+                store16(u32x4{x[0], x[1], x[2], x[3]}, d4);
+                store16(u32x4{x[4], x[5], x[6], x[7]}, d4 + 1);
             }
         }
         return;
@@ -2403,7 +2405,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
             if (!blk_ok) continue;
 #pragma unroll
             for (int i = 0; i < KI; ++i)
-                if (r < nrow && c0 + 16 * i < chunks) __builtin_nontemporal_store(kv[i], &k_dst[(int64_t)(c0 + 16 * i) * kBlockSize + r]);
+                if (r < nrow && c0 + 16 * i < chunks) store16(kv[i], &k_dst[(int64_t)(c0 + 16 * i) * kBlockSize + r]);
             if (e < row_elems) {
                 // quarters of a cache row (4 slots = 8 bytes) that the step covers whole are written with one store
                 // each, the ragged ends slot by slot
@@ -2431,6 +2433,23 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_
     else
         partly(std::integral_constant<int, 1>());
 }
+__global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(const uint16_t *k_new, const uint16_t *v_new, uint16_t *k_cache, uint16_t *v_cache,
+                                                                   const int32_t *block_tables, const int32_t *query_start_loc,
+                                                                   const int32_t *ctx_lens, int num_seqs, int total_q, int Hkv, int hd,
+                                                                   int max_blocks_per_seq, int64_t num_blocks, int parts, int by_rows)
+{
+    kv_append_body<true>(k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, num_seqs, total_q, Hkv, hd, max_blocks_per_seq,
+                         num_blocks, parts, by_rows);
+}
+__global__ __launch_bounds__(kAppendThreads) void kv_append_kernel_cached(const uint16_t *k_new, const uint16_t *v_new, uint16_t *k_cache,
+                                                                          uint16_t *v_cache, const int32_t *block_tables,
+                                                                          const int32_t *query_start_loc, const int32_t *ctx_lens, int num_seqs,
+                                                                          int total_q, int Hkv, int hd, int max_blocks_per_seq,
+                                                                          int64_t num_blocks, int parts, int by_rows)
+{
+    kv_append_body<false>(k_new, v_new, k_cache, v_cache, block_tables, query_start_loc, ctx_lens, num_seqs, total_q, Hkv, hd, max_blocks_per_seq,
+                          num_blocks, parts, by_rows);
+}
 
 hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache, void *v_cache, const int32_t *block_tables,
                             const int32_t *query_start_loc, const int32_t *ctx_lens, int num_seqs, int total_q, int Hkv,
@@ -2447,7 +2466,14 @@ hipError_t launch_kv_append(const void *k_new, const void *v_new, void *k_cache,
     const int64_t pairs = total_q / kBlockSize + 2 * (int64_t)num_seqs + 1;
     const bool by_rows = append_by_rows(total_q, num_seqs, pairs * parts, num_cus);
     const unsigned grid = (unsigned)((by_rows ? total_q : pairs) * parts);
-    hipLaunchKernelGGL(kv_append_kernel, dim3(grid), dim3(kAppendThreads), 0, s, (const uint16_t *)k_new,
+    // Attention reads what was appended next.  A few prompts' keys are all that it reads for a while, and it finds them in the caches
+    // unless they went past them; many decode rows, or a prefill part beside them, are faster out of the way of the old keys, and so
+    // is whatever is more than the caches keep.  Append and attention of a captured layer, MI355X (us), through the caches / past them:
+    // 1000 rows 27.0 / 28.4, prompts of 1000, 700 and 300 30.1 / 32.0, 1000 rows beside 8 / 16 / 32 decodes 26.9 / 29.4, 38.2 / 37.5,
+    // 58.9 / 57.2, 8 x 512 beside 128 287.6 / 279.7, 64 decodes 82.2 / 80.9, 200 160.3 / 154.7, 8 x 512 and 2 x 2048 rows level.  The
+    // append alone: 5 rows and 3 decodes 6.4 / 6.6, 1000 rows 6.2 / 5.8, 8 x 512 10.0 / 9.4, with 128 decodes 12.3 / 10.9.
+    const bool past = append_past_caches(total_q, num_seqs, 4 * (int64_t)total_q * Hkv * hd);
+    hipLaunchKernelGGL(past ? kv_append_kernel : kv_append_kernel_cached, dim3(grid), dim3(kAppendThreads), 0, s, (const uint16_t *)k_new,
                        (const uint16_t *)v_new, (uint16_t *)k_cache, (uint16_t *)v_cache, block_tables, query_start_loc,
                        ctx_lens, num_seqs, total_q, Hkv, hd, max_blocks_per_seq, num_blocks, parts, (int)by_rows);
     return hipGetLastError();

@@ -128,6 +128,27 @@ def test_append_of_partly_covered_blocks(Hkv, hd):
         assert (bits(d.k_cache) == k_ref).all() and (bits(d.v_cache) == v_ref).all(), odd
 
 
+@pytest.mark.parametrize("Hkv, hd, q_lens", [(8, 128, [1] * 15 + [90]), (8, 128, [1] * 14 + [90]),          # past the caches from 16 sequences on
+                                             (8, 128, [35] * 16), (8, 128, [120] * 16),                      # .. of fewer than 100 rows
+                                             (8, 128, [2048]), (8, 128, [2049]), (2, 64, [700, 33, 5])], ids=str)   # and from 8 MiB on
+def test_append_through_and_past_the_caches(Hkv, hd, q_lens):
+    ctx = [(29 * i + 7) % 50 for i in range(len(q_lens))]
+    need = int(sum((q + c + 15) // 16 for q, c in zip(q_lens, ctx)))
+    b = W.build_batch(Hq=Hkv, Hkv=Hkv, hd=hd, q_lens=q_lens, ctx_lens=ctx, num_blocks=need + 7, seed=92)
+    say(f"case: append through and past the caches {Hkv} {hd} {len(q_lens)} {b.total_q}")
+    rng = np.random.default_rng(6)
+    k_new, v_new = (rng.integers(0, 65536, size=(b.total_q, Hkv, hd)).astype(np.uint16) for _ in range(2))
+    k_ref, v_ref = b.k_cache.copy(), b.v_cache.copy()
+    ref_numpy.kv_append(k_new, v_new, k_ref, v_ref, b.block_tables, b.query_start_loc, b.ctx_lens)
+    d = W.to_device(b)
+    bt, sl, qsl, cl = device_meta(b)
+    to_dev = lambda a: torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
+    with B.Context(Hkv, Hkv, hd, b.BS, b.num_blocks, b.max_blocks_per_seq) as c:
+        c.kv_append(to_dev(k_new), to_dev(v_new), d.k_cache, d.v_cache, bt, qsl, cl)
+        torch.cuda.synchronize()
+    assert (bits(d.k_cache) == k_ref).all() and (bits(d.v_cache) == v_ref).all()
+
+
 @pytest.mark.parametrize("hd, q_lens", [(128, [1] * 62 + [0, 0, 1, 2]),              # one look at the lengths, a pair per row
                                         (128, [0] * 3 + [1] * 60 + [17]),           # 4 * 77 rows <= 5 * 64 sequences, a chunk of 17 rows
                                         (64, [1] * 300 + [0] * 30 + [33, 2]),       # more than 256 sequences

@@ -30,6 +30,7 @@ int arrivals(int w) { return MergeWord::arrivals(w); }
 int arrived_last(int w, int nparts) { return MergeWord::arrived_last(w, nparts); }
 int slice(int w) { return MergeWord::slice(w); }
 int last_event(int w, int nparts) { return MergeWord::last_event(w, nparts); }
+int past_caches(int total_q, int num_seqs, int64_t bytes) { return ooco::append_past_caches(total_q, num_seqs, bytes); }
 int by_rows(int total_q, int num_seqs, int64_t workgroups, int num_cus) { return ooco::append_by_rows(total_q, num_seqs, workgroups, num_cus); }
 }
 """
@@ -70,6 +71,15 @@ def test_run_bounds_by_reciprocal_equal_the_divisions(lib):
 def test_append_takes_a_workgroup_per_row_past_one_per_compute_unit(lib, n, rows, parts, cus, want):
     lib.by_rows.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int]
     assert bool(lib.by_rows(rows, n, (rows // 16 + 2 * n + 1) * parts, cus)) == want
+
+
+# (sequences, rows, bytes of K and V per row, past the caches)
+@pytest.mark.parametrize("n, rows, row, want", [(4, 8, 4096, False), (1, 1000, 4096, False), (9, 1008, 4096, False), (17, 1016, 4096, True), (16, 16, 1024, True),
+                                                (15, 15, 4096, False), (16, 1600, 4096, False), (16, 1599, 4096, True), (1, 2048, 4096, False),
+                                                (1, 2049, 4096, True), (8, 4096, 4096, True), (136, 4224, 4096, True), (1 << 20, 1 << 26, 1, True)])
+def test_append_goes_past_the_caches_by_size(lib, n, rows, row, want):
+    lib.past_caches.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64]
+    assert bool(lib.past_caches(rows, n, rows * row)) == want
 
 
 # A part: "work" before it arrives, "wait" while it looks at the counter, "merge" while it holds a slice, "gone".  An atomic is
