@@ -164,13 +164,16 @@ const char *ooco_last_error(const ooco_ctx *ctx);
  *                         unit beside a decode part of up to 150 us; a shorter one does not repay the lean decode
  *                         kernel's 4 %, a longer one not the lean prefill kernel's 9 %); 0 = never (the
  *                         stand-alone kernels side by side); 2 = whenever the batch holds both kinds of work.
- *   "decode_coop"         0/1/2 (default 1; batches without XCD weights or a dynamic tail): 1 = batches of up to two
- *                         beginnings of sequences per run (one beside a prefill part; half a one for equal lengths) and
- *                         70,000 (block, kv head) tiles run in workgroups of four waves that share every piece of a run and
- *                         merge in LDS, and batches of
- *                         sequences of at most 768 tokens (1536 with head_dim 64) take one such workgroup per
- *                         sequence and kv head while that is one per compute unit -- or up to four, where that is
- *                         measured faster than single waves; 0 = single waves; 2 = such workgroups always.  (Forcing "decode_nbi"
+ *   "decode_coop"         0/1/2 (default 1; batches without XCD weights or a dynamic tail): 1 = two kinds of batches run
+ *                         in workgroups of four waves that share their work and merge in LDS.  Batches of sequences of at
+ *                         most 768 tokens (1536 with head_dim 64) take one such workgroup per sequence and kv head
+ *                         while that is one per compute unit -- or up to four, where that is measured faster than single
+ *                         waves.  Of the others, one sequence, or sequences of more than 384 tokens (24 blocks) on average,
+ *                         run after run (n sequences, r = compute units / num_kv_heads runs; tiles: (block, kv head) pairs of
+ *                         head_dim 128, half as many of 64): beside a prefill part up to n = r and 70,000 tiles; else up
+ *                         to 36,864 tiles and n = 2 r, or n = r / 2 where the longest is at most 9/8 of the average; else
+ *                         up to 70,000 tiles whatever n is, with head_dim 64 only where the longest is more than 9/8 of
+ *                         the average.  0 = single waves; 2 = such workgroups always.  (Forcing "decode_nbi"
  *                         asks for single waves.)
  *   "prefill_waves"       waves per prefill workgroup: 4 (128 query columns per staged K/V tile), 8 (256), or
  *                         0 (default) = 4, and 8 where "mixed_lean" applies.  Other values -> OOCO_EINVAL.
@@ -328,6 +331,11 @@ ooco_status ooco_plan_kernels(const ooco_ctx *ctx, char *names /*HOST*/, size_t 
  * (one stream synchronisation) and plans by itself.
  * Launches one kernel, or at most two (decode with its in-kernel merge, and prefill chunks: see option "overlap"),
  * and no copies (batches above 960 sequences: one small copy).
+ * NaN and infinities in q and K: a (row, query head) that sees finite scores, or -inf beside them, is not affected by the
+ * scores of other rows and heads; one that sees a score of NaN or +inf is NaN.  V has to be finite in every slot of the
+ * sequence below seq_len, also where a row does not see the token.
+ * The rounding of an output is that of the batch's plan, and may in prefill also depend on the scores of the rows and heads
+ * beside it, where those rise by more than 2^8 over the keys; calls with the same plan and inputs repeat their bits.
  * Writes every row of out (and the context's workspace), nothing else.  num_seqs == 0 or
  * total_q_tokens == 0 returns OOCO_OK without launching anything.
  * Same context + same plan + same inputs give bit-identical output on every call (no

@@ -1,4 +1,4 @@
-"""Prefill with NaN and infinities in q and K: what is not finite stays in the (row, head) whose scores it reaches.  The columns of a
+"""NaN and infinities in q and K, prefill and decode: what is not finite stays in the (row, head) whose scores it reaches.  The columns of a
 wave share matrix products, in which 0 * NaN and 0 * inf are NaN, so every column of the batch that has only finite scores is
 compared with the float64 oracle, and every other one has to be NaN there and here."""
 import numpy as np
@@ -83,3 +83,30 @@ def test_other_columns_stay_finite(heads, kind):
     for w in wrong:
         say(f"  {w}")
     assert not wrong
+
+
+@pytest.mark.parametrize("kind", ["nan query", "inf query", "nan key", "inf key"])
+@pytest.mark.parametrize("heads", [(32, 4, 128), (14, 2, 128), (16, 2, 64)], ids=str)
+def test_other_heads_of_a_decode_row_stay_finite(heads, kind):
+    from gpu_util import MAX_ABS, REL_L2, run_gpu, say
+    Hq, Hkv, hd = heads
+    b = W.build_batch(Hq=Hq, Hkv=Hkv, hd=hd, q_lens=[1] * 5, ctx_lens=[3, 60, 333, 900, 2600], num_blocks=300, seed=29, poison=True)
+    value = NAN if "nan" in kind else INF
+    if "query" in kind:
+        b.q[1:, 1, 9] = value
+        b.q[0, Hq - 1, 9] = value
+    else:
+        for seq, token in ((1, 60), (2, 0), (3, 500), (4, 2599)):
+            k, v = W.gather_logical(b, seq)
+            k = k.copy()
+            k[token, 0, 3] = value
+            W.scatter_logical(b, seq, k, v)
+    want = ref_c.attn_mixed(b.q, b.k_cache, b.v_cache, b.block_tables, b.seq_lens, b.query_start_loc, b.ctx_lens)
+    lost = np.isnan(want).all(axis=2)
+    assert lost.any() and not lost.all() and (np.isnan(want).any(axis=2) == lost).all()
+    for opts in ({}, {"decode_coop": 0}, {"decode_coop": 2}, {"decode_coop": 0, "decode_segments": 7}, {"decode_coop": 0, "decode_segments": 60}):
+        say(f"case: {heads} {kind} {opts}")
+        got = W.bf16_bits_to_f32(run_gpu(b, options=opts)).astype(np.float64)
+        assert np.isnan(got[lost]).all() and np.isfinite(got[~lost]).all(), opts
+        diff = np.abs(got[~lost] - want[~lost])
+        assert diff.max() <= MAX_ABS and np.sqrt((diff ** 2).sum() / (want[~lost] ** 2).sum()) <= REL_L2, opts
