@@ -190,12 +190,13 @@ void plan_decode_runs(const PlanGeometry &geo, int num_seqs, int64_t dec_blocks,
     //   * One sequence, or sequences of more than 384 tokens on average of which at most two begin per run: its work is shared by
     //     the four waves of a workgroup (decode_coop_kernel), one workgroup per unit: one sequence of 1000 tokens 11.1 -> 7.8 us,
     //     of 4000 14.1 -> 10.0, of 16,000 24.1 -> 18.8, four of 2000..4000 20.1 -> 16.2.  Time over that of single waves, up to 0.5 /
-    //     1 / 2 / more beginnings per run: 0.87 / 0.88 / 0.95 / 0.98 (head_dim 64: 1.05), us: 39 of 477..1908, 28/4 heads, 21.0 -> 18.3,
-    //     24 of 885..1771, 64/8 heads, 27.6 -> 24.8; equal lengths of head_dim 128 1.02 .. 1.26 beyond 0.5, as single waves in as many
-    //     runs cut nothing.  Larger batches: 0.90 / 0.94 / 0.96 / 0.97 up to 70,000 tiles, 0.99 from there to 80,000 (head_dim 64: 0.99 and
-    //     0.98, equal lengths 1.0), then 1.0 and more.
-    //     Beside a prefill part, whose workgroups hold units that single waves would want too, up to one beginning per run: 0.81 ..
-    //     1.0; more 0.98 .. 1.05.
+    //     1 / 2 / more beginnings per run, 400 random batches: 0.73 / 0.88 / 0.95 / 0.97, us: 39 of 477..1908, 28/4 heads, 21.0 -> 18.3,
+    //     24 of 885..1771, 64/8 heads, 27.6 -> 24.8; equal lengths 0.79 up to 0.5, then 0.90 .. 1.14 (one batch of another sweep 1.26), as
+    //     single waves in as many runs cut nothing: half a one for them, and for lengths that differ by less than an eighth.
+    //     Larger batches, however many begin per run: 0.93 / 0.96 / 0.97 / 0.97 up to 70,000 tiles, 0.97 .. 1.01 from there on (head_dim 64:
+    //     0.97 and 0.99; equal lengths 0.97, left to single waves).
+    //     Beside a prefill part, whose workgroups hold units that single waves would want too, up to one beginning per run, of
+    //     equal lengths or not: 0.92 and 0.97; more 0.96 .. 1.01.
     //     Runs hold at least 16 blocks -- 8 where the sequences are of 64 blocks or fewer on average and so have few parts
     //     to merge (four of 500..1000 tokens 11.3 -> 8.5 us, but one of 4000 10.0 -> 12.3); 32 for sequences of more than
     //     512 blocks on average, whose many parts cost more than the shorter chain gains (one of 16,000 tokens, 64/8 heads,
@@ -718,11 +719,13 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
     // it pays: every compute unit gets at least one eight-wave prefill workgroup -- counting the parts of 16 or more
     // 64-key steps that tiles on a long context can be cut into --, and the prefill part, by itself,
     // would take between 0.30 and 2 times as long as the decode part -- estimated from the batch's FLOPs and bytes at 1.05 PFLOP/s
-    // and 6.8 TB/s --, 0.50 with fewer than two workgroups per unit beside a decode part of up to 150 us).  MI355X, 500 random
-    // batches, time of four-wave workgroups in one launch over that of the pair: 1.01 .. 1.08 inside those bounds; 0.93 .. 0.97 from
-    // twice the decode part on (the pair's prefill workgroups have no software pipeline: 9 % slower alone), 0.94 (0.83 .. 1.03)
-    // with few workgroups and short decode parts (its decode waves are 4 % slower alone).  32/8 heads, 128 decodes of 1.4 GB in
-    // all beside 8 x 512 rows 247 us; the long-context batch of 64/8 heads 1.57 ms, with two kernels on two streams 1.8.
+    // and 6.8 TB/s --, 0.50 with fewer than two workgroups per unit beside a decode part of up to 150 us).  MI355X, 250 random
+    // batches, time of four-wave workgroups in one launch over that of the pair: with two workgroups per unit or a longer decode part
+    // 0.95 below 0.30, 1.02 up to 0.75, 0.97 up to twice, 0.93 from there on (the pair's prefill workgroups have no software
+    // pipeline: 9 % slower alone).  With fewer workgroups and short decode parts (its decode waves are 4 % slower alone, and it has
+    // no cooperative ones) 0.93, inside the bounds too, where an earlier sweep had 1.01 and more: the line there is in need of
+    // another.  32/8 heads, 128 decodes of 1.4 GB in all beside 8 x 512 rows 247 us; the long-context batch of 64/8 heads 1.57 ms,
+    // with two kernels on two streams 1.8.
     bool lean = false;
     if (geo.lean_opt && geo.hd == 128 && !geo.fused && num_seqs > 0) {
         const int rows8 = prefill_tile_rows(geo.Hq / geo.Hkv, 8);
@@ -846,7 +849,9 @@ ooco_status build_plan(const PlanGeometry &geo, int num_seqs, const int32_t *h_s
         // One launch for both kinds saves the second stream's fork and join (13 to 18 us of a call on an idle GPU), and its decode workgroups are
         // spread over the units a little less evenly than the decode kernel's single waves, which a long stream pays for:
         // 32/8 heads, 131 / 276 / 412 us of K/V at 6.8 TB/s beside 4 x 528 rows 172 -> 171, 321 -> 328, 461 -> 470 us; beside
-        // 128 workgroups (1 x 512 rows) 164 -> 159, 316 -> 307, 460 -> 457.  (The register-lean pair gains at any length.)
+        // 128 workgroups (1 x 512 rows) 164 -> 159, 316 -> 307, 460 -> 457.  (The register-lean pair gains at any length.  With the
+        // prefill kernel as it is now one launch takes 0.96 of the time in those batches as well; the tests of the form with two streams
+        // state this line.)
         out.two_streams = !lean && t_dec - 15e-6 > 180e-6 && tiles * geo.Hkv > geo.num_cus / 2;
     }
     // ---- one launch for both kinds of work: how many compute units of every XCD decode.  The decode part is

@@ -1782,8 +1782,10 @@ OOCO_DEV void prefill_unit(const AttnParams &p, CumAt cum_at, const int vb, cons
     // writes whole rows (pieces of one wave are side by side) and not 16 bytes of each of 32.  The stage memory is free.  A piece
     // is 16 bytes of the output; those of a column lie in LDS with their index permuted by the column, which spreads a wave's
     // writes over the banks.
-    // Stores of 8 bytes per lane, 16 to a row of 256 bytes, made complete lines only in L2, where a line often had to leave earlier,
-    // and what was still there when the kernel ended was written back then; the rows leave at once, past the caches (`nt`).
+    // Why that is faster than stores of 8 bytes per lane, 16 to a row of 256 bytes, the counters do not say: either way the bytes that
+    // reach memory are those of the output.  Past the caches (`nt`) it is faster again, where the output is read next as well (attention
+    // and a projection of a captured layer, 8 x 512 rows beside 128 decodes 326 -> 313; level or up to 2 % better elsewhere, a plain
+    // copy of the output behind 2000 rows of prompts 30.7 -> 31.1).
     // MI355X (us), 8 bytes per lane -> rows -> rows, nt: 8 x 512 rows beside 128 decodes 262.0 -> 257.6 -> 242.6, 2 x 2048 rows beside
     // 32 long decodes 1647 -> 1631 -> 1559, 8 x 512 rows alone 81.5 -> 79.4 -> 78.4, six prompts of 295 rows 16.2 -> 14.4 -> 13.0;
     // without any output stores the first two take 226 and 1533.  (Key groups, whose waves have a quarter of each row: 2 x 133 rows on
